@@ -576,7 +576,7 @@ dr_status attn_launch(dr_ctx* ctx, const AttnArgs& a, bool pairs, hipStream_t s)
     } else if (attn_mfma_small_supported(a)) {
         DR_HIP(ctx, launch_attn_mfma_small(a, s));
     } else {
-        DR_HIP(ctx, launch_attn_generic(a, s));
+        DR_HIP(ctx, launch_attn_split(a, s));
     }
     return DR_OK;
 }

@@ -101,8 +101,8 @@ struct AttnArgs {
     // NULL: no second pass.
     int32_t* flags;              // [B * H * ceil(N / 128) * 4]
 };
-// Any d in {64,128}, Bs in {32,64,128}, f32 or bf16 storage; arithmetic in fp32 on the vector ALUs.
-hipError_t launch_attn_generic(const AttnArgs& a, hipStream_t s);
+// Any d in {64,128}, Bs in {32,64,128}, f32 or bf16 storage; fp32 accuracy (32-bit operands split for the bf16 matrix cores).
+hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s);
 // bf16 storage, d = 128, Bs = 128: MFMA path.  Returns hipErrorNotSupported for other shapes.
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s);
 bool attn_mfma_supported(const AttnArgs& a);

@@ -1,0 +1,506 @@
+// Stage (c) at fp32 accuracy: block-sparse softmax attention (paper Eqs. 12-13, epsilon -> 0) for fp32 storage and for
+// the bf16 shapes that k_attn_mfma* do not cover (d = 64), on the bf16 matrix instructions.  gfx950 only.
+//
+// What bounds it: the fp32 matrix instruction does 1/16 of the bf16 one's operations per cycle, the vector ALU no more.
+// So every 32-bit operand is split into three bf16 parts, x = h + m + l, which is exact (8 + 8 + 8 significant bits,
+// each part the rounding of what the parts before it leave), and a product is summed from part products on the bf16
+// matrix cores with fp32 accumulation.  Of the nine part products the three of order 2^-24 and below (m l, l m, l l)
+// are left out: 6 bf16 instructions for one, 2.7 times the rate of the fp32 instruction.  Inputs stored as bf16 are one
+// part (their products are exact); the probabilities stay 32-bit and are always three parts.
+// Times and errors against 64 bits are at the kernel's definition below.
+//
+// One workgroup owns one query block of one (batch, head).  It has kQ * kS wavefronts: wavefront (q, s) owns 32 queries
+// and walks every kS-th group of 32-key tiles, so that block sizes 64 and 32, whose rows share no key list, still fill
+// four wavefronts (the streams' partial sums are merged at the end, in a fixed order).  Keys and values of a stage (kT
+// tiles per stream) are fetched to registers while the stage before is computed, split once by the workgroup and
+// left in LDS as bf16 parts.  The logits are produced transposed, S^T = K Q^T (32x32x16), so that a lane's sixteen values
+// belong to one query, and the split probabilities are already the B operand of O^T += V^T P^T; V^T fragments come
+// from the row-major parts with the transposing LDS read.
+// Softmax is online in fp32; the exponent reference of a query is moved only when a logit exceeds it by 2^10, which
+// costs no accuracy (fp32 sums are scale free), so the steady state rescales nothing.
+//
+// Infinite inputs (or values that round to infinity in bf16) make inf - inf in a split.  A workgroup that finds a result
+// that is not finite takes its query block again with plain fp32 arithmetic on the vector ALU, whose answer stands.
+#include "attn_mfma_common.h"
+#include "dr_internal.h"
+
+namespace dr {
+namespace {
+
+using namespace mfma;
+
+constexpr float kMoveReference = 10.0f;     // log2 units a logit may exceed the reference by
+
+typedef __attribute__((address_space(3))) const v8bf* lds_v8;
+typedef __attribute__((address_space(3))) v4s* lds_v4;
+typedef float v4f32 __attribute__((ext_vector_type(4)));
+
+template <bool BF16, int D, int BS>
+struct Plan {
+    static constexpr int kIn = BF16 ? 1 : 3;                        // parts of Q, K, V
+    static constexpr int kQ = BS / 32;                              // wavefronts along the queries
+    static constexpr int kS = BS == 32 && !BF16 && D == 128 ? 2 : 4 / kQ;   // streams of key tiles (four would not fit the LDS there)
+    static constexpr int kThreads = 64 * kQ * kS;
+    static constexpr int kTileBytes = 32 * 2 * kIn * 2 * D;         // 32 keys of K and V, all parts
+    static constexpr int kT = (BF16 && D == 64) || (!BF16 && D == 64 && kS == 1) ? 2 : 1;   // 32-key tiles per stream and stage
+    static constexpr int kTiles = kS * kT, kRows = kTiles * 32;     // of a stage
+    static constexpr int kStageBytes = kTiles * kTileBytes;
+    static constexpr int kPlainRows = kThreads / 8, kPlainKeys = 32;
+    static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainKeys * D + kPlainRows * kPlainKeys);
+    static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
+    static constexpr int kMax1 = kStageBytes > kPlainBytes ? kStageBytes : kPlainBytes;
+    static constexpr int kLdsBytes = kMax1 > kMergeBytes ? kMax1 : kMergeBytes;
+    static constexpr int kRowUnits = D / 8;                         // a unit = 8 channels of one row
+    static constexpr int kPasses = kRows * kRowUnits / kThreads;    // units per thread, K and V each
+    static constexpr int kRowBytes = 2 * D;
+    static_assert(kRows * kRowUnits % kThreads == 0 && kLdsBytes <= 160 * 1024, "stage layout");
+};
+
+// 16-byte piece of row r at which channel piece p of a K part row is kept: the sixteen rows a ds_read_b128 touches per
+// cycle fall in distinct bank groups
+template <int D> __device__ __forceinline__ int k_piece(int p, int r) { return D == 128 ? p ^ (r & 15) : p ^ ((r >> 1) & 7); }
+// the same for V: the four rows of a transposing read's patch fall in distinct 64-byte groups
+template <int D> __device__ __forceinline__ int v_piece(int p, int r) { return D == 128 ? p ^ ((r & 3) << 2) : p ^ (((r >> 1) & 1) << 2); }
+
+__device__ __forceinline__ void split8(const float (&x)[8], v8bf (&part)[3]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const __bf16 h = (__bf16)x[i];
+        const float r = x[i] - (float)h;
+        const __bf16 m = (__bf16)r;
+        part[0][i] = h;
+        part[1][i] = m;
+        part[2][i] = (__bf16)(r - (float)m);
+    }
+}
+
+__device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
+    uint32_t u = __float_as_uint(f);
+    if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40);   // NaN stays NaN
+    u += 0x7fffu + ((u >> 16) & 1u);
+    return (uint16_t)(u >> 16);
+}
+
+// c += a b with both operands in parts: the six part products of order above 2^-24 (three when b is one part), small ones first
+template <int NA, int NB>
+__device__ __forceinline__ v16f mfma_parts(const v8bf (&a)[NA], const v8bf (&b)[NB], v16f c) {
+#pragma unroll
+    for (int order = 2; order >= 0; --order)
+#pragma unroll
+        for (int i = 0; i < NA; ++i) {
+            const int j = order - i;
+            if (j >= 0 && j < NB) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], c, 0, 0, 0);
+        }
+    return c;
+}
+
+template <bool BF16, int D>
+__device__ __forceinline__ void load_plain(const char* src, float* dst, int g) {
+    if (BF16) {
+        const uint16_t* p = reinterpret_cast<const uint16_t*>(src);
+        for (int c = g; c < D; c += 8) dst[c] = __uint_as_float((uint32_t)p[c] << 16);
+    } else {
+        const float* p = reinterpret_cast<const float*>(src);
+        for (int c = g; c < D; c += 8) dst[c] = p[c];
+    }
+}
+
+struct Item {
+    const char *Q, *K, *V;      // of this (batch, head)
+    char* O;
+    float* lse;                 // of this (batch, head), or NULL
+    const int32_t* list;        // the row's key blocks
+    int n_list, qb, Sb, N;
+    int64_t row_bytes;
+};
+
+// The query block in plain fp32 on the vector ALU (thread (r, g): row r, four of the 32 logits of a chunk, D / 8 output
+// channels).  Only for blocks whose inputs hold infinities or NaN.
+template <bool BF16, int D, int BS>
+__device__ __forceinline__ void plain_block(const Item& it, float* lds) {
+    using P = Plan<BF16, D, BS>;
+    constexpr int R = P::kPlainRows, C = P::kPlainKeys, DC = D / 8, LPT = C / 8;
+    float* sQ = lds;
+    float* sK = sQ + R * D;
+    float* sV = sK + C * (D + 1);
+    float* sP = sV + C * D;
+    const int tid = threadIdx.x, r = tid >> 3, g = tid & 7;
+    const float scale = 1.0f / sqrtf((float)D);
+    for (int row0 = it.qb * BS; row0 < min(it.N, it.qb * BS + BS); row0 += R) {
+        const bool row_ok = row0 + r < min(it.N, it.qb * BS + BS);
+        __syncthreads();
+        if (row_ok) load_plain<BF16, D>(it.Q + (int64_t)(row0 + r) * it.row_bytes, sQ + r * D, g);
+        else for (int c = g; c < D; c += 8) sQ[r * D + c] = 0.f;
+        float m_run = -INFINITY, l_run = 0.f, o[DC];
+#pragma unroll
+        for (int i = 0; i < DC; ++i) o[i] = 0.f;
+        for (int e = 0; e < it.n_list; ++e) {
+            const int kb = min(max(it.list[e], 0), it.Sb - 1);
+            const int k_end = min(it.N, (kb + 1) * BS);
+            for (int k0 = kb * BS; k0 < k_end; k0 += C) {
+                const int nk = min(C, k_end - k0);
+                __syncthreads();
+                for (int kr = tid >> 3; kr < C; kr += R) {
+                    if (kr < nk) {
+                        load_plain<BF16, D>(it.K + (int64_t)(k0 + kr) * it.row_bytes, sK + kr * (D + 1), g);
+                        load_plain<BF16, D>(it.V + (int64_t)(k0 + kr) * it.row_bytes, sV + kr * D, g);
+                    } else {
+                        for (int c = g; c < D; c += 8) { sK[kr * (D + 1) + c] = 0.f; sV[kr * D + c] = 0.f; }
+                    }
+                }
+                __syncthreads();
+                float s[LPT];
+#pragma unroll
+                for (int j = 0; j < LPT; ++j) s[j] = 0.f;
+                for (int c = 0; c < D; ++c) {
+                    const float qv = sQ[r * D + c];
+#pragma unroll
+                    for (int j = 0; j < LPT; ++j) s[j] = fmaf(qv, sK[(g + 8 * j) * (D + 1) + c], s[j]);
+                }
+                float mx = -INFINITY;
+#pragma unroll
+                for (int j = 0; j < LPT; ++j) {
+                    s[j] = (g + 8 * j < nk) ? s[j] * scale : -INFINITY;
+                    mx = fmaxf(mx, s[j]);
+                }
+                for (int off = 1; off < 8; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+                const float m_new = fmaxf(m_run, mx);
+                const float alpha = expf(m_run - m_new);
+                float ps = 0.f;
+#pragma unroll
+                for (int j = 0; j < LPT; ++j) {
+                    const float p = expf(s[j] - m_new);
+                    sP[r * C + g + 8 * j] = p;
+                    ps += p;
+                }
+                for (int off = 1; off < 8; off <<= 1) ps += __shfl_xor(ps, off);
+                l_run = l_run * alpha + ps;
+                m_run = m_new;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < DC; ++i) o[i] *= alpha;
+                for (int k = 0; k < nk; ++k) {
+                    const float p = sP[r * C + k];
+#pragma unroll
+                    for (int i = 0; i < DC; ++i) o[i] = fmaf(p, sV[k * D + g * DC + i], o[i]);
+                }
+            }
+        }
+        if (!row_ok) continue;
+        const float inv = (l_run > 0.f) ? 1.0f / l_run : 0.f;
+        char* dst = it.O + (int64_t)(row0 + r) * it.row_bytes;
+#pragma unroll
+        for (int i = 0; i < DC; ++i) {
+            const float val = o[i] * inv;
+            if (BF16) reinterpret_cast<uint16_t*>(dst)[g * DC + i] = f32_to_bf16_rne(val);
+            else reinterpret_cast<float*>(dst)[g * DC + i] = val;
+        }
+        if (it.lse && g == 0) it.lse[row0 + r] = (l_run > 0.f) ? m_run + logf(l_run) : -INFINITY;
+    }
+}
+
+template <bool BF16, int D, int BS>
+__device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
+    using P = Plan<BF16, D, BS>;
+    constexpr int kDB = D / 32, kKS = D / 16;       // channel blocks of O, contraction steps of a logit tile
+    constexpr int kPart = P::kRows * P::kRowBytes;  // bytes of one part of K (or V) of a stage
+    constexpr int kTPB = BS / 32;                   // 32-key tiles of a key block
+    constexpr float kScaleLog2 = (float)(1.4426950408889634 / (D == 128 ? 11.313708498984760 : 8.0));
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int wq = wave % P::kQ, ws = wave / P::kQ;
+
+    // one XCD walks a contiguous run of (batch, head, query block) items: neighbours share K and V in its L2
+    constexpr int kXcds = 8;
+    const int total = a.Sb * a.td.H * a.td.B, per_xcd = (total + kXcds - 1) / kXcds;
+    const int item = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if ((int)(blockIdx.x / kXcds) >= per_xcd || item >= total) return;
+    const int qb = item % a.Sb, h = (item / a.Sb) % a.td.H, b = item / (a.Sb * a.td.H);
+    constexpr int ES = BF16 ? 2 : 4;
+    const int N = a.td.N;
+    const int64_t head_off = ((int64_t)b * a.td.stride_b + (int64_t)h * a.td.stride_h) * ES;
+    Item it;
+    it.Q = reinterpret_cast<const char*>(a.Q) + head_off;
+    it.K = reinterpret_cast<const char*>(a.K) + head_off;
+    it.V = reinterpret_cast<const char*>(a.V) + head_off;
+    it.O = reinterpret_cast<char*>(a.O) + head_off;
+    it.lse = a.lse ? a.lse + ((int64_t)b * a.td.H + h) * N : nullptr;
+    it.row_bytes = a.td.stride_n * ES;
+    it.qb = qb; it.Sb = a.Sb; it.N = N;
+    const int mh = (a.mask_heads == 1) ? 0 : h;
+    const int32_t* rp = a.rowptr + ((int64_t)b * a.mask_heads + mh) * (a.Sb + 1);
+    // row range, clipped to the colidx array of this mask (a list cut short by a too small capacity stays in bounds)
+    const int lim = (int)min(a.colidx_stride, (int64_t)0x7fffffff);
+    const int beg = min(max(__builtin_amdgcn_readfirstlane(rp[qb]), 0), lim);
+    it.n_list = min(max(__builtin_amdgcn_readfirstlane(rp[qb + 1]), beg), lim) - beg;
+    it.list = a.colidx + ((int64_t)b * a.mask_heads + mh) * a.colidx_stride + beg;
+
+    // Q^T fragments (B operand): lane holds query l32, channels ks * 16 + 8 * half .. + 7
+    const int q_wave0 = qb * BS + wq * 32, qrow = q_wave0 + l32;
+    v8bf qf[kKS][P::kIn];
+    {
+        const char* src = it.Q + (int64_t)min(qrow, N - 1) * it.row_bytes + half * (8 * ES);
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            if constexpr (BF16) {
+                qf[ks][0] = *reinterpret_cast<const v8bf*>(src + ks * 32);
+            } else {
+                const v4f32 x0 = *reinterpret_cast<const v4f32*>(src + ks * 64), x1 = *reinterpret_cast<const v4f32*>(src + ks * 64 + 16);
+                const float x[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+                split8(x, qf[ks]);
+            }
+        }
+    }
+
+    // ---- the walk.  Tile t of the row = keys (t % kTPB) * 32 .. + 31 of its key block t / kTPB; stage g holds tiles
+    // g * kTiles .., stream s the kT consecutive ones from s * kT on.  The list is held in a 64-entry register window. ----
+    const int n_tiles = it.n_list * kTPB, stages = (n_tiles + P::kTiles - 1) / P::kTiles;
+    int wbase = 0, win = it.n_list > 0 ? it.list[min(lane, it.n_list - 1)] : 0;
+    auto tile_row0 = [&](int t) {          // t < n_tiles, its key block inside the window; clamped: a malformed list cannot address outside K / V
+        const int kb = min(max(__builtin_amdgcn_readlane(win, t / kTPB - wbase), 0), a.Sb - 1);
+        return kb * BS + (t % kTPB) * 32;
+    };
+    struct Raw { v4f32 x[BF16 ? 1 : 2]; };
+    Raw rk[P::kPasses], rv[P::kPasses];
+    int row0_next[P::kT], row0[P::kT];
+    auto fetch = [&](int g) {
+        const int e_first = g * P::kTiles / kTPB, e_last = min(((g + 1) * P::kTiles - 1) / kTPB, it.n_list - 1);
+        if (e_last - wbase >= 64) {          // wavefront-uniform
+            wbase = e_first;
+            win = it.list[min(wbase + lane, it.n_list - 1)];
+        }
+#pragma unroll
+        for (int c = 0; c < P::kT; ++c) row0_next[c] = tile_row0(min(g * P::kTiles + ws * P::kT + c, n_tiles - 1));
+#pragma unroll
+        for (int p = 0; p < P::kPasses; ++p) {
+            constexpr int kWaveRows = 64 / P::kRowUnits;          // rows of one wavefront and pass: they lie in one tile
+            const int wave_row = (p * P::kThreads + wave * 64) / P::kRowUnits;
+            const int r0 = tile_row0(min(g * P::kTiles + wave_row / 32, n_tiles - 1));
+            const int r = min(r0 + wave_row % 32 + lane / P::kRowUnits, N - 1);
+            const int64_t off = (int64_t)r * it.row_bytes + (lane % P::kRowUnits) * (8 * ES);
+            static_assert(32 % kWaveRows == 0, "a wavefront's rows lie in one tile");
+#pragma unroll
+            for (int i = 0; i < (BF16 ? 1 : 2); ++i) {
+                rk[p].x[i] = *reinterpret_cast<const v4f32*>(it.K + off + i * 16);
+                rv[p].x[i] = *reinterpret_cast<const v4f32*>(it.V + off + i * 16);
+            }
+        }
+    };
+    auto store = [&]() {          // split the fetched rows into their LDS parts
+#pragma unroll
+        for (int p = 0; p < P::kPasses; ++p) {
+            const int row = (p * P::kThreads + tid) / P::kRowUnits, piece = tid % P::kRowUnits;
+            unsigned char* dk = smem + row * P::kRowBytes + k_piece<D>(piece, row) * 16;
+            unsigned char* dv = smem + P::kIn * kPart + row * P::kRowBytes + v_piece<D>(piece, row) * 16;
+            if constexpr (BF16) {
+                *reinterpret_cast<v4f32*>(dk) = rk[p].x[0];
+                *reinterpret_cast<v4f32*>(dv) = rv[p].x[0];
+            } else {
+                const float xk[8] = {rk[p].x[0][0], rk[p].x[0][1], rk[p].x[0][2], rk[p].x[0][3], rk[p].x[1][0], rk[p].x[1][1], rk[p].x[1][2], rk[p].x[1][3]};
+                const float xv[8] = {rv[p].x[0][0], rv[p].x[0][1], rv[p].x[0][2], rv[p].x[0][3], rv[p].x[1][0], rv[p].x[1][1], rv[p].x[1][2], rv[p].x[1][3]};
+                v8bf part[3];
+                split8(xk, part);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<v8bf*>(dk + i * kPart) = part[i];
+                split8(xv, part);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) *reinterpret_cast<v8bf*>(dv + i * kPart) = part[i];
+            }
+        }
+    };
+
+    v16f o[kDB];
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+    float ref = -INFINITY, l_run = 0.f;      // exponent reference of this lane's query (log2 units), this half's normaliser
+
+    const uint32_t lds0 = lds_addr(smem);
+    uint32_t k_addr[kKS], v_addr[kDB];
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) k_addr[ks] = lds0 + l32 * P::kRowBytes + k_piece<D>(ks * 2 + half, l32) * 16;
+    {
+        const int v_e = (lane & 15) >> 2, v_c = lane & 3, v_grp = (lane >> 4) & 1;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+            v_addr[db] = lds0 + P::kIn * kPart + (half * 4 + v_e) * P::kRowBytes + v_piece<D>(db * 4 + v_grp * 2 + (v_c >> 1), v_e) * 16 + (v_c & 1) * 8;
+    }
+
+    if (stages > 0) fetch(0);
+    for (int g = 0; g < stages; ++g) {
+        __syncthreads();                     // the stage before is consumed
+        store();
+#pragma unroll
+        for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
+        __syncthreads();
+        if (g + 1 < stages) fetch(g + 1);
+#pragma unroll
+        for (int c = 0; c < P::kT; ++c) {
+            const int valid = N - row0[c];                       // keys of the tile (only the sequence's end has fewer than 32)
+            if (g * P::kTiles + ws * P::kT + c >= n_tiles || valid <= 0) continue;      // wavefront-uniform
+            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
+            v16f s;
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[j] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) {
+                v8bf kf[P::kIn];
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) kf[i] = *(lds_v8)(uintptr_t)(k_addr[ks] + tile + i * kPart);
+                s = mfma_parts<P::kIn, P::kIn>(kf, qf[ks], s);
+            }
+            if (valid < 32) {
+#pragma unroll
+                for (int j = 0; j < 16; ++j)
+                    if ((j >> 2) * 8 + half * 4 + (j & 3) >= valid) s[j] = -INFINITY;
+            }
+            float mx = s[0];
+#pragma unroll
+            for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+            mx = max_across_halves(mx) * kScaleLog2;             // finite for finite inputs: the tile holds at least one key
+            if (__any(mx > ref + kMoveReference)) {
+                const float ref_new = fmaxf(ref, mx);
+                const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);      // first tile: exp2(-inf) = 0
+                ref = ref_new;
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
+            }
+            v8bf pf[2][3];
+            float sum = 0.f;                                     // the tile's share first: fewer roundings at the running sum's size
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                float p[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t * 8 + i], kScaleLog2, -ref));
+                sum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+                split8(p, pf[t]);
+            }
+            l_run += sum;
+#pragma unroll
+            for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    v8bf vf[P::kIn];
+#pragma unroll
+                    for (int i = 0; i < P::kIn; ++i) {
+                        union { struct { v4s a, b; } s2; v8bf v; } u;
+                        const uint32_t at = v_addr[db] + tile + i * kPart + t * 16 * P::kRowBytes;
+                        u.s2.a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(uintptr_t)at);
+                        u.s2.b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4)(uintptr_t)(at + 8 * P::kRowBytes));
+                        vf[i] = u.v;
+                    }
+                    o[db] = mfma_parts<P::kIn, 3>(vf, pf[t], o[db]);
+                }
+        }
+    }
+
+    // ---- merge the streams of a query group (stream order), normalise, store ----
+    float l = l_run + __shfl_xor(l_run, 32);
+    if constexpr (P::kS > 1) {
+        __syncthreads();
+        float* sO = reinterpret_cast<float*>(smem);                           // [kS - 1][kQ][32 channels-and-queries x kDB]
+        float* sM = sO + (P::kS - 1) * P::kQ * 32 * D;                        // [kS][kQ][64]: reference, normaliser
+        sM[(ws * P::kQ + wq) * 64 + lane] = half ? l : ref;
+        __syncthreads();
+        float top = -INFINITY;
+#pragma unroll
+        for (int s = 0; s < P::kS; ++s) top = fmaxf(top, sM[(s * P::kQ + wq) * 64 + l32]);
+        const float mine = (ref == top) ? 1.0f : __builtin_amdgcn_exp2f(ref - top);      // (both -inf: nothing listed)
+        if (ws > 0) {
+            float* dst = sO + ((ws - 1) * P::kQ + wq) * 32 * D + lane;
+#pragma unroll
+            for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) dst[(db * 16 + j) * 64] = o[db][j] * mine;
+        }
+        __syncthreads();
+        if (ws == 0) {
+            l *= mine;
+#pragma unroll
+            for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                for (int j = 0; j < 16; ++j) o[db][j] *= mine;
+#pragma unroll
+            for (int s = 1; s < P::kS; ++s) {
+                const float r_s = sM[(s * P::kQ + wq) * 64 + l32], l_s = sM[(s * P::kQ + wq) * 64 + 32 + l32];
+                l += l_s * ((r_s == top) ? 1.0f : __builtin_amdgcn_exp2f(r_s - top));
+                const float* src = sO + ((s - 1) * P::kQ + wq) * 32 * D + lane;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) o[db][j] += src[(db * 16 + j) * 64];
+            }
+        }
+        ref = top;
+    }
+    bool bad = false;
+    if (ws == 0 && qrow < N) {
+        const float inv = (l > 0.f) ? 1.0f / l : 0.f;
+        float check = l;
+        char* dst = it.O + (int64_t)qrow * it.row_bytes;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int ch = db * 32 + q4 * 8 + half * 4;
+                v4f32 val;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    val[i] = o[db][q4 * 4 + i] * inv;
+                    check += fabsf(val[i]) * 0.f;                // NaN as soon as one value is not finite
+                }
+                if constexpr (BF16) {
+                    v4bf r;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[i] = (__bf16)val[i];
+                    *reinterpret_cast<v4bf*>(dst + ch * 2) = r;
+                } else {
+                    *reinterpret_cast<v4f32*>(dst + ch * 4) = val;
+                }
+            }
+        if (it.lse && half == 0)      // the two terms in 64 bits: the reference is a rounded multiple of the scale
+            it.lse[qrow] = (l > 0.f) ? (float)((double)ref * 0.69314718055994531 + log((double)l)) : -INFINITY;
+        bad = it.n_list > 0 && !(check > 0.f && check < INFINITY);
+    }
+    if (__syncthreads_or(bad ? 1 : 0)) plain_block<BF16, D, BS>(it, reinterpret_cast<float*>(smem));
+}
+
+// Measured against the vector-ALU kernel before it (one thread, eight logits and D / 8 channels of a row; 16 TFLOP/s at
+// d = 64, 7 at d = 128): bf16 d = 64, 17 550 tokens x 12 heads, block 64, 32 % of the blocks kept (0.30 TFLOP)
+// 18.43 -> 0.784 ms; fp32 d = 128, 6144 tokens x 8 heads, block 128, 48 % (0.073 TFLOP) 10.21 -> 0.617 ms.  Error against
+// 64 bits (2-norm): fp32 d = 128 O 1.9e-6 -> 1.4e-6, d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
+// The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two.
+template <bool BF16, int D, int BS>
+__global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu((!BF16 && D == 128) ? 1 : 2)))
+void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS>(a); }
+
+template <bool BF16, int D, int BS>
+hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
+    using P = Plan<BF16, D, BS>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, P::kLdsBytes);
+    if (e != hipSuccess) return e;
+    const int total = a.Sb * a.td.H * a.td.B, grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
+    hipLaunchKernelGGL((k_attn_split<BF16, D, BS>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
+    return hipGetLastError();
+}
+
+template <bool BF16, int D>
+hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
+    return a.Bs == 128 ? launch_t<BF16, D, 128>(a, s) : a.Bs == 64 ? launch_t<BF16, D, 64>(a, s) : launch_t<BF16, D, 32>(a, s);
+}
+
+}  // namespace
+
+hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s) {
+    if (a.td.d == 64) return a.bf16 ? launch_d<true, 64>(a, s) : launch_d<false, 64>(a, s);
+    if (a.td.d == 128) return a.bf16 ? launch_d<true, 128>(a, s) : launch_d<false, 128>(a, s);
+    return hipErrorNotSupported;
+}
+
+}  // namespace dr

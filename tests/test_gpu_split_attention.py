@@ -1,0 +1,109 @@
+"""Attention at fp32 accuracy (fp32 storage, and bf16 storage at d = 64): 32-bit operands as three bf16 parts on the
+matrix cores, against the oracle on every row, at the edges of its tiles, streams and list windows."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import dynamicrad_oracle as o
+from workloads import tiny_case
+
+from helpers import GpuRun, to_f64
+
+pytestmark = pytest.mark.gpu
+
+STORAGE = [("f32", 64), ("f32", 128), ("bf16", 64)]
+
+
+def _run(dtype, d, bs, frames, hg, wg, scale=1.0):
+    wl = dataclasses.replace(tiny_case("ragged128"), dtype=dtype, d=d, Bs=bs, Nf=frames, Hg=hg, Wg=wg, H=2, index=61)
+    run = GpuRun(wl)
+    if scale != 1.0:
+        run.Qc = (run.Qc.float() * scale).to(run.Qc.dtype)
+        run.Q = run.Qc.cuda()
+    return run
+
+
+def _csr(rows):
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    return rp, np.asarray([c for r in rows for c in r] or [0], dtype=np.int64)
+
+
+def _attend(run, rp, ci):
+    rowptr = torch.from_numpy(rp.astype(np.int32)).view(1, 1, -1).contiguous().cuda()
+    colidx = torch.from_numpy(ci.astype(np.int32)).view(1, 1, -1).contiguous().cuda()
+    return run.attention(rowptr, colidx, colidx.shape[2], want_lse=True)
+
+
+def _bounds(run, h):
+    """Rounding bounds for O and the log-sum-exp: a logit is a sum of d products, each correct to 2^-23, accumulated in
+    fp32; a relative change e of every probability moves O by at most 2 e max|V|; bf16 output rounds once more."""
+    q, k, v = (np.abs(to_f64(t[0, h])) for t in (run.Qc, run.Kc, run.Vc))
+    logit = 2.0 ** -22 * float((q @ k.T).max()) / np.sqrt(q.shape[1])
+    out = v.max() * (2.0 * logit + 2.0 ** -20)
+    return out + (v.max() * 2.0 ** -8 if run.wl.dtype == "bf16" else 0.0), logit + 2.0 ** -20
+
+
+def _check(run, rp, ci, O, lse):
+    for h in range(run.wl.H):
+        want, want_lse = o.masked_attention(to_f64(run.Qc[0, h]), to_f64(run.Kc[0, h]), to_f64(run.Vc[0, h]), rp, ci,
+                                            run.wl.Bs, return_lse=True)
+        tol, tol_lse = _bounds(run, h)
+        for qb, blk in want.items():
+            rows = slice(qb * run.wl.Bs, qb * run.wl.Bs + blk.shape[0])
+            assert np.abs(to_f64(O[0, h, rows]) - blk).max() <= tol, (h, qb, tol)
+            g, w = lse[0, h, rows].cpu().numpy().astype(np.float64), want_lse[qb]
+            with np.errstate(invalid="ignore"):
+                close = np.abs(g - w) <= tol_lse + 2.0 ** -23 * np.abs(w)
+            assert (close | (np.isinf(g) & np.isinf(w) & (g < 0) & (w < 0))).all(), (h, qb)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+@pytest.mark.parametrize("bs", [32, 64, 128])
+@pytest.mark.parametrize("frames,hg,wg,scale", [
+    (7, 9, 21, 1.0),        # N = 1323: a partial last block and a partial last tile at every block size
+    (3, 5, 11, 8.0),        # N = 165; large logits: the exponent reference moves
+    (7, 16, 24, 1.0),       # N = 2688 = 84 * 32: full lists outgrow the register window at block size 32
+    (1, 3, 7, 1.0),         # N = 21: one tile, and not a full one
+])
+def test_random_lists_against_the_oracle(dtype, d, bs, frames, hg, wg, scale):
+    run = _run(dtype, d, bs, frames, hg, wg, scale)
+    Sb = run.wl.Sb
+    rng = np.random.default_rng(frames * 100 + bs)
+    rows = [sorted(np.nonzero(rng.random(Sb) < 0.4)[0].tolist()) for _ in range(Sb)]
+    rows[-1] = list(range(Sb))
+    if Sb > 3:
+        rows[0], rows[1], rows[2] = [], [Sb - 1], list(range(Sb))[::-1]     # nothing; the partial block alone; not ascending
+    rp, ci = _csr(rows)
+    _check(run, rp, ci, *_attend(run, rp, ci))
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+@pytest.mark.parametrize("bs", [32, 64, 128])
+def test_infinite_inputs_give_what_fp32_arithmetic_gives(dtype, d, bs):
+    run = _run(dtype, d, bs, 5, 9, 13)                       # N = 585
+    Sb = run.wl.Sb
+    rp, ci = _csr([list(range(Sb))] * Sb)
+    run.Qc[..., 3] = run.Qc[..., 3].abs() + 0.5
+    run.Kc[:, 0, 40] = 0.0                                   # head 0: a key whose logit is -inf in every row
+    run.Vc[:, 1, 70, 5] = float("inf")                       # head 1: one infinite value
+    clean = {n: getattr(run, n).clone() for n in ("Qc", "Kc", "Vc")}
+    run.Kc[:, 0, 40, 3] = -float("inf")
+    clean["Kc"][:, 0, 40, 3] = -1e4                          # the same key out of reach by a finite logit
+    clean["Vc"][:, 1, 70, 5] = 0.0
+    run.Q, run.K, run.V = run.Qc.cuda(), run.Kc.cuda(), run.Vc.cuda()
+    O, lse = _attend(run, rp, ci)
+    assert torch.isposinf(O[0, 1, :, 5].float()).all()
+    O[0, 1, :, 5] = 0.0
+    run.Qc, run.Kc, run.Vc = clean["Qc"], clean["Kc"], clean["Vc"]
+    bounds = _bounds(run, 1)                                  # (head 0 holds the large stand-in key)
+    for h in range(2):
+        want, want_lse = o.masked_attention(to_f64(run.Qc[0, h]), to_f64(run.Kc[0, h]), to_f64(run.Vc[0, h]), rp, ci, bs,
+                                            return_lse=True)
+        for qb, blk in want.items():
+            if h == 1:
+                blk[:, 5] = 0.0
+            rows = slice(qb * bs, qb * bs + blk.shape[0])
+            assert np.abs(to_f64(O[0, h, rows]) - blk).max() <= bounds[0] * 4, (h, qb)
+            assert np.abs(lse[0, h, rows].cpu().numpy() - want_lse[qb]).max() <= bounds[1] * 4 + 1e-5, (h, qb)
