@@ -381,28 +381,34 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     attn_item<false>(a, item, smem);
 }
 
-// Second pass: the flagged items only.  Usually none is, so the grid is small and every workgroup looks at a
-// contiguous share of the flag words, one item per thread and step (a workgroup per item would spend 28 us at 23 640
-// items on starting workgroups that leave at once; one item per workgroup and step, 27 us on dependent loads).
+// Second pass: the flagged items only.  Usually none is, so the grid is small and every workgroup looks at its share of
+// the flag words, one item per thread and step (a workgroup per item would spend 28 us at 23 640 items on starting
+// workgroups that leave at once; one item per workgroup and step, 27 us on dependent loads).  Flagged rows come in
+// clusters (the tokens of one object), and a flagged item costs a whole walk, so neighbouring items must not fall to one
+// workgroup: runs of `slots` consecutive items (one per workgroup of an XCD) are dealt to the XCDs in turn.  With
+// contiguous shares the slowest of 1024 workgroups took 5 to 7 items where 229 to 619 of 22 296 were flagged (33 frames of
+// 45 x 80 tokens x 24 heads): 2.55 ms; dealt, the whole call went from 33.4 to 31.4 ms on one box.
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ unsigned char s_flagged[kThreads];
+    constexpr int kXcds = 8;                                             // the grid is a multiple of it
     const int total_items = a.Sb * a.td.H * a.td.B;
-    const int per = (total_items + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int begin = min((int)blockIdx.x * per, total_items), end = min(begin + per, total_items);
-    for (int base = begin; base < end; base += kThreads) {
-        const int mine = base + (int)threadIdx.x;
+    const int slots = (int)gridDim.x / kXcds, xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
+    const int runs = (total_items + slots - 1) / slots, mine_runs = (runs - xcd + kXcds - 1) / kXcds;      // this XCD's
+    for (int base = 0; base < mine_runs; base += kThreads) {
+        auto item_of = [&](int j) -> int64_t { return ((int64_t)(base + j) * kXcds + xcd) * slots + slot; };
+        const int64_t mine = item_of((int)threadIdx.x);
         int flagged = 0;
-        if (mine < end) {
-            const int4 f = *reinterpret_cast<const int4*>(a.flags + (int64_t)mine * 4);
+        if (mine < total_items) {
+            const int4 f = *reinterpret_cast<const int4*>(a.flags + mine * 4);
             flagged = (f.x | f.y | f.z | f.w) != 0;
         }
         if (!__syncthreads_or(flagged)) continue;
         s_flagged[threadIdx.x] = (unsigned char)flagged;
         __syncthreads();
-        for (int j = 0; j < kThreads && base + j < end; ++j) {
+        for (int j = 0; j < kThreads && base + j < mine_runs; ++j) {
             if (!s_flagged[j]) continue;          // the same for every thread
-            attn_item<true>(a, base + j, smem);
+            attn_item<true>(a, (int)item_of(j), smem);
             __syncthreads();          // the next item's tile loads overwrite LDS that slower waves may still be reading
         }
         __syncthreads();
@@ -426,7 +432,7 @@ static hipError_t allow_lds() {
 
 static void launch_second(const AttnArgs& a, hipStream_t s) {
     const int total = a.Sb * a.td.H * a.td.B;
-    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min(total, 1024)), dim3(kThreads), kLdsBytes, s, a);
+    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min((total + 7) / 8 * 8, 1024)), dim3(kThreads), kLdsBytes, s, a);
 }
 
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) {
