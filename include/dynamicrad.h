@@ -248,7 +248,7 @@ dr_status dr_sparse_attn_fwd(dr_ctx* ctx, const dr_shape* shape, const void* Q, 
  * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results; the scratch the
  * kernels need beyond their inputs and outputs (range flags of the bf16 MFMA paths; merged key-block lists and
  * their lengths for block sizes 32 / 64 and for the block-size-128 kernel that walks pairs of query blocks) lies in
- * a fixed 16 MiB area of device memory that is part of the library image (one copy per GPU, held until the process
+ * a fixed area of device memory (16 MiB, and 256 bytes of work queues) that is part of the library image (one copy per GPU, held until the process
  * ends) instead of context-owned allocations.  The call allocates and frees nothing.
  *   Needed: 16 bytes per 128 query rows and head, plus, on the list-walking paths, 4 bytes per entry of the colidx
  *   arrays given (B * mask_heads * colidx_stride) and 4 bytes per group of rows.  A call that needs more than the

@@ -16,8 +16,10 @@ using namespace dr;
 
 // Scratch of dr_sparse_attn_fwd_static: one copy per GPU the library runs on, held until the process ends.  In host
 // code this name is only a handle for hipGetSymbolAddress (dr_create resolves it, per device); kernels get the address.
-constexpr size_t kStaticScratchBytes = 16u << 20;
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+// Behind it lie the work queues of the attention kernel.
+constexpr size_t kStaticScratchBytes = 16u << 20, kQueueBytes = 256;
+static_assert(kAttnQueues * sizeof(int32_t) <= kQueueBytes, "work queues");
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kQueueBytes];
 
 struct dr_ctx {
     int device = 0;
@@ -37,6 +39,9 @@ struct dr_ctx {
     // stage (c) scratch (bf16 MFMA paths): per-wave range flags of the fast pass, read by the fp32-scaled second pass
     int32_t* attn_flags = nullptr;
     size_t attn_flags_bytes = 0;
+    int32_t* attn_queue = nullptr;             // work queues of the 256-query kernel
+    size_t attn_queue_bytes = 0;
+    int cus = 256;
     bool attn_pairs = true;      // block size 128: the kernel that walks pairs of query blocks (DR_ATTN_PAIRS=0 turns it off)
     // cached selection of the uniform rule (it depends on geometry, ratios and seed only): one mask of Sb rows
     uint32_t* uni_keep = nullptr;
@@ -255,6 +260,8 @@ dr_status dr_create(dr_ctx** out, int device) {
             return DR_ERR_HIP;
         }
         c->static_scratch = static_cast<unsigned char*>(p);
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) == hipSuccess && cus > 0) c->cus = cus;
     }
     *out = c;
     return DR_OK;
@@ -265,7 +272,7 @@ void dr_destroy(dr_ctx* ctx) {
     {
         DeviceGuard g(ctx->device);
         void* ptrs[] = {ctx->pooled, ctx->keepbits, ctx->counts, ctx->class_map, ctx->class_bits, ctx->row_sel, ctx->totals, ctx->gcol,
-                        ctx->gcount, ctx->attn_flags, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->proxy_partial};
+                        ctx->gcount, ctx->attn_flags, ctx->attn_queue, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->proxy_partial};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
     }
@@ -548,6 +555,7 @@ dr_status attn_prepare(dr_ctx* ctx, const dr_shape* shape, const void* Q, const 
     a.Bs = shape->Bs;
     a.Sb = (shape->N + shape->Bs - 1) / shape->Bs;
     a.bf16 = shape->dtype == DR_BF16;
+    a.cus = ctx->cus;
     if (attn_mfma_small_supported(a) && a.Sb >= (1 << 28))
         return fail(ctx, DR_ERR_UNSUPPORTED, "too many blocks for the packed group lists");
     // the pre-pass that merges the rows of a workgroup's query blocks keeps one presence bitmap of Sb bits per row in LDS
@@ -595,6 +603,8 @@ dr_status dr_sparse_attn_fwd(dr_ctx* ctx, const dr_shape* shape, const void* Q, 
     if (need.flags && (st = grow(ctx, (void**)&ctx->attn_flags, &ctx->attn_flags_bytes, need.flags)) != DR_OK) return st;
     if (need.gcol && (st = grow(ctx, (void**)&ctx->gcol, &ctx->gcol_bytes, need.gcol)) != DR_OK) return st;
     if (need.gcount && (st = grow(ctx, (void**)&ctx->gcount, &ctx->gcount_bytes, need.gcount)) != DR_OK) return st;
+    if (pairs && (st = grow(ctx, (void**)&ctx->attn_queue, &ctx->attn_queue_bytes, kQueueBytes)) != DR_OK) return st;
+    a.queue = pairs ? ctx->attn_queue : nullptr;
     a.flags = need.flags ? ctx->attn_flags : nullptr;
     a.gcol = need.gcol ? ctx->gcol : nullptr;
     a.gcount = need.gcount ? ctx->gcount : nullptr;
@@ -618,6 +628,7 @@ dr_status dr_sparse_attn_fwd_static(dr_ctx* ctx, const dr_shape* shape, const vo
                     "the static area holds %zu: use dr_sparse_attn_fwd", total, need.flags, need.gcount, need.gcol, kStaticScratchBytes);
     unsigned char* base = ctx->static_scratch;
     a.flags = need.flags ? reinterpret_cast<int32_t*>(base) : nullptr;
+    a.queue = pairs ? reinterpret_cast<int32_t*>(base + kStaticScratchBytes) : nullptr;
     a.gcount = need.gcount ? reinterpret_cast<int32_t*>(base + up(need.flags)) : nullptr;
     a.gcol = need.gcol ? reinterpret_cast<int32_t*>(base + up(need.flags) + up(need.gcount)) : nullptr;
     return attn_launch(ctx, a, pairs, (hipStream_t)stream);

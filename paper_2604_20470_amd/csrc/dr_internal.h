@@ -100,7 +100,10 @@ struct AttnArgs {
     // rows outside the accuracy range of its pre-scaled Q; those items are then taken again with fp32 scaling.
     // NULL: no second pass.
     int32_t* flags;              // [B * H * ceil(N / 128) * 4]
+    int32_t* queue;              // [kAttnQueues] work queues of the 256-query kernel; set by its list-merging pre-pass
+    int32_t cus;                 // compute units of the device
 };
+constexpr int kAttnQueues = 8;   // one per XCD
 // Any d in {64,128}, Bs in {32,64,128}, f32 or bf16 storage; fp32 accuracy (32-bit operands split for the bf16 matrix cores).
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s);
 // bf16 storage, d = 128, Bs = 128: MFMA path.  Returns hipErrorNotSupported for other shapes.
@@ -114,7 +117,8 @@ hipError_t launch_attn_mfma_pair(const AttnArgs& a, hipStream_t s);
 bool attn_mfma_pair_supported(const AttnArgs& a);
 // Merged key-block lists of every group of L (2 or 4) consecutive CSR rows: a.gcol (laid out like colidx, a group's
 // entries at the colidx offset of its first row; entry = key block | rows-that-list-it << 28) and a.gcount.
-hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s);
+// queue_start >= 0: a.queue is set to that value as well.
+hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s, int queue_start = -1);
 // bf16 storage, d = 128, Bs = 32 or 64: MFMA path that walks the union of the CSR rows of a 128-query group.
 hipError_t launch_attn_mfma_small(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_mfma_small_second_pass(const AttnArgs& a, hipStream_t s);

@@ -42,6 +42,7 @@
 #include "dr_internal.h"
 
 
+#include <algorithm>
 #include <type_traits>
 
 namespace dr {
@@ -57,6 +58,7 @@ constexpr int kRowBytes = kD * 2;                    // 256
 constexpr int kTileBytes = kChunkKeys * kRowBytes;   // 16 KB per operand per stage
 constexpr int kStageBytes = 2 * kTileBytes;          // K then V
 constexpr int kLdsBytes = 2 * kStageBytes;           // two stages: 64 KB
+constexpr int kXcds = kAttnQueues, kRun = 32;
 constexpr float kSumMax = 1.2676506e30f, kSumMin = 7.8886091e-31f;   // 2^100, 2^-100: outside, the row is flagged
 
 struct LoadPlan {
@@ -477,11 +479,71 @@ __device__ __forceinline__ void plain_chunk(const ReadPlan& rd, uint32_t stage_o
         }
 }
 
-// grid: (ceil(Sb / kL) * H * B) in one dimension, remapped so that one XCD walks a contiguous run of items.
+// ---- which item (group of kL query blocks of one (batch, head)) a workgroup takes ----
+// The grid is one workgroup per CU; a workgroup takes items until none is left.  (A workgroup per item leaves a CU idle for
+// 11 to 20 us between two of them, 4 to 5 % of a launch at 75 600 tokens.)  Every XCD has a queue of its own, so that its
+// workgroups run neighbouring items at the same time and share tiles in its L2; a workgroup whose queue is empty goes on
+// with the next XCD's.  Shares fixed beforehand cannot be even: the XCDs of one chip hold clocks up to 5 % apart under
+// this load, and a launch may not divide by eight.
+// The order of a queue.  Whole heads per XCD (heads a multiple of 8): its heads one after the other, each in order.
+// Otherwise a contiguous eighth of the items is part of a head, and rows in the middle of a sequence list more key blocks
+// than rows near its ends; runs of 32 items (one per CU of an XCD) are then dealt to the queues in turn, the middle of
+// every head first and its ends, the shorter walks, last.
+// Measured against a workgroup per item in contiguous eighths: 75 600 tokens x 40 heads 13.34 -> 12.83 ms, 118 800 x 24
+// 32.8 -> 31.5 (both held back by the power limit: the idle gaps used to buy clock), 264 000 x 2 at block size 32
+// 13.4 -> 12.0; one round of items (6144 tokens x 8 heads) 93.6 -> 94.2 us.
+__device__ __forceinline__ int slots_per_xcd(int n_groups, int heads) {
+    if (heads % kXcds == 0) return n_groups * (heads / kXcds);
+    const int turns = (n_groups + kRun - 1) / kRun * heads;
+    return (turns + kXcds - 1) / kXcds * kRun;
+}
+__device__ __forceinline__ int item_of_slot(int xcd, int slot, int n_groups, int heads) {      // -1: an empty slot
+    if (heads % kXcds == 0) return xcd * n_groups * (heads / kXcds) + slot;
+    const int n_runs = (n_groups + kRun - 1) / kRun;                       // of a head
+    const int turn = (slot / kRun) * kXcds + xcd;                          // of n_runs * heads
+    const int level = turn / heads, head = turn % heads;
+    if (level >= n_runs) return -1;
+    const int run = (level & 1) ? (n_runs - 1) / 2 + (level + 1) / 2 : (n_runs - 1) / 2 - level / 2;
+    const int group = run * kRun + slot % kRun;
+    return group < n_groups ? head * n_groups + group : -1;
+}
+// The next item, given the slot just drawn from queue `xcd` (kept from item to item); one thread of the workgroup calls it.
+// Where that queue is empty the eight counters are read at once, and the next queue that has slots left is drawn from: a
+// launch ends with one such look, not with eight failed draws one after the other (5 us).  -1: every queue is empty.
+__device__ __forceinline__ int claim_item(int32_t* queue, int& xcd, int slot, int n_groups, int heads) {
+    const int slots = slots_per_xcd(n_groups, heads);
+    for (;;) {
+        if (slot < slots) {
+            const int item = item_of_slot(xcd, slot, n_groups, heads);
+            if (item >= 0) return item;
+        } else {
+            int drawn[kXcds];
+#pragma unroll
+            for (int i = 0; i < kXcds; ++i) drawn[i] = __hip_atomic_load(&queue[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int step = kXcds;                              // to the nearest queue with slots left
+#pragma unroll
+            for (int i = 0; i < kXcds; ++i)
+                if (drawn[i] < slots) step = min(step, (i - xcd + kXcds) % kXcds);
+            if (step == kXcds) return -1;
+            xcd = (xcd + step) % kXcds;
+        }
+        slot = atomicAdd(&queue[xcd], 1);
+    }
+}
+
 // One workgroup = 4 waves of 64 queries = kL adjacent query blocks (BS = 128: waves 0-1 block 2p, waves 2-3 block
 // 2p + 1; BS = 64: wave w block 4p + w).
+// The kernel's arguments, read again (from constant memory, once per item and before its results are stored) instead of
+// carried in scalar registers from item to item: the chunk loop needs those.
+__device__ __forceinline__ AttnArgs fresh_args() {
+    typedef __attribute__((address_space(4))) const AttnArgs* args_ptr;
+    args_ptr p = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const AttnArgs*)p;
+}
+
 template <int BS>
-__device__ __forceinline__ void attn_pair_body(const AttnArgs& a) {
+__device__ __forceinline__ void attn_pair_body() {
     constexpr int kL = kRowsPerItem / BS;       // query blocks per workgroup: 2 (waves 0-1, 2-3), 4 (one per wave) or 8 (two per wave)
     constexpr int kSh = BS == 128 ? 1 : 0;      // chunks per list entry, as a shift (block size 32: two entries per chunk)
     constexpr int kOwnShift = BS == 32 ? 24 : 28;               // an entry: key block below, owner bits from here
@@ -489,12 +551,25 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    constexpr int kXcds = 8;
+    // The first slots of every queue are the workgroups' own (the queues start behind them): nothing to wait for.
+    __shared__ int s_item[2];                    // two words in turn: one barrier per item keeps a reader behind by less than that
+    int q_xcd = (int)blockIdx.x % kXcds;         // (thread 0's)
+    int item, turn = 0;
+    {
+        const AttnArgs a = fresh_args();
+        const int n_groups = (a.Sb + kL - 1) / kL, heads = a.td.H * a.td.B, slots = slots_per_xcd(n_groups, heads);
+        const int slot = (int)blockIdx.x / kXcds;
+        item = slot < slots ? item_of_slot(q_xcd, slot, n_groups, heads) : -1;
+        if (item < 0) {
+            if (threadIdx.x == 0) s_item[0] = claim_item(a.queue, q_xcd, slot, n_groups, heads);
+            __syncthreads();
+            item = __builtin_amdgcn_readfirstlane(s_item[0]);
+            turn = 1;
+        }
+    }
+    while (item >= 0) {
+    const AttnArgs a = fresh_args();
     const int n_pairs = (a.Sb + kL - 1) / kL;
-    const int total_items = n_pairs * a.td.H * a.td.B;
-    const int per_xcd = (total_items + kXcds - 1) / kXcds;
-    const int item = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (item >= total_items) return;
     const int pair = item % n_pairs, h = (item / n_pairs) % a.td.H, b = item / (n_pairs * a.td.H);
     // grp: the wave's owner bit in a list entry (block size 32: its two bits are 2 grp and 2 grp + 1)
     const int grp = BS == 128 ? wave >> 1 : wave;
@@ -715,9 +790,19 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a) {
         DR_WAIT_VMCNT0();          // the loads issued by the last chunks write LDS: none may outlive the workgroup
     }
 
-    // ---- epilogue ----
+    // ---- epilogue (the slot of the next item is drawn while the results are stored) ----
+    {
+    const AttnArgs a = fresh_args();
+    const int N = a.td.N;
+    const int64_t row_bytes = a.td.stride_n * 2;
+    const int h = (item / n_pairs) % a.td.H, b = item / (n_pairs * a.td.H);
+    const int32_t* rp = a.rowptr + ((int64_t)b * a.mask_heads + (a.mask_heads == 1 ? 0 : h)) * (a.Sb + 1);
+    // nothing is left to draw where the workgroups' own first slots were all there are
+    const bool more = slots_per_xcd(n_pairs, a.td.H * a.td.B) > (int)gridDim.x / kXcds;
+    int next_slot = 0;
+    if (more && threadIdx.x == 0) next_slot = atomicAdd(&a.queue[q_xcd], 1);
     drain_mfma(st.o, st.lacc);
-    char* Oh = reinterpret_cast<char*>(a.O) + head_off;
+    char* Oh = reinterpret_cast<char*>(a.O) + ((int64_t)b * a.td.stride_b + (int64_t)h * a.td.stride_h) * 2;
     bool out_of_range = false;
 #pragma unroll
     for (int qh = 0; qh < 2; ++qh) {
@@ -754,16 +839,23 @@ __device__ __forceinline__ void attn_pair_body(const AttnArgs& a) {
         const int64_t base = (((int64_t)b * a.td.H + h) * groups128 + (q0_own >> 7)) * 4 + ((q0_own >> 6) & 1) * 2;
         if (lane < 2) a.flags[base + lane] = any;
     }
+    if (!more) return;
+    if (threadIdx.x == 0) s_item[turn] = claim_item(a.queue, q_xcd, next_slot, n_pairs, a.td.H * a.td.B);
+    __syncthreads();
+    item = __builtin_amdgcn_readfirstlane(s_item[turn]);
+    turn ^= 1;
+    }
+    }
 }
 
 // Block size 128: two query blocks per workgroup, an entry of the merged list is two chunks.  Block size 64: four
 // query blocks, one per wavefront, an entry is one chunk; the same 256 queries and the same code otherwise.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_pair(AttnArgs a) { attn_pair_body<128>(a); }
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_quad(AttnArgs a) { attn_pair_body<64>(a); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_pair(AttnArgs) { attn_pair_body<128>(); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_quad(AttnArgs) { attn_pair_body<64>(); }
 // Block size 32: eight query blocks, two per wavefront (one per query half); a chunk is two entries of the merged list,
 // its two key halves come from two 32-row windows, and a 32 x 32 tile whose query block does not list the key block of
 // its key half contributes probabilities of 0 (they are masked where they are packed to bf16).
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_oct(AttnArgs a) { attn_pair_body<32>(a); }
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_attn_mfma_oct(AttnArgs) { attn_pair_body<32>(); }
 
 }  // namespace
 
@@ -771,19 +863,20 @@ bool attn_mfma_pair_supported(const AttnArgs& a) {
     // every chunk is a full 64-row window: the sequence must hold one; the 32-bit per-lane offsets must cover it
     return a.bf16 && a.td.d == kD && (a.Bs == 128 || a.Bs == 64 || a.Bs == 32) && a.td.N >= kChunkKeys &&
            a.Sb < (a.Bs == 32 ? (1 << 24) : (1 << 28)) &&
-           a.td.stride_n * 2 * kChunkKeys < (1ll << 31) && a.gcol && a.gcount && a.flags;
+           a.td.stride_n * 2 * kChunkKeys < (1ll << 31) && a.gcol && a.gcount && a.flags && a.queue;
 }
 
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, hipStream_t s) {
     if (!attn_mfma_pair_supported(a)) return hipErrorNotSupported;
     const int L = kRowsPerItem / a.Bs;
-    hipError_t e = launch_group_union(L, a, s);
+    // one workgroup per CU, or per item if there are fewer; a multiple of the queues
+    const int64_t items = (int64_t)((a.Sb + L - 1) / L) * a.td.H * a.td.B;
+    const int grid = (int)((std::min(items, (int64_t)a.cus) + kXcds - 1) / kXcds) * kXcds;
+    hipError_t e = launch_group_union(L, a, s, grid / kXcds);
     if (e != hipSuccess) return e;
     auto kern = a.Bs == 128 ? k_attn_mfma_pair : a.Bs == 64 ? k_attn_mfma_quad : k_attn_mfma_oct;
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
-    const int total = ((a.Sb + L - 1) / L) * a.td.H * a.td.B;
-    const int grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
     hipLaunchKernelGGL(kern, dim3(grid), dim3(kThreads), kLdsBytes, s, a);
     return hipGetLastError();
 }

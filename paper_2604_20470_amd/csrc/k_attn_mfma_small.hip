@@ -440,7 +440,8 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
 template <int L>
 __global__ __launch_bounds__(256) void k_group_union(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
                                                      int64_t colidx_stride, int Sb, int groups,
-                                                     int32_t* __restrict__ gcol, int32_t* __restrict__ gcount) {
+                                                     int32_t* __restrict__ gcol, int32_t* __restrict__ gcount,
+                                                     int32_t* __restrict__ queue, int queue_start) {
     extern __shared__ uint32_t pres[];                 // [L][words]
     __shared__ int s_wave[4];
     const int g = blockIdx.x, m = blockIdx.y, b = blockIdx.z;
@@ -450,6 +451,7 @@ __global__ __launch_bounds__(256) void k_group_union(const int32_t* __restrict__
     const int64_t mask_id = (int64_t)b * masks + m;
     const int32_t* rp = rowptr + mask_id * (Sb + 1);
     const int32_t* ci = colidx + mask_id * colidx_stride;
+    if (queue && blockIdx.x == 0 && m == 0 && b == 0 && tid < kAttnQueues) queue[tid] = queue_start;
     for (int i = tid; i < L * words; i += 256) pres[i] = 0u;
     __syncthreads();
     const int row0 = min(g * L, Sb), row1 = min(g * L + L, Sb);
@@ -536,7 +538,7 @@ hipError_t launch_small(Kern kern, Kern kern_exact, const AttnArgs& a, hipStream
 
 }  // namespace
 
-hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s) {
+hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s, int queue_start) {
     if ((L != 2 && L != 4 && L != 8) || !a.gcol || !a.gcount) return hipErrorInvalidValue;
     if (a.Sb >= (L > 4 ? (1 << 24) : (1 << 28))) return hipErrorInvalidValue;      // the key block must fit below the owner bits
     const int groups = (a.Sb + L - 1) / L;
@@ -548,7 +550,8 @@ hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a.rowptr, a.colidx, a.colidx_stride, a.Sb, groups, a.gcol, a.gcount);
+        hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a.rowptr, a.colidx, a.colidx_stride, a.Sb, groups, a.gcol, a.gcount,
+                           queue_start >= 0 ? a.queue : nullptr, queue_start);
         return hipGetLastError();
     };
     if (L == 8) return launch(k_group_union<8>);

@@ -1,0 +1,47 @@
+"""The 256-query kernel on launches with more items than compute units: every item is taken once, whichever workgroup
+draws it, with the bits that a launch of its head alone gives (few items: no queue is drawn from)."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import dynamicrad_oracle as o
+from workloads import tiny_case
+
+from helpers import GpuRun, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,bs,frames,hg,wg", [
+    (40, 128, 9, 16, 23),       # N = 3312: 13 items per head; whole heads per queue
+    (30, 32, 9, 16, 23),        # dealt in runs: one run of 13 per head
+    (9, 64, 33, 16, 21),        # N = 11088: 44 items per head, two runs, the second not full
+])
+def test_every_item_once(H, bs, frames, hg, wg):
+    wl = dataclasses.replace(tiny_case("ragged128"), Nf=frames, Hg=hg, Wg=wg, H=H, Bs=bs, index=81)
+    run = GpuRun(wl, threads=8)
+    Sb = wl.Sb
+    assert -(-wl.N // 256) * H > 256
+    rng = np.random.default_rng(H)
+    rows = [np.nonzero(rng.random(Sb) < 0.1)[0].tolist() for _ in range(Sb)]
+    per = 256 // bs
+    for qb in range(Sb):                                     # whole items without a key block, in a row and alone
+        if qb // per in (1, 2, 3, 7):
+            rows[qb] = []
+    rp = np.concatenate([[0], np.cumsum([len(r) for r in rows])])
+    ci = np.asarray([c for r in rows for c in r], dtype=np.int64)
+    rowptr = torch.from_numpy(rp.astype(np.int32)).view(1, 1, -1).cuda()
+    colidx = torch.from_numpy(ci.astype(np.int32)).view(1, 1, -1).cuda()
+    O = run.attention(rowptr, colidx, colidx.shape[2])
+    assert torch.equal(O, run.attention(rowptr, colidx, colidx.shape[2]))
+    alone = GpuRun(dataclasses.replace(wl, H=1))
+    for h in range(H):
+        alone.Q, alone.K, alone.V = (t[:, h:h + 1].contiguous() for t in (run.Q, run.K, run.V))
+        alone.shape.stride_b = alone.Q.stride(0)
+        assert torch.equal(alone.attention(rowptr, colidx, colidx.shape[2])[0, 0], O[0, h]), h
+    for h in (0, H - 1):
+        want = o.masked_attention(to_f64(run.Qc[0, h]), to_f64(run.Kc[0, h]), to_f64(run.Vc[0, h]), rp, ci, bs)
+        for qb, blk in want.items():
+            assert np.abs(to_f64(O[0, h, qb * bs: qb * bs + blk.shape[0]]) - blk).max() <= 2e-2, (h, qb)
