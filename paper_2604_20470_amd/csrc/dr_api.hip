@@ -55,6 +55,8 @@ struct dr_ctx {
     // token-level order: link bytes [B, masks, N, N] when the caller does not ask for them
     uint8_t* links = nullptr;
     size_t links_bytes = 0;
+    void* link_stats = nullptr;          // column sums and per-frame-pair statistics
+    size_t link_stats_bytes = 0;
     // cached candidate geometry
     uint8_t* class_map = nullptr;
     uint64_t* class_bits = nullptr;      // the classes as lane masks (block rows of at most kWaveSelectMaxBlocks)
@@ -272,7 +274,7 @@ void dr_destroy(dr_ctx* ctx) {
     {
         DeviceGuard g(ctx->device);
         void* ptrs[] = {ctx->pooled, ctx->keepbits, ctx->counts, ctx->class_map, ctx->class_bits, ctx->row_sel, ctx->totals, ctx->gcol,
-                        ctx->gcount, ctx->attn_flags, ctx->attn_queue, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->proxy_partial};
+                        ctx->gcount, ctx->attn_flags, ctx->attn_queue, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->link_stats, ctx->proxy_partial};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
     }
@@ -507,11 +509,13 @@ dr_status dr_build_mask_tokens(dr_ctx* ctx, const dr_shape* shape, double tau_ne
         if ((st = grow(ctx, (void**)&ctx->links, &ctx->links_bytes, need)) != DR_OK) return st;
         links = ctx->links;
     }
+    if ((st = grow(ctx, &ctx->link_stats, &ctx->link_stats_bytes, pair_links_scratch_bytes(shape->B, masks, shape->N, shape->Nf))) != DR_OK)
+        return st;
     FrameTab tab;
     fill_frame_table(shape->Nf, Nt, shape->Bs, p->gamma, lambda, &tab);
     const Geometry geo = make_geometry(shape, p);
     DR_HIP(ctx, launch_pair_links(token_scores, tab, shape->B, masks, shape->N, Nt, shape->Nf, tau_near,
-                                  p->has_tau_far ? p->tau_far : tau_near, links, s));
+                                  p->has_tau_far ? p->tau_far : tau_near, ctx->link_stats, links, s));
     DR_HIP(ctx, launch_aggregate_links(links, ctx->class_map, geo, shape->B, masks, ctx->keepbits, ctx->counts, s));
     DR_HIP(ctx, launch_emit(ctx->keepbits, ctx->counts, shape->B, masks, Sb, false, rowptr, colidx, colidx_capacity, nnz, s));
     return DR_OK;

@@ -1,6 +1,6 @@
 // Algorithm 1 of the paper in its own order, for small sequences (an evaluation aid beside the block-level path):
 //   k_token_scores     proxy score of every token pair (Eq. 9, fused-head mean of App. B) -> fp32 [N, N]
-//   k_pair_links       per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
+//   k_link_*, k_links  per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
 //                      it (Eq. 10), z >= tau_1 / tau_2 by decay state (Eq. 11), keep-one safeguard -> link bytes [N, N]
 //   k_aggregate_links  density rule per block pair ("Density control within blocks": a column is active when its
 //                      kept-row ratio exceeds theta_c, the block when its active-column ratio exceeds theta_m), plus the
@@ -81,157 +81,252 @@ __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restric
 
 #pragma clang fp contract(off)
 
-struct Best {
-    float s;
-    int idx;      // u * Nt + v, row-major inside the frame pair; -1: none
+// ---- links of every ordered frame pair, in five small launches.  What bounds this is the serial fp64 chain of a column
+// (the order of the sums is part of the definition) and three readings of the score matrix, so the columns of all pairs
+// are spread over the whole chip: a wavefront owns 64 key columns of one pair and reads whole row segments, sixteen rows
+// in flight.  (One workgroup per pair, 64 of them at 8 frames, left three quarters of the CUs idle: 1.85 ms at 8 x 1024
+// tokens, where the five launches take 0.144 ms: 24, 36, 16, 64 and 5 us.)
+//   k_link_sums<0>  column sums of the scores            k_link_sums<1>  of the squared deviations
+//   k_link_stats    deviation, and the test as one float   k_links  bytes, number of links, best score   k_link_safeguard
+struct PairStat {
+    double mu;
+    unsigned long long best;      // order-preserving image of the best score << 32 | ~(u * Nt + v)
+    float threshold;              // a pair is a link when its score is at least this
+    unsigned int kept;
 };
-__device__ __forceinline__ Best better(Best a, Best b) {
-    if (b.idx < 0) return a;
-    if (a.idx < 0) return b;
-    if (b.s > a.s || (b.s == a.s && b.idx < a.idx)) return b;
-    return a;
+
+__device__ __forceinline__ uint32_t score_image(float s) {      // ascending unsigned == ascending float, -0 below +0
+    const uint32_t u = __float_as_uint(s);
+    return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float image_score(uint32_t u) { return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u); }
+
+struct PairAt {
+    int i, j, t, w, flags;
+    int64_t mask, pair;           // (b, m) flattened; index into per-pair arrays
+    bool judged;                  // t >= 2 and retained: its links are decided by score
+};
+__device__ __forceinline__ PairAt pair_at(const FrameTab& tab, int Nf, int pair) {
+    PairAt p;
+    p.i = pair / Nf;
+    p.j = pair % Nf;
+    p.t = abs(p.i - p.j);
+    p.flags = tab.flags[p.t];
+    p.w = tab.w[p.t];
+    p.mask = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
+    p.pair = p.mask * Nf * Nf + pair;
+    p.judged = p.t > 1 && (p.flags & 1);
+    return p;
 }
 
-// grid: (Nf * Nf, masks, B).  LDS: Nt doubles (column sums).
-__global__ __launch_bounds__(kThreads) void k_pair_links(const float* __restrict__ scores, FrameTab tab, int N, int Nt,
-                                                         int Nf, double tau_near, double tau_far,
-                                                         uint8_t* __restrict__ links) {
-    extern __shared__ double colsum[];
-    __shared__ double s_stat[2];
-    __shared__ unsigned long long s_kept;
-    __shared__ float s_best_val[kThreads];
-    __shared__ int s_best_idx[kThreads];
-    const int i = blockIdx.x / Nf, j = blockIdx.x % Nf;
-    const int tid = threadIdx.x;
-    const int64_t plane = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * N * N;
-    const float* S = scores + plane + (int64_t)i * Nt * N + (int64_t)j * Nt;
-    uint8_t* L = links + plane + (int64_t)i * Nt * N + (int64_t)j * Nt;
-    const int t = i > j ? i - j : j - i;
-    const int flags = tab.flags[t];
-    if (t <= 1 || !(flags & 1)) {
-        const uint8_t fill = t <= 1 ? 1 : 0;
-        for (int u = 0; u < Nt; ++u)
-            for (int v = tid; v < Nt; v += kThreads) L[(int64_t)u * N + v] = fill;
-        return;
-    }
-    const int w = tab.w[t];
-    const double tau = ((flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
-    // ---- mean: column sums (u ascending), then across columns (v ascending)
-    for (int v = tid; v < Nt; v += kThreads) {
-        const int lo = max(0, v - w), hi = min(Nt - 1, v + w);
-        double acc = 0.0;
-        for (int u = lo; u <= hi; ++u) acc = acc + (double)S[(int64_t)u * N + v];
-        colsum[v] = acc;
-    }
+// The sum of Nt doubles, one by one in ascending order (every lane gets it).  LDS: Nt doubles.
+__device__ __forceinline__ double ordered_sum(const double* __restrict__ col, int Nt, double* sh) {
+    for (int v = threadIdx.x; v < Nt; v += 64) sh[v] = col[v];
     __syncthreads();
-    if (tid == 0) {
-        double total = 0.0;
-        long long n = 0;
-        for (int v = 0; v < Nt; ++v) {
-            total = total + colsum[v];
-            n += min(Nt - 1, v + w) - max(0, v - w) + 1;
-        }
-        s_stat[0] = total / (double)n;
-        s_stat[1] = (double)n;
-        s_kept = 0ull;
+    double total = 0.0;
+    int v = 0;
+    for (; v + 8 <= Nt; v += 8) {
+        double x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = sh[v + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) total = total + x[e];
     }
-    __syncthreads();
-    const double mu = s_stat[0];
-    // ---- standard deviation, same order
-    for (int v = tid; v < Nt; v += kThreads) {
-        const int lo = max(0, v - w), hi = min(Nt - 1, v + w);
-        double acc = 0.0;
-        for (int u = lo; u <= hi; ++u) {
-            const double dev = (double)S[(int64_t)u * N + v] - mu;
+    for (; v < Nt; ++v) total = total + sh[v];
+    return total;
+}
+__device__ __forceinline__ double window_size(int Nt, int w) {      // token pairs of a candidate set
+    long long n = 0;
+    for (int v = threadIdx.x; v < Nt; v += 64) n += min(Nt - 1, v + w) - max(0, v - w) + 1;
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
+    return (double)n;
+}
+
+// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs: [B * masks][Nf * Nf][Nt].
+// A column's rows are walked over the union of the wavefront's windows, so that all lanes read one row; a row outside a
+// lane's own window adds +0.0, which leaves its running sum bit for bit as it is (it starts at +0.0 and is never -0.0).
+template <int PASS>
+__global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
+                                                  double* __restrict__ sums, double* __restrict__ devs, PairStat* __restrict__ stats) {
+    extern __shared__ double sh[];
+    const int tiles = (Nt + 63) / 64;
+    const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
+    const PairAt p = pair_at(tab, Nf, pair);
+    if (!p.judged) return;
+    double mu = 0.0;
+    if constexpr (PASS == 1) {
+        mu = ordered_sum(sums + p.pair * Nt, Nt, sh) / window_size(Nt, p.w);
+        if (v0 == 0 && threadIdx.x == 0) stats[p.pair].mu = mu;
+    }
+    const int v = v0 + (int)threadIdx.x, vc = min(v, Nt - 1);
+    const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
+    const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, min(v0 + 63, Nt - 1) + p.w);      // of the wavefront
+    const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt + vc;
+    double acc = 0.0;
+    auto add = [&](float s, int u) {
+        if constexpr (PASS == 0) {
+            acc = acc + ((u >= lo && u <= hi) ? (double)s : 0.0);
+        } else {
+            const double dev = (double)s - mu;
             const double sq = dev * dev;
-            acc = acc + sq;
+            acc = acc + ((u >= lo && u <= hi) ? sq : 0.0);
         }
-        colsum[v] = acc;
+    };
+    int u = u_first;
+    constexpr int kAhead = 16;
+    for (; u + kAhead - 1 <= u_last; u += kAhead) {
+        float x[kAhead];
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) x[e] = S[(int64_t)(u + e) * N];
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) add(x[e], u + e);
     }
-    __syncthreads();
-    if (tid == 0) {
-        double total = 0.0;
-        for (int v = 0; v < Nt; ++v) total = total + colsum[v];
-        s_stat[0] = sqrt(total / s_stat[1]) + 1e-6;
-    }
-    __syncthreads();
-    const double denom = s_stat[0];
-    // ---- threshold, link bytes for the whole Nt x Nt tile, and the best score for the safeguard
-    unsigned long long kept = 0;
-    Best best{0.f, -1};
-    for (int v = tid; v < Nt; v += kThreads) {
-        const int lo = max(0, v - w), hi = min(Nt - 1, v + w);
-        for (int u = 0; u < Nt; ++u) {
-            uint8_t keep = 0;
-            if (u >= lo && u <= hi) {
-                const float s = S[(int64_t)u * N + v];
-                keep = (((double)s - mu) / denom >= tau) ? 1 : 0;
-                kept += keep;
-                best = better(best, Best{s, u * Nt + v});
-            }
-            L[(int64_t)u * N + v] = keep;
-        }
-    }
-    if (kept) atomicAdd(&s_kept, kept);
-    s_best_val[tid] = best.s;
-    s_best_idx[tid] = best.idx;
-    __syncthreads();
-    if (s_kept != 0ull) return;
-    // nothing passed: keep the highest score of the set (first in row-major order on ties)
-    for (int off = kThreads / 2; off > 0; off >>= 1) {
-        if (tid < off) {
-            const Best r = better(Best{s_best_val[tid], s_best_idx[tid]}, Best{s_best_val[tid + off], s_best_idx[tid + off]});
-            s_best_val[tid] = r.s;
-            s_best_idx[tid] = r.idx;
-        }
-        __syncthreads();
-    }
-    if (tid == 0 && s_best_idx[0] >= 0) L[(int64_t)(s_best_idx[0] / Nt) * N + (s_best_idx[0] % Nt)] = 1;
+    for (; u <= u_last; ++u) add(S[(int64_t)u * N], u);
+    if (v < Nt) (PASS == 0 ? sums : devs)[p.pair * Nt + v] = acc;
 }
 
-// grid: (Sb, masks, B).  LDS: words uint32 (the row's keep bitmap).
+// grid: (Nf * Nf, masks, B), 64 threads.  The test ((double)s - mu) / denom >= tau is monotone in s (IEEE subtraction and
+// division are), so the smallest float that passes, found by bisection over the floats in order, decides it exactly.
+__global__ __launch_bounds__(64) void k_link_stats(FrameTab tab, int Nt, int Nf, double tau_near, double tau_far,
+                                                   const double* __restrict__ devs, PairStat* __restrict__ stats) {
+    extern __shared__ double sh[];
+    const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
+    if (!p.judged) return;
+    const double denom = sqrt(ordered_sum(devs + p.pair * Nt, Nt, sh) / window_size(Nt, p.w)) + 1e-6;
+    if (threadIdx.x != 0) return;
+    const double mu = stats[p.pair].mu;
+    const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
+    uint32_t lo = score_image(-3.402823466e38f), hi = score_image(3.402823466e38f) + 1u;      // first image that passes; hi: none
+    while (lo < hi) {
+        const uint32_t mid = lo + (hi - lo) / 2;
+        if (((double)image_score(mid) - mu) / denom >= tau) hi = mid;
+        else lo = mid + 1u;
+    }
+    stats[p.pair].threshold = image_score(lo);      // + infinity when no float passes
+    stats[p.pair].kept = 0u;
+    stats[p.pair].best = 0ull;
+}
+
+// grid: (Nf * Nf * ceil(Nt / kLinkRows), masks, B).  A thread takes four consecutive key columns of a row at a time.
+constexpr int kLinkRows = 16;
+__global__ __launch_bounds__(kThreads) void k_links(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
+                                                    PairStat* __restrict__ stats, uint8_t* __restrict__ links) {
+    __shared__ unsigned long long s_best[kThreads / 64];
+    __shared__ unsigned int s_kept[kThreads / 64];
+    const int tiles = (Nt + kLinkRows - 1) / kLinkRows;
+    const PairAt p = pair_at(tab, Nf, (int)(blockIdx.x / tiles));
+    const int u0 = (int)(blockIdx.x % tiles) * kLinkRows, rows = min(kLinkRows, Nt - u0);
+    const int64_t at0 = p.mask * N * N + ((int64_t)p.i * Nt + u0) * N + (int64_t)p.j * Nt;
+    const int quads = (Nt + 3) / 4;
+    const float threshold = p.judged ? stats[p.pair].threshold : 0.f;
+    unsigned int kept = 0u;
+    unsigned long long best = 0ull;
+    for (int q = threadIdx.x; q < rows * quads; q += kThreads) {
+        const int r = q / quads, v = (q - r * quads) * 4, n = min(4, Nt - v), u = u0 + r;
+        const int64_t at = at0 + (int64_t)r * N + v;
+        uint8_t out[4] = {0, 0, 0, 0};
+        if (p.t <= 1) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) out[e] = 1;
+        } else if (p.judged) {
+            float s[4] = {0.f, 0.f, 0.f, 0.f};
+            if (n == 4) __builtin_memcpy(s, scores + at, 16);      // (4-byte aligned)
+            else for (int e = 0; e < n; ++e) s[e] = scores[at + e];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (e < n && abs(u - (v + e)) <= p.w) {
+                    out[e] = s[e] >= threshold ? 1 : 0;
+                    kept += out[e];
+                    const unsigned long long key = ((unsigned long long)score_image(s[e] + 0.0f) << 32) | (0xffffffffu - (uint32_t)(u * Nt + v + e));
+                    best = max(best, key);
+                }
+            }
+        }
+        if (n == 4) __builtin_memcpy(links + at, out, 4);
+        else for (int e = 0; e < n; ++e) links[at + e] = out[e];
+    }
+    if (!p.judged) return;
+    for (int off = 32; off > 0; off >>= 1) {
+        kept += __shfl_xor(kept, off);
+        best = max(best, (unsigned long long)__shfl_xor(best, off));
+    }
+    if ((threadIdx.x & 63) == 0) { s_kept[threadIdx.x >> 6] = kept; s_best[threadIdx.x >> 6] = best; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < kThreads / 64; ++i) { kept += s_kept[i]; best = max(best, s_best[i]); }
+        if (kept) atomicAdd(&stats[p.pair].kept, kept);
+        if (best) atomicMax(&stats[p.pair].best, best);
+    }
+}
+
+// A pair of frames in which nothing passed keeps the highest score of its set (the first in row-major order on ties).
+// grid: (ceil(Nf * Nf / 64), masks, B), 64 threads
+__global__ __launch_bounds__(64) void k_link_safeguard(FrameTab tab, int N, int Nt, int Nf, const PairStat* __restrict__ stats,
+                                                       uint8_t* __restrict__ links) {
+    const int pair = (int)(blockIdx.x * 64 + threadIdx.x);
+    if (pair >= Nf * Nf) return;
+    const PairAt p = pair_at(tab, Nf, pair);
+    if (!p.judged || stats[p.pair].kept != 0u) return;
+    const int idx = (int)(0xffffffffu - (uint32_t)stats[p.pair].best), u = idx / Nt, v = idx % Nt;
+    links[p.mask * N * N + ((int64_t)p.i * Nt + u) * N + (int64_t)p.j * Nt + v] = 1;
+}
+
+// Density rule.  One workgroup per query block; a thread sums the link bytes of sixteen consecutive key columns over the
+// block's rows, four to a 32-bit word (a count is at most 128), so that a wavefront reads 1 KB runs; the threads of a key
+// block then add their numbers of active columns.  Bound by reading the link bytes once.  (A lane per column, one byte at a
+// time and half the lanes idle at block size 32, took 380 us at 8192 tokens; this takes 20.)
+// grid: (Sb, masks, B).
 __global__ __launch_bounds__(kThreads) void k_aggregate_links(const uint8_t* __restrict__ links,
                                                               const uint8_t* __restrict__ class_map, Geometry g,
                                                               uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
-    extern __shared__ uint32_t bitmap[];
+    constexpr int kCols = 16 * kThreads;                    // columns of a step: 32, 64 or 128 key blocks
+    __shared__ uint32_t s_bits[4];
     __shared__ int s_count;
-    const int qb = blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int qb = blockIdx.x, tid = threadIdx.x;
     const int words = (g.Sb + 31) / 32;
     const int64_t mask_id = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
-    const uint8_t* L = links + mask_id * g.N * g.N;
-    for (int i = tid; i < words; i += kThreads) bitmap[i] = 0u;
-    if (tid == 0) s_count = 0;
-    __syncthreads();
-    const int r0 = qb * g.Bs, nr = min(g.Bs, g.N - r0);
-    const int row_min = nr == g.Bs ? g.row_min_full : g.row_min_tail;
-    int mine = 0;
-    for (int kb = wave; kb < g.Sb; kb += kThreads / 64) {
-        bool keep;
-        if (class_map[(int64_t)qb * g.Sb + kb] == 3) {          // holds a token pair with t <= 1
-            keep = true;
-        } else {
-            const int c0 = kb * g.Bs, nc = min(g.Bs, g.N - c0);
-            const int col_min = nc == g.Bs ? g.col_min_full : g.col_min_tail;
-            int active = 0;
-            for (int c = lane; c < nc; c += 64) {
-                int cnt = 0;
-                for (int r = 0; r < nr; ++r) cnt += L[(int64_t)(r0 + r) * g.N + c0 + c];
-                active += cnt >= row_min ? 1 : 0;
-            }
-            for (int off = 32; off > 0; off >>= 1) active += __shfl_down(active, off);
-            active = __shfl(active, 0);
-            keep = active >= col_min;
-        }
-        if (keep && lane == 0) {
-            atomicOr(&bitmap[kb >> 5], 1u << (kb & 31));
-            ++mine;
-        }
-    }
-    if (lane == 0 && mine) atomicAdd(&s_count, mine);
-    __syncthreads();
     const int64_t row = mask_id * g.Sb + qb;
-    for (int i = tid; i < words; i += kThreads) keepbits[row * words + i] = bitmap[i];
+    const int r0 = qb * g.Bs, nr = min(g.Bs, g.N - r0);
+    const uint8_t* L = links + mask_id * g.N * g.N + (int64_t)r0 * g.N;
+    const int row_min = nr == g.Bs ? g.row_min_full : g.row_min_tail;
+    const int per_block = g.Bs / 16;                        // threads of a key block: 2, 4 or 8
+    if (tid == 0) s_count = 0;
+    for (int c_step = 0; c_step < g.N; c_step += kCols) {
+        if (tid < 4) s_bits[tid] = 0u;
+        __syncthreads();
+        const int c = c_step + tid * 16, n = min(16, g.N - c);      // n <= 0: past the last column
+        uint32_t cnt[4] = {0u, 0u, 0u, 0u};
+        if (n == 16) {
+#pragma unroll 8
+            for (int r = 0; r < nr; ++r) {
+                uint32_t x[4];
+                __builtin_memcpy(x, L + (int64_t)r * g.N + c, 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) cnt[e] += x[e];
+            }
+        } else {
+            for (int e = 0; e < n; ++e)
+                for (int r = 0; r < nr; ++r) cnt[e >> 2] += (uint32_t)L[(int64_t)r * g.N + c + e] << (8 * (e & 3));
+        }
+        int active = 0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) active += (e < n && (int)((cnt[e >> 2] >> (8 * (e & 3))) & 255u) >= row_min) ? 1 : 0;
+        for (int off = 1; off < per_block; off <<= 1) active += __shfl_xor(active, off);
+        const int kb = c / g.Bs;
+        if (kb < g.Sb && tid % per_block == 0) {
+            const int nc = min(g.Bs, g.N - kb * g.Bs);
+            const int col_min = nc == g.Bs ? g.col_min_full : g.col_min_tail;
+            // a block that holds a token pair with t <= 1 is kept whatever its density
+            if (class_map[(int64_t)qb * g.Sb + kb] == 3 || active >= col_min) atomicOr(&s_bits[(kb - c_step / g.Bs) >> 5], 1u << (kb & 31));
+        }
+        __syncthreads();
+        const int w0 = c_step / g.Bs / 32, n_words = kCols / g.Bs / 32;
+        if (tid < n_words && w0 + tid < words) {
+            keepbits[row * words + w0 + tid] = s_bits[tid];
+            atomicAdd(&s_count, __popc(s_bits[tid]));
+        }
+        __syncthreads();
+    }
     if (tid == 0) counts[row] = s_count;
 }
 
@@ -246,18 +341,28 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
     return hipGetLastError();
 }
 
+size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf) {
+    return (size_t)B * masks * ((size_t)2 * Nf * N * sizeof(double) + (size_t)Nf * Nf * sizeof(PairStat));
+}
+
 hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, int masks, int N, int Nt, int Nf,
-                             double tau_near, double tau_far, uint8_t* links, hipStream_t s) {
-    hipLaunchKernelGGL(k_pair_links, dim3(Nf * Nf, masks, B), dim3(kThreads), (size_t)Nt * sizeof(double), s, scores, tab,
-                       N, Nt, Nf, tau_near, tau_far, links);
+                             double tau_near, double tau_far, void* scratch, uint8_t* links, hipStream_t s) {
+    double* sums = static_cast<double*>(scratch);
+    double* devs = sums + (size_t)B * masks * Nf * N;
+    PairStat* stats = reinterpret_cast<PairStat*>(devs + (size_t)B * masks * Nf * N);
+    const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64, rows = (Nt + kLinkRows - 1) / kLinkRows;
+    const size_t lds = (size_t)Nt * sizeof(double);
+    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, stats);
+    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, stats);
+    hipLaunchKernelGGL(k_link_stats, dim3(pairs, masks, B), dim3(64), lds, s, tab, Nt, Nf, tau_near, tau_far, devs, stats);
+    hipLaunchKernelGGL(k_links, dim3(pairs * rows, masks, B), dim3(kThreads), 0, s, scores, tab, N, Nt, Nf, stats, links);
+    hipLaunchKernelGGL(k_link_safeguard, dim3((pairs + 63) / 64, masks, B), dim3(64), 0, s, tab, N, Nt, Nf, stats, links);
     return hipGetLastError();
 }
 
 hipError_t launch_aggregate_links(const uint8_t* links, const uint8_t* class_map, const Geometry& g, int B, int masks,
                                   uint32_t* keepbits, int32_t* counts, hipStream_t s) {
-    const int words = (g.Sb + 31) / 32;
-    hipLaunchKernelGGL(k_aggregate_links, dim3(g.Sb, masks, B), dim3(kThreads), (size_t)words * 4, s, links, class_map, g,
-                       keepbits, counts);
+    hipLaunchKernelGGL(k_aggregate_links, dim3(g.Sb, masks, B), dim3(kThreads), 0, s, links, class_map, g, keepbits, counts);
     return hipGetLastError();
 }
 

@@ -1,0 +1,34 @@
+"""Token-level links and their aggregation where a row is longer than one step of the aggregation (4096 columns), frames are
+no multiple of a wavefront, and rows are aligned to nothing: bit for bit against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_20470_amd as dr
+from oracle import dynamicrad_oracle as o
+from workloads import Workload
+
+from helpers import GpuRun, assert_masks_equal
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("bs", [32, 64, 128])
+@pytest.mark.parametrize("frames,hg,wg,tau", [(5, 31, 33, 0.2), (9, 3, 157, 60.0)])      # N = 5115 and 4239; the second: safeguard only
+def test_links_and_masks_bit_exact(bs, frames, hg, wg, tau):
+    wl = Workload("wide", 91, 1, 1, 64, frames, hg, wg, bs, "f32", "field", "dynamic", 0.5, 0.9, 1.0, head_fuse=1)
+    run = GpuRun(wl, params=dr.MaskParams(gamma=1.5, head_fuse=1))
+    scores = torch.empty((1, 1, wl.N, wl.N), dtype=torch.float32, device="cuda")
+    dr.dr_token_scores(run.ctx, run.shape, run.Q, run.K, 1, scores)
+    cap, _ = dr.dr_mask_capacity(run.ctx, run.shape, wl.lam, run.params)
+    rowptr = torch.zeros((1, 1, wl.Sb + 1), dtype=torch.int32, device="cuda")
+    colidx = torch.zeros((1, 1, cap), dtype=torch.int32, device="cuda")
+    nnz = torch.zeros((1, 1), dtype=torch.int64, device="cuda")
+    links = torch.full((1, 1, wl.N, wl.N), 9, dtype=torch.uint8, device="cuda")
+    dr.dr_build_mask_tokens(run.ctx, run.shape, tau, wl.lam, run.params, scores, rowptr, colidx, cap, nnz, links)
+    tab = o.frame_table(wl.Nf, wl.Nt, wl.Bs, 1.5, wl.lam)
+    sc = scores.cpu().numpy()
+    want = o.select_token_links(sc[0, 0], wl.N, wl.Nt, tab, tau, tau)
+    got = links[0, 0].cpu().numpy()
+    assert got.max() <= 1 and (got.astype(bool) == want).all()
+    assert_masks_equal(rowptr, colidx, nnz, o.build_mask_from_tokens(sc, wl.N, wl.Nt, wl.Bs, tab, 0.15, 0.60, tau))
