@@ -5,6 +5,7 @@
 //                lanes own columns, ballots count active columns.
 //   k_select     one workgroup per (batch, mask, query block) row: compacts the selectable
 //                blocks into LDS as 64-bit keys (score descending, key block ascending), then
+//                (rows of more than 1024 key blocks; below, one wavefront per row: k_select_wave, k_select_mass)
 //                static top-k: radix selection of the k-th smallest key, keep every key up to it
 //                (paper Eq. 8 k rule); dynamic: bitonic sort and the cumulative-mass prefix
 //                (keep-one fallback of Eq. 11 / Algorithm 1).
@@ -274,6 +275,13 @@ __global__ __launch_bounds__(kThreads) void k_select(const uint8_t* __restrict__
     store_row(keep, words, row, keepbits, counts, &s_cnt);
 }
 
+// a wave's LDS operations execute in order; the fence keeps the compiler from moving reads above writes
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Static top-k / seeded sample for rows of at most 1024 key blocks: ONE wave per row, four rows per workgroup, no
 // barrier.  Lane l holds the keys of key blocks l, l + 64, ... in registers, complemented (kSlots 64-bit values; 0
 // where there is no key).  The classes arrive as lane masks (k_class_bits), so counting the selectable and the FAR
@@ -377,10 +385,7 @@ __device__ __forceinline__ bool kth_smallest_wave_short_list(const WaveKeys<kSlo
         if (__builtin_amdgcn_inverse_ballot_w64(reach[i])) list[mine] = w.c[i];
         at += __popcll(reach[i]);
     }
-    // the wave's LDS operations execute in order; the fence keeps the compiler from moving the read above the writes
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_lds_fence();
     WaveKeys<1> shortlist;
     shortlist.c[0] = (lane_id() < listed) ? list[lane_id()] : 0ull;
     __builtin_amdgcn_wave_barrier();
@@ -411,22 +416,23 @@ __device__ __forceinline__ uint32_t score_image(float s) {
     return u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
 }
 
-template <int kSlots>
-__global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __restrict__ class_bits,
-                                                          const float* __restrict__ scores, int64_t rows_total, int Sb,
-                                                          SelectArgs a, uint32_t* __restrict__ keepbits,
-                                                          int32_t* __restrict__ counts) {
-    __shared__ uint64_t s_list[kWaves][64];                       // a wave's short list of candidate keys
-    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;   // the same in every lane, and known to be
-    if (row >= rows_total) return;
-    const int qb = (int)(row % Sb);
-    const float* srow = scores + row * Sb;
-    const int words = (Sb + 31) / 32;
-    const uint64_t* cb = class_bits + (int64_t)qb * (kSlots * 3);
-    int index_bits = 0;
-    while ((1 << index_bits) < Sb) ++index_bits;
+__device__ __forceinline__ float image_score(uint32_t v) { return __uint_as_float((v & 0x80000000u) ? (v & 0x7fffffffu) : ~v); }
 
+// One row in the registers of a wave: the complemented keys and the classes as lane masks.
+template <int kSlots>
+struct WaveRow {
+    WaveKeys<kSlots> w;
+    uint64_t m_sel[kSlots], m_far[kSlots], m_forced[kSlots];      // m_far is empty unless the classes rank apart
+    int n, n_far;
+};
+// complemented key of key block kb: (not FAR) << 63 | image << 31 | ~kb (31 bits), the image being the order-preserving
+// integer of the score (or the complement of the sample hash); 0 where the class selects nothing
+template <int kSlots>
+__device__ __forceinline__ void load_wave_row(const uint64_t* __restrict__ class_bits, const float* __restrict__ scores, int64_t row,
+                                              int qb, int Sb, const SelectArgs& a, WaveRow<kSlots>& r) {
+    const int lane = lane_id();
+    const float* srow = scores + row * Sb;
+    const uint64_t* cb = class_bits + (int64_t)qb * (kSlots * 3);
     // every load of the row is issued before the first is used: the scores of all kSlots * 64 positions (those past
     // the row's end read its last entry) and the lane masks of the classes
     float sc[kSlots];
@@ -437,57 +443,276 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 #pragma unroll
         for (int i = 0; i < kSlots; ++i) sc[i] = 0.f;
     }
-    uint64_t m_sel[kSlots], m_far[kSlots], m_forced[kSlots];
     const uint64_t ranked_apart = a.two_ratio ? ~0ull : 0ull;
 #pragma unroll
     for (int i = 0; i < kSlots; ++i) {
-        m_sel[i] = cb[i * 3 + 0];
-        m_far[i] = cb[i * 3 + 1] & ranked_apart;
-        m_forced[i] = cb[i * 3 + 2];
+        r.m_sel[i] = cb[i * 3 + 0];
+        r.m_far[i] = cb[i * 3 + 1] & ranked_apart;
+        r.m_forced[i] = cb[i * 3 + 2];
     }
-    // complemented key of key block kb: (not FAR) << 63 | image << 31 | ~kb (31 bits), the image being the order-preserving
-    // integer of the score (or the complement of the sample hash); 0 where the class selects nothing
-    WaveKeys<kSlots> w;
-    int n = 0, n_far = 0;
+    r.n = 0;
+    r.n_far = 0;
     const uint32_t seed_row = (a.mode == 3) ? fmix32(a.seed ^ fmix32((uint32_t)qb)) : 0u;
 #pragma unroll
     for (int i = 0; i < kSlots; ++i) {
         const int kb = i * 64 + lane;
         const uint32_t v = (a.mode == 3) ? ~fmix32(seed_row + (uint32_t)kb) : score_image(sc[i]);
-        const bool selectable = __builtin_amdgcn_inverse_ballot_w64(m_sel[i]);
-        const bool far_key = __builtin_amdgcn_inverse_ballot_w64(m_far[i]);
+        const bool selectable = __builtin_amdgcn_inverse_ballot_w64(r.m_sel[i]);
+        const bool far_key = __builtin_amdgcn_inverse_ballot_w64(r.m_far[i]);
         const uint32_t hi = (v >> 1) | (far_key ? 0u : 0x80000000u), lo = (v << 31) | (0x7fffffffu ^ (uint32_t)kb);
-        w.c[i] = selectable ? (((uint64_t)hi << 32) | lo) : 0ull;
-        n += __popcll(m_sel[i]);
-        n_far += __popcll(m_far[i]);
+        r.w.c[i] = selectable ? (((uint64_t)hi << 32) | lo) : 0ull;
+        r.n += __popcll(r.m_sel[i]);
+        r.n_far += __popcll(r.m_far[i]);
     }
+}
+// the row's keep words and count: forced blocks, keys that reach c_near, FAR keys that reach c_far
+template <int kSlots>
+__device__ __forceinline__ void store_wave_row(const WaveRow<kSlots>& r, uint64_t c_near, uint64_t c_far, bool two_ratio, int64_t row,
+                                               int Sb, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
+    const int lane = lane_id(), words = (Sb + 31) / 32;
+    int kept = 0;
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+        uint64_t m = r.m_forced[i] | __ballot(r.w.c[i] >= c_near);
+        if (two_ratio) m |= __ballot(r.w.c[i] >= c_far) & r.m_far[i];
+        kept += __popcll(m);
+        if (lane < 2 && 2 * i + lane < words) keepbits[row * words + 2 * i + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+    }
+    if (lane == 0) counts[row] = kept;
+}
+template <int kSlots>
+__global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __restrict__ class_bits,
+                                                          const float* __restrict__ scores, int64_t rows_total, int Sb,
+                                                          SelectArgs a, uint32_t* __restrict__ keepbits,
+                                                          int32_t* __restrict__ counts) {
+    __shared__ uint64_t s_list[kWaves][64];                       // a wave's short list of candidate keys
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;   // the same in every lane, and known to be
+    if (row >= rows_total) return;
+    const int qb = (int)(row % Sb);
+    int index_bits = 0;
+    while ((1 << index_bits) < Sb) ++index_bits;
+    WaveRow<kSlots> r;
+    load_wave_row<kSlots>(class_bits, scores, row, qb, Sb, a, r);
     WaveThreshold t_near{0u, 0u}, t_far{0u, 0u};
     int k_near = 0, k_far = 0;
-    if (n > 0) {
-        const int n_near = n - n_far;                               // m_far is empty unless the classes rank apart
+    if (r.n > 0) {
+        const int n_near = r.n - r.n_far;
         k_near = keep_count(n_near, a.ratio);
-        k_far = a.two_ratio ? keep_count(n_far, a.ratio_far) : 0;
+        k_far = a.two_ratio ? keep_count(r.n_far, a.ratio_far) : 0;
         uint64_t* list = s_list[wave];
-        if (k_near > 0 && !(k_near <= kShortListMaxK && kth_smallest_wave_short_list<kSlots>(w, k_near, index_bits, list, &t_near)))
-            t_near = kth_smallest_wave<kSlots>(w, k_near, index_bits);
+        if (k_near > 0 && !(k_near <= kShortListMaxK && kth_smallest_wave_short_list<kSlots>(r.w, k_near, index_bits, list, &t_near)))
+            t_near = kth_smallest_wave<kSlots>(r.w, k_near, index_bits);
         const int k_all = n_near + k_far;
-        if (k_far > 0 && !(k_all <= kShortListMaxK && kth_smallest_wave_short_list<kSlots>(w, k_all, index_bits, list, &t_far)))
-            t_far = kth_smallest_wave<kSlots>(w, k_all, index_bits);
+        if (k_far > 0 && !(k_all <= kShortListMaxK && kth_smallest_wave_short_list<kSlots>(r.w, k_all, index_bits, list, &t_far)))
+            t_far = kth_smallest_wave<kSlots>(r.w, k_all, index_bits);
     }
     // a NEAR key's complement has bit 63 set and so has every threshold of the NEAR ranking: no FAR key reaches it;
     // the FAR ranking's threshold is reached by every NEAR key and by the k_far best FAR keys.  With nothing to rank
     // the threshold is beyond every key.
     const uint64_t c_near = k_near > 0 ? (((uint64_t)t_near.hi << 32) | t_near.lo) : ~0ull;
     const uint64_t c_far = k_far > 0 ? (((uint64_t)t_far.hi << 32) | t_far.lo) : ~0ull;
-    int kept = 0;
-#pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
-        uint64_t m = m_forced[i] | __ballot(w.c[i] >= c_near);
-        if (a.two_ratio) m |= __ballot(w.c[i] >= c_far) & m_far[i];
-        kept += __popcll(m);
-        if (lane < 2 && 2 * i + lane < words) keepbits[row * words + 2 * i + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
+    store_wave_row<kSlots>(r, c_near, c_far, a.two_ratio != 0, row, Sb, keepbits, counts);
+}
+
+// Cumulative mass for rows of at most 1024 key blocks, one wave per row.  The rule is a sum of fp64 exponentials one by
+// one in score order, compared with tau times the whole sum: a serial chain behind a sort, if taken literally (k_select:
+// 208 us at 40 x 591 rows; this kernel about 30).  Only the place where the prefix crosses the target is wanted, so it is
+// looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
+// bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) or whose
+// crossing lies among many equal scores is decided by the literal chain, in this wave.
+// LDS per wave: keys[cap] u64 | mass[cap] f64 | bins[256] u64, cap a power of two >= the largest selectable count of a row.
+constexpr int kBins = 256, kMaxTaken = 8;      // keys taken one by one before the row goes to the chain
+__host__ __device__ inline size_t select_mass_lds_bytes(int cap) { return (size_t)cap * 16 + kBins * 8; }
+
+__device__ __forceinline__ uint32_t key_image(uint64_t c) { return (uint32_t)(c >> 31); }
+// The rule taken literally by one wave: the n keys (complemented, in LDS, room for a power of two of them) are sorted, the
+// masses laid out in that order and added one by one; returns the key that ends the prefix.
+__device__ __forceinline__ uint64_t mass_threshold_by_chain(int n, float top, double tau, uint64_t* keys, double* mass) {
+    const int lane = lane_id();
+    int P = 1;
+    while (P < n) P <<= 1;
+#pragma unroll 1
+    for (int i = n + lane; i < P; i += 64) keys[i] = 0ull;
+    wave_lds_fence();
+#pragma unroll 1
+    for (int k = 2; k <= P; k <<= 1) {
+#pragma unroll 1
+        for (int j = k >> 1; j > 0; j >>= 1) {
+#pragma unroll 2
+            for (int t = lane; t < P / 2; t += 64) {
+                const int i = ((t & ~(j - 1)) << 1) | (t & (j - 1));
+                const uint64_t x = keys[i], y = keys[i | j];
+                if ((x < y) == ((i & k) == 0)) { keys[i] = y; keys[i | j] = x; }      // descending
+            }
+            wave_lds_fence();
+        }
     }
-    if (lane == 0) counts[row] = kept;
+#pragma unroll 1
+    for (int i = lane; i < n; i += 64) mass[i] = exp((double)image_score(key_image(keys[i])) - (double)top);
+    wave_lds_fence();
+    // one-by-one summation in the total order: the order is part of the definition.  Every lane runs the chain; eight loads
+    // are in flight ahead of the dependent additions, and the running sums replace the masses.
+    double cum = 0.0;
+    int i = 0;
+    for (; i + 8 <= n; i += 8) {
+        double v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = mass[i + e];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { cum = cum + v[e]; v[e] = cum; }
+        if (lane == 0) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) mass[i + e] = v[e];
+        }
+    }
+    for (; i < n; ++i) {
+        cum = cum + mass[i];
+        if (lane == 0) mass[i] = cum;
+    }
+    wave_lds_fence();
+    const double target = tau * cum;
+    int k = n;                                              // the first running sum that reaches the target ends the prefix
+#pragma unroll 1
+    for (int i0 = 0; i0 < n; i0 += 64) {
+        const uint64_t at = __ballot(i0 + lane < n && mass[min(i0 + lane, n - 1)] >= target);
+        if (at) {
+            k = i0 + __ffsll((unsigned long long)at);
+            break;
+        }
+    }
+    return keys[max(k, 1) - 1];
+}
+
+// The key that ends the prefix, by masses in fixed point (U: 32 or 64 bits; their sums do not depend on an order): the keys are
+// dropped into 256 bins of equal width in score (monotone in the score), the bins are scanned, and the keys of the bin in
+// which the sum crosses the target are taken from the top.  Nothing is decided when the bin holds too many keys to take, or
+// when the target lies within `slack(total)`, the largest error of a prefix, of either side of the crossing.
+enum class Crossing { kFound, kTooClose, kTooMany };
+template <typename U, class Mass, class Slack>
+__device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_scale, double tau, const uint64_t* keys, U* bins, Mass&& mass_of,
+                                              Slack&& slack, uint64_t* ends) {
+    const int lane = lane_id();
+    auto bin_of = [&](uint64_t c) { return (int)fminf((top - image_score(key_image(c))) * bin_scale, 255.0f); };
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bins[lane * 4 + e] = 0;
+    wave_lds_fence();
+#pragma unroll 1
+    for (int i = lane; i < n; i += 64) atomicAdd(&bins[bin_of(keys[i])], mass_of(keys[i]));
+    wave_lds_fence();
+    const U part[4] = {bins[lane * 4], bins[lane * 4 + 1], bins[lane * 4 + 2], bins[lane * 4 + 3]};
+    const U own = part[0] + part[1] + part[2] + part[3];
+    U incl = own;
+    for (int off = 1; off < 64; off <<= 1) {
+        const U t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
+    }
+    const double total = (double)__shfl(incl, 63), target = tau * total;
+    const uint64_t reach = __ballot((double)incl >= target);      // (never empty: tau <= 1)
+    const int l = reach ? __ffsll((unsigned long long)reach) - 1 : 63;
+    U before = incl - own;
+    int bin = lane * 4;
+    bool found = false;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+        if (!found) {
+            if ((double)(before + part[e]) >= target) found = true;
+            else { before += part[e]; ++bin; }
+        }
+    bin = __shfl(bin, l);
+    U prefix = __shfl(before, l), prev = prefix;
+    uint64_t last = ~0ull;
+    bool crossed = false;
+    for (int taken = 0; taken < kMaxTaken && !crossed; ++taken) {
+        uint64_t best = 0ull;
+#pragma unroll 1
+        for (int i = lane; i < n; i += 64) {
+            const uint64_t c = keys[i];
+            if (c < last && c > best && bin_of(c) == bin) best = c;
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)best, off);
+            best = t > best ? t : best;
+        }
+        if (best == 0ull) break;
+        last = best;
+        prev = prefix;
+        prefix += mass_of(best);
+        crossed = (double)prefix >= target;
+    }
+    const double E = slack(total);
+    *ends = last;
+    if (!crossed) return Crossing::kTooMany;
+    return (double)prev + E < tau * (total - E) && (double)prefix - E >= tau * (total + E) ? Crossing::kFound : Crossing::kTooClose;
+}
+
+template <int kSlots>
+__global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __restrict__ class_bits,
+                                                          const float* __restrict__ scores, int64_t rows_total, int Sb, int cap,
+                                                          SelectArgs a, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
+    extern __shared__ unsigned char smem[];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+    if (row >= rows_total) return;
+    unsigned char* mine = smem + (size_t)wave * select_mass_lds_bytes(cap);
+    uint64_t* keys = reinterpret_cast<uint64_t*>(mine);
+    double* mass = reinterpret_cast<double*>(mine + (size_t)cap * 8);
+    unsigned char* bins = mine + (size_t)cap * 16;
+    WaveRow<kSlots> r;
+    load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
+    uint64_t threshold = ~0ull;
+    const int n = r.n;
+    if (n > 0) {
+        int at = 0;
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            const int pos = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(r.m_sel[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)r.m_sel[i], 0u));
+            if (__builtin_amdgcn_inverse_ballot_w64(r.m_sel[i])) keys[pos] = r.w.c[i];
+            at += __popcll(r.m_sel[i]);
+        }
+        wave_lds_fence();
+        // (the packed keys are read from LDS again by every loop: few iterations, and registers for many waves)
+        uint32_t image_max = 0u, image_min = ~0u;
+#pragma unroll 1
+        for (int i = lane; i < n; i += 64) {
+            const uint32_t v = key_image(keys[i]);
+            image_max = max(image_max, v);
+            image_min = min(image_min, v);
+        }
+        for (int off = 32; off > 0; off >>= 1) {
+            image_max = max(image_max, (uint32_t)__shfl_xor((int)image_max, off));
+            image_min = min(image_min, (uint32_t)__shfl_xor((int)image_min, off));
+        }
+        const float top = image_score(image_max), range = top - image_score(image_min);
+        const float bin_scale = (range > 0.f && range < INFINITY) ? 255.0f / range : 0.f;
+        const int log_n = 32 - __clz(n);                    // n < 2^log_n: the sums of n masses below fit their types
+        // tau = 1 ends the prefix where the running sum stops growing: at the last key when even the smallest mass is above
+        // a rounding of the whole sum (at most n)
+        const bool all = a.tau >= 1.0 && range < 34.0f - (float)log_n;
+        const bool flat = range == 0.f;                     // every mass is 1: the running sum counts, in key-block order
+        Crossing got = (a.tau >= 1.0 || flat) ? Crossing::kTooMany : Crossing::kTooClose;
+        if (!all && got == Crossing::kTooClose) {
+            // 32 bits, exponentials in fp32.  The argument is off by at most 2^-23 |x| (and x e^-x <= 0.37), the
+            // instruction by 2^-23 relative, rounding to a unit by one half.
+            const float unit = __uint_as_float((uint32_t)(127 + 31 - log_n) << 23);
+            got = mass_crossing<uint32_t>(
+                n, top, bin_scale, a.tau, keys, reinterpret_cast<uint32_t*>(bins),
+                [&](uint64_t c) { return (uint32_t)__builtin_rintf(__builtin_amdgcn_exp2f((top - image_score(key_image(c))) * -1.44269504f) * unit); },
+                [&](double total) { return total * 0x1p-21 + (double)n + 4.0; }, &threshold);
+        }
+        if (!all && got == Crossing::kTooClose) {
+            // 64 bits, the rule's own exponentials: rounding to a unit, and the chain's own n roundings
+            const double unit = __longlong_as_double((long long)(1023 + 62 - log_n) << 52);
+            got = mass_crossing<unsigned long long>(
+                n, top, bin_scale, a.tau, keys, reinterpret_cast<unsigned long long*>(bins),
+                [&](uint64_t c) { return (unsigned long long)__builtin_rint(exp((double)image_score(key_image(c)) - (double)top) * unit); },
+                [&](double total) { return total * (double)(n + 8) * 0x1p-52 + (double)n + 4.0; }, &threshold);
+        }
+        if (all) threshold = 1ull;                          // every selectable key's complement is above 0
+        else if (flat) threshold = keys[max(1, (int)ceil(a.tau * (double)n)) - 1];      // (packed in that order)
+        else if (got != Crossing::kFound) threshold = mass_threshold_by_chain(n, top, a.tau, keys, mass);
+    }
+    store_wave_row<kSlots>(r, threshold, ~0ull, false, row, Sb, keepbits, counts);
 }
 
 // grid: (Sb, masks, B).  A candidate set of the row is identified by the frame f that realises its gap: the key
@@ -718,6 +943,26 @@ hipError_t launch_select(const uint8_t* class_map, const uint64_t* class_bits, c
         else DR_SELECT_WAVE(16);
 #undef DR_SELECT_WAVE
         return hipGetLastError();
+    }
+    // Cumulative mass, one wave per row as well (the prefix's end is found without sorting).
+    if (a.mode == 1 && class_bits && Sb <= kWaveSelectMaxBlocks) {
+        const int waves = rows_total >= kWaveSelectPackRows ? kWaves : 1;
+        const dim3 grid((unsigned)((rows_total + waves - 1) / waves)), block(64 * waves);
+        const int cap = (a.sort_cap + 1) & ~1, slots = wave_select_slots(Sb);      // (16-byte aligned bins)
+        const size_t lds = select_mass_lds_bytes(cap) * waves;
+        auto launch = [&](auto kern) -> hipError_t {
+            if (lds > 64 * 1024) {
+                hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e != hipSuccess) return e;
+            }
+            hipLaunchKernelGGL(kern, grid, block, lds, s, class_bits, scores, rows_total, Sb, cap, a, keepbits, counts);
+            return hipGetLastError();
+        };
+        if (slots == 2) return launch(k_select_mass<2>);
+        if (slots == 4) return launch(k_select_mass<4>);
+        if (slots == 8) return launch(k_select_mass<8>);
+        if (slots == 12) return launch(k_select_mass<12>);
+        return launch(k_select_mass<16>);
     }
     const size_t words = (Sb + 31) / 32;
     const size_t lds = (size_t)a.sort_cap * (a.mode == 1 ? 16 : 8) + words * 4;

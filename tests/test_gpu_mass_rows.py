@@ -1,0 +1,40 @@
+"""The cumulative-mass rule for rows of at most 1024 key blocks: the crossing found with fixed-point masses and bins, and the
+literal chain where the target lies too close to it, bit for bit against the oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2604_20470_amd as dr
+from workloads import tiny_case
+
+from helpers import GpuRun, assert_masks_equal, oracle_class_map, oracle_masks_from
+
+pytestmark = pytest.mark.gpu
+
+
+# rows on both sides of every register width, with one row per workgroup (one mask) and four (thirty)
+@pytest.mark.parametrize("frames,hg,wg", [(8, 8, 16), (16, 10, 25), (15, 16, 30), (32, 20, 23), (40, 20, 25), (33, 31, 32)])
+@pytest.mark.parametrize("heads", [1, 30])
+def test_prefix_bit_exact(frames, hg, wg, heads):
+    wl = dataclasses.replace(tiny_case("tiny8"), Nf=frames, Hg=hg, Wg=wg, H=heads, index=101)
+    params = dr.MaskParams(head_fuse=0, gamma=3.0)
+    run = GpuRun.__new__(GpuRun)
+    run.wl, run.heads, run.params, run.device, run.Sb = wl, list(range(heads)), params, "cuda:0", wl.Sb
+    run.ctx = dr.Context(0)
+    run.shape = dr.Shape(1, heads, wl.N, 64, frames, hg, wg, wl.Bs, 0, 0, wl.N * 64 * heads, wl.N * 64, 64)
+    assert wl.Sb <= 1024
+    g = torch.Generator().manual_seed(frames)
+    scores = torch.randn(1, heads, wl.Sb, wl.Sb, generator=g)
+    scores[:, 0, 1::7] = 0.25                                     # all equal: the sum hits tau * n exactly for some tau
+    scores[:, 0, 2::7] *= 40.0                                    # one key holds nearly everything
+    scores[:, 0, 3::7] = (scores[:, 0, 3::7] * 2).round()         # many ties, signed zeros
+    scores[:, 0, 4::7] *= 1e30                                    # masses of 0 and 1 only
+    scores = scores.cuda()
+    cls = oracle_class_map(wl, gamma=3.0)
+    for tau in (0.5, 0.9, 0.99, 1.0, 1e-9):
+        rowptr, colidx, nnz, cap = run.build_mask(scores, "dynamic", tau)
+        few = [0] if heads == 1 else [0, heads - 1]
+        want = oracle_masks_from(scores[:, few], cls, "dynamic", tau)
+        assert_masks_equal(rowptr[:, few], colidx[:, few], nnz[:, few], want)
