@@ -58,7 +58,7 @@ constexpr int kRowBytes = kD * 2;                    // 256
 constexpr int kTileBytes = kChunkKeys * kRowBytes;   // 16 KB per operand per stage
 constexpr int kStageBytes = 2 * kTileBytes;          // K then V
 constexpr int kLdsBytes = 2 * kStageBytes;           // two stages: 64 KB
-constexpr int kXcds = kAttnQueues, kRun = 32;
+constexpr int kXcds = kAttnQueues;
 constexpr float kSumMax = 1.2676506e30f, kSumMin = 7.8886091e-31f;   // 2^100, 2^-100: outside, the row is flagged
 
 struct LoadPlan {
@@ -485,48 +485,30 @@ __device__ __forceinline__ void plain_chunk(const ReadPlan& rd, uint32_t stage_o
 // workgroups run neighbouring items at the same time and share tiles in its L2; a workgroup whose queue is empty goes on
 // with the next XCD's.  Shares fixed beforehand cannot be even: the XCDs of one chip hold clocks up to 5 % apart under
 // this load, and a launch may not divide by eight.
-// The order of a queue.  Whole heads per XCD (heads a multiple of 8): its heads one after the other, each in order.
-// Otherwise a contiguous eighth of the items is part of a head, and rows in the middle of a sequence list more key blocks
-// than rows near its ends; runs of 32 items (one per CU of an XCD) are then dealt to the queues in turn, the middle of
-// every head first and its ends, the shorter walks, last.
+// A queue is a contiguous eighth of the items (batch, head, group), in order.
 // Measured against a workgroup per item in contiguous eighths: 75 600 tokens x 40 heads 13.34 -> 12.83 ms, 118 800 x 24
 // 32.8 -> 31.5 (both held back by the power limit: the idle gaps used to buy clock), 264 000 x 2 at block size 32
 // 13.4 -> 12.0; one round of items (6144 tokens x 8 heads) 93.6 -> 94.2 us.
-__device__ __forceinline__ int slots_per_xcd(int n_groups, int heads) {
-    if (heads % kXcds == 0) return n_groups * (heads / kXcds);
-    const int turns = (n_groups + kRun - 1) / kRun * heads;
-    return (turns + kXcds - 1) / kXcds * kRun;
-}
-__device__ __forceinline__ int item_of_slot(int xcd, int slot, int n_groups, int heads) {      // -1: an empty slot
-    if (heads % kXcds == 0) return xcd * n_groups * (heads / kXcds) + slot;
-    const int n_runs = (n_groups + kRun - 1) / kRun;                       // of a head
-    const int turn = (slot / kRun) * kXcds + xcd;                          // of n_runs * heads
-    const int level = turn / heads, head = turn % heads;
-    if (level >= n_runs) return -1;
-    const int run = (level & 1) ? (n_runs - 1) / 2 + (level + 1) / 2 : (n_runs - 1) / 2 - level / 2;
-    const int group = run * kRun + slot % kRun;
-    return group < n_groups ? head * n_groups + group : -1;
+__device__ __forceinline__ int slots_of_queue(int xcd, int items) {
+    const int per = (items + kXcds - 1) / kXcds;
+    return max(0, min(per, items - xcd * per));
 }
 // The next item, given the slot just drawn from queue `xcd` (kept from item to item); one thread of the workgroup calls it.
 // Where that queue is empty the eight counters are read at once, and the next queue that has slots left is drawn from: a
 // launch ends with one such look, not with eight failed draws one after the other (5 us).  -1: every queue is empty.
-__device__ __forceinline__ int claim_item(int32_t* queue, int& xcd, int slot, int n_groups, int heads) {
-    const int slots = slots_per_xcd(n_groups, heads);
+__device__ __forceinline__ int claim_item(int32_t* queue, int& xcd, int slot, int items) {
+    const int per = (items + kXcds - 1) / kXcds;
     for (;;) {
-        if (slot < slots) {
-            const int item = item_of_slot(xcd, slot, n_groups, heads);
-            if (item >= 0) return item;
-        } else {
-            int drawn[kXcds];
+        if (slot < slots_of_queue(xcd, items)) return xcd * per + slot;
+        int drawn[kXcds];
 #pragma unroll
-            for (int i = 0; i < kXcds; ++i) drawn[i] = __hip_atomic_load(&queue[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int step = kXcds;                              // to the nearest queue with slots left
+        for (int i = 0; i < kXcds; ++i) drawn[i] = __hip_atomic_load(&queue[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        int step = kXcds;                                  // to the nearest queue with slots left
 #pragma unroll
-            for (int i = 0; i < kXcds; ++i)
-                if (drawn[i] < slots) step = min(step, (i - xcd + kXcds) % kXcds);
-            if (step == kXcds) return -1;
-            xcd = (xcd + step) % kXcds;
-        }
+        for (int i = 0; i < kXcds; ++i)
+            if (drawn[i] < slots_of_queue(i, items)) step = min(step, (i - xcd + kXcds) % kXcds);
+        if (step == kXcds) return -1;
+        xcd = (xcd + step) % kXcds;
         slot = atomicAdd(&queue[xcd], 1);
     }
 }
@@ -557,11 +539,10 @@ __device__ __forceinline__ void attn_pair_body() {
     int item, turn = 0;
     {
         const AttnArgs a = fresh_args();
-        const int n_groups = (a.Sb + kL - 1) / kL, heads = a.td.H * a.td.B, slots = slots_per_xcd(n_groups, heads);
-        const int slot = (int)blockIdx.x / kXcds;
-        item = slot < slots ? item_of_slot(q_xcd, slot, n_groups, heads) : -1;
+        const int items = (a.Sb + kL - 1) / kL * a.td.H * a.td.B, slot = (int)blockIdx.x / kXcds;
+        item = slot < slots_of_queue(q_xcd, items) ? q_xcd * ((items + kXcds - 1) / kXcds) + slot : -1;
         if (item < 0) {
-            if (threadIdx.x == 0) s_item[0] = claim_item(a.queue, q_xcd, slot, n_groups, heads);
+            if (threadIdx.x == 0) s_item[0] = claim_item(a.queue, q_xcd, slot, items);
             __syncthreads();
             item = __builtin_amdgcn_readfirstlane(s_item[0]);
             turn = 1;
@@ -798,7 +779,8 @@ __device__ __forceinline__ void attn_pair_body() {
     const int h = (item / n_pairs) % a.td.H, b = item / (n_pairs * a.td.H);
     const int32_t* rp = a.rowptr + ((int64_t)b * a.mask_heads + (a.mask_heads == 1 ? 0 : h)) * (a.Sb + 1);
     // nothing is left to draw where the workgroups' own first slots were all there are
-    const bool more = slots_per_xcd(n_pairs, a.td.H * a.td.B) > (int)gridDim.x / kXcds;
+    const int items = n_pairs * a.td.H * a.td.B;
+    const bool more = items > (int)gridDim.x;
     int next_slot = 0;
     if (more && threadIdx.x == 0) next_slot = atomicAdd(&a.queue[q_xcd], 1);
     drain_mfma(st.o, st.lacc);
@@ -840,7 +822,7 @@ __device__ __forceinline__ void attn_pair_body() {
         if (lane < 2) a.flags[base + lane] = any;
     }
     if (!more) return;
-    if (threadIdx.x == 0) s_item[turn] = claim_item(a.queue, q_xcd, next_slot, n_pairs, a.td.H * a.td.B);
+    if (threadIdx.x == 0) s_item[turn] = claim_item(a.queue, q_xcd, next_slot, items);
     __syncthreads();
     item = __builtin_amdgcn_readfirstlane(s_item[turn]);
     turn ^= 1;

@@ -15,9 +15,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,bs,frames,hg,wg", [
-    (40, 128, 9, 16, 23),       # N = 3312: 13 items per head; whole heads per queue
-    (30, 32, 9, 16, 23),        # dealt in runs: one run of 13 per head
-    (9, 64, 33, 16, 21),        # N = 11088: 44 items per head, two runs, the second not full
+    (40, 128, 9, 16, 23),       # N = 3312: 13 items per head, 65 per queue
+    (30, 32, 9, 16, 23),        # 390 items: a queue ends inside a head
+    (9, 64, 33, 16, 21),        # N = 11088: 396 items, the last queue is shorter
 ])
 def test_every_item_once(H, bs, frames, hg, wg):
     wl = dataclasses.replace(tiny_case("ragged128"), Nf=frames, Hg=hg, Wg=wg, H=H, Bs=bs, index=81)
