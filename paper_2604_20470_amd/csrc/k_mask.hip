@@ -823,8 +823,8 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
 }
 
 // grid: (Sb, masks, B)
-// rowptr of every mask: the exclusive prefix of its rows' kept counts, one workgroup per mask (a row used to re-sum
-// all earlier counts itself: Sb^2 / 2 reads per mask).  grid: (masks, B).
+// rowptr of every mask of rows beyond 2048 key blocks: the exclusive prefix of its rows' kept counts, one workgroup per mask
+// (a row that re-sums all earlier counts itself reads Sb^2 / 2 of them per mask).  grid: (masks, B).
 __global__ __launch_bounds__(kThreads) void k_row_offsets(const int32_t* __restrict__ counts, int masks, int Sb, int shared,
                                                           int32_t* __restrict__ rowptr, int64_t* __restrict__ nnz) {
     __shared__ long long s_wave[kWaves];
@@ -991,43 +991,58 @@ hipError_t launch_select_zscore(const uint8_t* class_map, const float* scores, i
     return hipGetLastError();
 }
 
-// The same for rows of at most 2048 key blocks (64 bitmap words): one wave per row, no LDS and no barrier; four rows per
-// workgroup.  A lane loads one bitmap word; the wave then walks the row 64 key blocks at a time: the two words of that
-// stretch are read back as a wave-uniform lane mask, a lane whose bit is set stores its key block at the running
-// offset plus the number of set bits below it (v_mbcnt), so that each store instruction writes one contiguous run.
-// grid: ceil(B * masks * Sb / 4).
-__global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restrict__ keepbits, int64_t rows_total, int Sb,
-                                                        int shared, const int32_t* __restrict__ rowptr,
-                                                        int32_t* __restrict__ colidx, int64_t capacity) {
+// Offsets and column lists in one launch, for rows of at most 2048 key blocks (64 bitmap words): one wave per row, no LDS
+// and no barrier; four rows per workgroup.  The wave adds the counts of the mask's earlier rows itself (at most 32 coalesced
+// reads per lane out of L2; a launch of its own for the offsets costs 4 to 5 us, more than that sum for any row).  A lane
+// loads one bitmap word; the wave then walks the row 64 key blocks at a time: the two words of that stretch are read back
+// as a wave-uniform lane mask, a lane whose bit is set stores its key block at the running offset plus the number of set
+// bits below it (v_mbcnt), so that each store instruction writes one contiguous run.  grid: ceil(B * masks * Sb / 4).
+__global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts,
+                                                        int64_t rows_total, int Sb, int shared, int32_t* __restrict__ rowptr,
+                                                        int32_t* __restrict__ colidx, int64_t capacity, int64_t* __restrict__ nnz) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;      // (mask_id, qb) flattened
     if (r >= rows_total) return;
     const int64_t mask_id = r / Sb;
     const int qb = (int)(r - mask_id * Sb);
-    const int64_t row = shared ? qb : r;
+    const int64_t src = shared ? 0 : mask_id * Sb;                         // shared: one selection serves every (b, m)
+    const int64_t row = src + qb;
     const int words = (Sb + 31) / 32;
     const uint32_t wv = (lane < words) ? keepbits[row * words + lane] : 0u;
-    long long pos = (long long)rowptr[mask_id * (Sb + 1) + qb];            // negative only past 32-bit offsets
+    int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
+#pragma unroll 4
+    for (int i = lane; i < qb; i += 64) before += counts[src + i];
+    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+    int32_t* rp = rowptr + mask_id * (Sb + 1);
+    if (lane == 0) {
+        rp[qb] = before;
+        if (qb == Sb - 1) {
+            const int all = before + counts[row];
+            rp[Sb] = all;
+            nnz[mask_id] = all;
+        }
+    }
+    long long pos = before;
     int32_t* out = colidx + mask_id * capacity;
     const int stretches = (Sb + 63) / 64;
     for (int i = 0; i < stretches; ++i) {                                  // wave-uniform
         const uint32_t lo = __builtin_amdgcn_readlane(wv, 2 * i), hi = __builtin_amdgcn_readlane(wv, 2 * i + 1);
         const uint32_t mine = (lane < 32) ? (lo >> lane) : (hi >> (lane - 32));
         const long long p = pos + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-        if ((mine & 1u) && p >= 0 && p < capacity) out[p] = i * 64 + lane;
+        if ((mine & 1u) && p < capacity) out[p] = i * 64 + lane;
         pos += __popc(lo) + __popc(hi);
     }
 }
 
 hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, int masks, int Sb, bool shared,
                        int32_t* rowptr, int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s) {
-    hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
     if (Sb <= 64 * 32) {
         const int64_t rows_total = (int64_t)B * masks * Sb;
         const int waves = rows_total >= kWaveSelectPackRows ? kWaves : 1;
-        hipLaunchKernelGGL(k_emit_wave, dim3((unsigned)((rows_total + waves - 1) / waves)), dim3(64 * waves), 0, s, keepbits,
-                           rows_total, Sb, shared ? 1 : 0, rowptr, colidx, capacity);
+        hipLaunchKernelGGL(k_emit_wave, dim3((unsigned)((rows_total + waves - 1) / waves)), dim3(64 * waves), 0, s, keepbits, counts,
+                           rows_total, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
     } else {
+        hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
         hipLaunchKernelGGL(k_emit, dim3(Sb, masks, B), dim3(kThreads), 0, s, keepbits, masks, Sb, shared ? 1 : 0, rowptr,
                            colidx, capacity);
     }
