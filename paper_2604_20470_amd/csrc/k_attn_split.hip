@@ -16,8 +16,8 @@
 // left in LDS as bf16 parts.  The logits are produced transposed, S^T = K Q^T (32x32x16), so that a lane's sixteen values
 // belong to one query, and the split probabilities are already the B operand of O^T += V^T P^T; V^T fragments come
 // from the row-major parts with the transposing LDS read.
-// Softmax is online in fp32; the exponent reference of a query is moved only when a logit exceeds it by 2^10, which
-// costs no accuracy (fp32 sums are scale free), so the steady state rescales nothing.
+// Softmax is online in fp32; the exponent reference of a query is moved only when a tile's probabilities outgrow it by
+// 2^10, which costs no accuracy (fp32 sums are scale free), so the steady state forms no maximum and rescales nothing.
 //
 // Infinite inputs (or values that round to infinity in bf16) make inf - inf in a split.  A workgroup that finds a result
 // that is not finite takes its query block again with plain fp32 arithmetic on the vector ALU, whose answer stands.
@@ -29,7 +29,7 @@ namespace {
 
 using namespace mfma;
 
-constexpr float kMoveReference = 10.0f;     // log2 units a logit may exceed the reference by
+constexpr float kSumLimit = 1024.0f;      // a lane's sixteen probabilities of a tile may sum to at most this
 
 typedef __attribute__((address_space(3))) const v8bf* lds_v8;
 typedef __attribute__((address_space(3))) v4s* lds_v4;
@@ -45,10 +45,13 @@ struct Plan {
     static constexpr int kT = (BF16 && D == 64) || (!BF16 && D == 64 && kS == 1) ? 2 : 1;   // 32-key tiles per stream and stage
     static constexpr int kTiles = kS * kT, kRows = kTiles * 32;     // of a stage
     static constexpr int kStageBytes = kTiles * kTileBytes;
+    // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide the splitting of the next stage
+    // behind: it goes into a second buffer, between the matrix instructions, where two fit
+    static constexpr int kBuffers = !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024 ? 2 : 1;
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = 32;
     static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainKeys * D + kPlainRows * kPlainKeys);
     static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
-    static constexpr int kMax1 = kStageBytes > kPlainBytes ? kStageBytes : kPlainBytes;
+    static constexpr int kMax1 = kBuffers * kStageBytes > kPlainBytes ? kBuffers * kStageBytes : kPlainBytes;
     static constexpr int kLdsBytes = kMax1 > kMergeBytes ? kMax1 : kMergeBytes;
     static constexpr int kRowUnits = D / 8;                         // a unit = 8 channels of one row
     static constexpr int kPasses = kRows * kRowUnits / kThreads;    // units per thread, K and V each
@@ -62,16 +65,30 @@ template <int D> __device__ __forceinline__ int k_piece(int p, int r) { return D
 // the same for V: the four rows of a transposing read's patch fall in distinct 64-byte groups
 template <int D> __device__ __forceinline__ int v_piece(int p, int r) { return D == 128 ? p ^ ((r & 3) << 2) : p ^ (((r >> 1) & 1) << 2); }
 
-__device__ __forceinline__ void split8(const float (&x)[8], v8bf (&part)[3]) {
+// (the converted pair is unpacked again from its packed word, which costs two bit operations)
+__device__ __forceinline__ void split2(float r0, float r1, uint32_t (&part)[3]) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const __bf16 h = (__bf16)x[i];
-        const float r = x[i] - (float)h;
-        const __bf16 m = (__bf16)r;
-        part[0][i] = h;
-        part[1][i] = m;
-        part[2][i] = (__bf16)(r - (float)m);
+    for (int p = 0; p < 3; ++p) {
+        union { v2bf v; uint32_t u; } pk;
+        pk.v[0] = (__bf16)r0;
+        pk.v[1] = (__bf16)r1;
+        asm("" : "+v"(pk.u));                                // keeps the pair packed
+        part[p] = pk.u;
+        r0 -= __uint_as_float(pk.u << 16);
+        r1 -= __uint_as_float(pk.u & 0xffff0000u);
     }
+}
+__device__ __forceinline__ void split8(const float (&x)[8], v8bf (&part)[3]) {
+    union { uint32_t u[4]; v8bf v; } w[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t t[3];
+        split2(x[2 * i], x[2 * i + 1], t);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p].u[i] = t[p];
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) part[p] = w[p].v;
 }
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
@@ -261,6 +278,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
         const int kb = min(max(__builtin_amdgcn_readlane(win, t / kTPB - wbase), 0), a.Sb - 1);
         return kb * BS + (t % kTPB) * 32;
     };
+    const int64_t lane_off = (int64_t)(lane / P::kRowUnits) * it.row_bytes + (lane % P::kRowUnits) * (8 * ES);
     struct Raw { v4f32 x[BF16 ? 1 : 2]; };
     Raw rk[P::kPasses], rv[P::kPasses];
     int row0_next[P::kT], row0[P::kT];
@@ -275,11 +293,12 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 #pragma unroll
         for (int p = 0; p < P::kPasses; ++p) {
             constexpr int kWaveRows = 64 / P::kRowUnits;          // rows of one wavefront and pass: they lie in one tile
-            const int wave_row = (p * P::kThreads + wave * 64) / P::kRowUnits;
-            const int r0 = tile_row0(min(g * P::kTiles + wave_row / 32, n_tiles - 1));
-            const int r = min(r0 + wave_row % 32 + lane / P::kRowUnits, N - 1);
-            const int64_t off = (int64_t)r * it.row_bytes + (lane % P::kRowUnits) * (8 * ES);
             static_assert(32 % kWaveRows == 0, "a wavefront's rows lie in one tile");
+            const int wave_row = (p * P::kThreads + wave * 64) / P::kRowUnits;
+            const int r = tile_row0(min(g * P::kTiles + wave_row / 32, n_tiles - 1)) + wave_row % 32;      // the same in every lane
+            const int64_t base = (int64_t)r * it.row_bytes;
+            int64_t off = base + lane_off;
+            if (r + kWaveRows > N) off = (int64_t)min(r + lane / P::kRowUnits, N - 1) * it.row_bytes + (lane % P::kRowUnits) * (8 * ES);
 #pragma unroll
             for (int i = 0; i < (BF16 ? 1 : 2); ++i) {
                 rk[p].x[i] = *reinterpret_cast<const v4f32*>(it.K + off + i * 16);
@@ -287,27 +306,27 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             }
         }
     };
-    auto store = [&]() {          // split the fetched rows into their LDS parts
+    // split the fetched rows into their LDS parts, sixteen bytes of a row at a time (u: pass, K or V, half of the unit)
+    constexpr int kPieces = P::kPasses * 2 * (BF16 ? 1 : 2);
+    auto store_piece = [&](int u, int buffer) {
+        const int i = BF16 ? 0 : u & 1, v = (BF16 ? u : u >> 1) & 1, p = BF16 ? u >> 1 : u >> 2;
+        const int row = (p * P::kThreads + tid) / P::kRowUnits, piece = tid % P::kRowUnits;
+        unsigned char* dst = smem + buffer * P::kStageBytes + row * P::kRowBytes +
+                             (v ? P::kIn * kPart + v_piece<D>(piece, row) * 16 : k_piece<D>(piece, row) * 16);
+        const v4f32 x = v ? rv[p].x[i] : rk[p].x[i];
+        if constexpr (BF16) {
+            *reinterpret_cast<v4f32*>(dst) = x;
+        } else {
+            uint32_t a01[3], a23[3];
+            split2(x[0], x[1], a01);
+            split2(x[2], x[3], a23);
 #pragma unroll
-        for (int p = 0; p < P::kPasses; ++p) {
-            const int row = (p * P::kThreads + tid) / P::kRowUnits, piece = tid % P::kRowUnits;
-            unsigned char* dk = smem + row * P::kRowBytes + k_piece<D>(piece, row) * 16;
-            unsigned char* dv = smem + P::kIn * kPart + row * P::kRowBytes + v_piece<D>(piece, row) * 16;
-            if constexpr (BF16) {
-                *reinterpret_cast<v4f32*>(dk) = rk[p].x[0];
-                *reinterpret_cast<v4f32*>(dv) = rv[p].x[0];
-            } else {
-                const float xk[8] = {rk[p].x[0][0], rk[p].x[0][1], rk[p].x[0][2], rk[p].x[0][3], rk[p].x[1][0], rk[p].x[1][1], rk[p].x[1][2], rk[p].x[1][3]};
-                const float xv[8] = {rv[p].x[0][0], rv[p].x[0][1], rv[p].x[0][2], rv[p].x[0][3], rv[p].x[1][0], rv[p].x[1][1], rv[p].x[1][2], rv[p].x[1][3]};
-                v8bf part[3];
-                split8(xk, part);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<v8bf*>(dk + i * kPart) = part[i];
-                split8(xv, part);
-#pragma unroll
-                for (int i = 0; i < 3; ++i) *reinterpret_cast<v8bf*>(dv + i * kPart) = part[i];
-            }
+            for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(dst + q * kPart + i * 8) = make_uint2(a01[q], a23[q]);
         }
+    };
+    auto store = [&](int buffer) {
+#pragma unroll
+        for (int u = 0; u < kPieces; ++u) store_piece(u, buffer);
     };
 
     v16f o[kDB];
@@ -329,38 +348,106 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     }
 
     if (stages > 0) fetch(0);
-    for (int g = 0; g < stages; ++g) {
-        __syncthreads();                     // the stage before is consumed
-        store();
+    if constexpr (P::kBuffers == 2) {
+        if (stages > 0) {
+            store(0);
 #pragma unroll
-        for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
-        __syncthreads();
-        if (g + 1 < stages) fetch(g + 1);
+            for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
+            if (stages > 1) fetch(1);
+            __syncthreads();
+        }
+    }
+    for (int g = 0; g < stages; ++g) {
+        if constexpr (!BF16 && D == 128) {
+            // the Q parts are only ever operands of matrix instructions: they live in accumulation registers
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks)
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) asm volatile("" : "+a"(qf[ks][i]));
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) asm volatile("" : "+v"(o[db]));
+        }
+        const bool ahead = P::kBuffers == 2 && g + 1 < stages;      // the next stage waits in registers
+        const uint32_t buffer = P::kBuffers == 2 ? (uint32_t)(g & 1) * P::kStageBytes : 0u;
+        if constexpr (P::kBuffers == 1) {
+            __syncthreads();                     // the stage before is consumed
+            store(0);
+#pragma unroll
+            for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
+            __syncthreads();
+            if (g + 1 < stages) fetch(g + 1);
+        }
 #pragma unroll
         for (int c = 0; c < P::kT; ++c) {
             const int valid = N - row0[c];                       // keys of the tile (only the sequence's end has fewer than 32)
-            if (g * P::kTiles + ws * P::kT + c >= n_tiles || valid <= 0) continue;      // wavefront-uniform
-            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
+            const bool mine = g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0;      // wavefront-uniform
+            if constexpr (P::kBuffers == 1) {
+                if (!mine) continue;
+            }
+            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes) + buffer;
             v16f s;
 #pragma unroll
             for (int j = 0; j < 16; ++j) s[j] = 0.f;
+            // the fragments of a step are read while the step before is multiplied
+            v8bf kf[2][P::kIn];
+#pragma unroll
+            for (int i = 0; i < P::kIn; ++i) kf[0][i] = *(lds_v8)(uintptr_t)(k_addr[0] + tile + i * kPart);
 #pragma unroll
             for (int ks = 0; ks < kKS; ++ks) {
-                v8bf kf[P::kIn];
+                if (ks + 1 < kKS) {
 #pragma unroll
-                for (int i = 0; i < P::kIn; ++i) kf[i] = *(lds_v8)(uintptr_t)(k_addr[ks] + tile + i * kPart);
-                s = mfma_parts<P::kIn, P::kIn>(kf, qf[ks], s);
+                    for (int i = 0; i < P::kIn; ++i) kf[(ks + 1) & 1][i] = *(lds_v8)(uintptr_t)(k_addr[ks + 1] + tile + i * kPart);
+                }
+                s = mfma_parts<P::kIn, P::kIn>(kf[ks & 1], qf[ks], s);
+                if constexpr (P::kBuffers == 2) {
+                    // A lone wavefront issues in order: what stands behind a run of matrix instructions waits for all but the
+                    // last of them.  So the split of one piece (some thirty instructions) goes between the six, five to each.
+                    // (Past the last stage the registers' old rows go into the buffer nobody reads any more.)
+                    static_assert(P::kBuffers == 1 || (P::kT == 1 && kPieces == kKS), "one piece per contraction step");
+                    store_piece(ks, (g + 1) & 1);
+#pragma unroll
+                    for (int i = 0; i < 6; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
+                        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);      // vector ALU
+                        if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
+                    }
+                    __builtin_amdgcn_sched_group_barrier(0x200, 3, 0);          // LDS writes
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if constexpr (P::kBuffers == 2) {
+                if (ahead) {
+                    row0[c] = row0_next[c];
+                    if (g + 2 < stages) fetch(g + 2);
+                }
+                if (!mine) { __syncthreads(); continue; }
             }
             if (valid < 32) {
+                int base = half * 4;
+                asm volatile("" : "+v"(base));                   // (a branch, not sixteen selects on every tile)
 #pragma unroll
                 for (int j = 0; j < 16; ++j)
-                    if ((j >> 2) * 8 + half * 4 + (j & 3) >= valid) s[j] = -INFINITY;
+                    if ((j >> 2) * 8 + base + (j & 3) >= valid) s[j] = -INFINITY;
             }
-            float mx = s[0];
+            // The exponentials are taken against the reference as it stands; their sum, which joins the normaliser anyway,
+            // is also the guard: beyond 2^10 (or not a number, as before the first tile) the reference is moved to the row
+            // maximum and they are taken again, once.
+            float p[2][8], sum = 0.f;
+            auto exps = [&]() {
 #pragma unroll
-            for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
-            mx = max_across_halves(mx) * kScaleLog2;             // finite for finite inputs: the tile holds at least one key
-            if (__any(mx > ref + kMoveReference)) {
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) p[t][i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t * 8 + i], kScaleLog2, -ref));
+                // (the tile's share first: fewer roundings at the running sum's size)
+                sum = (((p[0][0] + p[0][1]) + (p[0][2] + p[0][3])) + ((p[0][4] + p[0][5]) + (p[0][6] + p[0][7]))) +
+                      (((p[1][0] + p[1][1]) + (p[1][2] + p[1][3])) + ((p[1][4] + p[1][5]) + (p[1][6] + p[1][7])));
+            };
+            exps();
+            if (__any(!(sum <= kSumLimit))) {
+                float mx = s[0];
+#pragma unroll
+                for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+                mx = max_across_halves(mx) * kScaleLog2;             // finite for finite inputs: the tile holds at least one key
                 const float ref_new = fmaxf(ref, mx);
                 const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);      // first tile: exp2(-inf) = 0
                 ref = ref_new;
@@ -369,22 +456,19 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 for (int db = 0; db < kDB; ++db)
 #pragma unroll
                     for (int j = 0; j < 16; ++j) o[db][j] *= alpha;
-            }
-            v8bf pf[2][3];
-            float sum = 0.f;                                     // the tile's share first: fewer roundings at the running sum's size
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                float p[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t * 8 + i], kScaleLog2, -ref));
-                sum += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
-                split8(p, pf[t]);
+                exps();
             }
             l_run += sum;
+            if constexpr (!BF16 && D == 128) {
 #pragma unroll
-            for (int db = 0; db < kDB; ++db)
+                for (int db = 0; db < kDB; ++db) asm volatile("" : "+v"(o[db]));
+            }
+            v8bf pf[2][3];
+            split8(p[0], pf[0]);
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
+            for (int t = 0; t < 2; ++t) {
+#pragma unroll
+                for (int db = 0; db < kDB; ++db) {
                     v8bf vf[P::kIn];
 #pragma unroll
                     for (int i = 0; i < P::kIn; ++i) {
@@ -396,6 +480,17 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                     }
                     o[db] = mfma_parts<P::kIn, 3>(vf, pf[t], o[db]);
                 }
+                if (t == 0) split8(p[1], pf[1]);          // (between the products of the first half)
+            }
+            constexpr int kPvMfma = kDB * (P::kIn == 3 ? 6 : 3);          // of one half
+            __builtin_amdgcn_sched_group_barrier(0x100, 2 * P::kIn, 1);
+#pragma unroll
+            for (int i = 0; i < 2 * kPvMfma; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+                __builtin_amdgcn_sched_group_barrier(0x100, 2 * P::kIn * kDB / kPvMfma, 1);
+                if (i < kPvMfma) __builtin_amdgcn_sched_group_barrier(0x002, (44 + kPvMfma - 1) / kPvMfma, 1);
+            }
+            if constexpr (P::kBuffers == 2) __syncthreads();
         }
     }
 
@@ -472,8 +567,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 
 // Measured against the vector-ALU kernel before it (one thread, eight logits and D / 8 channels of a row; 16 TFLOP/s at
 // d = 64, 7 at d = 128): bf16 d = 64, 17 550 tokens x 12 heads, block 64, 32 % of the blocks kept (0.30 TFLOP)
-// 18.43 -> 0.784 ms; fp32 d = 128, 6144 tokens x 8 heads, block 128, 48 % (0.073 TFLOP) 10.21 -> 0.617 ms.  Error against
-// 64 bits (2-norm): fp32 d = 128 O 1.9e-6 -> 1.4e-6, d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
+// 18.43 -> 0.70 ms, bound by the vector ALU (some 150 instructions a tile, 16 of them exponentials, beside 16 matrix
+// instructions); fp32 d = 128, 6144 tokens x 8 heads, block 128, 48 % (0.073 TFLOP, 384 workgroups: a round and a half)
+// 10.21 -> 0.51 ms.  The packed split (one conversion per pair and part), the guard by the sum and the two buffers at
+// d = 128 were worth 0.784 -> 0.70 and 0.617 -> 0.51.  Error against 64 bits (2-norm): fp32 d = 128 O 1.9e-6 -> 1.4e-6,
+// d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
 // The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two.
 template <bool BF16, int D, int BS>
 __global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu((!BF16 && D == 128) ? 1 : 2)))
