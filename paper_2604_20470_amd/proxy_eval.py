@@ -20,15 +20,24 @@ def attention_matrix(ctx: dr.Context, shape: dr.Shape, Q, K, rowptr, colidx, mas
     import torch
     B, H, N, d = Q.shape
     assert Q.dtype == torch.float32 and K.dtype == torch.float32, "the read-out uses the fp32 attention path"
-    A = torch.zeros((B, H, N, N), dtype=torch.float32, device=Q.device)
-    V = torch.zeros_like(Q)
+    A = torch.empty((B, H, N, N), dtype=torch.float32, device=Q.device)
     O = torch.empty_like(Q)
-    for c0 in range(0, N, d):
-        w = min(d, N - c0)
-        V.zero_()
-        idx = torch.arange(w, device=Q.device)
-        V[:, :, c0 + idx, idx] = 1.0                      # key c0 + j carries the unit vector e_j
-        dr.dr_sparse_attn_fwd(ctx, shape, Q, K, V, rowptr, colidx, mask_heads, capacity, O)
+    # One-hot values for the key range c0 .. c0 + w - 1 (key c0 + j carries the unit vector e_j).  With the heads' rows one
+    # after the other the range is moved by moving the start of the view: every head's w unit rows sit at its last rows,
+    # and a view that starts s rows later shows them s keys earlier (what it shows of the next head is zero).  The last
+    # range may overlap the one before it.
+    w = min(d, N)
+    flat = torch.zeros((B * H * N + N, d), dtype=torch.float32, device=Q.device)
+    flat[:B * H * N].view(B * H, N, d)[:, N - w:, :w] = torch.eye(w, dtype=torch.float32, device=Q.device)
+    straight = Q.is_contiguous()
+    V = None if straight else torch.empty_like(Q)
+    for c0 in sorted({min(c, N - w) for c in range(0, N, w)}):
+        s = N - w - c0
+        view = flat[s:s + B * H * N].view(B, H, N, d)
+        if not straight:                               # V shares the strides of Q
+            V.copy_(view)
+            view = V
+        dr.dr_sparse_attn_fwd(ctx, shape, Q, K, view, rowptr, colidx, mask_heads, capacity, O)
         A[:, :, :, c0:c0 + w] = O[:, :, :, :w]
     torch.cuda.synchronize()
     return A
