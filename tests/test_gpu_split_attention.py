@@ -107,3 +107,17 @@ def test_infinite_inputs_give_what_fp32_arithmetic_gives(dtype, d, bs):
             rows = slice(qb * bs, qb * bs + blk.shape[0])
             assert np.abs(to_f64(O[0, h, rows]) - blk).max() <= bounds[0] * 4, (h, qb)
             assert np.abs(lse[0, h, rows].cpu().numpy() - want_lse[qb]).max() <= bounds[1] * 4 + 1e-5, (h, qb)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+def test_lists_longer_than_every_streams_window(dtype, d):
+    """Block size 32: a stream of eight (four) sees every eighth (fourth) entry through a window of 64 of its own."""
+    wl = dataclasses.replace(tiny_case("ragged128"), dtype=dtype, d=d, Bs=32, Nf=19, Hg=27, Wg=33, H=1, index=62)
+    run = GpuRun(wl)
+    Sb = wl.Sb                                               # N = 16929: 530 blocks, the last of one key
+    assert Sb > 8 * 64
+    rows = [[] for _ in range(Sb)]
+    rows[0] = rows[5] = rows[Sb - 1] = list(range(Sb))
+    rows[7] = list(range(0, Sb, 2))
+    rp, ci = _csr(rows)
+    _check(run, rp, ci, *_attend(run, rp, ci))
