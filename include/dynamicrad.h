@@ -213,7 +213,9 @@ dr_status dr_build_mask(dr_ctx* ctx, const dr_shape* shape, int32_t mode, double
  *   lse          optional device float32 [B, H, N]: natural-log sum-exp of each row's logits
  * bf16 inputs with d = 128 use bf16 MFMA (operands Q * log2(e)/sqrt(d) re-rounded to bf16, K,
  * V and the probabilities rounded to bf16) with fp32 accumulation and fp32 softmax, for every
- * block size; fp32 inputs, and bf16 inputs with d = 64, are computed in fp32 throughout.
+ * block size; fp32 inputs, and bf16 inputs with d = 64, are computed at fp32 accuracy throughout (every 32-bit operand,
+ * probabilities included, as three bf16 parts on the matrix cores with fp32 accumulation; blocks with results that are
+ * not finite again in plain fp32 arithmetic).
  * Accuracy range of the bf16 MFMA path: the second rounding of the scaled Q adds a logit error
  * that grows with |logit|, so every group of 128 query rows that holds a row whose largest
  * logit exceeds 44 in magnitude (64 in units of log2) is computed a second time, by a pass
