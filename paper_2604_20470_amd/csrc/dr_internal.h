@@ -116,6 +116,7 @@ hipError_t launch_attn_mfma_second_pass(const AttnArgs& a, hipStream_t s);
 // bf16 storage, d = 128, Bs = 128, N >= 64: MFMA path that walks pairs of adjacent query blocks (one wave per SIMD,
 // 64 queries per wave); needs gcol / gcount / flags.  Rows it flags must be taken again by the second pass above.
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, hipStream_t s);
+hipError_t launch_attn_mfma_duo(const AttnArgs& a, int grid, hipStream_t s);      // (its variant of two wavefronts; lists of two rows are made)
 bool attn_mfma_pair_supported(const AttnArgs& a);
 // Merged key-block lists of every group of L (2 or 4) consecutive CSR rows: a.gcol (laid out like colidx, a group's
 // entries at the colidx offset of its first row; entry = key block | rows-that-list-it << 28) and a.gcount.
