@@ -282,7 +282,8 @@ dr_status dr_sparse_attn_fwd_static(dr_ctx* ctx, const dr_shape* shape, const vo
  *   P(i, j) = {(u, v): |u - v| <= w(t)}: mu = mean, sigma = population standard deviation of the scores,
  *   z = (s - mu) / (sigma + 1e-6), link when z >= tau, tau = `tau_near` when the decay length L(t) >= Bs, else
  *   params->tau_far (if has_tau_far, else tau_near); if no pair of the set passes, its highest score is a link
- *   (first in row-major (u, v) order on ties).  Statistics in fp64 with every sum taken column by column (u
+ *   (first in row-major (u, v) order on ties).  In a set that holds an infinity or a NaN no z is a number and nothing
+ *   passes; there a NaN ranks below every number.  Statistics in fp64 with every sum taken column by column (u
  *   ascending inside key column v, then the column sums with v ascending), one by one, no fused multiply-add:
  *   part of the definition, so that masks are reproducible bit for bit.
  *   Then block (qb, kb) is kept when it holds a token pair with t <= 1, or when

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restric
 struct PairStat {
     double mu;
     unsigned long long best;      // order-preserving image of the best score << 32 | ~(u * Nt + v)
-    float threshold;              // a pair is a link when its score is at least this
+    float threshold;              // a pair is a link when its score is at least this; NaN: none is
     unsigned int kept;
 };
 
@@ -186,7 +186,8 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
 }
 
 // grid: (Nf * Nf, masks, B), 64 threads.  The test ((double)s - mu) / denom >= tau is monotone in s (IEEE subtraction and
-// division are), so the smallest float that passes, found by bisection over the floats in order, decides it exactly.
+// division are), so the smallest float that passes, found by bisection over the floats in order, decides it exactly.  A set
+// that holds an infinity or a NaN has a mean or a deviation that is not a number, and no score passes, infinite ones included.
 __global__ __launch_bounds__(64) void k_link_stats(FrameTab tab, int Nt, int Nf, double tau_near, double tau_far,
                                                    const double* __restrict__ devs, PairStat* __restrict__ stats) {
     extern __shared__ double sh[];
@@ -196,13 +197,14 @@ __global__ __launch_bounds__(64) void k_link_stats(FrameTab tab, int Nt, int Nf,
     if (threadIdx.x != 0) return;
     const double mu = stats[p.pair].mu;
     const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
-    uint32_t lo = score_image(-3.402823466e38f), hi = score_image(3.402823466e38f) + 1u;      // first image that passes; hi: none
+    const uint32_t none = score_image(3.402823466e38f) + 1u;
+    uint32_t lo = score_image(-3.402823466e38f), hi = none;      // first image that passes
     while (lo < hi) {
         const uint32_t mid = lo + (hi - lo) / 2;
         if (((double)image_score(mid) - mu) / denom >= tau) hi = mid;
         else lo = mid + 1u;
     }
-    stats[p.pair].threshold = image_score(lo);      // + infinity when no float passes
+    stats[p.pair].threshold = lo < none ? image_score(lo) : __builtin_nanf("");
     stats[p.pair].kept = 0u;
     stats[p.pair].best = 0ull;
 }
@@ -237,7 +239,8 @@ __global__ __launch_bounds__(kThreads) void k_links(const float* __restrict__ sc
                 if (e < n && abs(u - (v + e)) <= p.w) {
                     out[e] = s[e] >= threshold ? 1 : 0;
                     kept += out[e];
-                    const unsigned long long key = ((unsigned long long)score_image(s[e] + 0.0f) << 32) | (0xffffffffu - (uint32_t)(u * Nt + v + e));
+                    const uint32_t image = s[e] == s[e] ? score_image(s[e] + 0.0f) : 0u;      // (a NaN ranks below every number)
+                    const unsigned long long key = ((unsigned long long)image << 32) | (0xffffffffu - (uint32_t)(u * Nt + v + e));
                     best = max(best, key);
                 }
             }
