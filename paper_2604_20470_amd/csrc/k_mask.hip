@@ -690,7 +690,8 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
         // a rounding of the whole sum (at most n)
         const bool all = a.tau >= 1.0 && range < 34.0f - (float)log_n;
         const bool flat = range == 0.f;                     // every mass is 1: the running sum counts, in key-block order
-        Crossing got = (a.tau >= 1.0 || flat) ? Crossing::kTooMany : Crossing::kTooClose;
+        // (infinities and NaN, or finite scores further apart than a float holds: the chain is the definition)
+        Crossing got = (a.tau >= 1.0 || flat || !(range < INFINITY)) ? Crossing::kTooMany : Crossing::kTooClose;
         if (!all && got == Crossing::kTooClose) {
             // 32 bits, exponentials in fp32.  The argument is off by at most 2^-23 |x| (and x e^-x <= 0.37), the
             // instruction by 2^-23 relative, rounding to a unit by one half.

@@ -38,3 +38,31 @@ def test_prefix_bit_exact(frames, hg, wg, heads):
         few = [0] if heads == 1 else [0, heads - 1]
         want = oracle_masks_from(scores[:, few], cls, "dynamic", tau)
         assert_masks_equal(rowptr[:, few], colidx[:, few], nnz[:, few], want)
+
+
+@pytest.mark.parametrize("bits", [0x7f800000, 0xff800000, 0x7fc00000, 0xffc00000])      # infinities and NaN of both signs
+@pytest.mark.parametrize("tau", [0.3, 1.0])
+def test_scores_that_are_not_finite_take_the_chain(bits, tau):
+    """Beyond the contract, but defined by the rule as written: where the whole sum is not a number no prefix reaches its
+    share and the row keeps every block; a mass of exp(-inf) = 0 is left out of a prefix that ends before it."""
+    wl = dataclasses.replace(tiny_case("tiny8"), Nf=8, Hg=10, Wg=17, Bs=32, H=1, index=102)
+    run = GpuRun.__new__(GpuRun)
+    run.wl, run.heads, run.params, run.device, run.Sb = wl, [0], dr.MaskParams(head_fuse=0, gamma=3.0), "cuda:0", wl.Sb
+    run.ctx = dr.Context(0)
+    run.shape = dr.Shape(1, 1, wl.N, 64, 8, 10, 17, 32, 0, 0, wl.N * 64, wl.N * 64, 64)
+    scores = torch.randn(1, 1, wl.Sb, wl.Sb, generator=torch.Generator().manual_seed(7))
+    special = torch.zeros(wl.Sb, dtype=torch.bool)
+    special[::5] = True
+    scores.view(torch.int32)[..., special] = bits - (1 << 32) if bits >> 31 else bits
+    rowptr, colidx, _, _ = run.build_mask(scores.cuda(), "dynamic", tau)
+    rp, ci, cls = rowptr[0, 0].cpu().numpy(), colidx[0, 0].cpu().numpy(), oracle_class_map(wl, gamma=3.0)
+    for qb in range(wl.Sb):
+        free = np.nonzero((cls[qb] == 1) | (cls[qb] == 2))[0]
+        forced = np.nonzero(cls[qb] == 3)[0]
+        kept = free
+        if bits == 0xff800000 or not special.numpy()[free].any():
+            s = scores[0, 0, qb].numpy()[free].astype(np.float64)
+            order = np.lexsort((free, -s))
+            run_sum = np.add.accumulate(np.exp(s[order] - s.max())) if free.size else np.zeros(0)
+            kept = free[order[:1 + int(np.argmax(run_sum >= tau * run_sum[-1]))]] if free.size else free
+        assert np.array_equal(ci[rp[qb]:rp[qb + 1]], np.union1d(kept, forced)), qb
