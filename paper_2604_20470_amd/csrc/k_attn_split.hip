@@ -52,8 +52,8 @@ struct Plan {
     // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide the splitting of the next stage
     // behind: it goes into a second buffer, between the matrix instructions, where two fit
     static constexpr int kBuffers = !kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024 ? 2 : 1;
-    static constexpr int kPlainRows = kThreads / 8, kPlainKeys = 32;
-    static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainKeys * D + kPlainRows * kPlainKeys);
+    static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
+    static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainRows * kPlainKeys);
     static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
     static constexpr int kMax1 = kBuffers * kStageBytes > kPlainBytes ? kBuffers * kStageBytes : kPlainBytes;
     static constexpr int kLdsBytes = kMax1 > kMergeBytes ? kMax1 : kMergeBytes;
@@ -136,16 +136,17 @@ struct Item {
     int64_t row_bytes;
 };
 
-// The query block in plain fp32 on the vector ALU (thread (r, g): row r, four of the 32 logits of a chunk, D / 8 output
-// channels).  Only for blocks whose inputs hold infinities or NaN.
+// The query block in plain fp32 on the vector ALU (thread (r, g): row r, every eighth logit of a chunk, D / 8 output
+// channels).  Only for blocks whose inputs hold infinities or NaN.  A chunk is 64 keys where the block has them: a row is lost
+// only when every logit of its first chunk is -inf (nothing finite to subtract), and shorter chunks lose more rows.  Keys and
+// values take turns in one LDS area, so that this pass, which is rarely made, asks for little more than the walk does.
 template <bool BF16, int D, int BS>
 __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
     using P = Plan<BF16, D, BS>;
     constexpr int R = P::kPlainRows, C = P::kPlainKeys, DC = D / 8, LPT = C / 8;
     float* sQ = lds;
-    float* sK = sQ + R * D;
-    float* sV = sK + C * (D + 1);
-    float* sP = sV + C * D;
+    float* sX = sQ + R * D;                    // keys, then values
+    float* sP = sX + C * (D + 1);
     const int tid = threadIdx.x, r = tid >> 3, g = tid & 7;
     const float scale = 1.0f / sqrtf((float)D);
     for (int row0 = it.qb * BS; row0 < min(it.N, it.qb * BS + BS); row0 += R) {
@@ -161,15 +162,14 @@ __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
             const int k_end = min(it.N, (kb + 1) * BS);
             for (int k0 = kb * BS; k0 < k_end; k0 += C) {
                 const int nk = min(C, k_end - k0);
-                __syncthreads();
-                for (int kr = tid >> 3; kr < C; kr += R) {
-                    if (kr < nk) {
-                        load_plain<BF16, D>(it.K + (int64_t)(k0 + kr) * it.row_bytes, sK + kr * (D + 1), g);
-                        load_plain<BF16, D>(it.V + (int64_t)(k0 + kr) * it.row_bytes, sV + kr * D, g);
-                    } else {
-                        for (int c = g; c < D; c += 8) { sK[kr * (D + 1) + c] = 0.f; sV[kr * D + c] = 0.f; }
+                auto load = [&](const char* X) {
+                    for (int kr = tid >> 3; kr < C; kr += R) {
+                        if (kr < nk) load_plain<BF16, D>(X + (int64_t)(k0 + kr) * it.row_bytes, sX + kr * (D + 1), g);
+                        else for (int c = g; c < D; c += 8) sX[kr * (D + 1) + c] = 0.f;
                     }
-                }
+                };
+                __syncthreads();
+                load(it.K);
                 __syncthreads();
                 float s[LPT];
 #pragma unroll
@@ -177,7 +177,7 @@ __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
                 for (int c = 0; c < D; ++c) {
                     const float qv = sQ[r * D + c];
 #pragma unroll
-                    for (int j = 0; j < LPT; ++j) s[j] = fmaf(qv, sK[(g + 8 * j) * (D + 1) + c], s[j]);
+                    for (int j = 0; j < LPT; ++j) s[j] = fmaf(qv, sX[(g + 8 * j) * (D + 1) + c], s[j]);
                 }
                 float mx = -INFINITY;
 #pragma unroll
@@ -199,12 +199,14 @@ __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
                 l_run = l_run * alpha + ps;
                 m_run = m_new;
                 __syncthreads();
+                load(it.V);
+                __syncthreads();
 #pragma unroll
                 for (int i = 0; i < DC; ++i) o[i] *= alpha;
                 for (int k = 0; k < nk; ++k) {
                     const float p = sP[r * C + k];
 #pragma unroll
-                    for (int i = 0; i < DC; ++i) o[i] = fmaf(p, sV[k * D + g * DC + i], o[i]);
+                    for (int i = 0; i < DC; ++i) o[i] = fmaf(p, sX[k * (D + 1) + g * DC + i], o[i]);
                 }
             }
         }

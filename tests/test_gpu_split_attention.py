@@ -121,3 +121,31 @@ def test_lists_longer_than_every_streams_window(dtype, d):
     rows[7] = list(range(0, Sb, 2))
     rp, ci = _csr(rows)
     _check(run, rp, ci, *_attend(run, rp, ci))
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+@pytest.mark.parametrize("bs", [64, 128])
+@pytest.mark.parametrize("hidden", [32, 33])
+def test_a_row_that_starts_with_a_whole_tile_of_minus_infinity(dtype, d, bs, hidden):
+    """The first tile of a row (32 keys), and a key of the next, are out of reach by a logit of -inf: weight 0."""
+    run = _run(dtype, d, bs, 5, 9, 13)                       # N = 585
+    Sb = run.wl.Sb
+    rp, ci = _csr([list(range(Sb))] * Sb)
+    run.Qc[..., 3] = run.Qc[..., 3].abs() + 0.5
+    run.Kc[:, :, :hidden] = 0.0
+    run.Kc[:, :, :hidden, 3] = -float("inf")
+    run.Q, run.K, run.V = run.Qc.cuda(), run.Kc.cuda(), run.Vc.cuda()
+    O, lse = _attend(run, rp, ci)
+    run.Kc[:, :, :hidden, 3] = -1e4                          # the same by a finite logit (its weight underflows in 64 bits too)
+    for h in range(2):
+        want, want_lse = o.masked_attention(to_f64(run.Qc[0, h]), to_f64(run.Kc[0, h]), to_f64(run.Vc[0, h]), rp, ci, bs,
+                                            return_lse=True)
+        finite = run.Kc.clone()
+        finite[:, :, :hidden] = 0.0                          # (the bounds: of the keys that carry weight)
+        q, k, v = (np.abs(to_f64(t[0, h])) for t in (run.Qc, finite, run.Vc))
+        logit = 2.0 ** -22 * float((q @ k.T).max()) / np.sqrt(d)
+        tol = v.max() * (2.0 * logit + 2.0 ** -20) + (v.max() * 2.0 ** -8 if dtype == "bf16" else 0.0)
+        for qb, blk in want.items():
+            rows = slice(qb * bs, qb * bs + blk.shape[0])
+            assert np.abs(to_f64(O[0, h, rows]) - blk).max() <= tol, (h, qb)
+            assert np.abs(lse[0, h, rows].cpu().numpy() - want_lse[qb]).max() <= logit + 2.0 ** -20 + 2.0 ** -23 * 16, (h, qb)
