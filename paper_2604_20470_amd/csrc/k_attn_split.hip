@@ -52,6 +52,7 @@ struct Plan {
     // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide the splitting of the next stage
     // behind: it goes into a second buffer, between the matrix instructions, where two fit
     static constexpr int kBuffers = !kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024 ? 2 : 1;
+    static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : BF16 && D == 64 && BS == 128 ? 4 : 2;      // wavefronts, at least
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
     static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainRows * kPlainKeys);
     static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
@@ -613,10 +614,20 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
         }
         ref = top;
     }
+    // Nothing is stored before every wavefront's results are known to stand: the plain pass reads Q again, which O may overlay.
+    const bool writer = ws == 0 && qrow < N;
+    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
     bool bad = false;
-    if (ws == 0 && qrow < N) {
-        const float inv = (l > 0.f) ? 1.0f / l : 0.f;
+    if (writer) {
         float check = l;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) check += fabsf(o[db][j] * inv) * 0.f;      // NaN as soon as one value is not finite
+        bad = it.n_list > 0 && !(check > 0.f && check < INFINITY);
+    }
+    const bool plain = __syncthreads_or(bad ? 1 : 0) != 0;
+    if (writer && !plain) {
         char* dst = it.O + (int64_t)qrow * it.row_bytes;
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
@@ -625,10 +636,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 const int ch = db * 32 + q4 * 8 + half * 4;
                 v4f32 val;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    val[i] = o[db][q4 * 4 + i] * inv;
-                    check += fabsf(val[i]) * 0.f;                // NaN as soon as one value is not finite
-                }
+                for (int i = 0; i < 4; ++i) val[i] = o[db][q4 * 4 + i] * inv;
                 if constexpr (BF16) {
                     v4bf r;
 #pragma unroll
@@ -640,9 +648,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             }
         if (it.lse && half == 0)      // the two terms in 64 bits: the reference is a rounded multiple of the scale
             it.lse[qrow] = (l > 0.f) ? (float)((double)ref * 0.69314718055994531 + log((double)l)) : -INFINITY;
-        bad = it.n_list > 0 && !(check > 0.f && check < INFINITY);
     }
-    if (__syncthreads_or(bad ? 1 : 0)) plain_block<BF16, D, BS>(it, reinterpret_cast<float*>(smem));
+    if (plain) plain_block<BF16, D, BS>(it, reinterpret_cast<float*>(smem));
 }
 
 // Measured against the vector-ALU kernel before it (one thread, eight logits and D / 8 channels of a row; 16 TFLOP/s at
@@ -654,9 +661,10 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
 // Block size 32, fp32 d = 64, 2048 tokens x 2 heads, all blocks: 700 us with the vector ALU, 45 us with four wavefronts that
 // share stages behind barriers, some 25 us with eight that walk alone.
-// The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two.
+// The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two or three, and bf16
+// d = 64 at block size 128, which fits 128 registers, four.
 template <bool BF16, int D, int BS>
-__global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu((!BF16 && D == 128) ? 1 : 2)))
+__global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS>::kPerSimd)))
 void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS>(a); }
 
 template <bool BF16, int D, int BS>

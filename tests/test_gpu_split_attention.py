@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import paper_2604_20470_amd as dr
 from oracle import dynamicrad_oracle as o
 from workloads import tiny_case
 
@@ -149,3 +150,23 @@ def test_a_row_that_starts_with_a_whole_tile_of_minus_infinity(dtype, d, bs, hid
             rows = slice(qb * bs, qb * bs + blk.shape[0])
             assert np.abs(to_f64(O[0, h, rows]) - blk).max() <= tol, (h, qb)
             assert np.abs(lse[0, h, rows].cpu().numpy() - want_lse[qb]).max() <= logit + 2.0 ** -20 + 2.0 ** -23 * 16, (h, qb)
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+@pytest.mark.parametrize("bs", [32, 64, 128])
+def test_output_over_q_for_every_input(dtype, d, bs):
+    """A query block reads only its own rows of Q, also when infinities send it to the plain pass: O may overlay Q."""
+    run = _run(dtype, d, bs, 5, 9, 13)                       # N = 585
+    Sb = run.wl.Sb
+    rows = [list(range(Sb))] * Sb
+    rows[1] = list(range(2, Sb))                             # not the key block of the infinity at any block size: stays finite
+    rp, ci = _csr(rows)
+    run.Vc[:, :, 20, 5] = float("inf")
+    run.V = run.Vc.cuda()
+    want, want_lse = _attend(run, rp, ci)
+    rowptr, colidx = (torch.from_numpy(x.astype(np.int32)).view(1, 1, -1).contiguous().cuda() for x in (rp, ci))
+    O, lse = run.Q.clone(), torch.empty_like(want_lse)
+    dr.dr_sparse_attn_fwd(run.ctx, run.shape, O, run.K, run.V, rowptr, colidx, 1, colidx.shape[2], O, lse)
+    torch.cuda.synchronize()
+    assert torch.isposinf(want[:, :, :bs, 5].float()).all() and torch.isfinite(want[:, :, bs:2 * bs].float()).all()
+    assert torch.equal(O.view(torch.uint8), want.view(torch.uint8)) and torch.equal(lse, want_lse)
