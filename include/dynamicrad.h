@@ -214,8 +214,12 @@ dr_status dr_build_mask(dr_ctx* ctx, const dr_shape* shape, int32_t mode, double
  * bf16 inputs with d = 128 use bf16 MFMA (operands Q * log2(e)/sqrt(d) re-rounded to bf16, K,
  * V and the probabilities rounded to bf16) with fp32 accumulation and fp32 softmax, for every
  * block size; fp32 inputs, and bf16 inputs with d = 64, are computed at fp32 accuracy throughout (every 32-bit operand,
- * probabilities included, as three bf16 parts on the matrix cores with fp32 accumulation; blocks with results that are
- * not finite again in plain fp32 arithmetic).
+ * probabilities included, as three bf16 parts on the matrix cores with fp32 accumulation; the three of nine part products
+ * that lie 2^-26 and more below the first are left out).  Three parts hold a value to 2^-134 at best, so a query block of
+ * fp32 storage is computed again in plain fp32 arithmetic when it has a result between 0 and 2^-108 (3e-33), queries beyond
+ * 2^100, or nonzero queries below 2^-108 beside keys beyond 2^100; so is a block, of either storage, with results that are
+ * not finite.  What is left: a value below 2^-133 (subnormal, 9e-41) counts as 0, and a probability below 2^-108 of its
+ * row's largest is correct to 2^-134 of that.
  * Accuracy range of the bf16 MFMA path: the second rounding of the scaled Q adds a logit error
  * that grows with |logit|, so every group of 128 query rows that holds a row whose largest
  * logit exceeds 44 in magnitude (64 in units of log2) is computed a second time, by a pass

@@ -2,9 +2,9 @@
 // the bf16 shapes that k_attn_mfma* do not cover (d = 64), on the bf16 matrix instructions.  gfx950 only.
 //
 // What bounds it: the fp32 matrix instruction does 1/16 of the bf16 one's operations per cycle, the vector ALU no more.
-// So every 32-bit operand is split into three bf16 parts, x = h + m + l, which is exact (8 + 8 + 8 significant bits,
-// each part the rounding of what the parts before it leave), and a product is summed from part products on the bf16
-// matrix cores with fp32 accumulation.  Of the nine part products the three of order 2^-24 and below (m l, l m, l l)
+// So every 32-bit operand is split into three bf16 parts, x = h + m + l, which is exact down to 2^-110 (8 + 8 + 8 significant
+// bits, each part the rounding of what the parts before it leave), and a product is summed from part products on the bf16
+// matrix cores with fp32 accumulation.  Of the nine part products the three of order 2^-26 and below (m l, l m, l l)
 // are left out: 6 bf16 instructions for one, 2.7 times the rate of the fp32 instruction.  Inputs stored as bf16 are one
 // part (their products are exact); the probabilities stay 32-bit and are always three parts.
 // Times and errors against 64 bits are at the kernel's definition below.
@@ -19,8 +19,9 @@
 // Softmax is online in fp32; the exponent reference of a query is moved only when a tile's probabilities outgrow it by
 // 2^10, which costs no accuracy (fp32 sums are scale free), so the steady state forms no maximum and rescales nothing.
 //
-// Infinite inputs (or values that round to infinity in bf16) make inf - inf in a split.  A workgroup that finds a result
-// that is not finite takes its query block again with plain fp32 arithmetic on the vector ALU, whose answer stands.
+// Infinite inputs (or values that round to infinity in bf16) make inf - inf in a split, and values far below 1 lose their
+// third part (kTiny).  A workgroup that finds a result that is not finite, or one that may have lost bits, takes its query
+// block again with plain fp32 arithmetic on the vector ALU, whose answer stands.
 #include "attn_mfma_common.h"
 #include "dr_internal.h"
 
@@ -30,6 +31,11 @@ namespace {
 using namespace mfma;
 
 constexpr float kSumLimit = 1024.0f;      // a lane's sixteen probabilities of a tile may sum to at most this
+// Three parts hold a value to 2^-134 at best (bf16 ends at 2^-133), that is, exactly down to 2^-110.  What that does to fp32
+// results: an output that is not 0 and below kTiny is taken again in plain fp32, and so is a block whose logits could feel
+// it, that is, where values of Q beyond kHuge, or nonzero ones below kTiny against keys beyond kHuge, leave an error of more
+// than 2^-34 in a product.
+constexpr float kTiny = 0x1p-108f, kHuge = 0x1p100f;
 
 typedef __attribute__((address_space(3))) const v8bf* lds_v8;
 typedef __attribute__((address_space(3))) v4s* lds_v4;
@@ -104,7 +110,7 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
     return (uint16_t)(u >> 16);
 }
 
-// c += a b with both operands in parts: the six part products of order above 2^-24 (three when b is one part), small ones first
+// c += a b with both operands in parts: the six part products of order above 2^-26 (three when b is one part), small ones first
 template <int NA, int NB>
 __device__ __forceinline__ v16f mfma_parts(const v8bf (&a)[NA], const v8bf (&b)[NB], v16f c) {
 #pragma unroll
@@ -128,6 +134,10 @@ __device__ __forceinline__ void load_plain(const char* src, float* dst, int g) {
     }
 }
 
+// |x| of a value that is not 0 as an integer, ascending like |x|; a zero gives the largest of all
+__device__ __forceinline__ uint32_t nonzero_magnitude(float x) { return (__float_as_uint(x) << 1) - 1u; }
+constexpr uint32_t kTinyMagnitude = ((127u - 108u) << 24) - 1u;      // of kTiny
+
 struct Item {
     const char *Q, *K, *V;      // of this (batch, head)
     char* O;
@@ -138,9 +148,10 @@ struct Item {
 };
 
 // The query block in plain fp32 on the vector ALU (thread (r, g): row r, every eighth logit of a chunk, D / 8 output
-// channels).  Only for blocks whose inputs hold infinities or NaN.  A chunk is 64 keys where the block has them: a row is lost
-// only when every logit of its first chunk is -inf (nothing finite to subtract), and shorter chunks lose more rows.  Keys and
-// values take turns in one LDS area, so that this pass, which is rarely made, asks for little more than the walk does.
+// channels).  Only for blocks with infinities or NaN, or beyond the range that three parts hold (kTiny).  A chunk is 64 keys
+// where the block has them: a row is lost only when every logit of its first chunk is -inf (nothing finite to subtract), and
+// shorter chunks lose more rows.  Keys and values take turns in one LDS area, so that this pass, which is rarely made, asks
+// for little more than the walk does.
 template <bool BF16, int D, int BS>
 __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
     using P = Plan<BF16, D, BS>;
@@ -224,6 +235,21 @@ __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
     }
 }
 
+// whether this thread's share of the listed keys (fp32) holds one beyond kHuge
+template <int D, int BS>
+__device__ __forceinline__ bool holds_huge_keys(const Item& it) {
+    float most = 0.f;
+    for (int e = 0; e < it.n_list; ++e) {
+        const int kb = min(max(it.list[e], 0), it.Sb - 1), rows = min(BS, it.N - kb * BS);
+        for (int u = threadIdx.x; u < rows * (D / 4); u += blockDim.x) {
+            const v4f32 x = *reinterpret_cast<const v4f32*>(it.K + (int64_t)(kb * BS + u / (D / 4)) * it.row_bytes + u % (D / 4) * 16);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) most = fmaxf(most, fabsf(x[i]));
+        }
+    }
+    return most >= kHuge;
+}
+
 template <bool BF16, int D, int BS>
 __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     using P = Plan<BF16, D, BS>;
@@ -234,6 +260,10 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
+    // Twelve idle instructions that only move the code behind them: a lone wavefront per SIMD with a loop of 9.5 KB waits for
+    // instruction fetches, and with the place of that loop, in steps of 4 bytes over a line of 64, the same code took 650 to
+    // 700 us (6144 tokens x 8 heads, 40 % kept).
+    if constexpr (!BF16 && D == 128 && BS == 32) asm volatile(".fill 12, 4, 0xbf800000");
     const int wq = wave % P::kQ, ws = wave / P::kQ;
 
     // one XCD walks a contiguous run of (batch, head, query block) items: neighbours share K and V in its L2
@@ -617,16 +647,45 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     // Nothing is stored before every wavefront's results are known to stand: the plain pass reads Q again, which O may overlay.
     const bool writer = ws == 0 && qrow < N;
     const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-    bool bad = false;
+    bool bad = false, q_tiny = false;
+    if constexpr (!BF16) {
+        // the first parts tell (a value that is 0 in all of them is below 2^-134 and lost to no purpose beside keys under kHuge)
+        typedef unsigned short v2us __attribute__((ext_vector_type(2)));
+        v2us least = {0xffff, 0xffff}, most = {0, 0};
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks)
+            if (ks % P::kS == ws) {                              // (the streams hold the same rows)
+                union { v8bf v; v2us u[4]; } w;
+                w.v = qf[ks][0];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const v2us twice = w.u[i] << 1;
+                    least = __builtin_elementwise_min(least, (v2us)(twice - 1));
+                    most = __builtin_elementwise_max(most, twice);
+                }
+            }
+        q_tiny = min(least[0], least[1]) < (kTinyMagnitude >> 16);
+        bad = max(most[0], most[1]) >= ((127 + 100) << 8);       // kHuge
+    }
     if (writer) {
         float check = l;
+        uint32_t least = ~0u;
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) check += fabsf(o[db][j] * inv) * 0.f;      // NaN as soon as one value is not finite
-        bad = it.n_list > 0 && !(check > 0.f && check < INFINITY);
+            for (int j = 0; j < 16; ++j) {
+                const float val = o[db][j] * inv;
+                check += fabsf(val) * 0.f;                       // NaN as soon as one value is not finite
+                if constexpr (!BF16) least = min(least, nonzero_magnitude(val));
+            }
+        bad = bad || !(check > 0.f && check < INFINITY) || least < kTinyMagnitude;
     }
-    const bool plain = __syncthreads_or(bad ? 1 : 0) != 0;
+    bad = bad && it.n_list > 0;
+    bool plain = __syncthreads_or((bad || (q_tiny && it.n_list > 0)) ? 1 : 0) != 0;
+    if constexpr (!BF16) {
+        // (tiny values of Q are at home among zeros; they matter beside huge keys alone)
+        if (plain && !__syncthreads_or(bad ? 1 : 0)) plain = __syncthreads_or(holds_huge_keys<D, BS>(it) ? 1 : 0) != 0;
+    }
     if (writer && !plain) {
         char* dst = it.O + (int64_t)qrow * it.row_bytes;
 #pragma unroll

@@ -170,3 +170,40 @@ def test_output_over_q_for_every_input(dtype, d, bs):
     torch.cuda.synchronize()
     assert torch.isposinf(want[:, :, :bs, 5].float()).all() and torch.isfinite(want[:, :, bs:2 * bs].float()).all()
     assert torch.equal(O.view(torch.uint8), want.view(torch.uint8)) and torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bs", [32, 64, 128])
+@pytest.mark.parametrize("q_by,k_by", [
+    (1e-36, 1e36),      # ordinary logits of factors whose third part lies below bf16's range
+    (1e36, 1e-36),
+    (1e-36, 1.0),       # tiny queries alone: every logit is 0 to any accuracy
+])
+def test_fp32_accuracy_of_logits_at_the_ends_of_the_range(d, bs, q_by, k_by):
+    """Errors relative to the results, as near 1; a few zeros, which say nothing about the range, stand among the values."""
+    run = _run("f32", d, bs, 5, 9, 13)                       # N = 585
+    Sb = run.wl.Sb
+    rp, ci = _csr([list(range(Sb))] * Sb)
+    for name, by in (("Qc", q_by), ("Kc", k_by)):
+        t = getattr(run, name)
+        t[:, :, ::17, 3] = 0.0
+        setattr(run, name, (t.double() * by).float())
+    run.Q, run.K = run.Qc.cuda(), run.Kc.cuda()
+    _check(run, rp, ci, *_attend(run, rp, ci))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bs", [32, 64, 128])
+@pytest.mark.parametrize("v_by", [1e-30, 1e-35, 1e-37])
+def test_fp32_values_whose_parts_end_below_the_range(d, bs, v_by):
+    """Every key of a head carries the same value row, so the result is that row however the weights round: a value held in
+    fewer bits shows as it is (1e-37: 4.5e-4 of it at bf16's last place) instead of averaging out."""
+    run = _run("f32", d, bs, 5, 9, 13)                       # N = 585
+    Sb = run.wl.Sb
+    rp, ci = _csr([list(range(Sb))] * Sb)
+    row = (run.Vc[:, :, :1].sign() * (run.Vc[:, :, :1].abs() + 0.5)).double() * v_by
+    run.Vc = row.float().expand_as(run.Vc).contiguous()
+    run.V = run.Vc.cuda()
+    O, _ = _attend(run, rp, ci)
+    # numerator and normaliser: chains of at most 585 additions of terms of one sign, each within 2^-24 of the running sum
+    assert ((O.cpu().double() - run.Vc.double()).abs() <= 2 * run.wl.N * 2.0 ** -24 * run.Vc.double().abs()).all()
