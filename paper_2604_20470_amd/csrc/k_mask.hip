@@ -824,8 +824,8 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
 }
 
 // grid: (Sb, masks, B)
-// rowptr of every mask of rows beyond 2048 key blocks: the exclusive prefix of its rows' kept counts, one workgroup per mask
-// (a row that re-sums all earlier counts itself reads Sb^2 / 2 of them per mask).  grid: (masks, B).
+// rowptr of every mask where the rows do not add up the earlier counts themselves (launch_emit): the exclusive prefix of its
+// rows' kept counts, one workgroup per mask.  grid: (masks, B).
 __global__ __launch_bounds__(kThreads) void k_row_offsets(const int32_t* __restrict__ counts, int masks, int Sb, int shared,
                                                           int32_t* __restrict__ rowptr, int64_t* __restrict__ nnz) {
     __shared__ long long s_wave[kWaves];
@@ -992,12 +992,13 @@ hipError_t launch_select_zscore(const uint8_t* class_map, const float* scores, i
     return hipGetLastError();
 }
 
-// Offsets and column lists in one launch, for rows of at most 2048 key blocks (64 bitmap words): one wave per row, no LDS
-// and no barrier; four rows per workgroup.  The wave adds the counts of the mask's earlier rows itself (at most 32 coalesced
-// reads per lane out of L2; a launch of its own for the offsets costs 4 to 5 us, more than that sum for any row).  A lane
-// loads one bitmap word; the wave then walks the row 64 key blocks at a time: the two words of that stretch are read back
-// as a wave-uniform lane mask, a lane whose bit is set stores its key block at the running offset plus the number of set
-// bits below it (v_mbcnt), so that each store instruction writes one contiguous run.  grid: ceil(B * masks * Sb / 4).
+// Column lists of rows of at most 2048 key blocks (64 bitmap words): one wave per row, no LDS and no barrier; four rows per
+// workgroup.  A lane loads one bitmap word; the wave then walks the row 64 key blocks at a time: the two words of that
+// stretch are read back as a wave-uniform lane mask, a lane whose bit is set stores its key block at the running offset plus
+// the number of set bits below it (v_mbcnt), so that each store instruction writes one contiguous run.
+// kOffsets: the row offsets are made here too: the wave adds the counts of the mask's earlier rows itself (at most 32
+// coalesced reads per lane out of L2).  grid: ceil(B * masks * Sb / 4).
+template <bool kOffsets>
 __global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts,
                                                         int64_t rows_total, int Sb, int shared, int32_t* __restrict__ rowptr,
                                                         int32_t* __restrict__ colidx, int64_t capacity, int64_t* __restrict__ nnz) {
@@ -1011,17 +1012,21 @@ __global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restri
     const int words = (Sb + 31) / 32;
     const uint32_t wv = (lane < words) ? keepbits[row * words + lane] : 0u;
     int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
-#pragma unroll 4
-    for (int i = lane; i < qb; i += 64) before += counts[src + i];
-    for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
     int32_t* rp = rowptr + mask_id * (Sb + 1);
-    if (lane == 0) {
-        rp[qb] = before;
-        if (qb == Sb - 1) {
-            const int all = before + counts[row];
-            rp[Sb] = all;
-            nnz[mask_id] = all;
+    if constexpr (kOffsets) {
+#pragma unroll 4
+        for (int i = lane; i < qb; i += 64) before += counts[src + i];
+        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
+        if (lane == 0) {
+            rp[qb] = before;
+            if (qb == Sb - 1) {
+                const int all = before + counts[row];
+                rp[Sb] = all;
+                nnz[mask_id] = all;
+            }
         }
+    } else {
+        before = rp[qb];
     }
     long long pos = before;
     int32_t* out = colidx + mask_id * capacity;
@@ -1037,13 +1042,19 @@ __global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restri
 
 hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, int masks, int Sb, bool shared,
                        int32_t* rowptr, int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s) {
-    if (Sb <= 64 * 32) {
-        const int64_t rows_total = (int64_t)B * masks * Sb;
-        const int waves = rows_total >= kWaveSelectPackRows ? kWaves : 1;
-        hipLaunchKernelGGL(k_emit_wave, dim3((unsigned)((rows_total + waves - 1) / waves)), dim3(64 * waves), 0, s, keepbits, counts,
-                           rows_total, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
-    } else {
+    const int64_t rows_total = (int64_t)B * masks * Sb;
+    // A launch of its own for the offsets costs about 2.3 us; adding up the earlier rows' counts costs some 0.06 us per 1000
+    // rows, for the dependent reads and the reduction, and as much again per 2000 counts of a row, for the reads: the two meet
+    // near 2^26 of this product.  Whole calls of the uniform rule, one launch against two: 9.3 / 11.0 us at one mask of 591
+    // rows, 15.4 / 15.3 at 40, 30.9 / 27.8 at 96; 14.0 / 17.7 at 4 masks of 2048 rows, 94 / 88 at 40.
+    const bool one_launch = Sb <= 64 * 32 && rows_total * (2048 + Sb) <= (int64_t)1 << 26;
+    if (!one_launch)
         hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
+    if (Sb <= 64 * 32) {
+        const int waves = rows_total >= kWaveSelectPackRows ? kWaves : 1;
+        hipLaunchKernelGGL(one_launch ? k_emit_wave<true> : k_emit_wave<false>, dim3((unsigned)((rows_total + waves - 1) / waves)),
+                           dim3(64 * waves), 0, s, keepbits, counts, rows_total, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
+    } else {
         hipLaunchKernelGGL(k_emit, dim3(Sb, masks, B), dim3(kThreads), 0, s, keepbits, masks, Sb, shared ? 1 : 0, rowptr,
                            colidx, capacity);
     }
