@@ -277,13 +277,16 @@ __global__ __launch_bounds__(64) void k_link_safeguard(FrameTab tab, int N, int 
 // Density rule.  One workgroup per query block; a thread sums the link bytes of sixteen consecutive key columns over the
 // block's rows, four to a 32-bit word (a count is at most 128), so that a wavefront reads 1 KB runs; the threads of a key
 // block then add their numbers of active columns.  Bound by reading the link bytes once.  (A lane per column, one byte at a
-// time and half the lanes idle at block size 32, took 380 us at 8192 tokens; this takes 20.)
+// time and half the lanes idle at block size 32, took 380 us at 8192 tokens; this takes 20.)  Where a row has fewer than
+// 128 such units the rows are shared out over the idle threads and their counts added up in LDS; the last unit of a row
+// whose length is no multiple of sixteen is the row's last sixteen bytes, of which its own columns count.
 // grid: (Sb, masks, B).
 __global__ __launch_bounds__(kThreads) void k_aggregate_links(const uint8_t* __restrict__ links,
                                                               const uint8_t* __restrict__ class_map, Geometry g,
                                                               uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
     constexpr int kCols = 16 * kThreads;                    // columns of a step: 32, 64 or 128 key blocks
     __shared__ uint32_t s_bits[4];
+    __shared__ uint4 s_part[kThreads];
     __shared__ int s_count;
     const int qb = blockIdx.x, tid = threadIdx.x;
     const int words = (g.Sb + 31) / 32;
@@ -293,30 +296,43 @@ __global__ __launch_bounds__(kThreads) void k_aggregate_links(const uint8_t* __r
     const uint8_t* L = links + mask_id * g.N * g.N + (int64_t)r0 * g.N;
     const int row_min = nr == g.Bs ? g.row_min_full : g.row_min_tail;
     const int per_block = g.Bs / 16;                        // threads of a key block: 2, 4 or 8
+    // threads per row: a power of two, whole key blocks; the others take rows of their own
+    int span = per_block;
+    while (span < kThreads && span * 16 < g.N) span <<= 1;
+    const int unit = tid & (span - 1), first = tid / span, groups = kThreads / span;
     if (tid == 0) s_count = 0;
     for (int c_step = 0; c_step < g.N; c_step += kCols) {
         if (tid < 4) s_bits[tid] = 0u;
         __syncthreads();
-        const int c = c_step + tid * 16, n = min(16, g.N - c);      // n <= 0: past the last column
+        const int c = c_step + unit * 16, n = min(16, g.N - c);      // n <= 0: past the last column
+        const int at = min(c, g.N - 16);                             // where the unit's sixteen bytes start (N >= 16)
         uint32_t cnt[4] = {0u, 0u, 0u, 0u};
-        if (n == 16) {
+        if (n > 0 && at >= 0) {
 #pragma unroll 8
-            for (int r = 0; r < nr; ++r) {
+            for (int r = first; r < nr; r += groups) {
                 uint32_t x[4];
-                __builtin_memcpy(x, L + (int64_t)r * g.N + c, 16);
+                __builtin_memcpy(x, L + (int64_t)r * g.N + at, 16);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) cnt[e] += x[e];
             }
-        } else {
+        } else {                                                     // (fewer than sixteen tokens in all)
             for (int e = 0; e < n; ++e)
-                for (int r = 0; r < nr; ++r) cnt[e >> 2] += (uint32_t)L[(int64_t)r * g.N + c + e] << (8 * (e & 3));
+                for (int r = first; r < nr; r += groups) cnt[(16 - n + e) >> 2] += (uint32_t)L[(int64_t)r * g.N + c + e] << (8 * ((16 - n + e) & 3));
         }
-        int active = 0;
+        if (groups > 1) {                                            // (a single step: the row fits the span)
+            s_part[tid] = make_uint4(cnt[0], cnt[1], cnt[2], cnt[3]);
+            __syncthreads();
+            for (int i = 1; i < groups; ++i) {
+                const uint4 p = s_part[(tid + i * span) & (kThreads - 1)];
+                cnt[0] += p.x; cnt[1] += p.y; cnt[2] += p.z; cnt[3] += p.w;
+            }
+        }
+        int active = 0;                                              // the unit's own columns are the last n of its sixteen
 #pragma unroll
-        for (int e = 0; e < 16; ++e) active += (e < n && (int)((cnt[e >> 2] >> (8 * (e & 3))) & 255u) >= row_min) ? 1 : 0;
+        for (int e = 0; e < 16; ++e) active += (e >= 16 - n && (int)((cnt[e >> 2] >> (8 * (e & 3))) & 255u) >= row_min) ? 1 : 0;
         for (int off = 1; off < per_block; off <<= 1) active += __shfl_xor(active, off);
         const int kb = c / g.Bs;
-        if (kb < g.Sb && tid % per_block == 0) {
+        if (kb < g.Sb && tid < span && unit % per_block == 0) {
             const int nc = min(g.Bs, g.N - kb * g.Bs);
             const int col_min = nc == g.Bs ? g.col_min_full : g.col_min_tail;
             // a block that holds a token pair with t <= 1 is kept whatever its density

@@ -14,7 +14,11 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("bs", [32, 64, 128])
-@pytest.mark.parametrize("frames,hg,wg,tau", [(5, 31, 33, 0.2), (9, 3, 157, 60.0)])      # N = 5115 and 4239; the second: safeguard only
+@pytest.mark.parametrize("frames,hg,wg,tau", [
+    (5, 31, 33, 0.2), (9, 3, 157, 60.0),                      # N = 5115 and 4239; the second: safeguard only
+    (3, 1, 5, 0.2), (2, 2, 4, 0.2), (4, 9, 11, 0.2),          # N = 15, 16, 396: rows shared out over idle threads
+    (16, 8, 16, 0.2), (23, 1, 89, 0.2),                       # N = 2048 and 2047: half of the threads have a row of their own
+])
 def test_links_and_masks_bit_exact(bs, frames, hg, wg, tau):
     wl = Workload("wide", 91, 1, 1, 64, frames, hg, wg, bs, "f32", "field", "dynamic", 0.5, 0.9, 1.0, head_fuse=1)
     run = GpuRun(wl, params=dr.MaskParams(gamma=1.5, head_fuse=1))
