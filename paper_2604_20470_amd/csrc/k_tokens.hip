@@ -307,14 +307,18 @@ __global__ __launch_bounds__(kThreads) void k_aggregate_links(const uint8_t* __r
         const int c = c_step + unit * 16, n = min(16, g.N - c);      // n <= 0: past the last column
         const int at = min(c, g.N - 16);                             // where the unit's sixteen bytes start (N >= 16)
         uint32_t cnt[4] = {0u, 0u, 0u, 0u};
-        if (n > 0 && at >= 0) {
-#pragma unroll 8
-            for (int r = first; r < nr; r += groups) {
-                uint32_t x[4];
-                __builtin_memcpy(x, L + (int64_t)r * g.N + at, 16);
+        auto add_row = [&](int r) {
+            uint32_t x[4];
+            __builtin_memcpy(x, L + (int64_t)r * g.N + at, 16);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) cnt[e] += x[e];
-            }
+            for (int e = 0; e < 4; ++e) cnt[e] += x[e];
+        };
+        if (n > 0 && at >= 0 && groups == 1) {                       // (apart from the other: a fixed step, eight loads in flight)
+#pragma unroll 8
+            for (int r = 0; r < nr; ++r) add_row(r);
+        } else if (n > 0 && at >= 0) {
+#pragma unroll 4
+            for (int r = first; r < nr; r += groups) add_row(r);
         } else {                                                     // (fewer than sixteen tokens in all)
             for (int e = 0; e < n; ++e)
                 for (int r = first; r < nr; r += groups) cnt[(16 - n + e) >> 2] += (uint32_t)L[(int64_t)r * g.N + c + e] << (8 * ((16 - n + e) & 3));
