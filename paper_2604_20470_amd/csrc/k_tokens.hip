@@ -1,6 +1,6 @@
 // Algorithm 1 of the paper in its own order, for small sequences (an evaluation aid beside the block-level path):
 //   k_token_scores     proxy score of every token pair (Eq. 9, fused-head mean of App. B) -> fp32 [N, N]
-//   k_link_*, k_links  per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
+//   k_link_*, k_links, k_pair_links_small  per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
 //                      it (Eq. 10), z >= tau_1 / tau_2 by decay state (Eq. 11), keep-one safeguard -> link bytes [N, N]
 //   k_aggregate_links  density rule per block pair ("Density control within blocks": a column is active when its
 //                      kept-row ratio exceeds theta_c, the block when its active-column ratio exceeds theta_m), plus the
@@ -101,6 +101,13 @@ __device__ __forceinline__ uint32_t score_image(float s) {      // ascending uns
 }
 __device__ __forceinline__ float image_score(uint32_t u) { return __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u); }
 
+// Rank of a candidate for the safeguard: the highest score, the first in row-major order on ties; a NaN ranks below every number.
+__device__ __forceinline__ unsigned long long best_key(float s, int index) {
+    const uint32_t image = s == s ? score_image(s + 0.0f) : 0u;
+    return ((unsigned long long)image << 32) | (0xffffffffu - (uint32_t)index);
+}
+__device__ __forceinline__ int best_index(unsigned long long key) { return (int)(0xffffffffu - (uint32_t)key); }
+
 struct PairAt {
     int i, j, t, w, flags;
     int64_t mask, pair;           // (b, m) flattened; index into per-pair arrays
@@ -137,7 +144,7 @@ __device__ __forceinline__ double ordered_sum(const double* __restrict__ col, in
 }
 __device__ __forceinline__ double window_size(int Nt, int w) {      // token pairs of a candidate set
     long long n = 0;
-    for (int v = threadIdx.x; v < Nt; v += 64) n += min(Nt - 1, v + w) - max(0, v - w) + 1;
+    for (int v = threadIdx.x & 63; v < Nt; v += 64) n += min(Nt - 1, v + w) - max(0, v - w) + 1;      // (every wavefront by itself)
     for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
     return (double)n;
 }
@@ -239,9 +246,7 @@ __global__ __launch_bounds__(kThreads) void k_links(const float* __restrict__ sc
                 if (e < n && abs(u - (v + e)) <= p.w) {
                     out[e] = s[e] >= threshold ? 1 : 0;
                     kept += out[e];
-                    const uint32_t image = s[e] == s[e] ? score_image(s[e] + 0.0f) : 0u;      // (a NaN ranks below every number)
-                    const unsigned long long key = ((unsigned long long)image << 32) | (0xffffffffu - (uint32_t)(u * Nt + v + e));
-                    best = max(best, key);
+                    best = max(best, best_key(s[e], u * Nt + v + e));
                 }
             }
         }
@@ -270,8 +275,84 @@ __global__ __launch_bounds__(64) void k_link_safeguard(FrameTab tab, int N, int 
     if (pair >= Nf * Nf) return;
     const PairAt p = pair_at(tab, Nf, pair);
     if (!p.judged || stats[p.pair].kept != 0u) return;
-    const int idx = (int)(0xffffffffu - (uint32_t)stats[p.pair].best), u = idx / Nt, v = idx % Nt;
+    const int idx = best_index(stats[p.pair].best), u = idx / Nt, v = idx % Nt;
     links[p.mask * N * N + ((int64_t)p.i * Nt + u) * N + (int64_t)p.j * Nt + v] = 1;
+}
+
+// The same for a pair of small frames (Nt <= kSmallFrame) in one launch: a workgroup holds the pair's scores in LDS (two such
+// workgroups share a CU at 128 tokens) and makes the statistics, the bytes and the safeguard itself.  Five launches cost 8 to
+// 16 us more than one where there is next to no work: whole calls, five launches / one, 4 frames of 64 tokens, block size
+// 128: 25 / 16 us; 33 of 64: 39 / 20; 256 of 64: 338 / 240; 33 of 121, eight masks, block size 32: 250 / 241, the line.
+// grid: (Nf * Nf, masks, B).  LDS: Nt doubles | Nt * Nt floats.
+constexpr int kSmallFrame = 128;
+__global__ __launch_bounds__(kThreads) void k_pair_links_small(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
+                                                               double tau_near, double tau_far, uint8_t* __restrict__ links) {
+    extern __shared__ double col[];
+    __shared__ double s_total;
+    __shared__ unsigned long long s_best;
+    __shared__ unsigned int s_kept;
+    float* S = reinterpret_cast<float*>(col + Nt);
+    const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
+    const int64_t at0 = p.mask * N * N + (int64_t)p.i * Nt * N + (int64_t)p.j * Nt;
+    const int tid = threadIdx.x, size = Nt * Nt;
+    if (!p.judged) {
+        for (int q = tid; q < size; q += kThreads) links[at0 + (int64_t)(q / Nt) * N + q % Nt] = p.t <= 1 ? 1 : 0;
+        return;
+    }
+    if (tid == 0) { s_kept = 0u; s_best = 0ull; }
+#pragma unroll 4
+    for (int q = tid; q < size; q += kThreads) S[q] = scores[at0 + (int64_t)(q / Nt) * N + q % Nt];
+    __syncthreads();
+    // sums of the columns' windows, then of the columns, one by one
+    auto total_of = [&](auto&& term) -> double {
+        if (tid < Nt) {
+            const int lo = max(0, tid - p.w), hi = min(Nt - 1, tid + p.w);
+            double acc = 0.0;
+#pragma unroll 8
+            for (int u = lo; u <= hi; ++u) acc = acc + term(S[u * Nt + tid]);
+            col[tid] = acc;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            double total = 0.0;
+#pragma unroll 8
+            for (int v = 0; v < Nt; ++v) total = total + col[v];
+            s_total = total;
+        }
+        __syncthreads();
+        return s_total;
+    };
+    const double n = window_size(Nt, p.w);
+    const double mu = total_of([](float s) { return (double)s; }) / n;
+    const double denom = sqrt(total_of([&](float s) {
+        const double dev = (double)s - mu;
+        const double sq = dev * dev;
+        return sq;
+    }) / n) + 1e-6;
+    const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
+    unsigned int kept = 0u;
+    unsigned long long best = 0ull;
+    for (int q = tid; q < size; q += kThreads) {
+        const int u = q / Nt, v = q - u * Nt;
+        uint8_t out = 0;
+        if (abs(u - v) <= p.w) {
+            const float s = S[q];
+            out = ((double)s - mu) / denom >= tau ? 1 : 0;
+            kept += out;
+            best = max(best, best_key(s, q));
+        }
+        links[at0 + (int64_t)u * N + v] = out;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        kept += __shfl_xor(kept, off);
+        best = max(best, (unsigned long long)__shfl_xor(best, off));
+    }
+    if ((tid & 63) == 0) { atomicAdd(&s_kept, kept); atomicMax(&s_best, best); }
+    __syncthreads();
+    if (s_kept == 0u && tid == 0) {
+        const int q = best_index(s_best);
+        links[at0 + (int64_t)(q / Nt) * N + q % Nt] = 1;
+    }
 }
 
 // Density rule.  One workgroup per query block; a thread sums the link bytes of sixteen consecutive key columns over the
@@ -365,6 +446,7 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
 }
 
 size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf) {
+    if (N / Nf <= kSmallFrame) return 0;
     return (size_t)B * masks * ((size_t)2 * Nf * N * sizeof(double) + (size_t)Nf * Nf * sizeof(PairStat));
 }
 
@@ -373,6 +455,16 @@ hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, in
     double* sums = static_cast<double*>(scratch);
     double* devs = sums + (size_t)B * masks * Nf * N;
     PairStat* stats = reinterpret_cast<PairStat*>(devs + (size_t)B * masks * Nf * N);
+    if (Nt <= kSmallFrame) {
+        const size_t lds = (size_t)Nt * sizeof(double) + (size_t)Nt * Nt * sizeof(float);
+        if (lds > 64 * 1024) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pair_links_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(k_pair_links_small, dim3((unsigned)Nf * Nf, masks, B), dim3(kThreads), lds, s, scores, tab, N, Nt, Nf,
+                           tau_near, tau_far, links);
+        return hipGetLastError();
+    }
     const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64, rows = (Nt + kLinkRows - 1) / kLinkRows;
     const size_t lds = (size_t)Nt * sizeof(double);
     hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, stats);

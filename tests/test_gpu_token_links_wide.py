@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (5, 31, 33, 0.2), (9, 3, 157, 60.0),                      # N = 5115 and 4239; the second: safeguard only
     (3, 1, 5, 0.2), (2, 2, 4, 0.2), (4, 9, 11, 0.2),          # N = 15, 16, 396: rows shared out over idle threads
     (16, 8, 16, 0.2), (23, 1, 89, 0.2),                       # N = 2048 and 2047: half of the threads have a row of their own
+    (5, 1, 127, 0.2), (5, 3, 43, 0.2), (5, 3, 43, 60.0),      # frames of 127 and 129 tokens: one launch and five
+    (70, 1, 1, 0.2), (40, 1, 3, 60.0),                        # frames of one token and of three
 ])
 def test_links_and_masks_bit_exact(bs, frames, hg, wg, tau):
     wl = Workload("wide", 91, 1, 1, 64, frames, hg, wg, bs, "f32", "field", "dynamic", 0.5, 0.9, 1.0, head_fuse=1)
@@ -41,6 +43,7 @@ def test_links_and_masks_bit_exact(bs, frames, hg, wg, tau):
 INF, NAN = float("inf"), float("nan")
 
 
+@pytest.mark.parametrize("hg,wg", [(8, 16), (3, 43)])        # a pair's links in one launch, and in five
 @pytest.mark.parametrize("edits,kept", [
     ({(3, 4): INF, (5, 5): INF, (9, 8): INF}, (3, 4)),       # nothing is above a mean of infinity: the first of the best
     ({(3, 4): INF, (5, 6): -INF}, (3, 4)),
@@ -48,9 +51,9 @@ INF, NAN = float("inf"), float("nan")
     ({(3, 4): NAN}, None),                                    # None: the highest number of the set
     ({(3, 4): -NAN, (7, 12): NAN}, None),
 ])
-def test_a_set_with_scores_that_are_not_finite_keeps_its_best_alone(edits, kept):
+def test_a_set_with_scores_that_are_not_finite_keeps_its_best_alone(edits, kept, hg, wg):
     """The mean or the deviation is then no number, no score passes the test, and the safeguard's one link is left."""
-    frames, hg, wg, bs = 4, 8, 16, 32
+    frames, bs = 4, 32
     Nt, N = hg * wg, frames * hg * wg
     wl = Workload("nonfinite", 92, 1, 1, 64, frames, hg, wg, bs, "f32", "field", "dynamic", 0.5, 0.9, 1.0, head_fuse=1)
     run = GpuRun(wl, params=dr.MaskParams(gamma=1.0, head_fuse=1))
