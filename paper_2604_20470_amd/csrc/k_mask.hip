@@ -519,10 +519,10 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 // one in score order, compared with tau times the whole sum: a serial chain behind a sort, if taken literally (k_select:
 // 208 us at 40 x 591 rows; this kernel about 30).  Only the place where the prefix crosses the target is wanted, so it is
 // looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
-// bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) or whose
-// crossing lies among many equal scores is decided by the literal chain, in this wave.
+// bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) is decided by
+// the literal chain, in this wave.
 // LDS per wave: keys[cap] u64 | mass[cap] f64 | bins[256] u64, cap a power of two >= the largest selectable count of a row.
-constexpr int kBins = 256, kMaxTaken = 8;      // keys taken one by one before the row goes to the chain
+constexpr int kBins = 256, kMaxTaken = 8;      // keys taken one by one from a bin
 __host__ __device__ inline size_t select_mass_lds_bytes(int cap) { return (size_t)cap * 16 + kBins * 8; }
 
 __device__ __forceinline__ uint32_t key_image(uint64_t c) { return (uint32_t)(c >> 31); }
@@ -586,59 +586,107 @@ __device__ __forceinline__ uint64_t mass_threshold_by_chain(int n, float top, do
 
 // The key that ends the prefix, by masses in fixed point (U: 32 or 64 bits; their sums do not depend on an order): the keys are
 // dropped into 256 bins of equal width in score (monotone in the score), the bins are scanned, and the keys of the bin in
-// which the sum crosses the target are taken from the top.  Nothing is decided when the bin holds too many keys to take, or
-// when the target lies within `slack(total)`, the largest error of a prefix, of either side of the crossing.
+// which the sum crosses the target are taken from the top.  kLevels > 1: what a bin still holds after that many is binned
+// again over its own range, or, where its scores are all the same, divided.  Nothing is decided when that does not reach the
+// crossing, or when the target lies within `slack(total)`, the largest error of a prefix, of either side of it.
 enum class Crossing { kFound, kTooClose, kTooMany };
-template <typename U, class Mass, class Slack>
+template <int kLevels, typename U, class Mass, class Slack>
 __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_scale, double tau, const uint64_t* keys, U* bins, Mass&& mass_of,
                                               Slack&& slack, uint64_t* ends) {
     const int lane = lane_id();
-    auto bin_of = [&](uint64_t c) { return (int)fminf((top - image_score(key_image(c))) * bin_scale, 255.0f); };
-#pragma unroll
-    for (int e = 0; e < 4; ++e) bins[lane * 4 + e] = 0;
-    wave_lds_fence();
-#pragma unroll 1
-    for (int i = lane; i < n; i += 64) atomicAdd(&bins[bin_of(keys[i])], mass_of(keys[i]));
-    wave_lds_fence();
-    const U part[4] = {bins[lane * 4], bins[lane * 4 + 1], bins[lane * 4 + 2], bins[lane * 4 + 3]};
-    const U own = part[0] + part[1] + part[2] + part[3];
-    U incl = own;
-    for (int off = 1; off < 64; off <<= 1) {
-        const U t = __shfl_up(incl, off);
-        if (lane >= off) incl += t;
-    }
-    const double total = (double)__shfl(incl, 63), target = tau * total;
-    const uint64_t reach = __ballot((double)incl >= target);      // (never empty: tau <= 1)
-    const int l = reach ? __ffsll((unsigned long long)reach) - 1 : 63;
-    U before = incl - own;
-    int bin = lane * 4;
-    bool found = false;
-#pragma unroll
-    for (int e = 0; e < 3; ++e)
-        if (!found) {
-            if ((double)(before + part[e]) >= target) found = true;
-            else { before += part[e]; ++bin; }
-        }
-    bin = __shfl(bin, l);
-    U prefix = __shfl(before, l), prev = prefix;
-    uint64_t last = ~0ull;
+    uint64_t low = 0ull, last = ~0ull;          // the keys still in question: low <= key < last
+    double total = 0.0, target = 0.0;
+    U prefix = 0, prev = 0;                     // mass of the keys from `last` up, and before the last of them
     bool crossed = false;
-    for (int taken = 0; taken < kMaxTaken && !crossed; ++taken) {
-        uint64_t best = 0ull;
+    for (int level = 0; level < kLevels && !crossed; ++level) {
+        auto bin_of = [&](uint64_t c) { return (int)fminf((top - image_score(key_image(c))) * bin_scale, 255.0f); };
+        auto asked = [&](uint64_t c) { return (kLevels == 1 || c >= low) && c < last; };
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bins[lane * 4 + e] = 0;
+        wave_lds_fence();
 #pragma unroll 1
-        for (int i = lane; i < n; i += 64) {
-            const uint64_t c = keys[i];
-            if (c < last && c > best && bin_of(c) == bin) best = c;
+        for (int i = lane; i < n; i += 64)
+            if (level == 0 || asked(keys[i])) atomicAdd(&bins[bin_of(keys[i])], mass_of(keys[i]));
+        wave_lds_fence();
+        const U part[4] = {bins[lane * 4], bins[lane * 4 + 1], bins[lane * 4 + 2], bins[lane * 4 + 3]};
+        const U own = part[0] + part[1] + part[2] + part[3];
+        U incl = own;
+        for (int off = 1; off < 64; off <<= 1) {
+            const U t = __shfl_up(incl, off);
+            if (lane >= off) incl += t;
         }
+        incl += prefix;
+        if (level == 0) {
+            total = (double)__shfl(incl, 63);
+            target = tau * total;
+        }
+        const uint64_t reach = __ballot((double)incl >= target);      // (never empty: tau <= 1)
+        const int l = reach ? __ffsll((unsigned long long)reach) - 1 : 63;
+        U before = incl - own;
+        int bin = lane * 4;
+        bool found = false;
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (!found) {
+                if ((double)(before + part[e]) >= target) found = true;
+                else { before += part[e]; ++bin; }
+            }
+        bin = __shfl(bin, l);
+        prefix = prev = __shfl(before, l);
+        uint64_t best = 0ull, least = ~0ull;          // of the bin, of what is not taken yet
+        for (int taken = 0; taken < kMaxTaken + (kLevels > 1) && !crossed; ++taken) {
+            best = 0ull;
+            least = ~0ull;
+#pragma unroll 1
+            for (int i = lane; i < n; i += 64) {
+                const uint64_t c = keys[i];
+                if (asked(c) && bin_of(c) == bin) {
+                    best = c > best ? c : best;
+                    if constexpr (kLevels > 1) least = c < least ? c : least;
+                }
+            }
+            for (int off = 32; off > 0; off >>= 1) {
+                const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)best, off);
+                best = t > best ? t : best;
+            }
+            if (best == 0ull || taken == kMaxTaken) break;
+            last = best;
+            prev = prefix;
+            prefix += mass_of(best);
+            crossed = (double)prefix >= target;
+        }
+        if (kLevels == 1 || crossed || best == 0ull) break;
         for (int off = 32; off > 0; off >>= 1) {
-            const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)best, off);
-            best = t > best ? t : best;
+            const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)least, off);
+            least = t < least ? t : least;
         }
-        if (best == 0ull) break;
-        last = best;
-        prev = prefix;
-        prefix += mass_of(best);
-        crossed = (double)prefix >= target;
+        if (key_image(least) == key_image(best)) {
+            // equal masses, in key-block order, which is the order of the packed keys
+            const U m = mass_of(best);
+            const int j = m ? (int)fmin(ceil((target - (double)prefix) / (double)m), 65536.0) : 0;
+            if (j < 1) break;
+            int at = 0;
+#pragma unroll 1
+            for (int i0 = 0; i0 < n; i0 += 64) {
+                const uint64_t c = i0 + lane < n ? keys[i0 + lane] : 0ull;
+                const uint64_t equal = __ballot(c >= least && c <= best);
+                const int nth = j - at;                                   // of this stretch
+                at += __popcll(equal);
+                if (at < j) continue;
+                const uint64_t mine = __ballot(c >= least && c <= best &&
+                                               (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(equal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)equal, 0u)) == nth - 1);
+                last = (uint64_t)__shfl((unsigned long long)c, __ffsll((unsigned long long)mine) - 1);
+                prev = prefix + (U)(j - 1) * m;
+                prefix = prev + m;
+                crossed = (double)prefix >= target && (double)prev < target;
+                break;
+            }
+            break;
+        }
+        low = least;
+        last = best + 1ull;
+        top = image_score(key_image(best));
+        bin_scale = 255.0f / (top - image_score(key_image(least)));
     }
     const double E = slack(total);
     *ends = last;
@@ -646,7 +694,11 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
     return (double)prev + E < tau * (total - E) && (double)prefix - E >= tau * (total + E) ? Crossing::kFound : Crossing::kTooClose;
 }
 
-template <int kSlots>
+// A row that the bins do not decide costs its wave a sort and the chain, 25 us at 1000 keys.  Among many rows that is shared out
+// (kLevels = 1); a launch of few rows waits for the slowest, and there the crossing bin is binned again twice (kLevels = 3,
+// 28 more registers): one mask of 1013 rows, smooth scores, 45 -> 24 us (34 us with the workgroup-wide sort of k_select), ties
+// 45 -> 24..35; 40 masks of 591 rows took 49 us with one level, 59 with three.
+template <int kSlots, int kLevels>
 __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __restrict__ class_bits,
                                                           const float* __restrict__ scores, int64_t rows_total, int Sb, int cap,
                                                           SelectArgs a, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
@@ -696,7 +748,7 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
             // 32 bits, exponentials in fp32.  The argument is off by at most 2^-23 |x| (and x e^-x <= 0.37), the
             // instruction by 2^-23 relative, rounding to a unit by one half.
             const float unit = __uint_as_float((uint32_t)(127 + 31 - log_n) << 23);
-            got = mass_crossing<uint32_t>(
+            got = mass_crossing<kLevels, uint32_t>(
                 n, top, bin_scale, a.tau, keys, reinterpret_cast<uint32_t*>(bins),
                 [&](uint64_t c) { return (uint32_t)__builtin_rintf(__builtin_amdgcn_exp2f((top - image_score(key_image(c))) * -1.44269504f) * unit); },
                 [&](double total) { return total * 0x1p-21 + (double)n + 4.0; }, &threshold);
@@ -704,7 +756,7 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
         if (!all && got == Crossing::kTooClose) {
             // 64 bits, the rule's own exponentials: rounding to a unit, and the chain's own n roundings
             const double unit = __longlong_as_double((long long)(1023 + 62 - log_n) << 52);
-            got = mass_crossing<unsigned long long>(
+            got = mass_crossing<kLevels, unsigned long long>(
                 n, top, bin_scale, a.tau, keys, reinterpret_cast<unsigned long long*>(bins),
                 [&](uint64_t c) { return (unsigned long long)__builtin_rint(exp((double)image_score(key_image(c)) - (double)top) * unit); },
                 [&](double total) { return total * (double)(n + 8) * 0x1p-52 + (double)n + 4.0; }, &threshold);
@@ -959,11 +1011,13 @@ hipError_t launch_select(const uint8_t* class_map, const uint64_t* class_bits, c
             hipLaunchKernelGGL(kern, grid, block, lds, s, class_bits, scores, rows_total, Sb, cap, a, keepbits, counts);
             return hipGetLastError();
         };
-        if (slots == 2) return launch(k_select_mass<2>);
-        if (slots == 4) return launch(k_select_mass<4>);
-        if (slots == 8) return launch(k_select_mass<8>);
-        if (slots == 12) return launch(k_select_mass<12>);
-        return launch(k_select_mass<16>);
+#define DR_SELECT_MASS(SLOTS) launch(waves > 1 ? k_select_mass<SLOTS, 1> : k_select_mass<SLOTS, 3>)
+        if (slots == 2) return DR_SELECT_MASS(2);
+        if (slots == 4) return DR_SELECT_MASS(4);
+        if (slots == 8) return DR_SELECT_MASS(8);
+        if (slots == 12) return DR_SELECT_MASS(12);
+        return DR_SELECT_MASS(16);
+#undef DR_SELECT_MASS
     }
     const size_t words = (Sb + 31) / 32;
     const size_t lds = (size_t)a.sort_cap * (a.mode == 1 ? 16 : 8) + words * 4;

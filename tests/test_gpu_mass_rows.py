@@ -66,3 +66,27 @@ def test_scores_that_are_not_finite_take_the_chain(bits, tau):
             run_sum = np.add.accumulate(np.exp(s[order] - s.max())) if free.size else np.zeros(0)
             kept = free[order[:1 + int(np.argmax(run_sum >= tau * run_sum[-1]))]] if free.size else free
         assert np.array_equal(ci[rp[qb]:rp[qb + 1]], np.union1d(kept, forced)), qb
+
+
+@pytest.mark.parametrize("frames,hg,wg", [(8, 8, 16), (15, 16, 30), (33, 31, 32)])
+@pytest.mark.parametrize("heads", [1, 30])                    # bins that are binned again (few rows), and not
+def test_crossing_among_many_keys_of_one_bin(frames, hg, wg, heads):
+    wl = dataclasses.replace(tiny_case("tiny8"), Nf=frames, Hg=hg, Wg=wg, H=heads, index=103)
+    run = GpuRun.__new__(GpuRun)
+    run.wl, run.heads, run.params, run.device, run.Sb = wl, list(range(heads)), dr.MaskParams(head_fuse=0, gamma=3.0), "cuda:0", wl.Sb
+    run.ctx = dr.Context(0)
+    run.shape = dr.Shape(1, heads, wl.N, 64, frames, hg, wg, wl.Bs, 0, 0, wl.N * 64 * heads, wl.N * 64, 64)
+    g = torch.Generator().manual_seed(frames)
+    noise = torch.randn(1, 1, wl.Sb, wl.Sb, generator=g)
+    scores = 2.0 + 1e-3 * noise                               # a cluster, which fills one bin
+    scores[:, :, 0::5, ::17] = 2.5                            # beside a few ahead of it
+    scores[:, :, 1::5] = (noise[:, :, 1::5] > 0.3).float()    # two values
+    scores[:, :, 2::5, ::2] = 2.0 + 1e-6 * noise[:, :, 2::5, ::2]                     # a cluster in the cluster's bin
+    scores[:, :, 3::5] = (noise[:, :, 3::5] * 64).round() / 64                        # groups of equal scores in every bin
+    scores[:, :, 4::5, ::31] = -30.0                          # everything else in one bin
+    scores = scores.expand(1, heads, -1, -1).contiguous()
+    cls = oracle_class_map(wl, gamma=3.0)
+    for tau in (0.1, 0.5, 0.9, 0.999):
+        rowptr, colidx, nnz, _ = run.build_mask(scores.cuda(), "dynamic", tau)
+        few = [0] if heads == 1 else [0, heads - 1]
+        assert_masks_equal(rowptr[:, few], colidx[:, few], nnz[:, few], oracle_masks_from(scores[:, few], cls, "dynamic", tau))
