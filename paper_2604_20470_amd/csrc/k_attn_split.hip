@@ -136,7 +136,7 @@ __device__ __forceinline__ void load_plain(const char* src, float* dst, int g) {
 
 // |x| of a value that is not 0 as an integer, ascending like |x|; a zero gives the largest of all
 __device__ __forceinline__ uint32_t nonzero_magnitude(float x) { return (__float_as_uint(x) << 1) - 1u; }
-constexpr uint32_t kTinyMagnitude = ((127u - 108u) << 24) - 1u;      // of kTiny
+constexpr uint32_t kTinyMagnitude = (__builtin_bit_cast(uint32_t, kTiny) << 1) - 1u;
 
 struct Item {
     const char *Q, *K, *V;      // of this (batch, head)
@@ -665,7 +665,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 }
             }
         q_tiny = min(least[0], least[1]) < (kTinyMagnitude >> 16);
-        bad = max(most[0], most[1]) >= ((127 + 100) << 8);       // kHuge
+        bad = max(most[0], most[1]) >= (__builtin_bit_cast(uint32_t, kHuge) >> 15);
     }
     if (writer) {
         float check = l;
