@@ -737,11 +737,11 @@ __device__ __forceinline__ void attn_pair_body() {
             {                                                                                                           \
                 DR_PIN_O();                                                                                             \
                 nx.c2 = min((C) + 2, n_chunks - 1);                                                                     \
-                const bool refill = (BS == 32 ? 2 * nx.c2 : nx.c2 >> kSh) >= wbase + 64;                                \
+                const int past = (BS == 32 ? 2 * nx.c2 : nx.c2 >> kSh) - 64;       /* the window's first entry, at least */ \
                 if (own_cur) {                                                                                          \
                     if constexpr (BS == 32) tile_masks(fr, own4_cur);                                                   \
                     run_slots<0, 27, false, STAGE, BS, WAVES>(rd, qf, st, fr, lp, nx);                                             \
-                    if (refill) { wbase += 64; win = gl[min(wbase + lane, cnt - 1)]; asm volatile("" : "+v"(win)); }   \
+                    if (past >= wbase) { wbase += 64; win = gl[min(wbase + lane, cnt - 1)]; asm volatile("" : "+v"(win)); }   \
                     nx.win = win;                                                                                       \
                     run_slots<27, kBarrierSlot, false, STAGE, BS, WAVES>(rd, qf, st, fr, lp, nx);                                  \
                     DR_WAIT_VMCNT0();                                                                                   \
@@ -750,7 +750,7 @@ __device__ __forceinline__ void attn_pair_body() {
                     run_slots<kBarrierSlot, kSlots, false, STAGE, BS, WAVES>(rd, qf, st, fr, lp, nx);                              \
                     if constexpr (BS == 32) fr.tm11_prev = fr.tm[1][1];                                                 \
                 } else {                                                                                                \
-                    if (refill) { wbase += 64; win = gl[min(wbase + lane, cnt - 1)]; asm volatile("" : "+v"(win)); }   \
+                    if (past >= wbase) { wbase += 64; win = gl[min(wbase + lane, cnt - 1)]; asm volatile("" : "+v"(win)); }   \
                     nx.win = win;                                                                                       \
                     next_step<0, BS>(nx); next_step<1, BS>(nx); next_step<2, BS>(nx); next_step<3, BS>(nx); next_step<4, BS>(nx);           \
                     next_step<5, BS>(nx); next_step<6, BS>(nx);                                                         \

@@ -97,4 +97,6 @@ def test_hand_scheduled_attention_kernel_compiles_without_spills_or_accumulator_
         assert 144 <= sum("v_mfma_f32_" in l for l in loop) <= 160    # two chunks of 72 slots (+ what drifts in from the drain)
         assert sum("v_mfma_f32_16x16x32_bf16" in l for l in loop) == 16   # the normaliser's eight per chunk, half length
         assert not any("v_accvgpr" in l for l in loop)
+        # no wavefront-uniform condition may wait in a lane mask: that takes vector slots and stalls the scalar unit (1.6 %)
+        assert not any("v_cndmask" in l or "v_cmp" in l for l in loop)
         assert not any("scratch_" in l or "buffer_store" in l for l in loop)
