@@ -64,8 +64,12 @@ def test_product_does_not_import_oracle():
                 assert "oracle" not in src.replace("no CPU fallback", ""), f
 
 
-def test_hand_scheduled_attention_kernel_compiles_without_spills_or_accumulator_copies():
-    """k_attn_mfma_pair issues its matrix instructions through inline assembly, so the compiler neither knows their
+@pytest.mark.parametrize("source,kernels", [
+    ("k_attn_mfma_pair.hip", ("k_attn_mfma_pairE", "k_attn_mfma_quadE", "k_attn_mfma_octE")),      # block sizes 128, 64 and 32
+    ("k_attn_mfma_duo.hip", ("k_attn_mfma_duoE",)),
+])
+def test_hand_scheduled_attention_kernel_compiles_without_spills_or_accumulator_copies(source, kernels):
+    """The body of these kernels issues its matrix instructions through inline assembly, so the compiler neither knows their
     latency nor may move an accumulator while one of them still writes it.  A register allocation that spills, or that
     copies accumulation registers inside the chunk loop, computes garbage without any error: check the compiler's own
     report and the loop's code (cross-compiled here, nothing runs)."""
@@ -75,15 +79,15 @@ def test_hand_scheduled_attention_kernel_compiles_without_spills_or_accumulator_
     from paper_2604_20470_amd import build as b
     if not (os.path.exists(b.HIPCC) or shutil.which(b.HIPCC)):
         pytest.skip("no hipcc")
-    src = os.path.join(b.CSRC, "k_attn_mfma_pair.hip")
+    src = os.path.join(b.CSRC, source)
     with tempfile.TemporaryDirectory() as tmp:
         asm = os.path.join(tmp, "pair.s")
         r = subprocess.run([b.HIPCC, *[f for f in b.FLAGS if f != "-fPIC"], "-Rpass-analysis=kernel-resource-usage", "-S",
                             "--cuda-device-only", src, "-o", asm], capture_output=True, text=True)
         assert r.returncode == 0, r.stderr[-2000:]
         reports = [blk for blk in r.stderr.split("Function Name:")[1:]
-                   if any(k in blk.splitlines()[0] for k in ("k_attn_mfma_pairE", "k_attn_mfma_quadE", "k_attn_mfma_octE"))]
-        assert len(reports) == 3                      # block sizes 128, 64 and 32
+                   if any(k in blk.splitlines()[0] for k in kernels)]
+        assert len(reports) == len(kernels)
         for report in reports:
             field = lambda name: int(re.search(name + r": (\d+)", report).group(1))
             assert field("VGPRs Spill") == 0 and field("SGPRs Spill") == 0
@@ -91,7 +95,7 @@ def test_hand_scheduled_attention_kernel_compiles_without_spills_or_accumulator_
         lines = open(asm).read().splitlines()
     begins = [i for i, l in enumerate(lines) if "; chunk loop begin" in l]
     ends = [i for i, l in enumerate(lines) if "; chunk loop end" in l]
-    assert len(begins) == 3 and len(ends) == 3
+    assert len(begins) == len(kernels) and len(ends) == len(kernels)
     for lo, hi in zip(begins, ends):
         loop = lines[lo:hi]
         assert 144 <= sum("v_mfma_f32_" in l for l in loop) <= 160    # two chunks of 72 slots (+ what drifts in from the drain)
