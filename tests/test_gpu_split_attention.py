@@ -207,3 +207,22 @@ def test_fp32_values_whose_parts_end_below_the_range(d, bs, v_by):
     O, _ = _attend(run, rp, ci)
     # numerator and normaliser: chains of at most 585 additions of terms of one sign, each within 2^-24 of the running sum
     assert ((O.cpu().double() - run.Vc.double()).abs() <= 2 * run.wl.N * 2.0 ** -24 * run.Vc.double().abs()).all()
+
+
+@pytest.mark.parametrize("bs", [32, 64, 128])
+def test_bf16_rows_too_far_apart_for_the_matrix_kernels(bs):
+    """bf16 at d = 128 with a token stride of 2^24 elements, beyond the 32-bit offsets of the kernels that serve it otherwise."""
+    run = _run("bf16", 128, bs, 2, 5, 7)                     # N = 70
+    N, far = run.wl.N, 1 << 24
+    Sb = run.wl.Sb
+    rp, ci = _csr([list(range(Sb))] * Sb)
+    wide = torch.zeros(N, far, dtype=torch.bfloat16, device="cuda")
+    views = [wide.as_strided((1, 2, N, 128), (1024, 512, far, 1), 128 * i) for i in range(4)]      # Q, K, V, O of both heads
+    for view, t in zip(views, (run.Q, run.K, run.V)):
+        view.copy_(t)
+    run.shape.stride_b, run.shape.stride_h, run.shape.stride_n = 1024, 512, far
+    rowptr, colidx = (torch.from_numpy(x.astype(np.int32)).view(1, 1, -1).contiguous().cuda() for x in (rp, ci))
+    lse = torch.empty(1, 2, N, dtype=torch.float32, device="cuda")
+    dr.dr_sparse_attn_fwd(run.ctx, run.shape, *views[:3], rowptr, colidx, 1, colidx.shape[2], views[3], lse)
+    torch.cuda.synchronize()
+    _check(run, rp, ci, views[3].contiguous(), lse)
