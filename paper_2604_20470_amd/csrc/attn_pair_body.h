@@ -65,7 +65,7 @@ constexpr float kSumMax = 1.2676506e30f, kSumMin = 7.8886091e-31f;   // 2^100, 2
 template <int WAVES>
 struct LoadPlan {
     static constexpr int kLoads = 16 / WAVES, kStep = 1024 * WAVES;   // a wave's pieces of a tile, and their distance in LDS
-    uint32_t koff_i[kLoads], voff_i[kLoads];   // per-lane byte offset of this lane's 16 bytes in the wave's four pieces of a chunk (swizzle folded in)
+    uint32_t koff_i[kLoads], voff_i[kLoads];   // per-lane byte offset of this lane's 16 bytes in each of the wave's pieces of a tile (swizzle folded in)
     uint32_t m0_k;                   // LDS address of this wave's first K piece in stage 0
 };
 
@@ -517,8 +517,6 @@ __device__ __forceinline__ int claim_item(int32_t* queue, int& xcd, int slot, in
     }
 }
 
-// One workgroup = 4 waves of 64 queries = kL adjacent query blocks (BS = 128: waves 0-1 block 2p, waves 2-3 block
-// 2p + 1; BS = 64: wave w block 4p + w).
 // The kernel's arguments, read again (from constant memory, once per item and before its results are stored) instead of
 // carried in scalar registers from item to item: the chunk loop needs those.
 __device__ __forceinline__ AttnArgs fresh_args() {
@@ -528,6 +526,8 @@ __device__ __forceinline__ AttnArgs fresh_args() {
     return *(const AttnArgs*)p;
 }
 
+// One workgroup = WAVES wavefronts of 64 queries = kL adjacent query blocks (item p: BS = 128: waves 0-1 block 2p, waves 2-3
+// block 2p + 1; BS = 64: wave w block kL p + w; BS = 32: wave w blocks 8p + 2w and 8p + 2w + 1).
 template <int BS, int WAVES>
 __device__ __forceinline__ void attn_pair_body() {
     static_assert(WAVES == 4 || (WAVES == 2 && BS == 64), "the owner bits and windows below");

@@ -118,8 +118,8 @@ hipError_t launch_attn_mfma_second_pass(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_mfma_pair(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_mfma_duo(const AttnArgs& a, int grid, hipStream_t s);      // (its variant of two wavefronts; lists of two rows are made)
 bool attn_mfma_pair_supported(const AttnArgs& a);
-// Merged key-block lists of every group of L (2 or 4) consecutive CSR rows: a.gcol (laid out like colidx, a group's
-// entries at the colidx offset of its first row; entry = key block | rows-that-list-it << 28) and a.gcount.
+// Merged key-block lists of every group of L (2, 4 or 8) consecutive CSR rows: a.gcol (laid out like colidx, a group's
+// entries at the colidx offset of its first row; entry = key block | rows-that-list-it << 28, << 24 for eight) and a.gcount.
 // queue_start >= 0: a.queue is set to that value as well.  flagged_only: only the groups (of 128 rows) that a.flags marks.
 hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s, int queue_start = -1, bool flagged_only = false);
 // bf16 storage, d = 128, Bs = 32 or 64: MFMA path that walks the union of the CSR rows of a 128-query group.
