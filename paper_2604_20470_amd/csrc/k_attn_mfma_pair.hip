@@ -31,10 +31,9 @@ hipError_t launch_attn_mfma_pair(const AttnArgs& a, hipStream_t s) {
     if (!attn_mfma_pair_supported(a)) return hipErrorNotSupported;
     // Masks of one head each: the selections of neighbouring query blocks differ, so at block size 64 the merged list of four
     // rows is long (1.38 times the kept blocks at 17 frames of 31 x 45 tokens, 1.14 for two) and every wavefront steps through
-    // all of it.  There two workgroups of two wavefronts share a CU instead: 1.86 -> 1.77 ms, 11 to 22 % less where one round
-    // of them fits the device, 2 to 11 % less beyond two rounds of the larger workgroup.  Between one and two rounds of
-    // that the smaller one measured 0 to 16 % longer (300 to 480 items: its last, short round starts as late), and the
-    // larger one stays.  Masks shared by the heads follow the field they were pooled from (1.06 for four rows at 75 600
+    // all of it.  There two workgroups of two wavefronts share a CU instead: 1.86 -> 1.77 ms, 1 to 19 % less up to one
+    // round of the larger workgroup, 0 to 2 % less beyond two.  Between one and two rounds the smaller one measured 0 to 10 %
+    // longer (288 to 512 items: its last, short round starts as late), and the larger one stays.  Masks shared by the heads follow the field they were pooled from (1.06 for four rows at 75 600
     // tokens), and a tile fetched once for four wavefronts costs half the traffic.  At block size 32 two wavefronts save
     // nothing (1.34 against 1.39).
     const int64_t items256 = ((int64_t)a.td.N + 255) / 256 * a.td.H * a.td.B;

@@ -719,7 +719,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // d = 128 were worth 0.784 -> 0.70 and 0.617 -> 0.51.  Error against 64 bits (2-norm): fp32 d = 128 O 1.9e-6 -> 1.4e-6,
 // d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
 // Block size 32, fp32 d = 64, 2048 tokens x 2 heads, all blocks: 700 us with the vector ALU, 45 us with four wavefronts that
-// share stages behind barriers, some 25 us with eight that walk alone.
+// share stages behind barriers, 24 to 30 us with eight that walk alone.
 // The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two or three, and bf16
 // d = 64 at block size 128, which fits 128 registers, four.
 template <bool BF16, int D, int BS>

@@ -517,7 +517,7 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 
 // Cumulative mass for rows of at most 1024 key blocks, one wave per row.  The rule is a sum of fp64 exponentials one by
 // one in score order, compared with tau times the whole sum: a serial chain behind a sort, if taken literally (k_select:
-// 208 us at 40 x 591 rows; this kernel about 30).  Only the place where the prefix crosses the target is wanted, so it is
+// 208 us at 40 x 591 rows; this kernel 32 with scores of a smooth field, 20 to 160 over other distributions).  Only the place where the prefix crosses the target is wanted, so it is
 // looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
 // bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) is decided by
 // the literal chain, in this wave.
