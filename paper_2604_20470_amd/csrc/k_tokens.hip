@@ -452,9 +452,6 @@ size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf) {
 
 hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, int masks, int N, int Nt, int Nf,
                              double tau_near, double tau_far, void* scratch, uint8_t* links, hipStream_t s) {
-    double* sums = static_cast<double*>(scratch);
-    double* devs = sums + (size_t)B * masks * Nf * N;
-    PairStat* stats = reinterpret_cast<PairStat*>(devs + (size_t)B * masks * Nf * N);
     if (Nt <= kSmallFrame) {
         const size_t lds = (size_t)Nt * sizeof(double) + (size_t)Nt * Nt * sizeof(float);
         if (lds > 64 * 1024) {
@@ -465,6 +462,9 @@ hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, in
                            tau_near, tau_far, links);
         return hipGetLastError();
     }
+    double* sums = static_cast<double*>(scratch);
+    double* devs = sums + (size_t)B * masks * Nf * N;
+    PairStat* stats = reinterpret_cast<PairStat*>(devs + (size_t)B * masks * Nf * N);
     const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64, rows = (Nt + kLinkRows - 1) / kLinkRows;
     const size_t lds = (size_t)Nt * sizeof(double);
     hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, stats);
