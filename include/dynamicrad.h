@@ -331,6 +331,21 @@ dr_status dr_proxy_loss(dr_ctx* ctx, const float* A_dense, const float* A_sparse
                         const int64_t* nnz, int32_t masks, int32_t Sb, double target, double alpha, double* out,
                         void* stream);
 
+/*
+ * The same objective from the tensors and the mask, without the matrices: A_dense is the softmax of Q_p . K_q / sqrt(d) over
+ * all keys, A_sparse that over the keys of the blocks listed in the CSR (a row that lists nothing is 0).  Per row the two
+ * squared norms follow from the sums of e^s and e^2s over the kept and the pruned keys; logits and row sums are fp32,
+ * quotients and sums over rows fp64 in a fixed order.
+ *   Q, K       device, float32, strides of `shape` (DR_ERR_UNSUPPORTED for bf16)
+ *   rowptr, colidx, mask_heads, colidx_stride   as in dr_sparse_attn_fwd; nnz  device int64 [B, mask_heads]
+ *   target, alpha, out   as in dr_proxy_loss
+ * At most 2^18 key blocks per row (DR_ERR_UNSUPPORTED).  The context holds 16 bytes per head and 16 tokens of scratch, grown
+ * on demand (DR_ERR_NOMEM).  Asynchronous on `stream`.
+ */
+dr_status dr_proxy_objective(dr_ctx* ctx, const dr_shape* shape, const void* Q, const void* K, const int32_t* rowptr,
+                             const int32_t* colidx, int32_t mask_heads, int64_t colidx_stride, const int64_t* nnz,
+                             double target, double alpha, double* out, void* stream);
+
 /* Library version string, e.g. "dynamicrad-gfx950 0.2". */
 const char* dr_version(void);
 

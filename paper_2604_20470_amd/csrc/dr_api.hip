@@ -655,6 +655,29 @@ dr_status dr_proxy_loss(dr_ctx* ctx, const float* A_dense, const float* A_sparse
     return DR_OK;
 }
 
+dr_status dr_proxy_objective(dr_ctx* ctx, const dr_shape* shape, const void* Q, const void* K, const int32_t* rowptr,
+                             const int32_t* colidx, int32_t mask_heads, int64_t colidx_stride, const int64_t* nnz,
+                             double target, double alpha, double* out, void* stream) {
+    if (!ctx) return DR_ERR_INVALID_ARG;
+    dr_status st;
+    if ((st = check_tensor_shape(ctx, shape)) != DR_OK) return st;
+    if (!Q || !K || !rowptr || !colidx || !nnz || !out) return fail(ctx, DR_ERR_INVALID_ARG, "NULL pointer");
+    if (shape->dtype != DR_F32) return fail(ctx, DR_ERR_UNSUPPORTED, "the objective takes fp32 tensors");
+    if (misaligned(Q) || misaligned(K)) return fail(ctx, DR_ERR_INVALID_ARG, "Q/K must be 16-byte aligned");
+    if (mask_heads != 1 && mask_heads != shape->H) return fail(ctx, DR_ERR_INVALID_ARG, "mask_heads must be 1 or H");
+    if (colidx_stride < 0) return fail(ctx, DR_ERR_INVALID_ARG, "negative colidx_stride");
+    if (std::isnan(target) || std::isnan(alpha)) return fail(ctx, DR_ERR_INVALID_ARG, "target or alpha is NaN");
+    const int Sb = (shape->N + shape->Bs - 1) / shape->Bs;
+    if (Sb > kProxyMaxBlocks) return fail(ctx, DR_ERR_UNSUPPORTED, "%d key blocks per row exceed %d", Sb, kProxyMaxBlocks);
+    DeviceGuard g(ctx->device);
+    const size_t need = (size_t)shape->B * shape->H * proxy_row_tiles(shape->N) * 2 * sizeof(double);
+    if ((st = grow(ctx, (void**)&ctx->proxy_partial, &ctx->proxy_bytes, need)) != DR_OK) return st;
+    TensorDesc td{shape->stride_b, shape->stride_h, shape->stride_n, shape->B, shape->H, shape->N, shape->d};
+    DR_HIP(ctx, launch_proxy_objective(static_cast<const float*>(Q), static_cast<const float*>(K), td, rowptr, colidx, colidx_stride,
+                                       mask_heads, shape->Bs, Sb, nnz, target, alpha, ctx->proxy_partial, out, (hipStream_t)stream));
+    return DR_OK;
+}
+
 dr_status dr_clock_probe(dr_ctx* ctx, uint64_t window_us, uint64_t* out, void* stream) {
     if (!ctx) return DR_ERR_INVALID_ARG;
     if (!out) return fail(ctx, DR_ERR_INVALID_ARG, "NULL output pointer");

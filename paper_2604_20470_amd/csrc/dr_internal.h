@@ -131,6 +131,13 @@ bool attn_mfma_small_supported(const AttnArgs& a);
 constexpr int kProxySlices = 64;     // partial sums per (b, h): partial is [B * H, kProxySlices, 2] doubles
 hipError_t launch_proxy_loss(const float* A_dense, const float* A_sparse, int BH, int N, const int64_t* nnz, int n_masks,
                              int Sb, double target, double alpha, double* partial, double* out, hipStream_t s);
+// The same objective from fp32 Q and K and the mask, without the matrices; partial: [B * H, proxy_row_tiles(N), 2] doubles.
+// Sb <= kProxyMaxBlocks (a bitmap of the row's key blocks in LDS).
+constexpr int kProxyMaxBlocks = 1 << 18;
+inline int proxy_row_tiles(int N) { return (N + 15) / 16; }
+hipError_t launch_proxy_objective(const float* Q, const float* K, const TensorDesc& td, const int32_t* rowptr, const int32_t* colidx,
+                                  int64_t colidx_stride, int mask_heads, int Bs, int Sb, const int64_t* nnz, double target,
+                                  double alpha, double* partial, double* out, hipStream_t s);
 
 // ---- measurement aid ---------------------------------------------------------------------
 // out[0] = shader-clock ticks, out[1] = 100 MHz ticks elapsed over a window of window_ticks (100 MHz units).

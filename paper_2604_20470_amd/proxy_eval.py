@@ -1,10 +1,11 @@
 """Evaluation utility on the GPU path: the objective of the paper's offline parameter search on its proxy task
-(App. C: drift-proxy features, proxy attention matrix, Eq. 22), computed with the library's own three stages.
+(App. C: drift-proxy features, proxy attention matrix, Eq. 22).  The loss is formed by dr_proxy_objective from the features and the mask; neither
+attention matrix is held.
 
-The attention *matrix* is not an output of the hot path, so it is read off the attention kernel column block by
-column block: with V set to the 128 one-hot columns of a key range, O = A V is that column range of A.  fp32 tensors
-keep the read-out exact to fp32 rounding (they run the fp32 attention kernel).  Meant for the small N of the proxy
-task (N x N floats are materialised); the Frobenius norms and the penalty are reduced on the device by dr_proxy_loss.
+attention_matrix gives the matrix itself, which is not an output of the hot path: it is read off the attention kernel
+column block by column block.  With V set to the one-hot columns of a key range, O = A V is that column range of A.  fp32
+tensors keep the read-out exact to fp32 rounding (they run the fp32 attention kernel).  Meant for the small N of the
+proxy task (N x N floats are materialised).
 """
 from __future__ import annotations
 
@@ -49,6 +50,7 @@ def proxy_loss(ctx: dr.Context, Q, K, Nf: int, Hg: int, Wg: int, Bs: int, mode: 
     (batch, head); `mode` is one of the library's selection rules or MODE_TOKENS: ||A_dense - A_sparse||_F^2 / ||A_dense||_F^2 + alpha * max(0, target - sparsity)."""
     import torch
     B, H, N, d = Q.shape
+    assert Q.dtype == torch.float32 and K.dtype == torch.float32, "the objective is computed from fp32 features"
     shape = dr.shape_of(Q, Nf, Hg, Wg, Bs)
     Sb = shape.Sb
     masks = 1 if params.head_fuse > 0 else H
@@ -64,13 +66,7 @@ def proxy_loss(ctx: dr.Context, Q, K, Nf: int, Hg: int, Wg: int, Bs: int, mode: 
     else:
         dr.dr_block_scores(ctx, shape, Q, K, params.head_fuse, scores)
         dr.dr_build_mask(ctx, shape, mode, ratio_or_tau, lam, params, scores, rowptr, colidx, cap, nnz)
-    A_sparse = attention_matrix(ctx, shape, Q, K, rowptr, colidx, masks, cap)
-    # dense reference through the same kernel: the all-ones block mask
-    full_rp = (torch.arange(Sb + 1, dtype=torch.int32, device=Q.device) * Sb).view(1, 1, -1).repeat(B, 1, 1).contiguous()
-    full_ci = torch.arange(Sb, dtype=torch.int32, device=Q.device).repeat(Sb).view(1, 1, -1).repeat(B, 1, 1).contiguous()
-    A_dense = attention_matrix(ctx, shape, Q, K, full_rp, full_ci, 1, Sb * Sb)
-    assert A_dense.is_contiguous() and A_sparse.is_contiguous() and nnz.is_contiguous()
     out = torch.empty(3, dtype=torch.float64, device=Q.device)
-    dr.dr_proxy_loss(ctx, A_dense, A_sparse, nnz, Sb, target, alpha, out)
+    dr.dr_proxy_objective(ctx, shape, Q, K, rowptr, colidx, masks, cap, nnz, target, alpha, out)
     loss, nmse, sparsity = out.tolist()
     return loss, nmse, sparsity
