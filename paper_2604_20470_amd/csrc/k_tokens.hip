@@ -14,68 +14,84 @@
 namespace dr {
 namespace {
 
-constexpr int kTile = 64;            // token-score tile (kTile x kTile outputs per workgroup)
-constexpr int kChunk = 32;           // channels staged per step
 constexpr int kThreads = 256;
 
-__device__ __forceinline__ float load_as_float(const void* base, int64_t idx, bool bf16) {
-    if (bf16) return __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(base)[idx] << 16);
-    return reinterpret_cast<const float*>(base)[idx];
+// Four consecutive channels of a row (the row's start need not be aligned).
+template <bool BF16>
+__device__ __forceinline__ float4 load_channels(const void* base, int64_t at) {
+    float4 x;
+    if constexpr (BF16) {
+        uint16_t u[4];
+        __builtin_memcpy(u, reinterpret_cast<const uint16_t*>(base) + at, 8);
+        x = make_float4(__uint_as_float((uint32_t)u[0] << 16), __uint_as_float((uint32_t)u[1] << 16),
+                        __uint_as_float((uint32_t)u[2] << 16), __uint_as_float((uint32_t)u[3] << 16));
+    } else {
+        __builtin_memcpy(&x, reinterpret_cast<const float*>(base) + at, 16);
+    }
+    return x;
 }
 
-// grid: (ceil(N / 64), ceil(N / 64), B * masks).  scores[b][m][p][q], fp32 accumulation.
+// scores[b][m][p][q] on the fp32 matrix instruction (fp32 products and sums).  2 x 2 wavefronts of 32 x 32 outputs; 32 channels
+// of 64 rows of either operand are staged through LDS, the next 32 on their way in registers.  A lane reads four
+// consecutive channels of its row and feeds one to each of four instructions: the order of the contraction is permuted alike
+// for both operands.  Bound by latency at the sizes of the search (1024 workgroups of four steps at 2048 tokens x 2 heads of 64
+// channels); a 4 x 4-per-thread product on the vector ALU with four-byte loads took 49 us there, this takes 16.7.
+// grid: (ceil(N / 64), ceil(N / 64), B * masks).
+constexpr int kTile = 64, kChunk = 32, kPitch = 36;      // row pitch 144 B keeps the 16-byte reads of 32 rows off the same banks
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+template <bool BF16>
 __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restrict__ Q, const void* __restrict__ K,
-                                                           TensorDesc td, int bf16, int masks, int heads_per_mask,
+                                                           TensorDesc td, int masks, int heads_per_mask,
                                                            float scale, float* __restrict__ scores) {
-    __shared__ float sq[kChunk][kTile + 1];
-    __shared__ float sk[kChunk][kTile + 1];
+    __shared__ __attribute__((aligned(16))) float sq[kTile][kPitch];
+    __shared__ __attribute__((aligned(16))) float sk[kTile][kPitch];
     const int b = blockIdx.z / masks, m = blockIdx.z % masks;
     const int p0 = blockIdx.y * kTile, q0 = blockIdx.x * kTile;
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    float acc[4][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, half = lane >> 5;
+    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+    v16f acc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    const int chunks = td.d / kChunk, steps = heads_per_mask * chunks;
+    const int row = tid >> 3, c4 = (tid & 7) * 4;            // of the first 32 rows; the thread takes row + 32 as well
+    float4 xq[2], xk[2];
+    auto fetch = [&](int step) {
+        const int h = (masks == 1 ? 0 : m) + step / chunks;
+        const int64_t at = (int64_t)b * td.stride_b + (int64_t)h * td.stride_h + (step % chunks) * kChunk + c4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-    for (int hh = 0; hh < heads_per_mask; ++hh) {
-        const int h = masks == 1 ? hh : m;
-        const int64_t head = (int64_t)b * td.stride_b + (int64_t)h * td.stride_h;
-        for (int c0 = 0; c0 < td.d; c0 += kChunk) {
-            // 64 rows x 32 channels per operand: thread -> (row = tid / 4, 8 channels)
-            const int r = tid >> 2, cc = (tid & 3) * 8;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int p = p0 + r, q = q0 + r;
-                sq[cc + e][r] = p < td.N ? load_as_float(Q, head + (int64_t)p * td.stride_n + c0 + cc + e, bf16) : 0.f;
-                sk[cc + e][r] = q < td.N ? load_as_float(K, head + (int64_t)q * td.stride_n + c0 + cc + e, bf16) : 0.f;
-            }
-            __syncthreads();
-#pragma unroll 8
-            for (int c = 0; c < kChunk; ++c) {
-                float a[4], bb[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    a[i] = sq[c][ty * 4 + i];
-                    bb[i] = sk[c][tx * 4 + i];
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * bb[j];
-            }
-            __syncthreads();
+        for (int i = 0; i < 2; ++i) {                        // rows past the end are read again from the last one
+            xq[i] = load_channels<BF16>(Q, at + (int64_t)min(p0 + row + 32 * i, td.N - 1) * td.stride_n);
+            xk[i] = load_channels<BF16>(K, at + (int64_t)min(q0 + row + 32 * i, td.N - 1) * td.stride_n);
         }
+    };
+    fetch(0);
+    for (int step = 0; step < steps; ++step) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            *reinterpret_cast<float4*>(&sq[row + 32 * i][c4]) = xq[i];
+            *reinterpret_cast<float4*>(&sk[row + 32 * i][c4]) = xk[i];
+        }
+        __syncthreads();
+        if (step + 1 < steps) fetch(step + 1);
+#pragma unroll
+        for (int g8 = 0; g8 < kChunk; g8 += 8) {
+            const float4 a = *reinterpret_cast<const float4*>(&sq[wr + l32][g8 + 4 * half]);
+            const float4 bb = *reinterpret_cast<const float4*>(&sk[wc + l32][g8 + 4 * half]);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, bb.x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, bb.y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, bb.z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, bb.w, acc, 0, 0, 0);
+        }
+        __syncthreads();
     }
+    // element e of lane (l32, half): row 8 * (e / 4) + 4 * half + e % 4, column l32
     float* out = scores + (int64_t)blockIdx.z * td.N * td.N;
+    const int q = q0 + wc + l32;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int p = p0 + ty * 4 + i;
-        if (p >= td.N) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int q = q0 + tx * 4 + j;
-            if (q < td.N) out[(int64_t)p * td.N + q] = acc[i][j] * scale;
-        }
+    for (int e = 0; e < 16; ++e) {
+        const int p = p0 + wr + 8 * (e >> 2) + 4 * half + (e & 3);
+        if (p < td.N && q < td.N) out[(int64_t)p * td.N + q] = acc[e] * scale;
     }
 }
 
@@ -440,7 +456,7 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
                                int heads_per_mask, float* scores, hipStream_t s) {
     const int tiles = (td.N + kTile - 1) / kTile;
     const float scale = (float)(1.0 / ((double)heads_per_mask * sqrt((double)td.d)));
-    hipLaunchKernelGGL(k_token_scores, dim3(tiles, tiles, td.B * masks), dim3(kThreads), 0, s, Q, K, td, bf16 ? 1 : 0,
+    hipLaunchKernelGGL(bf16 ? k_token_scores<true> : k_token_scores<false>, dim3(tiles, tiles, td.B * masks), dim3(kThreads), 0, s, Q, K, td,
                        masks, heads_per_mask, scale, scores);
     return hipGetLastError();
 }
