@@ -514,9 +514,8 @@ dr_status dr_build_mask_tokens(dr_ctx* ctx, const dr_shape* shape, double tau_ne
     FrameTab tab;
     fill_frame_table(shape->Nf, Nt, shape->Bs, p->gamma, lambda, &tab);
     const Geometry geo = make_geometry(shape, p);
-    DR_HIP(ctx, launch_pair_links(token_scores, tab, shape->B, masks, shape->N, Nt, shape->Nf, tau_near,
-                                  p->has_tau_far ? p->tau_far : tau_near, ctx->link_stats, links, s));
-    DR_HIP(ctx, launch_aggregate_links(links, ctx->class_map, geo, shape->B, masks, ctx->keepbits, ctx->counts, s));
+    DR_HIP(ctx, launch_token_mask(token_scores, tab, ctx->class_map, geo, shape->B, masks, tau_near, p->has_tau_far ? p->tau_far : tau_near,
+                                  ctx->link_stats, links, ctx->keepbits, ctx->counts, s));
     DR_HIP(ctx, launch_emit(ctx->keepbits, ctx->counts, shape->B, masks, Sb, false, rowptr, colidx, colidx_capacity, nnz, s));
     return DR_OK;
 }

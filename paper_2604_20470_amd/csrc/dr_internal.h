@@ -74,14 +74,13 @@ hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, i
 // scores[b][m][p][q] = (1 / (heads_per_mask * sqrt(d))) * sum_h Q_p . K_q
 hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const TensorDesc& td, int masks,
                                int heads_per_mask, float* scores, hipStream_t s);
-// links[b][m][p][q] = 1 where the token pair is kept (z-score thresholds inside every frame pair's candidate set);
-// scratch: column sums and per-pair statistics, of the size below
+// links[b][m][p][q] = 1 where the token pair is kept (z-score thresholds inside every frame pair's candidate set), and the density
+// rule per block pair -> the keepbits / counts that launch_emit reads.  scratch: column sums and per-pair statistics, of the
+// size below
 size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf);
-hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, int masks, int N, int Nt, int Nf,
-                             double tau_near, double tau_far, void* scratch, uint8_t* links, hipStream_t s);
-// density rule per block pair -> the keepbits / counts that launch_emit reads
-hipError_t launch_aggregate_links(const uint8_t* links, const uint8_t* class_map, const Geometry& g, int B, int masks,
-                                  uint32_t* keepbits, int32_t* counts, hipStream_t s);
+hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uint8_t* class_map, const Geometry& g, int B, int masks,
+                             double tau_near, double tau_far, void* scratch, uint8_t* links, uint32_t* keepbits, int32_t* counts,
+                             hipStream_t s);
 
 // ---- stage (c) -------------------------------------------------------------------------
 struct AttnArgs {

@@ -1,6 +1,6 @@
 // Algorithm 1 of the paper in its own order, for small sequences (an evaluation aid beside the block-level path):
 //   k_token_scores     proxy score of every token pair (Eq. 9, fused-head mean of App. B) -> fp32 [N, N]
-//   k_link_*, k_links, k_pair_links_small  per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
+//   k_link_*, k_pair_links_small  per ordered frame pair (i, j): candidate window (Eq. 7), population mean / std of the scores in
 //                      it (Eq. 10), z >= tau_1 / tau_2 by decay state (Eq. 11), keep-one safeguard -> link bytes [N, N]
 //   k_aggregate_links  density rule per block pair ("Density control within blocks": a column is active when its
 //                      kept-row ratio exceeds theta_c, the block when its active-column ratio exceeds theta_m), plus the
@@ -97,18 +97,16 @@ __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restric
 
 #pragma clang fp contract(off)
 
-// ---- links of every ordered frame pair, in five small launches.  What bounds this is the serial fp64 chain of a column
-// (the order of the sums is part of the definition) and three readings of the score matrix, so the columns of all pairs
-// are spread over the whole chip: a wavefront owns 64 key columns of one pair and reads whole row segments, sixteen rows
-// in flight.  (One workgroup per pair, 64 of them at 8 frames, left three quarters of the CUs idle: 1.85 ms at 8 x 1024
-// tokens, where the five launches take 0.144 ms: 24, 36, 16, 64 and 5 us.)
-//   k_link_sums<0>  column sums of the scores            k_link_sums<1>  of the squared deviations
-//   k_link_stats    deviation, and the test as one float   k_links  bytes, number of links, best score   k_link_safeguard
+// ---- links of every ordered frame pair, in four launches.  What bounds this is the serial fp64 chain of a column (the order of
+// the sums is part of the definition) and three readings of the score matrix, so the columns of all pairs are spread over the
+// whole chip: a wavefront owns 64 key columns of one pair and reads whole row segments, many rows in flight.
+//   k_link_sums<0>  column sums of the scores, highest score   k_link_sums<1>  column sums of the squared deviations
+//   k_link_stats    deviation, the test as one float, the pair that the safeguard keeps
+//   k_link_blocks   link bytes, and the density rule over them while they are at hand
 struct PairStat {
     double mu;
-    unsigned long long best;      // order-preserving image of the best score << 32 | ~(u * Nt + v)
     float threshold;              // a pair is a link when its score is at least this; NaN: none is
-    unsigned int kept;
+    int best;                     // where nothing passes: u * Nt + v of the highest score, which is kept; else -1
 };
 
 __device__ __forceinline__ uint32_t score_image(float s) {      // ascending unsigned == ascending float, -0 below +0
@@ -142,20 +140,47 @@ __device__ __forceinline__ PairAt pair_at(const FrameTab& tab, int Nf, int pair)
     return p;
 }
 
-// The sum of Nt doubles, one by one in ascending order (every lane gets it).  LDS: Nt doubles.
+// The sum of Nt doubles, one by one in ascending order (every lane gets it).  LDS: Nt doubles, up to a multiple of 16.  The next
+// sixteen are read while the current ones are added: the chain waits for the additions alone (2.4 ns each).
 __device__ __forceinline__ double ordered_sum(const double* __restrict__ col, int Nt, double* sh) {
-    for (int v = threadIdx.x; v < Nt; v += 64) sh[v] = col[v];
-    __syncthreads();
-    double total = 0.0;
-    int v = 0;
-    for (; v + 8 <= Nt; v += 8) {
-        double x[8];
+    const int padded = (Nt + 15) & ~15;
+    for (int v0 = threadIdx.x; v0 < padded; v0 += 64 * 16) {      // sixteen loads on their way: another XCD wrote the sums
+        double x[16];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = sh[v + e];
+        for (int e = 0; e < 16; ++e) x[e] = col[min(v0 + 64 * e, Nt - 1)];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) total = total + x[e];
+        for (int e = 0; e < 16; ++e) {
+            const int v = v0 + 64 * e;
+            if (v < padded) sh[v] = v < Nt ? x[e] : -0.0;         // (x + -0.0 is x, bit for bit)
+        }
     }
-    for (; v < Nt; ++v) total = total + sh[v];
+    __syncthreads();
+    double total = 0.0, x[2][16];
+    auto read = [&](double (&dst)[16], int v) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dst[e] = sh[v + e];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto add = [&](const double (&src)[16]) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) total = total + src[e];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read(x[0], 0);
+    int v = 16;
+    for (; v + 16 < padded; v += 32) {
+        read(x[1], v);
+        add(x[0]);
+        read(x[0], v + 16);
+        add(x[1]);
+    }
+    if (v < padded) {
+        read(x[1], v);
+        add(x[0]);
+        add(x[1]);
+    } else {
+        add(x[0]);
+    }
     return total;
 }
 __device__ __forceinline__ double window_size(int Nt, int w) {      // token pairs of a candidate set
@@ -165,142 +190,301 @@ __device__ __forceinline__ double window_size(int Nt, int w) {      // token pai
     return (double)n;
 }
 
-// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs: [B * masks][Nf * Nf][Nt].
+// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs, tops: [B * masks][Nf * Nf][Nt].
 // A column's rows are walked over the union of the wavefront's windows, so that all lanes read one row; a row outside a
 // lane's own window adds +0.0, which leaves its running sum bit for bit as it is (it starts at +0.0 and is never -0.0).
+// At 8 x 1024 tokens 672 wavefronts have work, fewer than one a SIMD, so the time is that of one wavefront's rows: the next
+// kAhead are fetched before the current ones are added, and rows that lie in every lane's window are added without a test
+// (23 -> 21 us and 36 -> 29 there; a third set of registers would not help: a wavefront counts at most 63 loads).
 template <int PASS>
 __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
-                                                  double* __restrict__ sums, double* __restrict__ devs, PairStat* __restrict__ stats) {
+                                                  double* __restrict__ sums, double* __restrict__ devs, float* __restrict__ tops,
+                                                  PairStat* __restrict__ stats) {
     extern __shared__ double sh[];
     const int tiles = (Nt + 63) / 64;
     const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
     const PairAt p = pair_at(tab, Nf, pair);
     if (!p.judged) return;
+    const int v = v0 + (int)threadIdx.x, vc = min(v, Nt - 1), v_last = min(v0 + 63, Nt - 1);
+    const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
+    const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, v_last + p.w);      // of the wavefront
+    const int every_first = max(0, v_last - p.w), every_last = min(Nt - 1, v0 + p.w);      // rows in all its windows
+    const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
+    constexpr int kAhead = 32;
+    float x[2][kAhead];
+    auto fetch = [&](float (&dst)[kAhead], int u) {                  // (past the window: its last row again)
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) dst[e] = (S + (int64_t)min(u + e, u_last) * N)[(uint32_t)vc];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(x[0], u_first);
     double mu = 0.0;
     if constexpr (PASS == 1) {
         mu = ordered_sum(sums + p.pair * Nt, Nt, sh) / window_size(Nt, p.w);
         if (v0 == 0 && threadIdx.x == 0) stats[p.pair].mu = mu;
     }
-    const int v = v0 + (int)threadIdx.x, vc = min(v, Nt - 1);
-    const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
-    const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, min(v0 + 63, Nt - 1) + p.w);      // of the wavefront
-    const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt + vc;
     double acc = 0.0;
-    auto add = [&](float s, int u) {
-        if constexpr (PASS == 0) {
-            acc = acc + ((u >= lo && u <= hi) ? (double)s : 0.0);
+    float top = __builtin_nanf("");                                  // (fmaxf passes NaN by: it ranks below every number)
+    auto term = [&](float s) {
+        const double dev = (double)s - mu;
+        return PASS == 0 ? (double)s : dev * dev;
+    };
+    auto add = [&](const float (&src)[kAhead], int u0) {
+        if (u0 >= every_first && u0 + kAhead - 1 <= every_last) {    // the same in every lane
+#pragma unroll
+            for (int e = 0; e < kAhead; ++e) {
+                acc = acc + term(src[e]);
+                if constexpr (PASS == 0) top = fmaxf(top, src[e]);
+            }
         } else {
-            const double dev = (double)s - mu;
-            const double sq = dev * dev;
-            acc = acc + ((u >= lo && u <= hi) ? sq : 0.0);
+#pragma unroll
+            for (int e = 0; e < kAhead; ++e) {
+                const bool in = u0 + e >= lo && u0 + e <= hi;        // (hi <= u_last)
+                const double t = term(src[e]);
+                acc = acc + (in ? t : 0.0);
+                if constexpr (PASS == 0) top = in ? fmaxf(top, src[e]) : top;
+            }
         }
     };
-    int u = u_first;
-    constexpr int kAhead = 16;
-    for (; u + kAhead - 1 <= u_last; u += kAhead) {
-        float x[kAhead];
-#pragma unroll
-        for (int e = 0; e < kAhead; ++e) x[e] = S[(int64_t)(u + e) * N];
-#pragma unroll
-        for (int e = 0; e < kAhead; ++e) add(x[e], u + e);
+    for (int u = u_first; u <= u_last; u += 2 * kAhead) {
+        fetch(x[1], u + kAhead);
+        add(x[0], u);
+        fetch(x[0], u + 2 * kAhead);
+        if (u + kAhead <= u_last) add(x[1], u + kAhead);
     }
-    for (; u <= u_last; ++u) add(S[(int64_t)u * N], u);
-    if (v < Nt) (PASS == 0 ? sums : devs)[p.pair * Nt + v] = acc;
+    if (v < Nt) {
+        (PASS == 0 ? sums : devs)[p.pair * Nt + v] = acc;
+        if constexpr (PASS == 0) tops[p.pair * Nt + v] = top;
+    }
 }
 
 // grid: (Nf * Nf, masks, B), 64 threads.  The test ((double)s - mu) / denom >= tau is monotone in s (IEEE subtraction and
-// division are), so the smallest float that passes, found by bisection over the floats in order, decides it exactly.  A set
-// that holds an infinity or a NaN has a mean or a deviation that is not a number, and no score passes, infinite ones included.
-__global__ __launch_bounds__(64) void k_link_stats(FrameTab tab, int Nt, int Nf, double tau_near, double tau_far,
-                                                   const double* __restrict__ devs, PairStat* __restrict__ stats) {
+// division are), so the smallest float that passes, found by a search over the floats in order (64 places a step), decides it
+// exactly.  A set that holds an infinity or a NaN has a mean or a deviation that is not a number, and no score passes,
+// infinite ones included.  Also clears the kept counts of the mask's rows, to which k_link_blocks adds.
+__global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf, int Sb,
+                                                   double tau_near, double tau_far, const double* __restrict__ devs,
+                                                   const float* __restrict__ tops, PairStat* __restrict__ stats, int32_t* __restrict__ counts) {
     extern __shared__ double sh[];
+    const int lane = threadIdx.x;
     const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
+    for (int r = (int)blockIdx.x * 64 + lane; r < Sb; r += (int)gridDim.x * 64) counts[p.mask * Sb + r] = 0;
     if (!p.judged) return;
+    float top = __builtin_nanf("");
+    for (int v0 = lane; v0 < Nt; v0 += 64 * 16) {
+        float x[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = tops[p.pair * Nt + min(v0 + 64 * e, Nt - 1)];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) top = fmaxf(top, x[e]);
+    }
+    for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
     const double denom = sqrt(ordered_sum(devs + p.pair * Nt, Nt, sh) / window_size(Nt, p.w)) + 1e-6;
-    if (threadIdx.x != 0) return;
     const double mu = stats[p.pair].mu;
     const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
+    auto passes = [&](float s) { return ((double)s - mu) / denom >= tau; };
+    // images lo .. none - 1 are the finite floats; the first that passes lies in [lo, lo + span]
     const uint32_t none = score_image(3.402823466e38f) + 1u;
-    uint32_t lo = score_image(-3.402823466e38f), hi = none;      // first image that passes
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if (((double)image_score(mid) - mu) / denom >= tau) hi = mid;
-        else lo = mid + 1u;
+    uint32_t lo = score_image(-3.402823466e38f), span = none - lo;
+    while (span > 0u) {
+        const uint32_t step = span / 64u + 1u;                             // lane l asks at lo + l * step
+        const uint32_t at = lo + (uint32_t)lane * step;
+        const uint64_t yes = __ballot((uint64_t)lane * step < span && passes(image_score(at)));
+        // the answer lies behind the last place that fails, up to the first that passes (or the end)
+        const int first = yes ? __ffsll((unsigned long long)yes) - 1 : (int)((span - 1u) / step) + 1;
+        if (first == 0) break;                                             // lo itself passes
+        const uint32_t end = yes ? (uint32_t)first * step : span;
+        const uint32_t from = (uint32_t)(first - 1) * step + 1u;
+        lo += from;
+        span = end - from;
     }
-    stats[p.pair].threshold = lo < none ? image_score(lo) : __builtin_nanf("");
-    stats[p.pair].kept = 0u;
-    stats[p.pair].best = 0ull;
-}
-
-// grid: (Nf * Nf * ceil(Nt / kLinkRows), masks, B).  A thread takes four consecutive key columns of a row at a time.
-constexpr int kLinkRows = 16;
-__global__ __launch_bounds__(kThreads) void k_links(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
-                                                    PairStat* __restrict__ stats, uint8_t* __restrict__ links) {
-    __shared__ unsigned long long s_best[kThreads / 64];
-    __shared__ unsigned int s_kept[kThreads / 64];
-    const int tiles = (Nt + kLinkRows - 1) / kLinkRows;
-    const PairAt p = pair_at(tab, Nf, (int)(blockIdx.x / tiles));
-    const int u0 = (int)(blockIdx.x % tiles) * kLinkRows, rows = min(kLinkRows, Nt - u0);
-    const int64_t at0 = p.mask * N * N + ((int64_t)p.i * Nt + u0) * N + (int64_t)p.j * Nt;
-    const int quads = (Nt + 3) / 4;
-    const float threshold = p.judged ? stats[p.pair].threshold : 0.f;
-    unsigned int kept = 0u;
-    unsigned long long best = 0ull;
-    for (int q = threadIdx.x; q < rows * quads; q += kThreads) {
-        const int r = q / quads, v = (q - r * quads) * 4, n = min(4, Nt - v), u = u0 + r;
-        const int64_t at = at0 + (int64_t)r * N + v;
-        uint8_t out[4] = {0, 0, 0, 0};
-        if (p.t <= 1) {
+    const float threshold = lo < none ? image_score(lo) : __builtin_nanf("");
+    int best = -1;
+    if (!(top >= threshold)) {
+        // nothing passes: the highest score, the first in row-major order on ties (-0 equals +0; in a set of NaN alone any is)
+        int best_u = Nt, best_v = 0;
+        const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
+        for (int v0 = 0; v0 < Nt; v0 += 64 * 16) {
+            float x[16];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) out[e] = 1;
-        } else if (p.judged) {
-            float s[4] = {0.f, 0.f, 0.f, 0.f};
-            if (n == 4) __builtin_memcpy(s, scores + at, 16);      // (4-byte aligned)
-            else for (int e = 0; e < n; ++e) s[e] = scores[at + e];
+            for (int e = 0; e < 16; ++e) x[e] = tops[p.pair * Nt + min(v0 + 64 * e + lane, Nt - 1)];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (e < n && abs(u - (v + e)) <= p.w) {
-                    out[e] = s[e] >= threshold ? 1 : 0;
-                    kept += out[e];
-                    best = max(best, best_key(s[e], u * Nt + v + e));
+            for (int e = 0; e < 16; ++e) {
+                uint64_t tied = __ballot(v0 + 64 * e + lane < Nt && (x[e] == top || top != top));
+                while (tied) {                                             // the same in every lane
+                    const int v = v0 + 64 * e + __ffsll((unsigned long long)tied) - 1;
+                    tied &= tied - 1;
+                    // a later column counts only by an earlier row
+                    const int first = max(0, v - p.w), last = min(min(Nt - 1, v + p.w), best_u - 1);
+                    for (int u0 = first; u0 <= last; u0 += 64) {
+                        const int u = u0 + lane;
+                        const float s = S[(int64_t)min(u, last) * N + v];
+                        const uint64_t hit = __ballot(u <= last && (s == top || top != top));
+                        if (hit) {
+                            best_u = u0 + __ffsll((unsigned long long)hit) - 1;
+                            best_v = v;
+                            break;
+                        }
+                    }
                 }
             }
         }
-        if (n == 4) __builtin_memcpy(links + at, out, 4);
-        else for (int e = 0; e < n; ++e) links[at + e] = out[e];
+        best = best_u * Nt + best_v;
     }
-    if (!p.judged) return;
-    for (int off = 32; off > 0; off >>= 1) {
-        kept += __shfl_xor(kept, off);
-        best = max(best, (unsigned long long)__shfl_xor(best, off));
+    if (lane == 0) {
+        stats[p.pair].threshold = threshold;
+        stats[p.pair].best = best;
     }
-    if ((threadIdx.x & 63) == 0) { s_kept[threadIdx.x >> 6] = kept; s_best[threadIdx.x >> 6] = best; }
+}
+
+// Link bytes and the density rule in one pass over the scores.  A workgroup owns a query block (Bs rows) and 1024 key columns;
+// a thread takes four consecutive columns, of every kGroups-th row, and keeps their numbers of links in the bytes of one
+// word (a count is at most 128), so that a wavefront reads 1 KB runs and writes 256-byte ones and the link bytes are not read
+// again; only scores inside some row's window are read.  Bound by memory: at 8192 tokens 41 us, 67 MB written and some 65 MB
+// read.  (Link bytes, safeguard and density in three launches took 90 us, the whole call 168 us where it takes 101.)
+// kGroups = 4 (1024 threads) up to kSmallGrid workgroups, two per compute unit: calls at 128 workgroups 42 us against 49, at 512
+// 152 against 171 (block size 128) and 62 against 62 (32), at 750 73 against 68.  grid: (Sb * ceil(N / 1024), masks, B).
+constexpr int kBlockCols = 1024;
+constexpr int64_t kSmallGrid = 512;
+template <int kGroups>
+__global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __restrict__ scores, FrameTab tab, const PairStat* __restrict__ stats,
+                                                               const uint8_t* __restrict__ class_map, Geometry g,
+                                                               uint8_t* __restrict__ links, uint32_t* __restrict__ keepbits,
+                                                               int32_t* __restrict__ counts) {
+    __shared__ uint32_t s_cnt[kGroups][256];
+    __shared__ uint32_t s_bits;
+    const int tid = threadIdx.x & 255, group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+    const int N = g.N, Nt = g.Nt, steps = (N + kBlockCols - 1) / kBlockCols;
+    const int qb = (int)blockIdx.x / steps, c_step = (int)blockIdx.x % steps;
+    const int64_t mask = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
+    const int r0 = qb * g.Bs, nr = min(g.Bs, N - r0), c0 = c_step * kBlockCols, c = c0 + tid * 4, n = min(4, N - c);
+    if (threadIdx.x == 0) s_bits = 0u;
+    uint32_t cnt = 0u;
+    if (n > 0) {
+        // per column: its frame and place there; for the rows of frame `i`, the window, the threshold and the safeguard's row
+        int j[4], v[4], from[4], kept_u[4];
+        uint32_t width[4], all = 0u;
+        float threshold[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int q = min(c + e, N - 1);
+            j[e] = q / Nt;
+            v[e] = q - j[e] * Nt;
+        }
+        const uint32_t present = n == 4 ? ~0u : (1u << (8 * n)) - 1u;
+        auto enter_frame = [&](int i) {
+            all = 0u;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int t = abs(i - j[e]);
+                const int flags = tab.flags[t];
+                if (t <= 1) all |= 1u << (8 * e);
+                from[e] = 0x40000000;                                    // an empty window: no row lies in it
+                width[e] = 0u;
+                threshold[e] = 0.f;
+                kept_u[e] = -1;
+                if (t > 1 && (flags & 1)) {
+                    const PairStat st = stats[(mask * g.Nf + i) * g.Nf + j[e]];
+                    from[e] = v[e] - tab.w[t];
+                    width[e] = 2u * (uint32_t)tab.w[t];
+                    threshold[e] = st.threshold;
+                    if (st.best >= 0 && st.best % Nt == v[e]) kept_u[e] = st.best / Nt;
+                }
+            }
+            all &= present;
+        };
+        const int64_t at0 = mask * N * N + (int64_t)r0 * N + c;
+        int frame = (r0 + group) / Nt, frame_row0 = frame * Nt - r0;      // the same in every lane
+        enter_frame(frame);
+        constexpr int kAhead = 4;
+        for (int r = group; r < nr; r += kGroups * kAhead) {
+            // only columns whose window some row of the batch lies in are read (all, where the batch leaves the frame)
+            const int row_last = min(r + (kAhead - 1) * kGroups, nr - 1);
+            const int u_first = r - frame_row0, u_last = row_last - frame_row0;
+            bool asks = u_last >= Nt;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) asks = asks || (from[e] <= u_last && u_first - from[e] <= (int)width[e]);
+            float x[kAhead][4];
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[a][e] = 0.f;
+            if (asks) {
+#pragma unroll
+                for (int a = 0; a < kAhead; ++a) {
+                    const int64_t at = at0 + (int64_t)min(r + a * kGroups, nr - 1) * N;
+                    if (n == 4) __builtin_memcpy(x[a], scores + at, 16);      // (4-byte aligned)
+                    else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) x[a][e] = scores[at + min(e, n - 1)];
+                    }
+                }
+            }
+            const bool any_asks = __any(asks);                            // the same in every lane
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const int row = r + a * kGroups;
+                if (row >= nr) break;
+                while (row - frame_row0 >= Nt) {
+                    ++frame;
+                    frame_row0 += Nt;
+                    enter_frame(frame);
+                }
+                const int u = row - frame_row0;
+                uint32_t out = all;
+                if (any_asks) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool link = u == kept_u[e] || ((uint32_t)(u - from[e]) <= width[e] && x[a][e] >= threshold[e]);
+                        out |= link ? 1u << (8 * e) : 0u;
+                    }
+                    out &= present;
+                }
+                const int64_t at = at0 + (int64_t)row * N;
+                if (n == 4) __builtin_memcpy(links + at, &out, 4);
+                else for (int e = 0; e < n; ++e) links[at + e] = (uint8_t)(out >> (8 * e));
+                cnt += out;
+            }
+        }
+    }
+    s_cnt[group][tid] = cnt;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < kThreads / 64; ++i) { kept += s_kept[i]; best = max(best, s_best[i]); }
-        if (kept) atomicAdd(&stats[p.pair].kept, kept);
-        if (best) atomicMax(&stats[p.pair].best, best);
+    if (group != 0) return;
+    for (int k = 1; k < kGroups; ++k) cnt += s_cnt[k][tid];
+    const int row_min = nr == g.Bs ? g.row_min_full : g.row_min_tail;
+    int active = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) active += (e < n && (int)((cnt >> (8 * e)) & 255u) >= row_min) ? 1 : 0;
+    const int per_block = g.Bs / 4;                                       // threads of a key block: 8, 16 or 32
+    for (int off = 1; off < per_block; off <<= 1) active += __shfl_xor(active, off);
+    const int kb = c / g.Bs;
+    if (n > 0 && tid % per_block == 0) {
+        const int nc = min(g.Bs, N - kb * g.Bs);
+        const int col_min = nc == g.Bs ? g.col_min_full : g.col_min_tail;
+        // a block that holds a token pair with t <= 1 is kept whatever its density
+        if (class_map[(int64_t)qb * g.Sb + kb] == 3 || active >= col_min) atomicOr(&s_bits, 1u << (kb - c0 / g.Bs));
     }
+    __syncthreads();
+    // the step's 8, 16 or 32 bits as bytes of the row's bitmap; the last step clears what is left of the last word
+    const int64_t row = mask * g.Sb + qb;
+    const int words = (g.Sb + 31) / 32, step_bytes = kBlockCols / g.Bs / 8, at = c_step * step_bytes;
+    uint8_t* bytes = reinterpret_cast<uint8_t*>(keepbits + row * words);
+    const int to = c_step + 1 == steps ? words * 4 : at + step_bytes;
+    if (tid < to - at && at + tid < words * 4) bytes[at + tid] = tid < step_bytes ? (uint8_t)(s_bits >> (8 * tid)) : (uint8_t)0;
+    if (tid == 0 && s_bits) atomicAdd(&counts[row], __popc(s_bits));
 }
 
-// A pair of frames in which nothing passed keeps the highest score of its set (the first in row-major order on ties).
-// grid: (ceil(Nf * Nf / 64), masks, B), 64 threads
-__global__ __launch_bounds__(64) void k_link_safeguard(FrameTab tab, int N, int Nt, int Nf, const PairStat* __restrict__ stats,
-                                                       uint8_t* __restrict__ links) {
-    const int pair = (int)(blockIdx.x * 64 + threadIdx.x);
-    if (pair >= Nf * Nf) return;
-    const PairAt p = pair_at(tab, Nf, pair);
-    if (!p.judged || stats[p.pair].kept != 0u) return;
-    const int idx = best_index(stats[p.pair].best), u = idx / Nt, v = idx % Nt;
-    links[p.mask * N * N + ((int64_t)p.i * Nt + u) * N + (int64_t)p.j * Nt + v] = 1;
-}
-
-// The same for a pair of small frames (Nt <= kSmallFrame) in one launch: a workgroup holds the pair's scores in LDS (two such
-// workgroups share a CU at 128 tokens) and makes the statistics, the bytes and the safeguard itself.  Five launches cost 8 to
-// 16 us more than one where there is next to no work: whole calls, five launches / one, 4 frames of 64 tokens, block size
-// 128: 25 / 16 us; 33 of 64: 39 / 20; 256 of 64: 338 / 240; 33 of 121, eight masks, block size 32: 250 / 241, the line.
-// grid: (Nf * Nf, masks, B).  LDS: Nt doubles | Nt * Nt floats.
+// The same for pairs of small frames in one launch: a workgroup holds the pair's scores in LDS (two such workgroups share a CU at
+// 128 tokens) and makes the statistics, the bytes and the safeguard itself; the density rule follows.  Where there is little
+// work four launches cost more than two, where there is much the serial chains of a workgroup do: whole calls, four launches /
+// two, 4 frames of 64 tokens, block size 128: 19 / 13 us; 33 of 64: 31 / 26; 16 of 128: 37 / 35; 33 of 96 (10 million token
+// pairs): 57 / 46; 33 of 121 (16 million): 63 / 71; 60 of 128: 91 / 134; 128 of 64: 73 / 87.
 constexpr int kSmallFrame = 128;
+constexpr int64_t kSmallPairs = 12 << 20;
+inline bool small_frames(int B, int masks, int N, int Nf) {
+    return N / Nf <= kSmallFrame && (int64_t)B * masks * N * N <= kSmallPairs;
+}
+// grid: (Nf * Nf, masks, B).  LDS: Nt doubles | Nt * Nt floats.
 __global__ __launch_bounds__(kThreads) void k_pair_links_small(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
                                                                double tau_near, double tau_far, uint8_t* __restrict__ links) {
     extern __shared__ double col[];
@@ -462,13 +646,15 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
 }
 
 size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf) {
-    if (N / Nf <= kSmallFrame) return 0;
-    return (size_t)B * masks * ((size_t)2 * Nf * N * sizeof(double) + (size_t)Nf * Nf * sizeof(PairStat));
+    if (small_frames(B, masks, N, Nf)) return 0;
+    return (size_t)B * masks * ((size_t)Nf * N * (2 * sizeof(double) + sizeof(float)) + (size_t)Nf * Nf * sizeof(PairStat));
 }
 
-hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, int masks, int N, int Nt, int Nf,
-                             double tau_near, double tau_far, void* scratch, uint8_t* links, hipStream_t s) {
-    if (Nt <= kSmallFrame) {
+hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uint8_t* class_map, const Geometry& g, int B, int masks,
+                             double tau_near, double tau_far, void* scratch, uint8_t* links, uint32_t* keepbits, int32_t* counts,
+                             hipStream_t s) {
+    const int N = g.N, Nt = g.Nt, Nf = g.Nf;
+    if (small_frames(B, masks, N, Nf)) {
         const size_t lds = (size_t)Nt * sizeof(double) + (size_t)Nt * Nt * sizeof(float);
         if (lds > 64 * 1024) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pair_links_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -476,24 +662,25 @@ hipError_t launch_pair_links(const float* scores, const FrameTab& tab, int B, in
         }
         hipLaunchKernelGGL(k_pair_links_small, dim3((unsigned)Nf * Nf, masks, B), dim3(kThreads), lds, s, scores, tab, N, Nt, Nf,
                            tau_near, tau_far, links);
+        hipLaunchKernelGGL(k_aggregate_links, dim3(g.Sb, masks, B), dim3(kThreads), 0, s, links, class_map, g, keepbits, counts);
         return hipGetLastError();
     }
+    const size_t columns = (size_t)B * masks * Nf * N;
     double* sums = static_cast<double*>(scratch);
-    double* devs = sums + (size_t)B * masks * Nf * N;
-    PairStat* stats = reinterpret_cast<PairStat*>(devs + (size_t)B * masks * Nf * N);
-    const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64, rows = (Nt + kLinkRows - 1) / kLinkRows;
-    const size_t lds = (size_t)Nt * sizeof(double);
-    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, stats);
-    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, stats);
-    hipLaunchKernelGGL(k_link_stats, dim3(pairs, masks, B), dim3(64), lds, s, tab, Nt, Nf, tau_near, tau_far, devs, stats);
-    hipLaunchKernelGGL(k_links, dim3(pairs * rows, masks, B), dim3(kThreads), 0, s, scores, tab, N, Nt, Nf, stats, links);
-    hipLaunchKernelGGL(k_link_safeguard, dim3((pairs + 63) / 64, masks, B), dim3(64), 0, s, tab, N, Nt, Nf, stats, links);
-    return hipGetLastError();
-}
-
-hipError_t launch_aggregate_links(const uint8_t* links, const uint8_t* class_map, const Geometry& g, int B, int masks,
-                                  uint32_t* keepbits, int32_t* counts, hipStream_t s) {
-    hipLaunchKernelGGL(k_aggregate_links, dim3(g.Sb, masks, B), dim3(kThreads), 0, s, links, class_map, g, keepbits, counts);
+    double* devs = sums + columns;
+    PairStat* stats = reinterpret_cast<PairStat*>(devs + columns);
+    float* tops = reinterpret_cast<float*>(stats + (size_t)B * masks * Nf * Nf);
+    const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64;
+    const size_t lds = (size_t)((Nt + 15) & ~15) * sizeof(double);
+    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, tops, stats);
+    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, tops, stats);
+    hipLaunchKernelGGL(k_link_stats, dim3(pairs, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, g.Sb, tau_near, tau_far,
+                       devs, tops, stats, counts);
+    const dim3 grid((unsigned)g.Sb * ((N + kBlockCols - 1) / kBlockCols), masks, B);
+    if ((int64_t)grid.x * masks * B <= kSmallGrid)
+        hipLaunchKernelGGL(k_link_blocks<4>, grid, dim3(1024), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
+    else
+        hipLaunchKernelGGL(k_link_blocks<1>, grid, dim3(256), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
     return hipGetLastError();
 }
 
