@@ -55,8 +55,8 @@ struct Plan {
     static constexpr int kTiles = kS * kT;                          // of a stage
     static constexpr int kRows = kAlone ? 32 : kTiles * 32;         // of an LDS region
     static constexpr int kStageBytes = kTiles * kTileBytes;
-    // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide the splitting of the next stage
-    // behind: it goes into a second buffer, between the matrix instructions, where two fit
+    // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide its vector instructions behind: they go
+    // between the matrix instructions, with a second buffer, where two fit
     static constexpr int kBuffers = !kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024 ? 2 : 1;
     static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : BF16 && D == 64 && BS == 128 ? 4 : 2;      // wavefronts, at least
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
@@ -523,17 +523,308 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             use_tile(s, valid, 0u);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-    } else {
-    if (stages > 0) fetch(0);
-    if constexpr (P::kBuffers == 2) {
-        if (stages > 0) {
-            store(0);
+    } else if constexpr (P::kBuffers == 2) {
+        // One wavefront per SIMD issues in order, so the vector instructions of a tile (the exponentials, the split of its
+        // probabilities, the split of the rows fetched for later tiles) stand between matrix instructions that do not wait for
+        // them, some five to each: the softmax of tile g under the logits of tile g + 1, the splits of rows under the products
+        // with the values of tile g.  Keys of tile t are in the key part of buffer t % 2, its values in the value part.
+        // The four wavefronts read every fragment, so the LDS is nearly as busy as the matrix pipes: values are kept
+        // transposed (a channel's 32 keys in 64 bytes, in the order in which the probabilities lie in a lane), which a fragment
+        // reads with one 16-byte load instead of two transposing 8-byte ones, at twice the rate.
+        static_assert(P::kS == 1 && P::kT == 1 && kPieces == 8 && kKS == 8 && kDB == 4 && D == 128 && P::kThreads == 256,
+                      "eight steps of six matrix instructions each, four pieces of sixteen bytes a thread");
+        typedef float v2f32 __attribute__((ext_vector_type(2)));
+        // keys: a thread splits eight channels of two rows.  Rows past the sequence's end are read again from its last.
+        auto key_offsets = [&](int row0, int64_t (&off)[2]) {
 #pragma unroll
-            for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
-            if (stages > 1) fetch(1);
+            for (int p = 0; p < 2; ++p) {
+                const int r = p * 16 + wave * 4 + (lane >> 4);
+                off[p] = (int64_t)(min(row0 + r, N - 1) - row0) * it.row_bytes + (lane & 15) * 32;
+            }
+        };
+        auto fetch_k = [&](int row0, const int64_t (&off)[2]) {
+            const char* base = it.K + (int64_t)row0 * it.row_bytes;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) rk[p].x[i] = *reinterpret_cast<const v4f32*>(base + off[p] + i * 16);
+        };
+        // values: a thread splits two channels of the eight keys that one lane half of a product takes, key e of them being
+        // (wave / 2) * 16 + (wave % 2) * 4 + e % 4 + 8 * (e / 4): a wavefront reads whole rows
+        v2f32 xv[8];
+        const int v_row = (wave >> 1) * 16 + (wave & 1) * 4;
+        constexpr int kVRow[8] = {0, 1, 2, 3, 8, 9, 10, 11};
+        auto load_v = [&](uint64_t row, int e) {
+            asm("" : "+s"(row));                   // (a scalar base and the lane's offset, not a 64-bit product per lane)
+            xv[e] = *reinterpret_cast<const __attribute__((address_space(1))) v2f32*>(row + (uint32_t)lane * 8u);
+        };
+        auto fetch_v = [&](int row0) {             // rows past the sequence's end are read again from its last
+#pragma unroll
+            for (int e = 0; e < 8; ++e) load_v((uint64_t)(it.V + (int64_t)min(row0 + v_row + kVRow[e], N - 1) * it.row_bytes), e);
+        };
+        // LDS place of a thread's four pieces: keys of pass 0 and 1, values of channel 2 * lane and 2 * lane + 1
+        auto v_unit = [](int channel, int unit) { return channel * 64 + ((unit ^ ((channel >> 2) & 3)) << 4); };
+        uint32_t put[4];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const int row = p * 16 + wave * 4 + (lane >> 4);
+            put[p] = row * P::kRowBytes + k_piece<D>(lane & 15, row) * 16;
+            put[2 + p] = P::kIn * kPart + v_unit(2 * lane + p, wave);
+        }
+        auto pair_of = [&](int u, int j, int h) -> float {      // element h of pair j of piece u
+            return u < 2 ? rk[u].x[j >> 1][2 * (j & 1) + h] : xv[2 * j + h][u - 2];
+        };
+        auto row_of = [&](int t) { return tile_row0(min(t, n_tiles - 1)); };      // first row of tile t (past the end: of the last)
+        auto at_buffer = [&](uint32_t addr, uint32_t buffer) {      // (opaque: the parts' offsets stay immediates of the reads)
+            uint32_t at = addr + buffer;
+            asm("" : "+v"(at));
+            return at;
+        };
+        uint32_t vt_addr[2];                       // of the lane's unit of either half tile; channel block db is 2 KB further
+#pragma unroll
+        for (int t = 0; t < 2; ++t) vt_addr[t] = lds0 + P::kIn * kPart + v_unit(l32, t * 2 + half);
+        auto read_k = [&](uint32_t at, int i, v8bf (&kf)[P::kIn]) { kf[i] = *(lds_v8)(uintptr_t)(at + i * kPart); };
+        auto read_v = [&](uint32_t at, int c, int i, v8bf (&vf)[P::kIn]) {      // step c: keys 16 * (c / 4) .., channels 32 * (c % 4) ..
+            vf[i] = *(lds_v8)(uintptr_t)(at + i * kPart + (c & 3) * 2048);
+        };
+        // first: cvt of part q of a pair; second: what the part leaves.  (A conversion's result is read an instruction later at
+        // the earliest, so the two are apart.)
+        auto convert = [](float r0, float r1) {
+            union { v2bf v; uint32_t u; } pk;
+            pk.v[0] = (__bf16)r0;
+            pk.v[1] = (__bf16)r1;
+            asm("" : "+v"(pk.u));                  // keeps the pair packed
+            return pk.u;
+        };
+        auto subtract = [](float (&r)[2], uint32_t part) {
+            r[0] -= __uint_as_float(part << 16);
+            r[1] -= __uint_as_float(part & 0xffff0000u);
+        };
+        typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+        v4u word[3];                               // a piece's parts
+        float rest[2][2];
+        // Slot i (0 .. 11) of the split of piece u into buffer `to`: two pairs at a time, six slots each
+        auto split_slot = [&](int u, int i, uint32_t to) {
+            const int a = i < 6 ? 0 : 2, b = a + 1, k = i % 6;
+            if (k == 0) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) { rest[0][h] = pair_of(u, a, h); rest[1][h] = pair_of(u, b, h); }
+                word[0][a] = convert(rest[0][0], rest[0][1]);
+                word[0][b] = convert(rest[1][0], rest[1][1]);
+            } else if (k == 1) {
+                subtract(rest[0], word[0][a]);
+            } else if (k == 2) {
+                word[1][a] = convert(rest[0][0], rest[0][1]);
+                subtract(rest[1], word[0][b]);
+            } else if (k == 3) {
+                word[1][b] = convert(rest[1][0], rest[1][1]);
+                subtract(rest[0], word[1][a]);
+            } else if (k == 4) {
+                word[2][a] = convert(rest[0][0], rest[0][1]);
+                subtract(rest[1], word[1][b]);
+            } else {
+                word[2][b] = convert(rest[1][0], rest[1][1]);
+            }
+            if (i == 8 || i == 10 || i == 11) {
+                const int q = i == 8 ? 0 : i == 10 ? 1 : 2;
+                *reinterpret_cast<v4u*>(smem + put[u] + to + q * kPart) = word[q];
+            }
+        };
+        auto split_piece = [&](int u, uint32_t to) {
+#pragma unroll
+            for (int i = 0; i < 12; ++i) split_slot(u, i, to);
+        };
+        // operands of the six part products in the order of mfma_parts
+        constexpr int kPartA[6] = {0, 1, 2, 0, 1, 0}, kPartB[6] = {2, 1, 0, 1, 0, 0};
+        v16f s;
+        v16f bias;                                 // what the logits of tile g + 1 start from: -inf for keys past the sequence's end
+        int row_1 = 0, row_2 = 0, row_3 = 0;       // first rows of tiles g + 1, g + 2, g + 3
+        int64_t off_k[2];                          // of tile g + 3
+        uint32_t edge = 0u;                        // bits 1, 2, 3: tiles g + 1, g + 2, g + 3 reach past the sequence's end
+        bool look = true;                          // something of the next lines' is due
+        auto past_end = [&](int row0) { return row0 + 32 > N ? 1u : 0u; };
+        auto bias_of = [&](int row0) {
+            int base = half * 4 + row0 - N;
+            asm volatile("" : "+v"(base));
+#pragma unroll
+            for (int j = 0; j < 16; ++j) bias[j] = (j >> 2) * 8 + (j & 3) + base >= 0 ? -INFINITY : 0.f;
+        };
+        if (stages > 0) {
+            const int row_0 = row_of(0);
+            key_offsets(row_0, off_k);
+            fetch_k(row_0, off_k);
+            fetch_v(row_0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) split_piece(u, 0u);
+            row_1 = row_of(1);
+            key_offsets(row_1, off_k);
+            fetch_k(row_1, off_k);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) split_piece(u, P::kStageBytes);
+            row_2 = row_of(2);
+            key_offsets(row_2, off_k);
+            fetch_k(row_2, off_k);
+            fetch_v(row_1);
+            row_3 = row_of(3);
+            edge = past_end(row_1) << 1 | past_end(row_2) << 2 | past_end(row_3) << 3;
+            __syncthreads();
+            bias_of(row_0);
+            s = bias;
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) {
+                v8bf kf[P::kIn];
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) read_k(k_addr[ks], i, kf);
+                s = mfma_parts<P::kIn, P::kIn>(kf, qf[ks], s);
+            }
+        }
+        for (int g = 0; g < stages; ++g) {
+            // the Q parts are only ever operands of matrix instructions, and O leaves them only where the reference moves: they
+            // live in accumulation registers
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks)
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) asm volatile("" : "+a"(qf[ks][i]));
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) asm volatile("" : "+a"(o[db]));
+            asm volatile("" : "+a"(bias));
+            const uint32_t buffer = (uint32_t)(g & 1) * P::kStageBytes, other = P::kStageBytes - buffer;
+            v8bf kf[2][P::kIn], vf[2][P::kIn];
+            {
+                const uint32_t at = at_buffer(k_addr[0], other);
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) read_k(at, i, kf[0]);
+            }
+            if (__builtin_expect(look, 0)) {        // wavefront-uniform, and rare: one branch for all that is, out of the loop's line
+                if ((g + 4) / kTPB - wbase >= 64) {
+                    wbase = (g + 4) / kTPB;
+                    win = it.list[min(wbase + lane, it.n_list - 1)];
+                    asm volatile("" : "+v"(win));   // (waited for here: behind the branch the wait would be for every load)
+                }
+                key_offsets(row_3, off_k);
+                if (edge & 2u) {                    // the loop's own loads took another row
+                    fetch_v(row_1);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(xv[e]));
+                }
+                bias_of(row_1);
+            }
+            // tile g + 2's values: row by row from v_at on; where a row would lie past the end, the sequence's first row instead
+            const int64_t whole = (int64_t)((edge >> 2) & 1u) - 1;      // all bits, or none: without a branch
+            uint64_t v_at = (uint64_t)(it.V + (whole & ((int64_t)(row_2 + v_row) * it.row_bytes)));
+            const int64_t v_step = whole & it.row_bytes;
+            v16f s_next = bias;
+            float p[16], quad[4], sum = 0.f;
+            union { uint32_t u[4]; v8bf v; } pf[2][3];
+            auto exp_of = [&](int e) { p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[e], kScaleLog2, -ref)); };
+            auto quad_of = [&](int c) { quad[c] = (p[4 * c] + p[4 * c + 1]) + (p[4 * c + 2] + p[4 * c + 3]); };
+            float left[2][2];
+            auto split_p = [&](int a, int k) {      // slot k (0 .. 5) of the split of pairs a and a + 1 of the probabilities, as in split_slot
+                auto w = [&](int j, int q) -> uint32_t& { return pf[j >> 2][q].u[j & 3]; };
+                if (k == 0) {
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) { left[0][h] = p[2 * a + h]; left[1][h] = p[2 * a + 2 + h]; }
+                    w(a, 0) = convert(left[0][0], left[0][1]);
+                    w(a + 1, 0) = convert(left[1][0], left[1][1]);
+                } else if (k == 1) {
+                    subtract(left[0], w(a, 0));
+                } else if (k == 2) {
+                    w(a, 1) = convert(left[0][0], left[0][1]);
+                    subtract(left[1], w(a + 1, 0));
+                } else if (k == 3) {
+                    w(a + 1, 1) = convert(left[1][0], left[1][1]);
+                    subtract(left[0], w(a, 1));
+                } else if (k == 4) {
+                    w(a, 2) = convert(left[0][0], left[0][1]);
+                    subtract(left[1], w(a + 1, 1));
+                } else {
+                    w(a + 1, 2) = convert(left[1][0], left[1][1]);
+                }
+            };
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) {
+                const uint32_t at = ks + 1 < kKS ? at_buffer(k_addr[ks + 1], other) : at_buffer(vt_addr[0], buffer);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const int slot = ks * 6 + i;
+                    s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks & 1][kPartA[i]], qf[ks][kPartB[i]], s_next, 0, 0, 0);
+                    if (i < P::kIn) {
+                        if (ks + 1 < kKS) read_k(at, i, kf[(ks + 1) & 1]);
+                        else read_v(at, 0, i, vf[0]);
+                    }
+                    if (slot < 16) exp_of(slot);
+                    else if (slot < 40) split_p(2 * ((slot - 16) / 6), (slot - 16) % 6);
+                    if (slot >= 40 && slot < 44) quad_of(slot - 40);
+                    if (slot == 44) sum = (quad[0] + quad[1]) + (quad[2] + quad[3]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            // The exponentials are taken against the reference as it stands; their sum, which joins the normaliser anyway, is also
+            // the guard: beyond 2^10 (or not a number, as before the first tile) the reference is moved to the row maximum and
+            // they are taken again, once.
+            if (__builtin_expect(__any(!(sum <= kSumLimit)), 0)) {
+                float mx = s[0];
+#pragma unroll
+                for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+                mx = max_across_halves(mx) * kScaleLog2;             // finite for finite inputs: the tile holds at least one key
+                const float ref_new = fmaxf(ref, mx);
+                const float alpha = __builtin_amdgcn_exp2f(ref - ref_new);      // first tile: exp2(-inf) = 0
+                ref = ref_new;
+                l_run *= alpha;
+                // O is rescaled where it lies (the compiler would move it out of the accumulation registers on every tile).  Its
+                // last matrix instruction is a phase of 48 others back; the wait states behind cover the one that reads it next.
+#pragma unroll
+                for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                    for (int j = 0; j < 16; ++j) {
+                        float x = o[db][j], t;
+                        asm volatile("v_accvgpr_read_b32 %1, %0\n\tv_mul_f32 %1, %1, %2\n\tv_accvgpr_write_b32 %0, %1"
+                                     : "+a"(x), "=&v"(t) : "v"(alpha));
+                        o[db][j] = x;
+                    }
+                asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+#pragma unroll
+                for (int e = 0; e < 16; ++e) exp_of(e);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) quad_of(c);
+#pragma unroll
+                for (int j = 0; j < 24; ++j) split_p(2 * (j / 6), j % 6);
+                sum = (quad[0] + quad[1]) + (quad[2] + quad[3]);
+            }
+            l_run += sum;
+            const v8bf pt[2][3] = {{pf[0][0].v, pf[0][1].v, pf[0][2].v}, {pf[1][0].v, pf[1][1].v, pf[1][2].v}};
+            __builtin_amdgcn_sched_barrier(0);
+            uint32_t at = at_buffer(vt_addr[0], buffer);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                if (c == 3) at = at_buffer(vt_addr[1], buffer);
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const int slot = c * 6 + i;
+                    o[c & 3] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[c & 1][kPartA[i]], pt[c >> 2][kPartB[i]], o[c & 3], 0, 0, 0);
+                    if (c + 1 < 8 && i < P::kIn) read_v(at, c + 1, i, vf[(c + 1) & 1]);
+                    // values of tile g + 1 first, keys of tile g + 2 behind them (past the last tile: rows that nobody reads)
+                    split_slot(slot < 24 ? 2 + slot / 12 : slot / 12 - 2, slot % 12, slot < 24 ? other : buffer);
+                    if (slot >= 24 && slot < 32) {
+                        load_v(v_at, slot - 24);
+                        if (slot < 31) v_at += slot == 27 ? 5 * v_step : v_step;
+                    }
+                    if (slot == 47) fetch_k(row_3, off_k);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            const int row_4 = row_of(g + 4);
+            const uint32_t was = edge;
+            edge = edge >> 1 | past_end(row_4) << 3;
+            row_1 = row_2;
+            row_2 = row_3;
+            row_3 = row_4;
+            look = ((was | edge) & 14u) != 0u || (g + 5) / kTPB - wbase >= 64;
+            s = s_next;
             __syncthreads();
         }
-    }
+    } else {
+    if (stages > 0) fetch(0);
     for (int g = 0; g < stages; ++g) {
         if constexpr (!BF16 && D == 128) {
             // the Q parts are only ever operands of matrix instructions: they live in accumulation registers
@@ -544,24 +835,17 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 #pragma unroll
             for (int db = 0; db < kDB; ++db) asm volatile("" : "+v"(o[db]));
         }
-        const bool ahead = P::kBuffers == 2 && g + 1 < stages;      // the next stage waits in registers
-        const uint32_t buffer = P::kBuffers == 2 ? (uint32_t)(g & 1) * P::kStageBytes : 0u;
-        if constexpr (P::kBuffers == 1) {
-            __syncthreads();                     // the stage before is consumed
-            store(0);
+        __syncthreads();                     // the stage before is consumed
+        store(0);
 #pragma unroll
-            for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
-            __syncthreads();
-            if (g + 1 < stages) fetch(g + 1);
-        }
+        for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
+        __syncthreads();
+        if (g + 1 < stages) fetch(g + 1);
 #pragma unroll
         for (int c = 0; c < P::kT; ++c) {
             const int valid = N - row0[c];                       // keys of the tile (only the sequence's end has fewer than 32)
-            const bool mine = g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0;      // wavefront-uniform
-            if constexpr (P::kBuffers == 1) {
-                if (!mine) continue;
-            }
-            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes) + buffer;
+            if (!(g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0)) continue;      // wavefront-uniform
+            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
             v16f s;
 #pragma unroll
             for (int j = 0; j < 16; ++j) s[j] = 0.f;
@@ -576,31 +860,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                     for (int i = 0; i < P::kIn; ++i) kf[(ks + 1) & 1][i] = *(lds_v8)(uintptr_t)(k_addr[ks + 1] + tile + i * kPart);
                 }
                 s = mfma_parts<P::kIn, P::kIn>(kf[ks & 1], qf[ks], s);
-                if constexpr (P::kBuffers == 2) {
-                    // A lone wavefront issues in order: what stands behind a run of matrix instructions waits for all but the
-                    // last of them.  So the split of one piece (some thirty instructions) goes between the six, five to each.
-                    // (Past the last stage the registers' old rows go into the buffer nobody reads any more.)
-                    static_assert(P::kBuffers == 1 || (P::kT == 1 && kPieces == kKS), "one piece per contraction step");
-                    store_piece(ks, (g + 1) & 1);
-#pragma unroll
-                    for (int i = 0; i < 6; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // matrix instruction
-                        __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);      // vector ALU
-                        if (i < 3) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
-                    }
-                    __builtin_amdgcn_sched_group_barrier(0x200, 3, 0);          // LDS writes
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            if constexpr (P::kBuffers == 2) {
-                if (ahead) {
-                    row0[c] = row0_next[c];
-                    if (g + 2 < stages) fetch(g + 2);
-                }
-                if (!mine) { __syncthreads(); continue; }
             }
             use_tile(s, valid, tile);
-            if constexpr (P::kBuffers == 2) __syncthreads();
         }
     }
     }
@@ -715,7 +976,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // d = 64, 7 at d = 128): bf16 d = 64, 17 550 tokens x 12 heads, block 64, 32 % of the blocks kept (0.30 TFLOP)
 // 18.43 -> 0.70 ms, bound by the vector ALU (some 150 instructions a tile, 16 of them exponentials, beside 16 matrix
 // instructions); fp32 d = 128, 6144 tokens x 8 heads, block 128, 48 % (0.073 TFLOP, 384 workgroups: a round and a half)
-// 10.21 -> 0.51 ms.  The packed split (one conversion per pair and part), the guard by the sum and the two buffers at
+// 10.21 -> 0.53 ms, and 0.53 -> 0.45 with the exponentials, both splits and their LDS traffic placed between the matrix
+// instructions (5000 cycles a tile for 96 of 33: what is left is the issue of 800 instructions by one wavefront).  The packed split (one conversion per pair and part), the guard by the sum and the two buffers at
 // d = 128 were worth 0.784 -> 0.70 and 0.617 -> 0.51.  Error against 64 bits (2-norm): fp32 d = 128 O 1.9e-6 -> 1.4e-6,
 // d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
 // Block size 32, fp32 d = 64, 2048 tokens x 2 heads, all blocks: 700 us with the vector ALU, 45 us with four wavefronts that
