@@ -410,6 +410,42 @@ __global__ __launch_bounds__(kThreads) void k_class_bits(const uint8_t* __restri
     }
 }
 
+// Reductions and scans over a wavefront in the vector ALU's own lane moves (a shuffle goes through the LDS, some 120 cycles
+// each, and a row's selection is a chain of them).  `none`: what lanes without a source read.
+template <int kCtrl, int kRows, typename T>
+__device__ __forceinline__ T moved(T none, T x) {
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_update_dpp((int)none, (int)x, kCtrl, kRows, 0xf, false);
+    } else {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)none, (int)(uint32_t)x, kCtrl, kRows, 0xf, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(none >> 32), (int)(uint32_t)(x >> 32), kCtrl, kRows, 0xf, false);
+        return (T)(((uint64_t)hi << 32) | lo);
+    }
+}
+// inclusive scan: rows of sixteen (row_shr 1, 2, 4, 8), then the rows' last lanes into the rows behind (row_bcast 15, 31)
+template <typename T, class Op>
+__device__ __forceinline__ T wave_scan(T x, T none, Op&& op) {
+    x = op(x, moved<0x111, 0xf>(none, x));
+    x = op(x, moved<0x112, 0xf>(none, x));
+    x = op(x, moved<0x114, 0xf>(none, x));
+    x = op(x, moved<0x118, 0xf>(none, x));
+    x = op(x, moved<0x142, 0xa>(none, x));
+    x = op(x, moved<0x143, 0xc>(none, x));
+    return x;
+}
+template <typename T>
+__device__ __forceinline__ T from_lane(T x, int lane) {                 // lane: the same in every lane
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_readlane((int)x, lane);
+    } else {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, lane), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), lane);
+        return (T)(((uint64_t)hi << 32) | lo);
+    }
+}
+template <typename T> __device__ __forceinline__ T wave_max(T x) { return from_lane(wave_scan(x, (T)0, [](T a, T b) { return a > b ? a : b; }), 63); }
+template <typename T> __device__ __forceinline__ T wave_min(T x) { return from_lane(wave_scan(x, (T)~(T)0, [](T a, T b) { return a < b ? a : b; }), 63); }
+template <typename T> __device__ __forceinline__ T wave_prefix(T x) { return wave_scan(x, (T)0, [](T a, T b) { return (T)(a + b); }); }      // inclusive sums
+
 // ascending unsigned == ascending float, -0 counted as +0
 __device__ __forceinline__ uint32_t score_image(float s) {
     const uint32_t u = __float_as_uint(s + 0.0f);
@@ -521,9 +557,10 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 // looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
 // bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) is decided by
 // the literal chain, in this wave.
-// LDS per wave: keys[cap] u64 | mass[cap] f64 | bins[256] u64, cap a power of two >= the largest selectable count of a row.
+// LDS per wave: keys[cap] u64 | mass[cap] f64 over bins[256] u64 (the chain comes when the bins are done with), cap a power of two
+// >= the largest selectable count of a row.  A quarter more rows in flight than with bins of their own, at 256 keys.
 constexpr int kBins = 256, kMaxTaken = 8;      // keys taken one by one from a bin
-__host__ __device__ inline size_t select_mass_lds_bytes(int cap) { return (size_t)cap * 16 + kBins * 8; }
+__host__ __device__ inline size_t select_mass_lds_bytes(int cap) { return (size_t)cap * 8 + (cap > kBins ? (size_t)cap * 8 : kBins * 8); }
 
 __device__ __forceinline__ uint32_t key_image(uint64_t c) { return (uint32_t)(c >> 31); }
 // The rule taken literally by one wave: the n keys (complemented, in LDS, room for a power of two of them) are sorted, the
@@ -610,14 +647,9 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
         wave_lds_fence();
         const U part[4] = {bins[lane * 4], bins[lane * 4 + 1], bins[lane * 4 + 2], bins[lane * 4 + 3]};
         const U own = part[0] + part[1] + part[2] + part[3];
-        U incl = own;
-        for (int off = 1; off < 64; off <<= 1) {
-            const U t = __shfl_up(incl, off);
-            if (lane >= off) incl += t;
-        }
-        incl += prefix;
+        const U incl = prefix + wave_prefix(own);
         if (level == 0) {
-            total = (double)__shfl(incl, 63);
+            total = (double)from_lane(incl, 63);
             target = tau * total;
         }
         const uint64_t reach = __ballot((double)incl >= target);      // (never empty: tau <= 1)
@@ -631,8 +663,8 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
                 if ((double)(before + part[e]) >= target) found = true;
                 else { before += part[e]; ++bin; }
             }
-        bin = __shfl(bin, l);
-        prefix = prev = __shfl(before, l);
+        bin = from_lane(bin, l);
+        prefix = prev = from_lane(before, l);
         uint64_t best = 0ull, least = ~0ull;          // of the bin, of what is not taken yet
         for (int taken = 0; taken < kMaxTaken + (kLevels > 1) && !crossed; ++taken) {
             best = 0ull;
@@ -645,10 +677,7 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
                     if constexpr (kLevels > 1) least = c < least ? c : least;
                 }
             }
-            for (int off = 32; off > 0; off >>= 1) {
-                const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)best, off);
-                best = t > best ? t : best;
-            }
+            best = wave_max(best);
             if (best == 0ull || taken == kMaxTaken) break;
             last = best;
             prev = prefix;
@@ -656,10 +685,7 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
             crossed = (double)prefix >= target;
         }
         if (kLevels == 1 || crossed || best == 0ull) break;
-        for (int off = 32; off > 0; off >>= 1) {
-            const uint64_t t = (uint64_t)__shfl_xor((unsigned long long)least, off);
-            least = t < least ? t : least;
-        }
+        least = wave_min(least);
         if (key_image(least) == key_image(best)) {
             // equal masses, in key-block order, which is the order of the packed keys
             const U m = mass_of(best);
@@ -675,7 +701,7 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
                 if (at < j) continue;
                 const uint64_t mine = __ballot(c >= least && c <= best &&
                                                (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(equal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)equal, 0u)) == nth - 1);
-                last = (uint64_t)__shfl((unsigned long long)c, __ffsll((unsigned long long)mine) - 1);
+                last = from_lane(c, __ffsll((unsigned long long)mine) - 1);
                 prev = prefix + (U)(j - 1) * m;
                 prefix = prev + m;
                 crossed = (double)prefix >= target && (double)prev < target;
@@ -709,7 +735,7 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
     unsigned char* mine = smem + (size_t)wave * select_mass_lds_bytes(cap);
     uint64_t* keys = reinterpret_cast<uint64_t*>(mine);
     double* mass = reinterpret_cast<double*>(mine + (size_t)cap * 8);
-    unsigned char* bins = mine + (size_t)cap * 16;
+    unsigned char* bins = mine + (size_t)cap * 8;
     WaveRow<kSlots> r;
     load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
     uint64_t threshold = ~0ull;
@@ -731,10 +757,8 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
             image_max = max(image_max, v);
             image_min = min(image_min, v);
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            image_max = max(image_max, (uint32_t)__shfl_xor((int)image_max, off));
-            image_min = min(image_min, (uint32_t)__shfl_xor((int)image_min, off));
-        }
+        image_max = wave_max(image_max);
+        image_min = wave_min(image_min);
         const float top = image_score(image_max), range = top - image_score(image_min);
         const float bin_scale = (range > 0.f && range < INFINITY) ? 255.0f / range : 0.f;
         const int log_n = 32 - __clz(n);                    // n < 2^log_n: the sums of n masses below fit their types
@@ -876,8 +900,8 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
 }
 
 // grid: (Sb, masks, B)
-// rowptr of every mask where the rows do not add up the earlier counts themselves (launch_emit): the exclusive prefix of its
-// rows' kept counts, one workgroup per mask.  grid: (masks, B).
+// rowptr of every mask whose rows are longer than 2048 key blocks: the exclusive prefix of its rows' kept counts, one workgroup
+// per mask.  grid: (masks, B).
 __global__ __launch_bounds__(kThreads) void k_row_offsets(const int32_t* __restrict__ counts, int masks, int Sb, int shared,
                                                           int32_t* __restrict__ rowptr, int64_t* __restrict__ nnz) {
     __shared__ long long s_wave[kWaves];
@@ -1046,45 +1070,12 @@ hipError_t launch_select_zscore(const uint8_t* class_map, const float* scores, i
     return hipGetLastError();
 }
 
-// Column lists of rows of at most 2048 key blocks (64 bitmap words): one wave per row, no LDS and no barrier; four rows per
-// workgroup.  A lane loads one bitmap word; the wave then walks the row 64 key blocks at a time: the two words of that
-// stretch are read back as a wave-uniform lane mask, a lane whose bit is set stores its key block at the running offset plus
-// the number of set bits below it (v_mbcnt), so that each store instruction writes one contiguous run.
-// kOffsets: the row offsets are made here too: the wave adds the counts of the mask's earlier rows itself (at most 32
-// coalesced reads per lane out of L2).  grid: ceil(B * masks * Sb / 4).
-template <bool kOffsets>
-__global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts,
-                                                        int64_t rows_total, int Sb, int shared, int32_t* __restrict__ rowptr,
-                                                        int32_t* __restrict__ colidx, int64_t capacity, int64_t* __restrict__ nnz) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;      // (mask_id, qb) flattened
-    if (r >= rows_total) return;
-    const int64_t mask_id = r / Sb;
-    const int qb = (int)(r - mask_id * Sb);
-    const int64_t src = shared ? 0 : mask_id * Sb;                         // shared: one selection serves every (b, m)
-    const int64_t row = src + qb;
-    const int words = (Sb + 31) / 32;
-    const uint32_t wv = (lane < words) ? keepbits[row * words + lane] : 0u;
-    int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
-    int32_t* rp = rowptr + mask_id * (Sb + 1);
-    if constexpr (kOffsets) {
-#pragma unroll 4
-        for (int i = lane; i < qb; i += 64) before += counts[src + i];
-        for (int off = 32; off > 0; off >>= 1) before += __shfl_xor(before, off);
-        if (lane == 0) {
-            rp[qb] = before;
-            if (qb == Sb - 1) {
-                const int all = before + counts[row];
-                rp[Sb] = all;
-                nnz[mask_id] = all;
-            }
-        }
-    } else {
-        before = rp[qb];
-    }
-    long long pos = before;
-    int32_t* out = colidx + mask_id * capacity;
-    const int stretches = (Sb + 63) / 64;
+// Column lists of rows of at most 2048 key blocks (64 bitmap words).  A lane loads one bitmap word; the wave then walks the row 64
+// key blocks at a time: the two words of that stretch are read back as a wave-uniform lane mask, a lane whose bit is set stores
+// its key block at the running offset plus the number of set bits below it (v_mbcnt), so that each store instruction writes
+// one contiguous run.
+__device__ __forceinline__ void emit_row(uint32_t wv, int Sb, long long pos, int32_t* __restrict__ out, int64_t capacity) {
+    const int lane = lane_id(), stretches = (Sb + 63) / 64;
     for (int i = 0; i < stretches; ++i) {                                  // wave-uniform
         const uint32_t lo = __builtin_amdgcn_readlane(wv, 2 * i), hi = __builtin_amdgcn_readlane(wv, 2 * i + 1);
         const uint32_t mine = (lane < 32) ? (lo >> lane) : (hi >> (lane - 32));
@@ -1094,23 +1085,95 @@ __global__ __launch_bounds__(kThreads) void k_emit_wave(const uint32_t* __restri
     }
 }
 
+// One wave per row and workgroup: calls of few rows, which spread over as many CUs as there are rows.  The wave adds up the
+// counts of the mask's earlier rows itself (at most 32 coalesced reads per lane out of L2).  grid: B * masks * Sb.
+__global__ __launch_bounds__(64) void k_emit_wave(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts, int Sb,
+                                                  int shared, int32_t* __restrict__ rowptr, int32_t* __restrict__ colidx,
+                                                  int64_t capacity, int64_t* __restrict__ nnz) {
+    const int lane = lane_id();
+    const int64_t r = blockIdx.x, mask_id = r / Sb;                        // (mask_id, qb) flattened
+    const int qb = (int)(r - mask_id * Sb);
+    const int64_t src = shared ? 0 : mask_id * Sb;                         // shared: one selection serves every (b, m)
+    const int words = (Sb + 31) / 32;
+    const uint32_t wv = (lane < words) ? keepbits[(src + qb) * words + lane] : 0u;
+    int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
+    int32_t* rp = rowptr + mask_id * (Sb + 1);
+#pragma unroll 4
+    for (int i = lane; i < qb; i += 64) before += counts[src + i];
+    before = from_lane(wave_prefix(before), 63);
+    if (lane == 0) {
+        rp[qb] = before;
+        if (qb == Sb - 1) {
+            const int all = before + counts[src + qb];
+            rp[Sb] = all;
+            nnz[mask_id] = all;
+        }
+    }
+    emit_row(wv, Sb, before, colidx + mask_id * capacity, capacity);
+}
+
+// Four rows of one mask per workgroup, a wave each, whose bitmaps are on their way while the workgroup adds up the counts of the
+// mask's earlier rows, once for all four.  (Each wave for itself: 13 us of launch at 40 masks of 591 rows where this takes 11;
+// 8 masks of 2000 rows, whole call, 148 -> 144.  Eight rows: 1 us less at 40 x 591, up to 0.3 us more at 4 x 591; sixteen: 2 more.)
+// grid: B * masks * ceil(Sb / 4).
+constexpr int kEmitRows = 4;
+__global__ __launch_bounds__(kThreads) void k_emit_rows(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts, int Sb,
+                                                        int shared, int32_t* __restrict__ rowptr, int32_t* __restrict__ colidx,
+                                                        int64_t capacity, int64_t* __restrict__ nnz) {
+    __shared__ int s_part[kWaves];
+    constexpr int kOwn = kEmitRows / kWaves;
+    const int tiles = (Sb + kEmitRows - 1) / kEmitRows;
+    const int64_t mask_id = blockIdx.x / tiles;
+    const int q0 = (int)(blockIdx.x - mask_id * tiles) * kEmitRows;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t src = shared ? 0 : mask_id * Sb;
+    const int words = (Sb + 31) / 32;
+    uint32_t wv[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int qb = q0 + wave * kOwn + i;
+        wv[i] = (lane < words && qb < Sb) ? keepbits[(src + qb) * words + lane] : 0u;
+    }
+    const int own = (lane < kEmitRows && q0 + lane < Sb) ? counts[src + q0 + lane] : 0;
+    int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
+    int c[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) c[e] = tid + e * kThreads < q0 ? counts[src + tid + e * kThreads] : 0;      // q0 < 2048
+#pragma unroll
+    for (int e = 0; e < 8; ++e) before += c[e];
+    before = wave_prefix(before);
+    if (lane == 63) s_part[wave] = before;
+    __syncthreads();
+    before = s_part[0] + s_part[1] + s_part[2] + s_part[3];
+    const int incl = before + wave_prefix(own);                            // lane r: with the counts of rows q0 .. q0 + r
+    int32_t* rp = rowptr + mask_id * (Sb + 1);
+    if (wave == 0 && lane < kEmitRows && q0 + lane < Sb) {
+        rp[q0 + lane] = incl - own;
+        if (q0 + lane == Sb - 1) {
+            rp[Sb] = incl;
+            nnz[mask_id] = incl;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int r = wave * kOwn + i;
+        if (q0 + r < Sb) emit_row(wv[i], Sb, from_lane(incl - own, r), colidx + mask_id * capacity, capacity);
+    }
+}
+static_assert(8 * kThreads >= 64 * 32, "the earlier rows of a mask");
+
 hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, int masks, int Sb, bool shared,
                        int32_t* rowptr, int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s) {
     const int64_t rows_total = (int64_t)B * masks * Sb;
-    // A launch of its own for the offsets costs about 2.3 us; adding up the earlier rows' counts costs some 0.06 us per 1000
-    // rows, for the dependent reads and the reduction, and as much again per 2000 counts of a row, for the reads: the two meet
-    // near 2^26 of this product.  Whole calls of the uniform rule, one launch against two: 9.3 / 11.0 us at one mask of 591
-    // rows, 15.4 / 15.3 at 40, 30.9 / 27.8 at 96; 14.0 / 17.7 at 4 masks of 2048 rows, 94 / 88 at 40.
-    const bool one_launch = Sb <= 64 * 32 && rows_total * (2048 + Sb) <= (int64_t)1 << 26;
-    if (!one_launch)
+    if (Sb > 64 * 32) {
         hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
-    if (Sb <= 64 * 32) {
-        const int waves = rows_total >= kWaveSelectPackRows ? kWaves : 1;
-        hipLaunchKernelGGL(one_launch ? k_emit_wave<true> : k_emit_wave<false>, dim3((unsigned)((rows_total + waves - 1) / waves)),
-                           dim3(64 * waves), 0, s, keepbits, counts, rows_total, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
-    } else {
         hipLaunchKernelGGL(k_emit, dim3(Sb, masks, B), dim3(kThreads), 0, s, keepbits, masks, Sb, shared ? 1 : 0, rowptr,
                            colidx, capacity);
+    } else if (rows_total >= kWaveSelectPackRows) {
+        hipLaunchKernelGGL(k_emit_rows, dim3((unsigned)((int64_t)B * masks * ((Sb + kEmitRows - 1) / kEmitRows))), dim3(kThreads), 0, s, keepbits,
+                           counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
+    } else {
+        hipLaunchKernelGGL(k_emit_wave, dim3((unsigned)rows_total), dim3(64), 0, s, keepbits, counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
     }
     return hipGetLastError();
 }
