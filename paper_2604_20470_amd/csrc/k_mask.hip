@@ -117,10 +117,11 @@ __device__ __forceinline__ uint64_t make_sample_key(uint32_t seed, int qb, int k
 }
 
 // keep bitmask of one row -> global memory, and the row's count
+template <int kT = kThreads>
 __device__ __forceinline__ void store_row(const uint32_t* keep, int words, int64_t row, uint32_t* __restrict__ keepbits,
                                           int32_t* __restrict__ counts, int* s_cnt) {
     int c = 0;
-    for (int i = threadIdx.x; i < words; i += kThreads) {
+    for (int i = threadIdx.x; i < words; i += kT) {
         const uint32_t wv = keep[i];
         keepbits[row * words + i] = wv;
         c += __popc(wv);
@@ -809,7 +810,8 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
 // only when the estimate lies within 2^-50 |tau| of tau is the division itself evaluated.
 constexpr uint32_t kNoMember = 0x7fc0dead;
 
-__global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __restrict__ class_map,
+template <int kT>
+__global__ __launch_bounds__(kT) void k_select_zscore(const uint8_t* __restrict__ class_map,
                                                             const float* __restrict__ scores, int masks, int Sb,
                                                             int maxlen, SelectArgs a, uint32_t* __restrict__ keepbits,
                                                             int32_t* __restrict__ counts) {
@@ -824,13 +826,13 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
     const int64_t row = ((int64_t)b * masks + m) * Sb + qb;
     const float* srow = scores + row * Sb;
     const uint8_t* crow = class_map + (int64_t)qb * Sb;
-    for (int i = tid; i < words; i += kThreads) keep[i] = 0u;
+    for (int i = tid; i < words; i += kT) keep[i] = 0u;
     if (tid == 0) s_cnt = 0;
-    for (int i = tid; i < maxlen * a.Nf; i += kThreads) tile[i] = kNoMember;
+    for (int i = tid; i < maxlen * a.Nf; i += kT) tile[i] = kNoMember;
     __syncthreads();
     const int r0 = qb * a.Bs, r1 = min(a.N, r0 + a.Bs);
     const int i0 = r0 / a.Nt, i1 = (r1 - 1) / a.Nt;
-    for (int kb = tid; kb < Sb; kb += kThreads) {
+    for (int kb = tid; kb < Sb; kb += kT) {
         const int c = crow[kb];
         if (c == 3) atomicOr(&keep[kb >> 5], 1u << (kb & 31));
         if (c == 1 || c == 2) {
@@ -843,7 +845,7 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
         }
     }
     __syncthreads();
-    for (int f = tid; f < a.Nf; f += kThreads) {
+    for (int f = tid; f < a.Nf; f += kT) {
         const bool after = f > i1 + 1, before = f < i0 - 1;                      // gaps 0 and 1 are the never-pruned zone
         if (!after && !before) continue;
         const int gap = after ? f - i1 : i0 - f;
@@ -896,7 +898,7 @@ __global__ __launch_bounds__(kThreads) void k_select_zscore(const uint8_t* __res
         if (!any) atomicOr(&keep[(kb_lo + best_p) >> 5], 1u << ((kb_lo + best_p) & 31));
     }
     __syncthreads();
-    store_row(keep, words, row, keepbits, counts, &s_cnt);
+    store_row<kT>(keep, words, row, keepbits, counts, &s_cnt);
 }
 
 // grid: (Sb, masks, B)
@@ -1059,13 +1061,19 @@ hipError_t launch_select_zscore(const uint8_t* class_map, const float* scores, i
                                 const SelectArgs& a, uint32_t* keepbits, int32_t* counts, hipStream_t s) {
     const size_t lds = select_zscore_lds_bytes(Sb, a.Nt, a.Nf, a.Bs);
     if (lds > kSelectZscoreMaxLds) return hipErrorInvalidValue;      // the host layer checks this before calling
+    // In the serial part as many lanes work as there are frames, so where many rows wait one wave per row keeps four times as
+    // many of them in flight, if their tiles let them: whole calls, four waves a row / one, 40 masks of 591 rows 131 / 88 us, 12 of
+    // 370 28.6 / 22.3, 8 of 700 (4 frames) 164 / 105, 3 of 929 26.6 / 22.4, 2 of 2000 (tiles of 5.5 KB) 58.4 / 56.5.
+    const int64_t rows_total = (int64_t)B * masks * Sb;
+    const bool one_wave = rows_total >= kWaveSelectPackRows && lds <= 8 * 1024;
+    auto kern = one_wave ? k_select_zscore<64> : k_select_zscore<kThreads>;
     if (lds > 64 * 1024) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_select_zscore),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
     const int maxlen = (a.Nt + a.Bs - 1) / a.Bs + 1;          // key blocks that can touch one frame
-    hipLaunchKernelGGL(k_select_zscore, dim3(Sb, masks, B), dim3(kThreads), lds, s, class_map, scores, masks, Sb, maxlen,
+    hipLaunchKernelGGL(kern, dim3(Sb, masks, B), dim3(one_wave ? 64 : kThreads), lds, s, class_map, scores, masks, Sb, maxlen,
                        a, keepbits, counts);
     return hipGetLastError();
 }
