@@ -181,6 +181,59 @@ __global__ __launch_bounds__(256) void k_scores_mfma(const float* __restrict__ p
         }
 }
 
+// The same for short rows, where 64 x 64 tiles are a handful of workgroups that wait for eight chunks one after the other: a
+// wavefront owns 16 x 16 outputs and takes 128 channels of its rows at a time straight from memory to registers, the next 128 on
+// their way meanwhile.  v_mfma_f32_16x16x4_f32; a lane feeds one of its four consecutive channels to each of four
+// instructions with sums of their own (the order of the contraction is permuted alike for both operands).
+// grid: (ceil(Sb / 16), ceil(Sb / 16), B * masks).
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <int D>
+__global__ __launch_bounds__(64) void k_scores_short(const float* __restrict__ pooled, int B, int Hs, int masks, int heads_per_mask, int Sb,
+                                                     float scale, float* __restrict__ scores) {
+    constexpr int kVec = D / 16;
+    const int bm = blockIdx.z, b = bm / masks, h0 = masks == 1 ? 0 : bm % masks;
+    const int lane = threadIdx.x, r16 = lane & 15, quarter = lane >> 4;
+    const int q0 = blockIdx.y * 16, k0 = blockIdx.x * 16;
+    const int64_t plane = (int64_t)Sb * D;
+    const float* qb = pooled + ((int64_t)b * Hs + h0) * plane + (int64_t)min(q0 + r16, Sb - 1) * D + 4 * quarter;
+    const float* kb = pooled + (((int64_t)B + b) * Hs + h0) * plane + (int64_t)min(k0 + r16, Sb - 1) * D + 4 * quarter;
+    v4f a[2][kVec], c[2][kVec], acc[4];
+    auto fetch = [&](int hh, int into) {
+#pragma unroll
+        for (int j = 0; j < kVec; ++j) {
+            a[into][j] = *reinterpret_cast<const v4f*>(qb + hh * plane + 16 * j);
+            c[into][j] = *reinterpret_cast<const v4f*>(kb + hh * plane + 16 * j);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] = v4f{0.f, 0.f, 0.f, 0.f};
+    auto multiply = [&](int from) {
+#pragma unroll
+        for (int j = 0; j < kVec; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[from][j][e], c[from][j][e], acc[e], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(0, 0);
+    int hh = 0;
+    for (; hh + 1 < heads_per_mask; hh += 2) {
+        fetch(hh + 1, 1);
+        multiply(0);
+        if (hh + 2 < heads_per_mask) fetch(hh + 2, 0);
+        multiply(1);
+    }
+    if (hh < heads_per_mask) multiply(0);
+    const v4f sum = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    // element i: row 4 * quarter + i, column r16
+    float* out = scores + (int64_t)bm * Sb * Sb;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int q = q0 + 4 * quarter + i;
+        if (q < Sb && k0 + r16 < Sb) out[(int64_t)q * Sb + k0 + r16] = sum[i] * scale;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_pool(const void* Q, const void* K, bool bf16, const TensorDesc& td, int Hs, int Bs, int Sb,
@@ -202,7 +255,14 @@ hipError_t launch_scores(const float* pooled, int B, int Hs, int masks, int head
     const int t128 = (Sb + 127) / 128, t64 = (Sb + 63) / 64;
     // 128 x 128 tiles pay once a row holds thousands of blocks (at 8250 blocks 0.44 against 0.47 ms); below, their
     // rounding up of Sb and the short contraction loop cost more than they save (591 blocks x 40 heads: 66 against 47 us)
-    if (Sb >= 4096 && (int64_t)t128 * t128 * B * masks >= 512)
+    // One wavefront per 16 x 16 outputs up to eight a compute unit: whole stage, 64 x 64 tiles / these, 371 blocks x 2 heads 13.3 /
+    // 10.3 us, 591 x 2 (1369 wavefronts) 21.7 / 20.7, 96 blocks x 8 heads of one mask 32 / 12, 40 masks of 75 (1000) 34.8 / 33.7;
+    // 929 x 2 (3481) 28 / 35, 24 masks of 371 (13 824) 58 / 71.  (10.3 us is two launches from the host.)
+    const int t16 = (Sb + 15) / 16;
+    if ((int64_t)t16 * t16 * B * masks <= 2048)
+        hipLaunchKernelGGL(d == 64 ? k_scores_short<64> : k_scores_short<128>, dim3(t16, t16, B * masks), dim3(64), 0, s, pooled, B, Hs, masks,
+                           heads_per_mask, Sb, scale, scores);
+    else if (Sb >= 4096 && (int64_t)t128 * t128 * B * masks >= 512)
         hipLaunchKernelGGL(k_scores_mfma<2>, dim3(t128, t128, B * masks), dim3(256), 0, s, pooled, B, Hs, masks,
                            heads_per_mask, Sb, d, scale, scores);
     else
