@@ -453,6 +453,10 @@ dr_status dr_build_mask(dr_ctx* ctx, const dr_shape* shape, int32_t mode, double
         for (int t = 0; t < shape->Nf; ++t)
             if (((tab.flags[t] >> 1) & 3) == DR_CLASS_NEAR) a.near_mask[t >> 6] |= 1ull << (t & 63);
     }
+    if (mask_short_supported(mode, shape->B, masks, Sb)) {
+        DR_HIP(ctx, launch_mask_short(ctx->class_bits, scores, shape->B, masks, Sb, a, rowptr, colidx, colidx_capacity, nnz, s));
+        return DR_OK;
+    }
     if (mode == DR_MODE_ZSCORE_THRESHOLD)
         DR_HIP(ctx, launch_select_zscore(ctx->class_map, scores, shape->B, masks, Sb, a, ctx->keepbits, ctx->counts, s));
     else

@@ -517,27 +517,18 @@ __device__ __forceinline__ void store_wave_row(const WaveRow<kSlots>& r, uint64_
     }
     if (lane == 0) counts[row] = kept;
 }
+// The thresholds of the static rules: NEAR keys that reach c_near are kept, FAR keys that reach c_far (rule with two ratios).
+// list: 64 words of LDS that belong to this wave.
 template <int kSlots>
-__global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __restrict__ class_bits,
-                                                          const float* __restrict__ scores, int64_t rows_total, int Sb,
-                                                          SelectArgs a, uint32_t* __restrict__ keepbits,
-                                                          int32_t* __restrict__ counts) {
-    __shared__ uint64_t s_list[kWaves][64];                       // a wave's short list of candidate keys
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;   // the same in every lane, and known to be
-    if (row >= rows_total) return;
-    const int qb = (int)(row % Sb);
+__device__ __forceinline__ void select_wave_row(const WaveRow<kSlots>& r, int Sb, const SelectArgs& a, uint64_t* list, uint64_t* c_near, uint64_t* c_far) {
     int index_bits = 0;
     while ((1 << index_bits) < Sb) ++index_bits;
-    WaveRow<kSlots> r;
-    load_wave_row<kSlots>(class_bits, scores, row, qb, Sb, a, r);
     WaveThreshold t_near{0u, 0u}, t_far{0u, 0u};
     int k_near = 0, k_far = 0;
     if (r.n > 0) {
         const int n_near = r.n - r.n_far;
         k_near = keep_count(n_near, a.ratio);
         k_far = a.two_ratio ? keep_count(r.n_far, a.ratio_far) : 0;
-        uint64_t* list = s_list[wave];
         if (k_near > 0 && !(k_near <= kShortListMaxK && kth_smallest_wave_short_list<kSlots>(r.w, k_near, index_bits, list, &t_near)))
             t_near = kth_smallest_wave<kSlots>(r.w, k_near, index_bits);
         const int k_all = n_near + k_far;
@@ -547,8 +538,22 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
     // a NEAR key's complement has bit 63 set and so has every threshold of the NEAR ranking: no FAR key reaches it;
     // the FAR ranking's threshold is reached by every NEAR key and by the k_far best FAR keys.  With nothing to rank
     // the threshold is beyond every key.
-    const uint64_t c_near = k_near > 0 ? (((uint64_t)t_near.hi << 32) | t_near.lo) : ~0ull;
-    const uint64_t c_far = k_far > 0 ? (((uint64_t)t_far.hi << 32) | t_far.lo) : ~0ull;
+    *c_near = k_near > 0 ? (((uint64_t)t_near.hi << 32) | t_near.lo) : ~0ull;
+    *c_far = k_far > 0 ? (((uint64_t)t_far.hi << 32) | t_far.lo) : ~0ull;
+}
+template <int kSlots>
+__global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __restrict__ class_bits,
+                                                          const float* __restrict__ scores, int64_t rows_total, int Sb,
+                                                          SelectArgs a, uint32_t* __restrict__ keepbits,
+                                                          int32_t* __restrict__ counts) {
+    __shared__ uint64_t s_list[kWaves][64];                       // a wave's short list of candidate keys
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;   // the same in every lane, and known to be
+    if (row >= rows_total) return;
+    WaveRow<kSlots> r;
+    load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
+    uint64_t c_near, c_far;
+    select_wave_row<kSlots>(r, Sb, a, s_list[wave], &c_near, &c_far);
     store_wave_row<kSlots>(r, c_near, c_far, a.two_ratio != 0, row, Sb, keepbits, counts);
 }
 
@@ -721,24 +726,14 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
     return (double)prev + E < tau * (total - E) && (double)prefix - E >= tau * (total + E) ? Crossing::kFound : Crossing::kTooClose;
 }
 
-// A row that the bins do not decide costs its wave a sort and the chain, 25 us at 1000 keys.  Among many rows that is shared out
-// (kLevels = 1); a launch of few rows waits for the slowest, and there the crossing bin is binned again twice (kLevels = 3,
-// 28 more registers): one mask of 1013 rows, smooth scores, 45 -> 24 us (34 us with the workgroup-wide sort of k_select), ties
-// 45 -> 24..35; 40 masks of 591 rows took 49 us with one level, 59 with three.
+// The threshold of the cumulative-mass rule: every selectable key that reaches it is kept.  `mine`: select_mass_lds_bytes(cap) of LDS
+// that belong to this wave.
 template <int kSlots, int kLevels>
-__global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __restrict__ class_bits,
-                                                          const float* __restrict__ scores, int64_t rows_total, int Sb, int cap,
-                                                          SelectArgs a, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
-    extern __shared__ unsigned char smem[];
-    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
-    if (row >= rows_total) return;
-    unsigned char* mine = smem + (size_t)wave * select_mass_lds_bytes(cap);
+__device__ __forceinline__ uint64_t select_mass_row(const WaveRow<kSlots>& r, const SelectArgs& a, unsigned char* mine, int cap) {
+    const int lane = lane_id();
     uint64_t* keys = reinterpret_cast<uint64_t*>(mine);
     double* mass = reinterpret_cast<double*>(mine + (size_t)cap * 8);
     unsigned char* bins = mine + (size_t)cap * 8;
-    WaveRow<kSlots> r;
-    load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
     uint64_t threshold = ~0ull;
     const int n = r.n;
     if (n > 0) {
@@ -790,7 +785,78 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
         else if (flat) threshold = keys[max(1, (int)ceil(a.tau * (double)n)) - 1];      // (packed in that order)
         else if (got != Crossing::kFound) threshold = mass_threshold_by_chain(n, top, a.tau, keys, mass);
     }
+    return threshold;
+}
+
+// A row that the bins do not decide costs its wave a sort and the chain, 25 us at 1000 keys.  Among many rows that is shared out
+// (kLevels = 1); a launch of few rows waits for the slowest, and there the crossing bin is binned again twice (kLevels = 3,
+// 28 more registers): one mask of 1013 rows, smooth scores, 45 -> 24 us (34 us with the workgroup-wide sort of k_select), ties
+// 45 -> 24..35; 40 masks of 591 rows took 49 us with one level, 59 with three.
+template <int kSlots, int kLevels>
+__global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __restrict__ class_bits,
+                                                          const float* __restrict__ scores, int64_t rows_total, int Sb, int cap,
+                                                          SelectArgs a, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
+    extern __shared__ unsigned char smem[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
+    if (row >= rows_total) return;
+    WaveRow<kSlots> r;
+    load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
+    const uint64_t threshold = select_mass_row<kSlots, kLevels>(r, a, smem + (size_t)wave * select_mass_lds_bytes(cap), cap);
     store_wave_row<kSlots>(r, threshold, ~0ull, false, row, Sb, keepbits, counts);
+}
+
+// The whole mask in one launch where it has at most 32 rows of at most 32 key blocks (a row is one lane mask): a workgroup of
+// sixteen waves takes a mask, a wave every sixteenth row; the counts of the rows meet in LDS and each wave writes its own out.
+// Selection and emission apart are two launches: 11.3 us a call from the host, this 8.3 (1 to 256 masks of 9 to 32 rows); a
+// whole call on 256 tokens 27.9 / 25.0.  With 48 rows, three to a wave, the mask alone still gains (11.2 / 8.5), but a call that
+// the GPU bounds loses 1.4 us (6144 tokens x 8 heads 85.0 / 86.5), and 40 masks of 64 rows 10.4 / 11.2 by cumulative mass.
+// grid: B * masks.  LDS: 16 x select_mass_lds_bytes(cap), or 16 x 64 keys.
+constexpr int kShortMask = 32, kShortWaves = 16;
+template <bool kMass>
+__global__ __launch_bounds__(64 * kShortWaves) void k_mask_short(const uint64_t* __restrict__ class_bits, const float* __restrict__ scores, int Sb,
+                                                                 int cap, SelectArgs a, int32_t* __restrict__ rowptr, int32_t* __restrict__ colidx,
+                                                                 int64_t capacity, int64_t* __restrict__ nnz) {
+    extern __shared__ unsigned char smem[];
+    __shared__ int s_count[kShortMask];
+    constexpr int kSlots = 2, kOwn = kShortMask / kShortWaves;
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t mask_id = blockIdx.x;
+    uint64_t kept[kOwn];
+    if (threadIdx.x < kShortMask) s_count[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int qb = i * kShortWaves + wave;
+        kept[i] = 0ull;
+        if (qb >= Sb) continue;                                            // the same in every lane
+        WaveRow<kSlots> r;
+        load_wave_row<kSlots>(class_bits, scores, mask_id * Sb + qb, qb, Sb, a, r);
+        uint64_t c_near, c_far = ~0ull;
+        if constexpr (kMass) c_near = select_mass_row<kSlots, 3>(r, a, smem + (size_t)wave * select_mass_lds_bytes(cap), cap);
+        else select_wave_row<kSlots>(r, Sb, a, reinterpret_cast<uint64_t*>(smem) + wave * 64, &c_near, &c_far);
+        kept[i] = r.m_forced[0] | __ballot(r.w.c[0] >= c_near);
+        if (!kMass && a.two_ratio) kept[i] |= __ballot(r.w.c[0] >= c_far) & r.m_far[0];
+        if (lane == 0) s_count[qb] = __popcll(kept[i]);
+    }
+    __syncthreads();
+    const int own = lane < kShortMask ? s_count[lane] : 0, incl = wave_prefix(own);
+    if (wave == 0) {
+        int32_t* rp = rowptr + mask_id * (Sb + 1);
+        if (lane < Sb) rp[lane] = incl - own;
+        if (lane == Sb - 1) {
+            rp[Sb] = incl;
+            nnz[mask_id] = incl;
+        }
+    }
+    int32_t* out = colidx + mask_id * capacity;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int qb = i * kShortWaves + wave;
+        if (qb >= Sb) continue;
+        const int64_t p = from_lane(incl - own, qb) + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept[i], 0u));
+        if (((kept[i] >> lane) & 1ull) && p < capacity) out[p] = lane;
+    }
 }
 
 // grid: (Sb, masks, B).  A candidate set of the row is identified by the frame f that realises its gap: the key
@@ -1054,6 +1120,18 @@ hipError_t launch_select(const uint8_t* class_map, const uint64_t* class_bits, c
     }
     hipLaunchKernelGGL(k_select, dim3(Sb, masks, B), dim3(kThreads), lds, s, class_map, scores, masks, Sb, a,
                        keepbits, counts);
+    return hipGetLastError();
+}
+
+bool mask_short_supported(int mode, int B, int masks, int Sb) {
+    return (mode == 0 || mode == 1) && Sb <= kShortMask && (int64_t)B * masks <= 256;
+}
+hipError_t launch_mask_short(const uint64_t* class_bits, const float* scores, int B, int masks, int Sb, const SelectArgs& a, int32_t* rowptr,
+                             int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s) {
+    const int cap = (a.sort_cap + 1) & ~1;      // (16-byte aligned bins)
+    const size_t lds = a.mode == 1 ? select_mass_lds_bytes(cap) * kShortWaves : (size_t)kShortWaves * 64 * 8;
+    hipLaunchKernelGGL(a.mode == 1 ? k_mask_short<true> : k_mask_short<false>, dim3((unsigned)(B * masks)), dim3(64 * kShortWaves), lds, s, class_bits,
+                       scores, Sb, cap, a, rowptr, colidx, capacity, nnz);
     return hipGetLastError();
 }
 
