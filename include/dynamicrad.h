@@ -34,7 +34,7 @@
  *     Argument errors are detected on the host before anything is launched.
  *   - A dr_ctx owns device scratch and caches; it is bound to one device and
  *     must not be used from two threads at once.  Two calls on different
- *     streams that share one ctx race on its scratch (lists, flags and work
+ *     streams that share one ctx race on its scratch (lists, flags, partial sums and work
  *     queues: results may be wrong and output rows left unwritten).
  */
 #ifndef DYNAMICRAD_H_

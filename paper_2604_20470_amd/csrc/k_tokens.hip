@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __re
             all &= present;
         };
         const int64_t at0 = mask * N * N + (int64_t)r0 * N + c;
-        int frame = (r0 + group) / Nt, frame_row0 = frame * Nt - r0;      // the same in every lane
+        int frame = min(r0 + group, N - 1) / Nt, frame_row0 = frame * Nt - r0;      // the same in every lane (a group may be without rows)
         enter_frame(frame);
         constexpr int kAhead = 4;
         for (int r = group; r < nr; r += kGroups * kAhead) {
