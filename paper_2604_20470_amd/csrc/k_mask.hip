@@ -14,8 +14,9 @@
 //   k_select_zscore  the paper's dynamic rule (Eqs. 10-11) per row: lanes own candidate sets
 //                (frame distance, side), standardise the scores of a set in fp64 and keep
 //                z >= tau_1 / tau_2, with the keep-one fallback.
-//   k_emit       per row: offset = sum of the previous rows' counts, bit-expansion to
+//   k_emit*      per row: offset = sum of the previous rows' counts, bit-expansion to
 //                ascending key-block indices.
+//   k_mask_short both, for masks of at most 32 rows.
 #include "dr_internal.h"
 
 namespace dr {
