@@ -761,6 +761,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp
                 for (int i = 0; i < P::kIn; ++i) read_k(k_addr[ks], i, kf);
                 s = mfma_parts<P::kIn, P::kIn>(kf, qf[ks], s);
             }
+            __syncthreads();                       // tile 0's keys are read by all: the loop's first pass puts tile 2's over them
         }
         for (int g = 0; g < stages; ++g) {
             // the Q parts are only ever operands of matrix instructions, and O leaves them only where the reference moves: they
