@@ -243,9 +243,6 @@ dr_status dr_build_mask(dr_ctx* ctx, const dr_shape* shape, int32_t mode, double
  * (B * mask_heads * colidx_stride entries), grown on demand: DR_ERR_NOMEM if that allocation fails.
  * The pre-pass holds one bitmap of Sb bits per merged row in LDS: DR_ERR_UNSUPPORTED when
  * (256 / Bs) * Sb bits exceed 160 KB (beyond 5 million tokens at block size 32, 84 million at 128).
- * On the fp32-accuracy path (fp32 inputs, bf16 with d = 64) at block sizes 128 and 64 the key lists of the query blocks that would
- * leave compute units idle are cut into pieces, one workgroup each, whose sums a second launch merges in order: up to
- * 17 MiB of context-owned scratch, grown on demand (DR_ERR_NOMEM if that allocation fails).
  * Argument errors (NULL or misaligned pointers, strides, mask_heads) are rejected on the host
  * before any launch; the call itself is asynchronous on `stream`.
  */
@@ -258,7 +255,7 @@ dr_status dr_sparse_attn_fwd(dr_ctx* ctx, const dr_shape* shape, const void* Q, 
  * loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical results; the scratch the
  * kernels need beyond their inputs and outputs (range flags of the bf16 MFMA paths; merged key-block lists and
  * their lengths for block sizes 32 / 64 and for the block-size-128 kernel that walks pairs of query blocks) lies in
- * a fixed area of device memory (16 MiB, 256 bytes of work queues and 17 MiB of partial sums) that is part of the library image (one copy per GPU, held until the process
+ * a fixed area of device memory (16 MiB, and 256 bytes of work queues) that is part of the library image (one copy per GPU, held until the process
  * ends) instead of context-owned allocations.  The call allocates and frees nothing.
  *   Needed: 16 bytes per 128 query rows and head, plus, on the list-walking paths, 4 bytes per entry of the colidx
  *   arrays given (B * mask_heads * colidx_stride) and 4 bytes per group of rows.  A call that needs more than the

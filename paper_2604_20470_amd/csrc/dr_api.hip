@@ -16,10 +16,10 @@ using namespace dr;
 
 // Scratch of dr_sparse_attn_fwd_static: one copy per GPU the library runs on, held until the process ends.  In host
 // code this name is only a handle for hipGetSymbolAddress (dr_create resolves it, per device); kernels get the address.
-// Behind it lie the work queues of the attention kernel and the partial sums of the fp32-accuracy one.
+// Behind it lie the work queues of the attention kernel.
 constexpr size_t kStaticScratchBytes = 16u << 20, kQueueBytes = 256;
 static_assert(kAttnQueues * sizeof(int32_t) <= kQueueBytes, "work queues");
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kQueueBytes + kSplitScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kQueueBytes];
 
 struct dr_ctx {
     int device = 0;
@@ -41,8 +41,6 @@ struct dr_ctx {
     size_t attn_flags_bytes = 0;
     int32_t* attn_queue = nullptr;             // work queues of the 256-query kernel
     size_t attn_queue_bytes = 0;
-    float* attn_partial = nullptr;             // partial sums of the fp32-accuracy kernel
-    size_t attn_partial_bytes = 0;
     int cus = 256;
     bool attn_pairs = true;      // block size 128: the kernel that walks pairs of query blocks (DR_ATTN_PAIRS=0 turns it off)
     // cached selection of the uniform rule (it depends on geometry, ratios and seed only): one mask of Sb rows
@@ -276,7 +274,7 @@ void dr_destroy(dr_ctx* ctx) {
     {
         DeviceGuard g(ctx->device);
         void* ptrs[] = {ctx->pooled, ctx->keepbits, ctx->counts, ctx->class_map, ctx->class_bits, ctx->row_sel, ctx->totals, ctx->gcol,
-                        ctx->gcount, ctx->attn_flags, ctx->attn_queue, ctx->attn_partial, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->link_stats, ctx->proxy_partial};
+                        ctx->gcount, ctx->attn_flags, ctx->attn_queue, ctx->uni_keep, ctx->uni_counts, ctx->links, ctx->link_stats, ctx->proxy_partial};
         for (void* p : ptrs)
             if (p) (void)hipFree(p);
     }
@@ -530,15 +528,12 @@ namespace {
 
 // Scratch that the attention kernels need beyond their inputs and outputs, in bytes: the per-wave range flags of the
 // bf16 MFMA paths, and for the paths that walk merged key-block lists (block sizes 32 / 64, and the pair kernel of
-// block size 128) the lists and their lengths; on the fp32-accuracy path the partial sums of shared items.
-struct AttnScratchNeed { size_t flags, gcount, gcol, partial; };
+// block size 128) the lists and their lengths.  Zero for the fp32 arithmetic path.
+struct AttnScratchNeed { size_t flags, gcount, gcol; };
 
 AttnScratchNeed attn_scratch_need(const AttnArgs& a, bool pairs) {
-    AttnScratchNeed n{0, 0, 0, 0};
-    if (!attn_mfma_supported(a) && !attn_mfma_small_supported(a)) {
-        n.partial = attn_split_scratch_bytes(a);
-        return n;
-    }
+    AttnScratchNeed n{0, 0, 0};
+    if (!attn_mfma_supported(a) && !attn_mfma_small_supported(a)) return n;
     const size_t groups128 = ((size_t)a.td.N + 127) / 128;
     n.flags = (size_t)a.td.B * a.td.H * groups128 * 4 * sizeof(int32_t);
     const bool lists = attn_mfma_small_supported(a) || pairs;
@@ -616,8 +611,6 @@ dr_status dr_sparse_attn_fwd(dr_ctx* ctx, const dr_shape* shape, const void* Q, 
     if (need.gcol && (st = grow(ctx, (void**)&ctx->gcol, &ctx->gcol_bytes, need.gcol)) != DR_OK) return st;
     if (need.gcount && (st = grow(ctx, (void**)&ctx->gcount, &ctx->gcount_bytes, need.gcount)) != DR_OK) return st;
     if (pairs && (st = grow(ctx, (void**)&ctx->attn_queue, &ctx->attn_queue_bytes, kQueueBytes)) != DR_OK) return st;
-    if (need.partial && (st = grow(ctx, (void**)&ctx->attn_partial, &ctx->attn_partial_bytes, need.partial)) != DR_OK) return st;
-    a.partial = need.partial ? ctx->attn_partial : nullptr;
     a.queue = pairs ? ctx->attn_queue : nullptr;
     a.flags = need.flags ? ctx->attn_flags : nullptr;
     a.gcol = need.gcol ? ctx->gcol : nullptr;
@@ -643,7 +636,6 @@ dr_status dr_sparse_attn_fwd_static(dr_ctx* ctx, const dr_shape* shape, const vo
     unsigned char* base = ctx->static_scratch;
     a.flags = need.flags ? reinterpret_cast<int32_t*>(base) : nullptr;
     a.queue = pairs ? reinterpret_cast<int32_t*>(base + kStaticScratchBytes) : nullptr;
-    a.partial = need.partial ? reinterpret_cast<float*>(base + kStaticScratchBytes + kQueueBytes) : nullptr;
     a.gcount = need.gcount ? reinterpret_cast<int32_t*>(base + up(need.flags)) : nullptr;
     a.gcol = need.gcol ? reinterpret_cast<int32_t*>(base + up(need.flags) + up(need.gcount)) : nullptr;
     return attn_launch(ctx, a, pairs, (hipStream_t)stream);

@@ -107,14 +107,10 @@ struct AttnArgs {
     int32_t* flags;              // [B * H * ceil(N / 128) * 4]
     int32_t* queue;              // [kAttnQueues] work queues of the 256-query kernel; set by its list-merging pre-pass
     int32_t cus;                 // compute units of the device
-    float* partial;              // scratch of the fp32-accuracy kernel, attn_split_scratch_bytes
 };
 constexpr int kAttnQueues = 8;   // one per XCD
 // Any d in {64,128}, Bs in {32,64,128}, f32 or bf16 storage; fp32 accuracy (32-bit operands split for the bf16 matrix cores).
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s);
-// Scratch (a.partial) for the items it shares out over several workgroups; never more than kSplitScratchBytes.
-constexpr size_t kSplitScratchBytes = (size_t)17 << 20;
-size_t attn_split_scratch_bytes(const AttnArgs& a);
 // bf16 storage, d = 128, Bs = 128: MFMA path.  Returns hipErrorNotSupported for other shapes.
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s);
 bool attn_mfma_supported(const AttnArgs& a);

@@ -25,8 +25,6 @@
 #include "attn_mfma_common.h"
 #include "dr_internal.h"
 
-#include <type_traits>
-
 namespace dr {
 namespace {
 
@@ -52,7 +50,6 @@ struct Plan {
     static constexpr bool kAlone = BS == 32;
     static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : 4 / kQ;        // streams of key tiles
     static constexpr int kThreads = 64 * kQ * kS;
-    static constexpr bool kShare = !kAlone;                         // whether several workgroups may share an item
     static constexpr int kTileBytes = 32 * (kAlone ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
     static constexpr int kT = !kAlone && ((BF16 && D == 64) || (!BF16 && D == 64 && kS == 1)) ? 2 : 1;   // 32-key tiles per stream and stage
     static constexpr int kTiles = kS * kT;                          // of a stage
@@ -253,96 +250,8 @@ __device__ __forceinline__ bool holds_huge_keys(const Item& it) {
     return most >= kHuge;
 }
 
-template <bool BF16>
-__device__ __forceinline__ Item item_of(const AttnArgs& a, int item) {
-    const int qb = item % a.Sb, h = (item / a.Sb) % a.td.H, b = item / (a.Sb * a.td.H);
-    constexpr int ES = BF16 ? 2 : 4;
-    const int64_t head_off = ((int64_t)b * a.td.stride_b + (int64_t)h * a.td.stride_h) * ES;
-    Item it;
-    it.Q = reinterpret_cast<const char*>(a.Q) + head_off;
-    it.K = reinterpret_cast<const char*>(a.K) + head_off;
-    it.V = reinterpret_cast<const char*>(a.V) + head_off;
-    it.O = reinterpret_cast<char*>(a.O) + head_off;
-    it.lse = a.lse ? a.lse + ((int64_t)b * a.td.H + h) * a.td.N : nullptr;
-    it.row_bytes = a.td.stride_n * ES;
-    it.qb = qb; it.Sb = a.Sb; it.N = a.td.N;
-    const int mh = (a.mask_heads == 1) ? 0 : h;
-    const int32_t* rp = a.rowptr + ((int64_t)b * a.mask_heads + mh) * (a.Sb + 1);
-    // row range, clipped to the colidx array of this mask (a list cut short by a too small capacity stays in bounds)
-    const int lim = (int)min(a.colidx_stride, (int64_t)0x7fffffff);
-    const int beg = min(max(__builtin_amdgcn_readfirstlane(rp[qb]), 0), lim);
-    it.n_list = min(max(__builtin_amdgcn_readfirstlane(rp[qb + 1]), beg), lim) - beg;
-    it.list = a.colidx + ((int64_t)b * a.mask_heads + mh) * a.colidx_stride + beg;
-    return it;
-}
-
-// How a launch is cut.  Every XCD has a run of per_xcd items; the first `full` are one workgroup each, the others `pieces`
-// workgroups each, which leave sums, normalisers and references in `partial` for k_attn_split_merge.
-constexpr int kXcds = 8;
-struct Cut {
-    int per_xcd, full, pieces;
-    float* partial;
-};
-template <int D, int BS> constexpr size_t kPartialFloats = (size_t)BS * D + 2 * BS + 64;      // of a piece: O, (reference, normaliser), flags
-
-// What a block's results say about its arithmetic, and their way to memory; `val` is O's lane-and-register layout of the channel
-// blocks db0, db0 + step, .. that the wavefront holds.
-template <bool BF16, int D, int BS, bool kMerged, class Val>
-__device__ __forceinline__ void finish_block(const Item& it, float l, float ref, bool writer, bool bad, bool q_tiny, int qrow, int db0, int step,
-                                             bool first, float* smem, Val&& val) {
-    constexpr int kDB = D / 32;
-    const int half = (threadIdx.x >> 5) & 1;
-    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-    if (writer) {
-        float check = l;
-        uint32_t least = ~0u;
-#pragma unroll
-        for (int db = 0; db < kDB; ++db) {
-            if (kMerged && (db < db0 || (db - db0) % step != 0)) continue;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                const float x = val(db, j) * inv;
-                check += fabsf(x) * 0.f;                         // NaN as soon as one value is not finite
-                if constexpr (!BF16) least = min(least, nonzero_magnitude(x));
-            }
-        }
-        bad = bad || !(check > 0.f && check < INFINITY) || least < kTinyMagnitude;
-    }
-    bad = bad && it.n_list > 0;
-    bool plain = __syncthreads_or((bad || (q_tiny && it.n_list > 0)) ? 1 : 0) != 0;
-    if constexpr (!BF16) {
-        // (tiny values of Q are at home among zeros; they matter beside huge keys alone)
-        if (plain && !__syncthreads_or(bad ? 1 : 0)) plain = __syncthreads_or(holds_huge_keys<D, BS>(it) ? 1 : 0) != 0;
-    }
-    if (writer && !plain) {
-        char* dst = it.O + (int64_t)qrow * it.row_bytes;
-#pragma unroll
-        for (int db = 0; db < kDB; ++db) {
-            if (kMerged && (db < db0 || (db - db0) % step != 0)) continue;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int ch = db * 32 + q4 * 8 + half * 4;
-                v4f32 x;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = val(db, q4 * 4 + i) * inv;
-                if constexpr (BF16) {
-                    v4bf r;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) r[i] = (__bf16)x[i];
-                    *reinterpret_cast<v4bf*>(dst + ch * 2) = r;
-                } else {
-                    *reinterpret_cast<v4f32*>(dst + ch * 4) = x;
-                }
-            }
-        }
-        if (it.lse && half == 0 && first)      // the two terms in 64 bits: the reference is a rounded multiple of the scale
-            it.lse[qrow] = (l > 0.f) ? (float)((double)ref * 0.69314718055994531 + log((double)l)) : -INFINITY;
-    }
-    if (plain) plain_block<BF16, D, BS>(it, smem);
-}
-
 template <bool BF16, int D, int BS>
-__device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp) {
+__device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     using P = Plan<BF16, D, BS>;
     constexpr int kDB = D / 32, kKS = D / 16;       // channel blocks of O, contraction steps of a logit tile
     constexpr int kPart = P::kRows * P::kRowBytes;  // bytes of one part of K (or V) of a stage
@@ -351,23 +260,37 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, l32 = lane & 31;
-    // Idle instructions that only move the code behind them: a lone wavefront per SIMD with a loop of 9.5 KB waits for
-    // instruction fetches, and with the place of that loop, in steps of 4 bytes over a line of 64, the same code took 640 to
-    // 696 us at block size 32 and 567 to 589 at 64 (6144 tokens x 8 heads, 48 % kept).  At 128 the place does not matter.
-    if constexpr (!BF16 && D == 128 && BS == 32) asm volatile(".fill 15, 4, 0xbf800000");
-    if constexpr (!BF16 && D == 128 && BS == 64) asm volatile(".fill 12, 4, 0xbf800000");
+    // Twelve idle instructions that only move the code behind them: a lone wavefront per SIMD with a loop of 9.5 KB waits for
+    // instruction fetches, and with the place of that loop, in steps of 4 bytes over a line of 64, the same code took 650 to
+    // 700 us (6144 tokens x 8 heads, 40 % kept).
+    if constexpr (!BF16 && D == 128 && BS == 32) asm volatile(".fill 12, 4, 0xbf800000");
     const int wq = wave % P::kQ, ws = wave / P::kQ;
 
-    // one XCD walks a contiguous run of (batch, head, query block) items: neighbours share K and V in its L2; the last of the
-    // run may be shared by several workgroups, each a stretch of the key list
-    const int unit = (int)(blockIdx.x / kXcds), xcd = (int)(blockIdx.x % kXcds);
-    const bool shared = P::kShare && unit >= sp.full && sp.pieces > 1;
-    const int at = shared ? sp.full + (unit - sp.full) / sp.pieces : unit;
-    // (both at once: a branch between them would wait for the kernel's arguments twice)
-    if ((at >= sp.per_xcd) | (xcd * sp.per_xcd + at >= a.Sb * a.td.H * a.td.B)) return;
-    Item it = item_of<BF16>(a, xcd * sp.per_xcd + at);
-    const int N = it.N, qb = it.qb;
+    // one XCD walks a contiguous run of (batch, head, query block) items: neighbours share K and V in its L2
+    constexpr int kXcds = 8;
+    const int total = a.Sb * a.td.H * a.td.B, per_xcd = (total + kXcds - 1) / kXcds;
+    const int item = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if ((int)(blockIdx.x / kXcds) >= per_xcd || item >= total) return;
+    const int qb = item % a.Sb, h = (item / a.Sb) % a.td.H, b = item / (a.Sb * a.td.H);
     constexpr int ES = BF16 ? 2 : 4;
+    const int N = a.td.N;
+    const int64_t head_off = ((int64_t)b * a.td.stride_b + (int64_t)h * a.td.stride_h) * ES;
+    Item it;
+    it.Q = reinterpret_cast<const char*>(a.Q) + head_off;
+    it.K = reinterpret_cast<const char*>(a.K) + head_off;
+    it.V = reinterpret_cast<const char*>(a.V) + head_off;
+    it.O = reinterpret_cast<char*>(a.O) + head_off;
+    it.lse = a.lse ? a.lse + ((int64_t)b * a.td.H + h) * N : nullptr;
+    it.row_bytes = a.td.stride_n * ES;
+    it.qb = qb; it.Sb = a.Sb; it.N = N;
+    const int mh = (a.mask_heads == 1) ? 0 : h;
+    const int32_t* rp = a.rowptr + ((int64_t)b * a.mask_heads + mh) * (a.Sb + 1);
+    // row range, clipped to the colidx array of this mask (a list cut short by a too small capacity stays in bounds)
+    const int lim = (int)min(a.colidx_stride, (int64_t)0x7fffffff);
+    const int beg = min(max(__builtin_amdgcn_readfirstlane(rp[qb]), 0), lim);
+    it.n_list = min(max(__builtin_amdgcn_readfirstlane(rp[qb + 1]), beg), lim) - beg;
+    it.list = a.colidx + ((int64_t)b * a.mask_heads + mh) * a.colidx_stride + beg;
+
     // Q^T fragments (B operand): lane holds query l32, channels ks * 16 + 8 * half .. + 7
     const int q_wave0 = qb * BS + wq * 32, qrow = q_wave0 + l32;
     v8bf qf[kKS][P::kIn];
@@ -383,13 +306,6 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp
                 split8(x, qf[ks]);
             }
         }
-    }
-
-    if (shared) {                          // (behind the loads of Q: the row's length is not waited for before them)
-        const int piece = (unit - sp.full) % sp.pieces;
-        const int from = (int)((int64_t)it.n_list * piece / sp.pieces), to = (int)((int64_t)it.n_list * (piece + 1) / sp.pieces);
-        it.list += from;
-        it.n_list = to - from;
     }
 
     // ---- the walk.  Tile t of the row = keys (t % kTPB) * 32 .. + 31 of its key block t / kTPB; stage g holds tiles
@@ -992,6 +908,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp
     }
     // Nothing is stored before every wavefront's results are known to stand: the plain pass reads Q again, which O may overlay.
     const bool writer = ws == 0 && qrow < N;
+    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
     bool bad = false, q_tiny = false;
     if constexpr (!BF16) {
         // the first parts tell (a value that is 0 in all of them is below 2^-134 and lost to no purpose beside keys under kHuge)
@@ -1012,58 +929,48 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a, const Cut& sp
         q_tiny = min(least[0], least[1]) < (kTinyMagnitude >> 16);
         bad = max(most[0], most[1]) >= (__builtin_bit_cast(uint32_t, kHuge) >> 15);
     }
-    if (shared) {
-        float* dst = sp.partial + (size_t)(xcd * (sp.per_xcd - sp.full) * sp.pieces + unit - sp.full) * kPartialFloats<D, BS>;
-        if (ws == 0) {
+    if (writer) {
+        float check = l;
+        uint32_t least = ~0u;
 #pragma unroll
-            for (int db = 0; db < kDB; ++db)
+        for (int db = 0; db < kDB; ++db)
 #pragma unroll
-                for (int j = 0; j < 16; ++j) dst[((wq * kDB + db) * 16 + j) * 64 + lane] = o[db][j];
-            dst[BS * D + wq * 64 + lane] = half ? l : ref;
-        }
-        const int flags = (__syncthreads_or(bad ? 1 : 0) ? 1 : 0) | (__syncthreads_or(q_tiny ? 1 : 0) ? 2 : 0);
-        if (tid == 0) dst[BS * D + 2 * BS] = (float)flags;
-        return;
+            for (int j = 0; j < 16; ++j) {
+                const float val = o[db][j] * inv;
+                check += fabsf(val) * 0.f;                       // NaN as soon as one value is not finite
+                if constexpr (!BF16) least = min(least, nonzero_magnitude(val));
+            }
+        bad = bad || !(check > 0.f && check < INFINITY) || least < kTinyMagnitude;
     }
-    finish_block<BF16, D, BS, false>(it, l, ref, writer, bad, q_tiny, qrow, 0, 1, true, reinterpret_cast<float*>(smem),
-                                     [&](int db, int j) { return o[db][j]; });
-}
-
-// The shared items: their pieces' sums against the largest reference, pieces in order, then as an item of one workgroup ends.
-// Wavefront (q, s) takes every kS-th channel block of its queries.  Reads 64 KB a piece at d = 128, block size 128.
-// grid: (8 * (per_xcd - full)).
-template <bool BF16, int D, int BS>
-__global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) void k_attn_split_merge(AttnArgs a, Cut sp) {
-    using P = Plan<BF16, D, BS>;
-    constexpr int kDB = D / 32;
-    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wq = wave % P::kQ, ws = wave / P::kQ, half = lane >> 5, l32 = lane & 31;
-    const int xcd = (int)(blockIdx.x % kXcds), rest = (int)(blockIdx.x / kXcds), at = sp.full + rest;
-    if (xcd * sp.per_xcd + at >= a.Sb * a.td.H * a.td.B) return;
-    const Item it = item_of<BF16>(a, xcd * sp.per_xcd + at);
-    const float* src = sp.partial + (size_t)(xcd * (sp.per_xcd - sp.full) + rest) * sp.pieces * kPartialFloats<D, BS>;
-    float ref = -INFINITY;
-    for (int i = 0; i < sp.pieces; ++i) ref = fmaxf(ref, src[i * kPartialFloats<D, BS> + BS * D + wq * 64 + l32]);
-    float l = 0.f, o[kDB][16];
-#pragma unroll
-    for (int db = 0; db < kDB; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
-    for (int i = 0; i < sp.pieces; ++i) {
-        const float* from = src + i * kPartialFloats<D, BS>;
-        const float r = from[BS * D + wq * 64 + l32], scale = (r == ref) ? 1.0f : __builtin_amdgcn_exp2f(r - ref);      // (both -inf: nothing listed)
-        l += from[BS * D + wq * 64 + 32 + l32] * scale;
-#pragma unroll
-        for (int db = 0; db < kDB; ++db) {
-            if (db % P::kS != ws) continue;                        // wavefront-uniform
-#pragma unroll
-            for (int j = 0; j < 16; ++j) o[db][j] += from[((wq * kDB + db) * 16 + j) * 64 + lane] * scale;
-        }
+    bad = bad && it.n_list > 0;
+    bool plain = __syncthreads_or((bad || (q_tiny && it.n_list > 0)) ? 1 : 0) != 0;
+    if constexpr (!BF16) {
+        // (tiny values of Q are at home among zeros; they matter beside huge keys alone)
+        if (plain && !__syncthreads_or(bad ? 1 : 0)) plain = __syncthreads_or(holds_huge_keys<D, BS>(it) ? 1 : 0) != 0;
     }
-    const int flags = (int)src[BS * D + 2 * BS], qrow = it.qb * BS + wq * 32 + l32;
-    finish_block<BF16, D, BS, true>(it, l, ref, ws < kDB && qrow < it.N, (flags & 1) != 0, (flags & 2) != 0, qrow, ws, P::kS, ws == 0,
-                                    reinterpret_cast<float*>(smem), [&](int db, int j) { return o[db][j]; });
+    if (writer && !plain) {
+        char* dst = it.O + (int64_t)qrow * it.row_bytes;
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const int ch = db * 32 + q4 * 8 + half * 4;
+                v4f32 val;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) val[i] = o[db][q4 * 4 + i] * inv;
+                if constexpr (BF16) {
+                    v4bf r;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) r[i] = (__bf16)val[i];
+                    *reinterpret_cast<v4bf*>(dst + ch * 2) = r;
+                } else {
+                    *reinterpret_cast<v4f32*>(dst + ch * 4) = val;
+                }
+            }
+        if (it.lse && half == 0)      // the two terms in 64 bits: the reference is a rounded multiple of the scale
+            it.lse[qrow] = (l > 0.f) ? (float)((double)ref * 0.69314718055994531 + log((double)l)) : -INFINITY;
+    }
+    if (plain) plain_block<BF16, D, BS>(it, reinterpret_cast<float*>(smem));
 }
 
 // Measured against the vector-ALU kernel before it (one thread, eight logits and D / 8 channels of a row; 16 TFLOP/s at
@@ -1080,59 +987,7 @@ __global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) void k_attn_split_me
 // d = 64 at block size 128, which fits 128 registers, four.
 template <bool BF16, int D, int BS>
 __global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS>::kPerSimd)))
-void k_attn_split(AttnArgs a, Cut sp) { attn_split_body<BF16, D, BS>(a, sp); }
-
-// Workgroups of one kernel that a compute unit holds.
-template <bool BF16, int D, int BS>
-int resident() {
-    static const int n = [] {
-        using P = Plan<BF16, D, BS>;
-        int blocks = 0;
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS>), hipFuncAttributeMaxDynamicSharedMemorySize, P::kLdsBytes) != hipSuccess ||
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, reinterpret_cast<const void*>(k_attn_split<BF16, D, BS>), P::kThreads, P::kLdsBytes) != hipSuccess)
-            return 1;
-        return blocks < 1 ? 1 : blocks;
-    }();
-    return n;
-}
-
-// Whether the items behind the last full round of workgroups are shared, and by how many each.  Left whole they take a round of
-// their own, however few they are: 384 items on 256 compute units two, 96 items one with 160 units idle.  Taken is the number
-// of pieces that makes this round shortest, if by at least a twentieth and by an estimated 20 us: the merge is another launch,
-// 5 us, and its traffic (a row's length is estimated by the capacity of the lists; 25 ns a matrix instruction and wavefront
-// of the SIMD).  Whole / shared, 48 % of the blocks kept: fp32 d = 128, block size 128, 6144 tokens x 8 heads (384 items)
-// 450 / 394 us, 2 heads 265 / 142, 9000 tokens x 5 heads (355) 600 / 478, 2000 x 3 94 / 56; d = 64, 6144 x 2 200 / 78; block
-// size 64 121 / 79; bf16 d = 64, 6144 x 2 101 / 41.  After eight rounds there is nothing to win.  Block size 32 is left out:
-// its workgroups have eight streams already, and the extra code cost the many-item calls more (3 to 7 %) than it saved.
-template <bool BF16, int D, int BS>
-Cut cut_of(const AttnArgs& a) {
-    using P = Plan<BF16, D, BS>;
-    const int total = a.Sb * a.td.H * a.td.B;
-    Cut c{(total + kXcds - 1) / kXcds, 0, 1, nullptr};
-    const int blocks = resident<BF16, D, BS>(), slots = (a.cus + kXcds - 1) / kXcds * blocks;
-    const int rest = c.per_xcd % slots;
-    c.full = c.per_xcd - rest;
-    const double entries = (double)(a.colidx_stride / a.Sb < a.Sb ? a.colidx_stride / a.Sb : a.Sb);
-    constexpr int kMfma = (D / 16) * (P::kIn == 3 ? 6 : 1) + (D / 16) * (P::kIn == 3 ? 6 : 3);      // of a 32 x 32 tile
-    const double item_us = entries * (BS / 32) / P::kS * kMfma * 0.025 * (blocks * P::kThreads / 256.0);
-    double best = 1.0;
-    if (!P::kShare || rest == 0 || c.full >= 8 * slots) return c;
-    for (int k = 2; k <= 8 && 2 * k <= entries; ++k) {
-        if ((size_t)kXcds * rest * k * kPartialFloats<D, BS> * sizeof(float) > kSplitScratchBytes) break;
-        const double rounds = (double)((rest * k + slots - 1) / slots) / k;
-        if (rounds <= best - 0.05 && item_us * (1.0 - rounds) >= 20.0) {
-            best = rounds;
-            c.pieces = k;
-        }
-    }
-    return c;
-}
-
-template <bool BF16, int D, int BS>
-size_t scratch_t(const AttnArgs& a) {
-    const Cut c = cut_of<BF16, D, BS>(a);
-    return c.pieces > 1 ? (size_t)kXcds * (c.per_xcd - c.full) * c.pieces * kPartialFloats<D, BS> * sizeof(float) : 0;
-}
+void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS>(a); }
 
 template <bool BF16, int D, int BS>
 hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
@@ -1140,46 +995,22 @@ hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, P::kLdsBytes);
     if (e != hipSuccess) return e;
-    Cut c = cut_of<BF16, D, BS>(a);
-    c.partial = a.partial;
-    const int rest = c.per_xcd - c.full, units = c.full + rest * c.pieces;          // every XCD gets the same number
-    hipLaunchKernelGGL((k_attn_split<BF16, D, BS>), dim3(kXcds * units), dim3(P::kThreads), P::kLdsBytes, s, a, c);
-    if constexpr (P::kShare) if (c.pieces > 1) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split_merge<BF16, D, BS>), hipFuncAttributeMaxDynamicSharedMemorySize, P::kPlainBytes);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_attn_split_merge<BF16, D, BS>), dim3(kXcds * rest), dim3(P::kThreads), P::kPlainBytes, s, a, c);
-    }
+    const int total = a.Sb * a.td.H * a.td.B, grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
+    hipLaunchKernelGGL((k_attn_split<BF16, D, BS>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
     return hipGetLastError();
 }
 
-template <class F>
-auto with_kernel(const AttnArgs& a, F&& f) {
-    auto by_block = [&](auto bf16, auto d) {
-        constexpr bool B = decltype(bf16)::value;
-        constexpr int D = decltype(d)::value;
-        return a.Bs == 128 ? f.template operator()<B, D, 128>() : a.Bs == 64 ? f.template operator()<B, D, 64>() : f.template operator()<B, D, 32>();
-    };
-    using std::integral_constant;
-    if (a.td.d == 64)
-        return a.bf16 ? by_block(std::true_type{}, integral_constant<int, 64>{}) : by_block(std::false_type{}, integral_constant<int, 64>{});
-    return a.bf16 ? by_block(std::true_type{}, integral_constant<int, 128>{}) : by_block(std::false_type{}, integral_constant<int, 128>{});
+template <bool BF16, int D>
+hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
+    return a.Bs == 128 ? launch_t<BF16, D, 128>(a, s) : a.Bs == 64 ? launch_t<BF16, D, 64>(a, s) : launch_t<BF16, D, 32>(a, s);
 }
-struct Launch {
-    const AttnArgs& a;
-    hipStream_t s;
-    template <bool BF16, int D, int BS> hipError_t operator()() { return launch_t<BF16, D, BS>(a, s); }
-};
-struct Scratch {
-    const AttnArgs& a;
-    template <bool BF16, int D, int BS> size_t operator()() { return scratch_t<BF16, D, BS>(a); }
-};
 
 }  // namespace
 
-size_t attn_split_scratch_bytes(const AttnArgs& a) { return a.td.d == 64 || a.td.d == 128 ? with_kernel(a, Scratch{a}) : 0; }
-
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s) {
-    return a.td.d == 64 || a.td.d == 128 ? with_kernel(a, Launch{a, s}) : hipErrorNotSupported;
+    if (a.td.d == 64) return a.bf16 ? launch_d<true, 64>(a, s) : launch_d<false, 64>(a, s);
+    if (a.td.d == 128) return a.bf16 ? launch_d<true, 128>(a, s) : launch_d<false, 128>(a, s);
+    return hipErrorNotSupported;
 }
 
 }  // namespace dr

@@ -1,6 +1,6 @@
-"""The fp32-accuracy kernel where several workgroups share a query block's key list: launches that do not fill the chip, rows of very
-different lengths (none, one, fewer entries than pieces), a partial last block, infinities in a shared block, O over Q, and the
-entry point with static scratch bit for bit."""
+"""The fp32-accuracy kernel in launches that do not fill the chip or end in a round that does not (one workgroup walks a query
+block's whole list there too): rows of very different lengths (none, one, three), a partial last block, infinities, O over Q, and
+the entry point with static scratch bit for bit."""
 import dataclasses
 
 import numpy as np
