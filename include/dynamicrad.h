@@ -324,7 +324,7 @@ dr_status dr_build_mask_tokens(dr_ctx* ctx, const dr_shape* shape, double tau_ne
  *   out        device float64 [3]: loss, nmse, sparsity
  * All sums are taken in fp64 in a fixed order (per (b, h): one workgroup, each thread over a strided subset, then a
  * tree over the threads), so the result is reproducible run to run.  A (b, h) slice with ||A_dense||_F = 0
- * contributes 0.  Asynchronous on `stream`; allocates nothing.  Errors: DR_ERR_INVALID_ARG for NULL pointers or
+ * contributes 0; one that holds a NaN or an infinity makes loss and nmse NaN or infinite.  Asynchronous on `stream`; allocates nothing.  Errors: DR_ERR_INVALID_ARG for NULL pointers or
  * non-positive sizes.
  */
 dr_status dr_proxy_loss(dr_ctx* ctx, const float* A_dense, const float* A_sparse, int32_t B, int32_t H, int32_t N,

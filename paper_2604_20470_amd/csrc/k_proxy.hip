@@ -27,6 +27,9 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* sh) {
     b = sh[kThreads];
 }
 
+// (a norm that is not a number, from features that are not, stays one: it must not look like a perfect reconstruction)
+__device__ __forceinline__ double ratio_of(double num, double den) { return den == 0.0 ? 0.0 : num / den; }
+
 __device__ __forceinline__ void store_objective(double ratio_sum, double nnz_sum, int BH, int n_masks, int Sb, double target, double alpha,
                                                 double* __restrict__ out) {
     const double nmse = ratio_sum / (double)BH;
@@ -70,7 +73,7 @@ __global__ __launch_bounds__(kThreads) void k_proxy_final(const double* __restri
             num += partial[((long long)bh * kProxySlices + s) * 2 + 0];
             den += partial[((long long)bh * kProxySlices + s) * 2 + 1];
         }
-        ratio_sum += den > 0.0 ? num / den : 0.0;
+        ratio_sum += ratio_of(num, den);
     }
     for (int m = threadIdx.x; m < n_masks; m += kThreads) nnz_sum += (double)nnz[m];
     block_sum2(ratio_sum, nnz_sum, sh);
@@ -252,7 +255,7 @@ __global__ __launch_bounds__(kThreads) void k_proxy_fold(const double* __restric
             num += __shfl_xor(num, off);
             den += __shfl_xor(den, off);
         }
-        if (lane == 0) ratio_sum += den > 0.0 ? num / den : 0.0;
+        if (lane == 0) ratio_sum += ratio_of(num, den);
     }
     for (int m = threadIdx.x; m < n_masks; m += kThreads) nnz_sum += (double)nnz[m];
     block_sum2(ratio_sum, nnz_sum, sh);
