@@ -334,8 +334,8 @@ dr_status dr_proxy_loss(dr_ctx* ctx, const float* A_dense, const float* A_sparse
 /*
  * The same objective from the tensors and the mask, without the matrices: A_dense is the softmax of Q_p . K_q / sqrt(d) over
  * all keys, A_sparse that over the keys of the blocks listed in the CSR (a row that lists nothing is 0).  Per row the two
- * squared norms follow from the sums of e^s and e^2s over the kept and the pruned keys; logits and row sums are fp32,
- * quotients and sums over rows fp64 in a fixed order.
+ * squared norms follow from the sums of e^s and e^2s over the kept and the pruned keys; logits and exponentials are fp32,
+ * all sums and quotients fp64 in a fixed order.
  *   Q, K       device, float32, strides of `shape` (DR_ERR_UNSUPPORTED for bf16)
  *   rowptr, colidx, mask_heads, colidx_stride   as in dr_sparse_attn_fwd; nnz  device int64 [B, mask_heads]
  *   target, alpha, out   as in dr_proxy_loss

@@ -83,8 +83,8 @@ __global__ __launch_bounds__(kThreads) void k_proxy_final(const double* __restri
 // The same sums without the matrices.  In a row of A_dense and A_sparse (both softmaxes of the same logits s, one over all
 // keys, one over the kept ones) let l and E be the sums of e^s and of e^2s over the kept (k) and the pruned (u) keys:
 //   ||a_dense||^2 = (E_k + E_u) / (l_k + l_u)^2,   ||a_dense - a_sparse||^2 = (E_u + l_u^2 E_k / l_k^2) / (l_k + l_u)^2,
-// all terms positive, so nothing cancels where the two rows are nearly alike.  Every sum is taken online in fp32 against its
-// own moving reference; the quotients and the sums over rows are fp64.
+// all terms positive, so nothing cancels where the two rows are nearly alike.  Logits and exponentials are fp32; every sum is fp64,
+// taken online against its own moving reference, a whole power of two, so that moving it rounds nothing.
 // One pass over the logits, which the fp32 matrix instruction forms (fp32 products and sums): what bounds it is that
 // instruction, 1.1 GFLOP at 2048 tokens x 2 heads of 64 channels.  A workgroup owns 16 queries, so that 2048 tokens x 2 heads
 // are 256 of them; its eight wavefronts take every eighth group of 32 keys, straight from memory to registers (a lane
@@ -98,13 +98,21 @@ constexpr int kRowWaves = 8, kRowTile = 16;
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 struct RowSums {
-    float m, l, e;      // reference (log2 units), sum of 2^(x - m), sum of its squares
-    __device__ __forceinline__ void merge(float m2, float l2, float e2) {
-        const float top = fmaxf(m, m2), ref = top == -INFINITY ? 0.f : top;
-        const float a = __builtin_amdgcn_exp2f(m - ref), b = __builtin_amdgcn_exp2f(m2 - ref);
-        l = l * a + l2 * b;
-        e = e * (a * a) + e2 * (b * b);
-        m = top;
+    float m;            // reference (log2 units, a whole number, or -inf before the first key)
+    double l, e;        // sum of 2^(x - m), sum of its squares
+    // the sums against a reference not below this one (both -inf: they are 0; infinite logits have made them NaN already)
+    __device__ __forceinline__ void move(float ref) {
+        const int by = (int)fmaxf(m - ref, -4096.f);
+        l = __builtin_ldexp(l, by);
+        e = __builtin_ldexp(e, 2 * by);
+        m = ref;
+    }
+    __device__ __forceinline__ void merge(RowSums o) {
+        const float top = fmaxf(m, o.m);
+        move(top);
+        o.move(top);
+        l += o.l;
+        e += o.e;
     }
 };
 
@@ -149,7 +157,7 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_proxy_rows(const float* __re
         }
     }
     __syncthreads();
-    RowSums kept = {-INFINITY, 0.f, 0.f}, pruned = kept;      // of query r16, over this lane's keys
+    RowSums kept = {-INFINITY, 0.0, 0.0}, pruned = kept;      // of query r16, over this lane's keys
     for (int group = wave; group < groups; group += kRowWaves) {
         v4f k[2][kVec];
 #pragma unroll
@@ -184,26 +192,22 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_proxy_rows(const float* __re
             float mx = s[0][0];
 #pragma unroll
             for (int i = 1; i < 8; ++i) mx = fmaxf(mx, s[i >> 2][i & 3]);
-            const float top = fmaxf(st.m, mx * kScaleLog2), ref = top == -INFINITY ? 0.f : top;
-            const float a = __builtin_amdgcn_exp2f(st.m - ref);
-            float l = 0.f, e = 0.f;
+            const float top = fmaxf(st.m, ceilf(mx * kScaleLog2)), ref = top == -INFINITY ? 0.f : top;
+            st.move(top);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i >> 2][i & 3], kScaleLog2, -ref));
-                l += p;
-                e += p * p;
+                const double p = (double)__builtin_amdgcn_exp2f(__builtin_fmaf(s[i >> 2][i & 3], kScaleLog2, -ref));
+                st.l += p;
+                st.e = __builtin_fma(p, p, st.e);
             }
-            st.l = st.l * a + l;
-            st.e = st.e * (a * a) + e;
-            st.m = top;
         };
         const int kb = group * 32 / Bs;         // (a key block holds whole groups)
         if (__builtin_amdgcn_readfirstlane(s_kept[kb >> 5] >> (kb & 31)) & 1u) add(kept);
         else add(pruned);
     }
     for (int off = 16; off < 64; off <<= 1) {
-        kept.merge(__shfl_xor(kept.m, off), __shfl_xor(kept.l, off), __shfl_xor(kept.e, off));
-        pruned.merge(__shfl_xor(pruned.m, off), __shfl_xor(pruned.l, off), __shfl_xor(pruned.e, off));
+        kept.merge({__shfl_xor(kept.m, off), __shfl_xor(kept.l, off), __shfl_xor(kept.e, off)});
+        pruned.merge({__shfl_xor(pruned.m, off), __shfl_xor(pruned.l, off), __shfl_xor(pruned.e, off)});
     }
     if (quarter == 0) {
         s_part[wave][0][r16] = kept;
@@ -212,19 +216,17 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_proxy_rows(const float* __re
     __syncthreads();
     if (tid >= 2 * kRowTile) return;
     RowSums own = s_part[0][quarter][r16];      // quarter 0: kept keys, 1: pruned ones
-    for (int w = 1; w < kRowWaves; ++w) {
-        const RowSums o = s_part[w][quarter][r16];
-        own.merge(o.m, o.l, o.e);
-    }
-    const float m_u = __shfl_xor(own.m, 16), l_u = __shfl_xor(own.l, 16), e_u = __shfl_xor(own.e, 16);
+    for (int w = 1; w < kRowWaves; ++w) own.merge(s_part[w][quarter][r16]);
+    RowSums u = {__shfl_xor(own.m, 16), __shfl_xor(own.l, 16), __shfl_xor(own.e, 16)};
     double num = 0.0, den = 0.0;
     if (quarter == 0 && q0 + r16 < N) {
-        const float top = fmaxf(own.m, m_u), ref = top == -INFINITY ? 0.f : top;
-        const double ak = __builtin_amdgcn_exp2f(own.m - ref), au = __builtin_amdgcn_exp2f(m_u - ref);
-        const double lu = (double)l_u * au, eu = (double)e_u * (au * au), all = (double)own.l * ak + lu;
-        const double of_kept = own.l == 0.f ? 0.0 : (double)own.e / ((double)own.l * (double)own.l);      // (a row that keeps nothing is 0)
-        num = (eu + lu * lu * of_kept) / (all * all);
-        den = ((double)own.e * (ak * ak) + eu) / (all * all);
+        const double of_kept = own.l == 0.0 ? 0.0 : own.e / (own.l * own.l);      // (a row that keeps nothing is 0)
+        const float top = fmaxf(own.m, u.m);
+        own.move(top);
+        u.move(top);
+        const double all = own.l + u.l;
+        num = (u.e + u.l * u.l * of_kept) / (all * all);
+        den = (own.e + u.e) / (all * all);
     }
     for (int off = 1; off < 16; off <<= 1) {
         num += __shfl_xor(num, off);
