@@ -101,7 +101,7 @@ __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restric
 // the sums is part of the definition) and three readings of the score matrix, so the columns of all pairs are spread over the
 // whole chip: a wavefront owns 64 key columns of one pair and reads whole row segments, many rows in flight.
 //   k_link_sums<0>  column sums of the scores, highest score   k_link_sums<1>  column sums of the squared deviations
-//   k_link_stats    deviation, the test as one float, the pair that the safeguard keeps
+//   k_link_stats    deviation, the test as one float, the pair that the safeguard keeps (from the columns' highest scores)
 //   k_link_blocks   link bytes, and the density rule over them while they are at hand
 struct PairStat {
     double mu;
@@ -190,16 +190,19 @@ __device__ __forceinline__ double window_size(int Nt, int w) {      // token pai
     return (double)n;
 }
 
-// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs, tops: [B * masks][Nf * Nf][Nt].
+// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs, tops, rows: [B * masks][Nf * Nf][Nt]; a column's highest score
+// and the place of the first kAhead rows that hold it, for the safeguard (the row itself would cost four instructions a row:
+// 8 x 1024 tokens, whole call, 104.3 -> 111.1 us, with the place 104.5 -> 104.8).
 // A column's rows are walked over the union of the wavefront's windows, so that all lanes read one row; a row outside a
 // lane's own window adds +0.0, which leaves its running sum bit for bit as it is (it starts at +0.0 and is never -0.0).
 // At 8 x 1024 tokens 672 wavefronts have work, fewer than one a SIMD, so the time is that of one wavefront's rows: the next
 // kAhead are fetched before the current ones are added, and rows that lie in every lane's window are added without a test
 // (23 -> 21 us and 36 -> 29 there; a third set of registers would not help: a wavefront counts at most 63 loads).
+constexpr int kAhead = 32;
 template <int PASS>
 __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
                                                   double* __restrict__ sums, double* __restrict__ devs, float* __restrict__ tops,
-                                                  PairStat* __restrict__ stats) {
+                                                  int32_t* __restrict__ rows, PairStat* __restrict__ stats) {
     extern __shared__ double sh[];
     const int tiles = (Nt + 63) / 64;
     const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
@@ -210,7 +213,6 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
     const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, v_last + p.w);      // of the wavefront
     const int every_first = max(0, v_last - p.w), every_last = min(Nt - 1, v0 + p.w);      // rows in all its windows
     const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
-    constexpr int kAhead = 32;
     float x[2][kAhead];
     auto fetch = [&](float (&dst)[kAhead], int u) {                  // (past the window: its last row again)
 #pragma unroll
@@ -224,17 +226,19 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
         if (v0 == 0 && threadIdx.x == 0) stats[p.pair].mu = mu;
     }
     double acc = 0.0;
-    float top = __builtin_nanf("");                                  // (fmaxf passes NaN by: it ranks below every number)
+    float top = __builtin_nanf("");
+    int row = 0;                                                     // of the first batch of rows that holds `top`
     auto term = [&](float s) {
         const double dev = (double)s - mu;
         return PASS == 0 ? (double)s : dev * dev;
     };
     auto add = [&](const float (&src)[kAhead], int u0) {
+        float most = __builtin_nanf("");                             // (fmaxf passes NaN by: it ranks below every number)
         if (u0 >= every_first && u0 + kAhead - 1 <= every_last) {    // the same in every lane
 #pragma unroll
             for (int e = 0; e < kAhead; ++e) {
                 acc = acc + term(src[e]);
-                if constexpr (PASS == 0) top = fmaxf(top, src[e]);
+                if constexpr (PASS == 0) most = fmaxf(most, src[e]);
             }
         } else {
 #pragma unroll
@@ -242,8 +246,13 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
                 const bool in = u0 + e >= lo && u0 + e <= hi;        // (hi <= u_last)
                 const double t = term(src[e]);
                 acc = acc + (in ? t : 0.0);
-                if constexpr (PASS == 0) top = in ? fmaxf(top, src[e]) : top;
+                if constexpr (PASS == 0) most = in ? fmaxf(most, src[e]) : most;
             }
+        }
+        if constexpr (PASS == 0) {
+            const bool higher = most > top || top != top;
+            top = higher ? most : top;
+            row = higher ? u0 : row;
         }
     };
     for (int u = u_first; u <= u_last; u += 2 * kAhead) {
@@ -254,7 +263,10 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
     }
     if (v < Nt) {
         (PASS == 0 ? sums : devs)[p.pair * Nt + v] = acc;
-        if constexpr (PASS == 0) tops[p.pair * Nt + v] = top;
+        if constexpr (PASS == 0) {
+            tops[p.pair * Nt + v] = top;
+            rows[p.pair * Nt + v] = row;
+        }
     }
 }
 
@@ -264,7 +276,8 @@ __global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scor
 // infinite ones included.  Also clears the kept counts of the mask's rows, to which k_link_blocks adds.
 __global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf, int Sb,
                                                    double tau_near, double tau_far, const double* __restrict__ devs,
-                                                   const float* __restrict__ tops, PairStat* __restrict__ stats, int32_t* __restrict__ counts) {
+                                                   const float* __restrict__ tops, const int32_t* __restrict__ rows,
+                                                   PairStat* __restrict__ stats, int32_t* __restrict__ counts) {
     extern __shared__ double sh[];
     const int lane = threadIdx.x;
     const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
@@ -301,31 +314,44 @@ __global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ sco
     const float threshold = lo < none ? image_score(lo) : __builtin_nanf("");
     int best = -1;
     if (!(top >= threshold)) {
-        // nothing passes: the highest score, the first in row-major order on ties (-0 equals +0; in a set of NaN alone any is)
-        int best_u = Nt, best_v = 0;
+        // nothing passes: the highest score, the first in row-major order on ties (-0 equals +0; in a set of NaN alone any is).  A lane
+        // takes a column that holds it and looks at the kAhead rows that are known to; a later column counts only by an earlier
+        // row.  (Column after column, a row of the wavefront's after the other, cost 0.5 us for each that shares the highest score:
+        // scores that depend on their row alone, nothing passing, 8 x 1024 tokens 587 us where this takes 123, 4 x 4096 7412 / 410.)
+        int best_u = top == top ? Nt : 0, best_v = 0;
         const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
-        for (int v0 = 0; v0 < Nt; v0 += 64 * 16) {
-            float x[16];
+        for (int v0 = lane; v0 < Nt + lane; v0 += 64 * 8) {
+            float x[8];
+            int first[8];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) x[e] = tops[p.pair * Nt + min(v0 + 64 * e + lane, Nt - 1)];
+            for (int e = 0; e < 8; ++e) {
+                x[e] = tops[p.pair * Nt + min(v0 + 64 * e, Nt - 1)];
+                first[e] = rows[p.pair * Nt + min(v0 + 64 * e, Nt - 1)];
+            }
+#pragma unroll 1
+            for (int e = 0; e < 8; ++e) {
+                const int v = v0 + 64 * e, vc = min(v, Nt - 1);
+                const bool asks = v < Nt && x[0] == top && first[0] < best_u;
+                const int u0 = first[0];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                uint64_t tied = __ballot(v0 + 64 * e + lane < Nt && (x[e] == top || top != top));
-                while (tied) {                                             // the same in every lane
-                    const int v = v0 + 64 * e + __ffsll((unsigned long long)tied) - 1;
-                    tied &= tied - 1;
-                    // a later column counts only by an earlier row
-                    const int first = max(0, v - p.w), last = min(min(Nt - 1, v + p.w), best_u - 1);
-                    for (int u0 = first; u0 <= last; u0 += 64) {
-                        const int u = u0 + lane;
-                        const float s = S[(int64_t)min(u, last) * N + v];
-                        const uint64_t hit = __ballot(u <= last && (s == top || top != top));
-                        if (hit) {
-                            best_u = u0 + __ffsll((unsigned long long)hit) - 1;
-                            best_v = v;
-                            break;
-                        }
-                    }
+                for (int k = 0; k < 7; ++k) {
+                    x[k] = x[k + 1];
+                    first[k] = first[k + 1];
+                }
+                if (!__any(asks)) continue;
+                const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
+                float s[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) s[k] = S[(int64_t)min(max(u0 + k, lo), hi) * N + vc];
+                int at = Nt;
+#pragma unroll
+                for (int k = kAhead - 1; k >= 0; --k)
+                    if (asks && u0 + k >= lo && u0 + k <= hi && s[k] == top) at = u0 + k;
+                int least = at;
+                for (int off = 32; off > 0; off >>= 1) least = min(least, __shfl_xor(least, off));
+                if (least < best_u) {                                      // the same in every lane
+                    best_u = least;
+                    best_v = v - lane + __ffsll((unsigned long long)__ballot(at == least)) - 1;
                 }
             }
         }
@@ -647,7 +673,7 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
 
 size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf) {
     if (small_frames(B, masks, N, Nf)) return 0;
-    return (size_t)B * masks * ((size_t)Nf * N * (2 * sizeof(double) + sizeof(float)) + (size_t)Nf * Nf * sizeof(PairStat));
+    return (size_t)B * masks * ((size_t)Nf * N * (2 * sizeof(double) + sizeof(float) + sizeof(int32_t)) + (size_t)Nf * Nf * sizeof(PairStat));
 }
 
 hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uint8_t* class_map, const Geometry& g, int B, int masks,
@@ -670,12 +696,13 @@ hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uin
     double* devs = sums + columns;
     PairStat* stats = reinterpret_cast<PairStat*>(devs + columns);
     float* tops = reinterpret_cast<float*>(stats + (size_t)B * masks * Nf * Nf);
+    int32_t* rows = reinterpret_cast<int32_t*>(tops + columns);
     const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64;
     const size_t lds = (size_t)((Nt + 15) & ~15) * sizeof(double);
-    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, tops, stats);
-    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, tops, stats);
+    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, tops, rows, stats);
+    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, tops, rows, stats);
     hipLaunchKernelGGL(k_link_stats, dim3(pairs, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, g.Sb, tau_near, tau_far,
-                       devs, tops, stats, counts);
+                       devs, tops, rows, stats, counts);
     const dim3 grid((unsigned)g.Sb * ((N + kBlockCols - 1) / kBlockCols), masks, B);
     if ((int64_t)grid.x * masks * B <= kSmallGrid)
         hipLaunchKernelGGL(k_link_blocks<4>, grid, dim3(1024), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
