@@ -969,8 +969,8 @@ __global__ __launch_bounds__(kT) void k_select_zscore(const uint8_t* __restrict_
 }
 
 // grid: (Sb, masks, B)
-// rowptr of every mask whose rows are longer than 2048 key blocks: the exclusive prefix of its rows' kept counts, one workgroup
-// per mask.  grid: (masks, B).
+// rowptr of every mask where the rows do not add up the earlier counts themselves (launch_emit): the exclusive prefix of its
+// rows' kept counts, one workgroup per mask.  grid: (masks, B).
 __global__ __launch_bounds__(kThreads) void k_row_offsets(const int32_t* __restrict__ counts, int masks, int Sb, int shared,
                                                           int32_t* __restrict__ rowptr, int64_t* __restrict__ nnz) {
     __shared__ long long s_wave[kWaves];
@@ -1249,13 +1249,41 @@ __global__ __launch_bounds__(kThreads) void k_emit_rows(const uint32_t* __restri
 }
 static_assert(8 * kThreads >= 64 * 32, "the earlier rows of a mask");
 
+// The same with the offsets made by k_row_offsets before: a wave writes its row without waiting for any other.  (The row is worked out
+// in vector registers: the same in scalar ones puts argument loads behind the row's and takes 18.5 us a call where this takes 15.5,
+// 2000 masks of 40 rows.)  grid: ceil(B * masks * Sb / 4).
+__global__ __launch_bounds__(kThreads) void k_emit_rows_at(const uint32_t* __restrict__ keepbits, uint32_t rows_total, int Sb, int shared,
+                                                           const int32_t* __restrict__ rowptr, int32_t* __restrict__ colidx,
+                                                           int64_t capacity) {
+    const int lane = lane_id();
+    const uint32_t r = blockIdx.x * kWaves + (threadIdx.x >> 6);           // (mask_id, qb) flattened
+    if (r >= rows_total) return;
+    const uint32_t mask_id = r / (uint32_t)Sb;
+    const int qb = (int)(r - mask_id * (uint32_t)Sb);
+    const int64_t src = shared ? 0 : (int64_t)mask_id * Sb;
+    const int words = (Sb + 31) / 32;
+    const uint32_t wv = (lane < words) ? keepbits[(src + qb) * words + lane] : 0u;
+    const int before = rowptr[(int64_t)mask_id * (Sb + 1) + qb];
+    emit_row(wv, Sb, from_lane(before, 0), colidx + (int64_t)__builtin_amdgcn_readfirstlane(mask_id) * capacity, capacity);
+}
+
 hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, int masks, int Sb, bool shared,
                        int32_t* rowptr, int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s) {
     const int64_t rows_total = (int64_t)B * masks * Sb;
+    // A launch of its own for the offsets costs 2 to 5 us, the more the longer the rows (a workgroup walks the counts of a mask); made
+    // in the emission's launch they cost each workgroup a round of reads and a barrier, of which long rows hide more.  Whole calls of
+    // the uniform rule, offsets in the emission's launch / apart, rows of 40 key blocks: 20 000 rows 6.5 / 8.4 us, 30 000 8.7 / 8.5,
+    // 80 000 19.7 / 15.7; of 300: 30 000 12.4 / 12.5, 80 000 26.8 / 23.6, 240 000 71 / 57; of 591: 40 000 20.1 / 20.9, 60 000 28.3 / 27.7,
+    // 160 000 67 / 60; of 1024: 60 000 36.3 / 37.2, 100 000 57.4 / 55.8; of 2040: 50 000 50 / 54, 118 000 113 / 115.
+    const int64_t line = 20000 + 55 * (int64_t)Sb;
+    const bool apart = Sb > 64 * 32 || rows_total >= (line > 30000 ? line : 30000);
+    if (apart) hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
     if (Sb > 64 * 32) {
-        hipLaunchKernelGGL(k_row_offsets, dim3(masks, B), dim3(kThreads), 0, s, counts, masks, Sb, shared ? 1 : 0, rowptr, nnz);
         hipLaunchKernelGGL(k_emit, dim3(Sb, masks, B), dim3(kThreads), 0, s, keepbits, masks, Sb, shared ? 1 : 0, rowptr,
                            colidx, capacity);
+    } else if (apart) {
+        hipLaunchKernelGGL(k_emit_rows_at, dim3((unsigned)((rows_total + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, keepbits, (uint32_t)rows_total,
+                           Sb, shared ? 1 : 0, rowptr, colidx, capacity);
     } else if (rows_total >= kWaveSelectPackRows) {
         hipLaunchKernelGGL(k_emit_rows, dim3((unsigned)((int64_t)B * masks * ((Sb + kEmitRows - 1) / kEmitRows))), dim3(kThreads), 0, s, keepbits,
                            counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);

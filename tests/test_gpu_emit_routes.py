@@ -14,10 +14,17 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("frames,hg,wg,heads", [
-    (15, 32, 20, 95),        # 300 rows: 95 and 96 masks are the rule's two sides
+    (15, 32, 20, 95),        # 300 rows: 121 and 122 masks are the rule's two sides
     (15, 32, 20, 96),
-    (16, 64, 64, 8),         # 2048 rows, the longest of one wavefront: 8 and 9
+    (15, 32, 20, 121),
+    (15, 32, 20, 122),
+    (16, 64, 64, 8),         # 2048 rows, the longest of one wavefront: 64 and 65
     (16, 64, 64, 9),
+    (16, 64, 64, 64),
+    (16, 64, 64, 65),
+    (4, 16, 20, 749),        # 40 rows: 749 and 750
+    (4, 16, 20, 750),
+    (5, 7, 30, 911),         # 33 rows, no multiple of a workgroup's four: 909 and 910
 ])
 @pytest.mark.parametrize("mode,par", [("static", 0.1), ("uniform", 0.1)])
 def test_every_mask_alike(frames, hg, wg, heads, mode, par):
