@@ -182,8 +182,8 @@ __global__ __launch_bounds__(256) void k_scores_mfma(const float* __restrict__ p
 }
 
 // The same for short rows, where 64 x 64 tiles are a handful of workgroups that wait for eight chunks one after the other: a
-// wavefront owns 16 x 16 outputs and takes 128 channels of its rows at a time straight from memory to registers, the next 128 on
-// their way meanwhile.  v_mfma_f32_16x16x4_f32; a lane feeds one of its four consecutive channels to each of four
+// wavefront owns 16 x 16 outputs and takes a head's D channels of its rows at a time straight from memory to registers, the next
+// head's on their way meanwhile.  v_mfma_f32_16x16x4_f32; a lane feeds one of its four consecutive channels to each of four
 // instructions with sums of their own (the order of the contraction is permuted alike for both operands).
 // grid: (ceil(Sb / 16), ceil(Sb / 16), B * masks).
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -255,11 +255,13 @@ hipError_t launch_scores(const float* pooled, int B, int Hs, int masks, int head
     const int t128 = (Sb + 127) / 128, t64 = (Sb + 63) / 64;
     // 128 x 128 tiles pay once a row holds thousands of blocks (at 8250 blocks 0.44 against 0.47 ms); below, their
     // rounding up of Sb and the short contraction loop cost more than they save (591 blocks x 40 heads: 66 against 47 us)
-    // One wavefront per 16 x 16 outputs up to eight a compute unit: whole stage, 64 x 64 tiles / these, 371 blocks x 2 heads 13.3 /
-    // 10.3 us, 591 x 2 (1369 wavefronts) 21.7 / 20.7, 96 blocks x 8 heads of one mask 32 / 12, 40 masks of 75 (1000) 34.8 / 33.7;
-    // 929 x 2 (3481) 28 / 35, 24 masks of 371 (13 824) 58 / 71.  (10.3 us is two launches from the host.)
-    const int t16 = (Sb + 15) / 16;
-    if ((int64_t)t16 * t16 * B * masks <= 2048)
+    // One wavefront per 16 x 16 outputs up to six or seven a compute unit; beyond, that they read every row four times as often as tiles
+    // do costs more than the tiles' waiting.  Whole stage, 64 x 64 tiles / these, d = 128: one mask of 96 blocks x 8 heads 32.3 /
+    // 11.8 us, 370 x 2 13.3 / 9.4, 590 (1369 wavefronts) x 2 14.9 / 14.2, x 40 200 / 178, 650 (1681) x 2 15.7 / 15.3, x 40 208 / 202, 700 (1936)
+    // x 2 16.0 / 16.2, x 8 43.9 / 46.3, x 40 215 / 225; masks of one head: 40 of 75 blocks (1000) 16.2 / 15.0, 40 of 96 (1440) 17.9 / 17.6,
+    // 30 of 100 (1470) 16.0 / 16.1, at d = 64 13.3 / 13.9, 40 of 110 (1960) 19.1 / 20.4.
+    const int t16 = (Sb + 15) / 16, most = masks > 1 ? 1450 : 1700;
+    if ((int64_t)t16 * t16 * B * masks <= most)
         hipLaunchKernelGGL(d == 64 ? k_scores_short<64> : k_scores_short<128>, dim3(t16, t16, B * masks), dim3(64), 0, s, pooled, B, Hs, masks,
                            heads_per_mask, Sb, scale, scores);
     else if (Sb >= 4096 && (int64_t)t128 * t128 * B * masks >= 512)
