@@ -698,7 +698,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             }
             if (__builtin_expect(look, 0)) {        // wavefront-uniform, and rare: one branch for all that is, out of the loop's line
                 if ((g + 4) / kTPB - wbase >= 64) {
-                    wbase = (g + 4) / kTPB;
+                    wbase = min((g + 4) / kTPB, it.n_list - 1);      // (the tiles past the end are of the last entry)
                     win = it.list[min(wbase + lane, it.n_list - 1)];
                     asm volatile("" : "+v"(win));   // (waited for here: behind the branch the wait would be for every load)
                 }

@@ -126,6 +126,27 @@ def test_lists_longer_than_every_streams_window(dtype, d):
 
 @pytest.mark.parametrize("dtype,d", STORAGE)
 @pytest.mark.parametrize("bs", [64, 128])
+def test_lists_around_the_window_of_64_entries(dtype, d, bs):
+    """Block sizes 128 and 64: the list is held 64 entries at a time, and the loop of d = 128, block size 128 asks for entries four
+    tiles ahead, past the list's end too.  Rows on both sides of one, two and (block size 64) four windows, that end with the
+    partial last block and that do not, between rows that list nothing; the first and the last row are full."""
+    frames, hg, wg = 13, 31, 41                              # N = 16523: the last block has 11 keys at either block size
+    wl = dataclasses.replace(tiny_case("ragged128"), dtype=dtype, d=d, Bs=bs, Nf=frames, Hg=hg, Wg=wg, H=1, index=65)
+    run = GpuRun(wl)
+    Sb = wl.Sb
+    assert Sb >= 130 and wl.N % bs == 11
+    rng = np.random.default_rng(bs + d)
+    rows = [[] for _ in range(Sb)]
+    rows[0] = rows[Sb - 1] = list(range(Sb))
+    for at, n in enumerate(n for n in (1, 2, 63, 64, 65, 66, 67, 68, 69, 127, 128, 129, 191, 192, 193, 256, 257) if n < Sb):
+        rows[2 + 3 * at] = sorted(rng.choice(Sb - 1, n, replace=False).tolist())
+        rows[3 + 3 * at] = sorted(rng.choice(Sb - 1, n - 1, replace=False).tolist()) + [Sb - 1]
+    rp, ci = _csr(rows)
+    _check(run, rp, ci, *_attend(run, rp, ci))
+
+
+@pytest.mark.parametrize("dtype,d", STORAGE)
+@pytest.mark.parametrize("bs", [64, 128])
 @pytest.mark.parametrize("hidden", [32, 33])
 def test_a_row_that_starts_with_a_whole_tile_of_minus_infinity(dtype, d, bs, hidden):
     """The first tile of a row (32 keys), and a key of the next, are out of reach by a logit of -inf: weight 0."""
