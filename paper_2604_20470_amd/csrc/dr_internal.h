@@ -59,7 +59,7 @@ struct SelectArgs {
 // keepbits[(b*masks+m)*Sb + qb][words], counts[(b*masks+m)*Sb + qb]
 hipError_t launch_select(const uint8_t* class_map, const uint64_t* class_bits, const float* scores, int B, int masks,
                          int Sb, const SelectArgs& a, uint32_t* keepbits, int32_t* counts, hipStream_t s);
-// Static top-k and cumulative mass of masks of at most 64 rows: selection and emission in one launch.
+// Static top-k and cumulative mass of at most 256 masks of at most 32 rows: selection and emission in one launch.
 bool mask_short_supported(int mode, int B, int masks, int Sb);
 hipError_t launch_mask_short(const uint64_t* class_bits, const float* scores, int B, int masks, int Sb, const SelectArgs& a, int32_t* rowptr,
                              int32_t* colidx, int64_t capacity, int64_t* nnz, hipStream_t s);
