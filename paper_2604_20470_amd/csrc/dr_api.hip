@@ -121,6 +121,14 @@ dr_status grow(dr_ctx* ctx, void** p, size_t* have, size_t need) {
     return DR_OK;
 }
 
+// Whether work for the stream goes into a graph, where nothing can be allocated.
+bool capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 dr_status check_geometry(dr_ctx* ctx, const dr_shape* s) {
     if (!s) return fail(ctx, DR_ERR_INVALID_ARG, "shape is NULL");
     if (s->Nf <= 0 || s->Hg <= 0 || s->Wg <= 0 || s->N <= 0) return fail(ctx, DR_ERR_INVALID_ARG, "non-positive dimension");
@@ -513,13 +521,20 @@ dr_status dr_build_mask_tokens(dr_ctx* ctx, const dr_shape* shape, double tau_ne
         if ((st = grow(ctx, (void**)&ctx->links, &ctx->links_bytes, need)) != DR_OK) return st;
         links = ctx->links;
     }
-    if ((st = grow(ctx, &ctx->link_stats, &ctx->link_stats_bytes, pair_links_scratch_bytes(shape->B, masks, shape->N, shape->Nf))) != DR_OK)
-        return st;
+    // small frames can do without the sums' scratch: in a graph's capture, and where there is no memory for it
+    const size_t stats_need = pair_links_scratch_bytes(shape->B, masks, shape->N, shape->Nf);
+    void* stats = nullptr;
+    if (stats_need && (Nt > kSmallFrame || ctx->link_stats_bytes >= stats_need || !capturing(s))) {
+        st = grow(ctx, &ctx->link_stats, &ctx->link_stats_bytes, stats_need);
+        if (st != DR_OK && Nt > kSmallFrame) return st;
+        if (st != DR_OK) (void)hipGetLastError();      // (else the launches below would report it)
+        else stats = ctx->link_stats;
+    }
     FrameTab tab;
     fill_frame_table(shape->Nf, Nt, shape->Bs, p->gamma, lambda, &tab);
     const Geometry geo = make_geometry(shape, p);
     DR_HIP(ctx, launch_token_mask(token_scores, tab, ctx->class_map, geo, shape->B, masks, tau_near, p->has_tau_far ? p->tau_far : tau_near,
-                                  ctx->link_stats, links, ctx->keepbits, ctx->counts, s));
+                                  stats, links, ctx->keepbits, ctx->counts, s));
     DR_HIP(ctx, launch_emit(ctx->keepbits, ctx->counts, shape->B, masks, Sb, false, rowptr, colidx, colidx_capacity, nnz, s));
     return DR_OK;
 }

@@ -82,6 +82,8 @@ hipError_t launch_token_scores(const void* Q, const void* K, bool bf16, const Te
 // rule per block pair -> the keepbits / counts that launch_emit reads.  scratch: column sums and per-pair statistics, of the
 // size below
 size_t pair_links_scratch_bytes(int B, int masks, int N, int Nf);
+// Frames that can do without (scratch = NULL), if more slowly beyond the size from which pair_links_scratch_bytes asks for some.
+constexpr int kSmallFrame = 128;
 hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uint8_t* class_map, const Geometry& g, int B, int masks,
                              double tau_near, double tau_far, void* scratch, uint8_t* links, uint32_t* keepbits, int32_t* counts,
                              hipStream_t s);

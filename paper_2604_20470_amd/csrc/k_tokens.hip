@@ -505,7 +505,6 @@ __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __re
 // work four launches cost more than two, where there is much the serial chains of a workgroup do: whole calls, four launches /
 // two, 4 frames of 64 tokens, block size 128: 19 / 13 us; 33 of 64: 31 / 26; 16 of 128: 37 / 35; 33 of 96 (10 million token
 // pairs): 57 / 46; 33 of 121 (16 million): 63 / 71; 60 of 128: 91 / 134; 128 of 64: 73 / 87.
-constexpr int kSmallFrame = 128;
 constexpr int64_t kSmallPairs = 12 << 20;
 inline bool small_frames(int B, int masks, int N, int Nf) {
     return N / Nf <= kSmallFrame && (int64_t)B * masks * N * N <= kSmallPairs;
@@ -680,7 +679,7 @@ hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uin
                              double tau_near, double tau_far, void* scratch, uint8_t* links, uint32_t* keepbits, int32_t* counts,
                              hipStream_t s) {
     const int N = g.N, Nt = g.Nt, Nf = g.Nf;
-    if (small_frames(B, masks, N, Nf)) {
+    if (small_frames(B, masks, N, Nf) || !scratch) {      // (the caller has no scratch: Nt <= kSmallFrame)
         const size_t lds = (size_t)Nt * sizeof(double) + (size_t)Nt * Nt * sizeof(float);
         if (lds > 64 * 1024) {
             hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_pair_links_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
