@@ -194,9 +194,14 @@ __global__ __launch_bounds__(64 * kRowWaves) void k_proxy_rows(const float* __re
             for (int i = 1; i < 8; ++i) mx = fmaxf(mx, s[i >> 2][i & 3]);
             const float top = fmaxf(st.m, ceilf(mx * kScaleLog2)), ref = top == -INFINITY ? 0.f : top;
             st.move(top);
+            // The product rounds once, with the subtraction.  Where logits are so large that a reference can be off the product it is the
+            // rounding of by more than an exponent holds, it rounds before: the difference to the highest is then 0.
+            const bool far = fabsf(ref) >= 0x1p28f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                const double p = (double)__builtin_amdgcn_exp2f(__builtin_fmaf(s[i >> 2][i & 3], kScaleLog2, -ref));
+#pragma clang fp contract(off)
+                const float x = s[i >> 2][i & 3], by = far ? x * kScaleLog2 - ref : __builtin_fmaf(x, kScaleLog2, -ref);
+                const double p = (double)__builtin_amdgcn_exp2f(by);
                 st.l += p;
                 st.e = __builtin_fma(p, p, st.e);
             }

@@ -10,6 +10,36 @@ import paper_2604_20470_amd as dr
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("scale", [1e3, 1e4, 2e4, 4e4, 1e6, 1e9, 1e15, 1e18])
+@pytest.mark.parametrize("d", [64, 128])
+def test_logits_of_any_size(scale, d):
+    """Features so large that a row of either matrix is 1 at its highest logit and 0 elsewhere (products of Q and K from 1e7 to 5e37): a row whose
+    highest key is pruned has an error of 2, any other of 0."""
+    B, H, frames, hg, wg, bs = 1, 2, 6, 9, 5, 32
+    N, Sb = frames * hg * wg, 9
+    g = torch.Generator(device="cuda").manual_seed(d)
+    Q, K = (scale * torch.randn(B, H, N, d, generator=g, device="cuda") for _ in range(2))
+    keep = np.random.default_rng(d).random((Sb, Sb)) < 0.5
+    keep[:, 0] = True
+    rowptr = torch.from_numpy(np.concatenate([[0], keep.sum(1).cumsum()]).astype(np.int32)).view(1, 1, -1).cuda()
+    colidx = torch.from_numpy(np.nonzero(keep)[1].astype(np.int32)).view(1, 1, -1).contiguous().cuda()
+    nnz = torch.tensor([[int(keep.sum())]], device="cuda")
+    out = torch.zeros(3, dtype=torch.float64, device="cuda")
+    dr.dr_proxy_objective(dr.Context(0), dr.shape_of(Q, frames, hg, wg, bs), Q, K, rowptr, colidx, 1, colidx.shape[2], nnz, 0.8, 10.0, out)
+    s = Q.double() @ K.double().transpose(-1, -2) / d ** 0.5
+    top = s.topk(2, -1).values
+    # no row is near a tie: the two highest differ by more than the products and sums round, d 2^-24 of the terms' magnitudes
+    room = d * 2.0 ** -24 * (Q.double().abs() @ K.double().abs().transpose(-1, -2)).amax(-1) / d ** 0.5 + 60.0
+    allowed = torch.from_numpy(keep).cuda().repeat_interleave(bs, 0)[:N].repeat_interleave(bs, 1)[:, :N]
+    best = s.masked_fill(~allowed, -torch.inf).topk(2, -1).values
+    clear = (top[..., 0] - top[..., 1] > room) & (best[..., 0] - best[..., 1] > room)
+    assert float((~clear).double().mean()) <= 0.05
+    wrong = (best[..., 0] < top[..., 0]).double() * 2.0
+    # (a row near a tie may count for anything from 0 to 2)
+    low, high = float((wrong * clear).mean()), float((wrong * clear + 2.0 * (~clear)).mean())
+    assert low - 1e-12 <= out[1].item() <= high + 1e-12
+
+
 @pytest.mark.parametrize("frames,hg,wg,bs", [(1, 1, 5, 32), (7, 9, 21, 32), (7, 9, 21, 64), (5, 24, 32, 128), (8, 32, 32, 32)])
 @pytest.mark.parametrize("d", [64, 128])
 def test_equal_logits(frames, hg, wg, bs, d):
