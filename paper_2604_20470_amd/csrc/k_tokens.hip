@@ -97,14 +97,14 @@ __global__ __launch_bounds__(kThreads) void k_token_scores(const void* __restric
 
 #pragma clang fp contract(off)
 
-// ---- links of every ordered frame pair, in four launches.  What bounds this is the serial fp64 chain of a column (the order of
+// ---- links of every ordered frame pair, in three launches.  What bounds this is the serial fp64 chain of a column (the order of
 // the sums is part of the definition) and three readings of the score matrix, so the columns of all pairs are spread over the
-// whole chip: a wavefront owns 64 key columns of one pair and reads whole row segments, many rows in flight.
-//   k_link_sums<0>  column sums of the scores, highest score   k_link_sums<1>  column sums of the squared deviations
-//   k_link_stats    deviation, the test as one float, the pair that the safeguard keeps (from the columns' highest scores)
+// whole chip: a workgroup owns 64 key columns of one pair and reads whole row segments, many rows in flight.
+//   k_link_sums<0>  column sums of the scores, highest score
+//   k_link_sums<1>  column sums of the squared deviations; the last workgroup of a pair then forms its deviation, the test as one
+//                   float and the pair that the safeguard keeps (from the columns' highest scores)
 //   k_link_blocks   link bytes, and the density rule over them while they are at hand
 struct PairStat {
-    double mu;
     float threshold;              // a pair is a link when its score is at least this; NaN: none is
     int best;                     // where nothing passes: u * Nt + v of the highest score, which is kept; else -1
 };
@@ -132,7 +132,9 @@ __device__ __forceinline__ PairAt pair_at(const FrameTab& tab, int Nf, int pair)
     p.i = pair / Nf;
     p.j = pair % Nf;
     p.t = abs(p.i - p.j);
-    p.flags = tab.flags[p.t];
+    uint32_t word;                // (a scalar load, as of w: of a byte there is none)
+    __builtin_memcpy(&word, tab.flags + (p.t & ~3), 4);
+    p.flags = (int)(word >> (8 * (p.t & 3))) & 255;
     p.w = tab.w[p.t];
     p.mask = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
     p.pair = p.mask * Nf * Nf + pair;
@@ -140,21 +142,30 @@ __device__ __forceinline__ PairAt pair_at(const FrameTab& tab, int Nf, int pair)
     return p;
 }
 
-// The sum of Nt doubles, one by one in ascending order (every lane gets it).  LDS: Nt doubles, up to a multiple of 16.  The next
-// sixteen are read while the current ones are added: the chain waits for the additions alone (2.4 ns each).
-__device__ __forceinline__ double ordered_sum(const double* __restrict__ col, int Nt, double* sh) {
+// The sum of Nt doubles, one by one in ascending order.  lay_out (all threads of the workgroup, a barrier behind it) puts them into LDS,
+// up to a multiple of 16; ordered_sum is one wavefront's.  The next sixteen are read while the current ones are added: the
+// chain waits for the additions alone (2.4 ns each).  (Every wavefront for itself: the reads of three workgroups fill a
+// compute unit's LDS, 52 us a launch at 8 x 1024 tokens.)
+template <bool kSameLaunch, int kSumThreads, class Meanwhile>      // whether other workgroups of this launch wrote them; what to do while they are on their way
+__device__ __forceinline__ void lay_out(const double* col, int Nt, double* sh, Meanwhile&& meanwhile) {
     const int padded = (Nt + 15) & ~15;
-    for (int v0 = threadIdx.x; v0 < padded; v0 += 64 * 16) {      // sixteen loads on their way: another XCD wrote the sums
-        double x[16];
+    for (int v0 = threadIdx.x; v0 < padded || v0 == (int)threadIdx.x; v0 += kSumThreads * 4) {
+        double x[4];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = col[min(v0 + 64 * e, Nt - 1)];
+        for (int e = 0; e < 4; ++e) {
+            const double* at = col + min(v0 + kSumThreads * e, Nt - 1);
+            x[e] = kSameLaunch ? __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : *at;
+        }
+        if (v0 == (int)threadIdx.x) meanwhile();
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int v = v0 + 64 * e;
+        for (int e = 0; e < 4; ++e) {
+            const int v = v0 + kSumThreads * e;
             if (v < padded) sh[v] = v < Nt ? x[e] : -0.0;         // (x + -0.0 is x, bit for bit)
         }
     }
-    __syncthreads();
+}
+__device__ __forceinline__ double ordered_sum(int Nt, const double* sh) {
+    const int padded = (Nt + 15) & ~15;
     double total = 0.0, x[2][16];
     auto read = [&](double (&dst)[16], int v) {
 #pragma unroll
@@ -183,118 +194,29 @@ __device__ __forceinline__ double ordered_sum(const double* __restrict__ col, in
     }
     return total;
 }
-__device__ __forceinline__ double window_size(int Nt, int w) {      // token pairs of a candidate set
-    long long n = 0;
-    for (int v = threadIdx.x & 63; v < Nt; v += 64) n += min(Nt - 1, v + w) - max(0, v - w) + 1;      // (every wavefront by itself)
-    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off);
-    return (double)n;
+// token pairs of a candidate set: Nt of one place each, and Nt - k at distance k either way, up to w
+__device__ __forceinline__ double window_size(int Nt, int w) {
+    const long long m = min(w, Nt - 1);
+    return (double)(Nt + 2 * (m * Nt - m * (m + 1) / 2));
 }
 
-// grid: (Nf * Nf * ceil(Nt / 64), masks, B), 64 threads.  sums, devs, tops, rows: [B * masks][Nf * Nf][Nt]; a column's highest score
-// and the place of the first kAhead rows that hold it, for the safeguard (the row itself would cost four instructions a row:
-// 8 x 1024 tokens, whole call, 104.3 -> 111.1 us, with the place 104.5 -> 104.8).
-// A column's rows are walked over the union of the wavefront's windows, so that all lanes read one row; a row outside a
-// lane's own window adds +0.0, which leaves its running sum bit for bit as it is (it starts at +0.0 and is never -0.0).
-// At 8 x 1024 tokens 672 wavefronts have work, fewer than one a SIMD, so the time is that of one wavefront's rows: the next
-// kAhead are fetched before the current ones are added, and rows that lie in every lane's window are added without a test
-// (23 -> 21 us and 36 -> 29 there; a third set of registers would not help: a wavefront counts at most 63 loads).
-constexpr int kAhead = 32;
-template <int PASS>
-__global__ __launch_bounds__(64) void k_link_sums(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
-                                                  double* __restrict__ sums, double* __restrict__ devs, float* __restrict__ tops,
-                                                  int32_t* __restrict__ rows, PairStat* __restrict__ stats) {
-    extern __shared__ double sh[];
-    const int tiles = (Nt + 63) / 64;
-    const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
-    const PairAt p = pair_at(tab, Nf, pair);
-    if (!p.judged) return;
-    const int v = v0 + (int)threadIdx.x, vc = min(v, Nt - 1), v_last = min(v0 + 63, Nt - 1);
-    const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
-    const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, v_last + p.w);      // of the wavefront
-    const int every_first = max(0, v_last - p.w), every_last = min(Nt - 1, v0 + p.w);      // rows in all its windows
-    const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
-    float x[2][kAhead];
-    auto fetch = [&](float (&dst)[kAhead], int u) {                  // (past the window: its last row again)
-#pragma unroll
-        for (int e = 0; e < kAhead; ++e) dst[e] = (S + (int64_t)min(u + e, u_last) * N)[(uint32_t)vc];
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    fetch(x[0], u_first);
-    double mu = 0.0;
-    if constexpr (PASS == 1) {
-        mu = ordered_sum(sums + p.pair * Nt, Nt, sh) / window_size(Nt, p.w);
-        if (v0 == 0 && threadIdx.x == 0) stats[p.pair].mu = mu;
-    }
-    double acc = 0.0;
-    float top = __builtin_nanf("");
-    int row = 0;                                                     // of the first batch of rows that holds `top`
-    auto term = [&](float s) {
-        const double dev = (double)s - mu;
-        return PASS == 0 ? (double)s : dev * dev;
-    };
-    auto add = [&](const float (&src)[kAhead], int u0) {
-        float most = __builtin_nanf("");                             // (fmaxf passes NaN by: it ranks below every number)
-        if (u0 >= every_first && u0 + kAhead - 1 <= every_last) {    // the same in every lane
-#pragma unroll
-            for (int e = 0; e < kAhead; ++e) {
-                acc = acc + term(src[e]);
-                if constexpr (PASS == 0) most = fmaxf(most, src[e]);
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < kAhead; ++e) {
-                const bool in = u0 + e >= lo && u0 + e <= hi;        // (hi <= u_last)
-                const double t = term(src[e]);
-                acc = acc + (in ? t : 0.0);
-                if constexpr (PASS == 0) most = in ? fmaxf(most, src[e]) : most;
-            }
-        }
-        if constexpr (PASS == 0) {
-            const bool higher = most > top || top != top;
-            top = higher ? most : top;
-            row = higher ? u0 : row;
-        }
-    };
-    for (int u = u_first; u <= u_last; u += 2 * kAhead) {
-        fetch(x[1], u + kAhead);
-        add(x[0], u);
-        fetch(x[0], u + 2 * kAhead);
-        if (u + kAhead <= u_last) add(x[1], u + kAhead);
-    }
-    if (v < Nt) {
-        (PASS == 0 ? sums : devs)[p.pair * Nt + v] = acc;
-        if constexpr (PASS == 0) {
-            tops[p.pair * Nt + v] = top;
-            rows[p.pair * Nt + v] = row;
-        }
-    }
-}
-
-// grid: (Nf * Nf, masks, B), 64 threads.  The test ((double)s - mu) / denom >= tau is monotone in s (IEEE subtraction and
-// division are), so the smallest float that passes, found by a search over the floats in order (64 places a step), decides it
-// exactly.  A set that holds an infinity or a NaN has a mean or a deviation that is not a number, and no score passes,
-// infinite ones included.  Also clears the kept counts of the mask's rows, to which k_link_blocks adds.
-__global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf, int Sb,
-                                                   double tau_near, double tau_far, const double* __restrict__ devs,
-                                                   const float* __restrict__ tops, const int32_t* __restrict__ rows,
-                                                   PairStat* __restrict__ stats, int32_t* __restrict__ counts) {
-    extern __shared__ double sh[];
-    const int lane = threadIdx.x;
-    const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
-    for (int r = (int)blockIdx.x * 64 + lane; r < Sb; r += (int)gridDim.x * 64) counts[p.mask * Sb + r] = 0;
-    if (!p.judged) return;
+__device__ __forceinline__ float highest(const float* __restrict__ tops, int Nt) {      // (one wavefront)
+    const int lane = threadIdx.x & 63;
     float top = __builtin_nanf("");
     for (int v0 = lane; v0 < Nt; v0 += 64 * 16) {
         float x[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = tops[p.pair * Nt + min(v0 + 64 * e, Nt - 1)];
+        for (int e = 0; e < 16; ++e) x[e] = tops[min(v0 + 64 * e, Nt - 1)];
 #pragma unroll
         for (int e = 0; e < 16; ++e) top = fmaxf(top, x[e]);
     }
     for (int off = 32; off > 0; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
-    const double denom = sqrt(ordered_sum(devs + p.pair * Nt, Nt, sh) / window_size(Nt, p.w)) + 1e-6;
-    const double mu = stats[p.pair].mu;
-    const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
+    return top;
+}
+constexpr int kRun = 16;                  // rows of a run: what k_link_sums remembers of the place of a column's highest score
+__device__ __forceinline__ void set_stats(const float* __restrict__ S, const PairAt& p, int N, int Nt, double mu, double denom, double tau,
+                                          float top, const float* __restrict__ tops, const int32_t* __restrict__ rows, PairStat* __restrict__ stats) {
+    const int lane = threadIdx.x & 63;
     auto passes = [&](float s) { return ((double)s - mu) / denom >= tau; };
     // images lo .. none - 1 are the finite floats; the first that passes lies in [lo, lo + span]
     const uint32_t none = score_image(3.402823466e38f) + 1u;
@@ -315,11 +237,10 @@ __global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ sco
     int best = -1;
     if (!(top >= threshold)) {
         // nothing passes: the highest score, the first in row-major order on ties (-0 equals +0; in a set of NaN alone any is).  A lane
-        // takes a column that holds it and looks at the kAhead rows that are known to; a later column counts only by an earlier
+        // takes a column that holds it and looks at the run of rows that is known to; a later column counts only by an earlier
         // row.  (Column after column, a row of the wavefront's after the other, cost 0.5 us for each that shares the highest score:
         // scores that depend on their row alone, nothing passing, 8 x 1024 tokens 587 us where this takes 123, 4 x 4096 7412 / 410.)
         int best_u = top == top ? Nt : 0, best_v = 0;
-        const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
         for (int v0 = lane; v0 < Nt + lane; v0 += 64 * 8) {
             float x[8];
             int first[8];
@@ -340,12 +261,12 @@ __global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ sco
                 }
                 if (!__any(asks)) continue;
                 const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
-                float s[kAhead];
+                float s[kRun];
 #pragma unroll
-                for (int k = 0; k < kAhead; ++k) s[k] = S[(int64_t)min(max(u0 + k, lo), hi) * N + vc];
+                for (int k = 0; k < kRun; ++k) s[k] = S[(int64_t)min(max(u0 + k, lo), hi) * N + vc];
                 int at = Nt;
 #pragma unroll
-                for (int k = kAhead - 1; k >= 0; --k)
+                for (int k = kRun - 1; k >= 0; --k)
                     if (asks && u0 + k >= lo && u0 + k <= hi && s[k] == top) at = u0 + k;
                 int least = at;
                 for (int off = 32; off > 0; off >>= 1) least = min(least, __shfl_xor(least, off));
@@ -363,11 +284,180 @@ __global__ __launch_bounds__(64) void k_link_stats(const float* __restrict__ sco
     }
 }
 
+// grid: (Nf * Nf * ceil(Nt / 64), masks, B).  sums, devs, tops, rows: [B * masks][Nf * Nf][Nt]; a column's highest score
+// and the first run of kRun rows that holds it, for the safeguard.
+// A column's rows are walked over the union of the workgroup's windows, so that all lanes read one row; a row outside a
+// lane's own window adds +0.0, which leaves its running sum bit for bit as it is (it starts at +0.0 and is never -0.0).
+// At 8 x 1024 tokens 672 workgroups have work, so a wavefront that did it all alone (one to a SIMD at most) would pay for every
+// wait and every instruction one after the other: 20 and 29 us, and 10 for the statistics in a launch of their own.  Only the
+// additions have to be serial, so kFeeders wavefronts fetch the rows and lay them out in LDS, kRun rows in turn, and
+// one adds up the round before.  Three feeders: 15 us, and 32 with the statistics, of which the two chains of 1024 sums and what they
+// wait for take 18; 256 tokens a frame (8 frames) 10.8, 11.8 and 6.4 -> 7.6 and 12.  (More rows on their way, in registers or in
+// LDS, up to four rounds: 16 to 18 and 33 to 45.)  Where workgroups wait for a place a feeder each is enough, and more of them
+// are in flight: whole calls, alone / three feeders / one, by the number of workgroups, 192: 128 / 98 / 126 us; 384: 335 / 309 / 389;
+// 672: 101 / 89 / 104; 880: 61.4 / 54.7 / 57.2; 1344: 70.1 / 68.8 / 70.0; 1680: 102 / 104 / 98; 2024: 78.7 / 77.5 / 72.4; 2394: 120 / 112 / 108;
+// 3720: 101 / 111 / 100; 6486: 98.1 / 98.9 / 87.8.  Drawn at six a compute unit, what the LDS of three feeders lets it hold.
+// Pass 1: the workgroup that is last of its pair to store its sums forms the pair's statistics (arrivals are counted in the
+// `best` of the pair, which pass 0 clears); nobody waits for another.  Pass 0 also clears the kept counts of the mask's rows, to
+// which k_link_blocks adds.
+constexpr int64_t kSumGrid = 6 * 256;
+template <int PASS, int kFeeders>
+__global__ __launch_bounds__(64 * (kFeeders + 1)) void k_link_sums(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf, int Sb,
+                                                                   double tau_near, double tau_far, double* __restrict__ sums, double* devs,
+                                                                   float* __restrict__ tops, int32_t* __restrict__ rows, PairStat* stats,
+                                                                   int32_t* __restrict__ counts) {
+    constexpr int kSumThreads = 64 * (kFeeders + 1), kRound = kFeeders * kRun;
+    extern __shared__ double s_sums[];
+    __shared__ float s_rows[2][kRound][64];
+    __shared__ float s_top[kFeeders][64];
+    __shared__ int s_row[kFeeders][64];
+    __shared__ int s_last;
+    const int tiles = (Nt + 63) / 64;
+    const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
+    const PairAt p = pair_at(tab, Nf, pair);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if constexpr (PASS == 0) {
+        for (int r = (int)(blockIdx.x * kSumThreads + threadIdx.x); r < Sb; r += (int)gridDim.x * kSumThreads) counts[p.mask * Sb + r] = 0;
+        if (v0 == 0 && threadIdx.x == 0) stats[p.pair].best = 0;
+    }
+    if (!p.judged) return;
+    const int v = v0 + lane, vc = min(v, Nt - 1), v_last = min(v0 + 63, Nt - 1);
+    const int lo = max(0, vc - p.w), hi = min(Nt - 1, vc + p.w);
+    const int u_first = max(0, v0 - p.w), u_last = min(Nt - 1, v_last + p.w);      // of the workgroup
+    const int every_first = max(0, v_last - p.w), every_last = min(Nt - 1, v0 + p.w);      // rows in all its windows
+    const int rounds = (u_last - u_first) / kRound + 1;
+    const float* S = scores + p.mask * N * N + ((int64_t)p.i * Nt) * N + (int64_t)p.j * Nt;
+    // a feeder's rows of a round: u_first + round * kRound + wave * kRun ..  (past the window: its last row again)
+    const uint32_t row_bytes = (uint32_t)N * 4u, at_last = (uint32_t)u_last * row_bytes + (uint32_t)vc * 4u;
+    uint32_t at = (uint32_t)(u_first + wave * kRun) * row_bytes + (uint32_t)vc * 4u;      // (a frame's rows: below 2^32 bytes)
+    float x[kRun];
+    auto fetch = [&]() {
+#pragma unroll
+        for (int e = 0; e < kRun; ++e) x[e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(S) + min(at + (uint32_t)e * row_bytes, at_last));
+        at += (uint32_t)kRound * row_bytes;
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto first_rows = [&]() {
+        if (wave < kFeeders) fetch();
+    };
+    if constexpr (PASS == 1) lay_out<false, kSumThreads>(sums + p.pair * Nt, Nt, s_sums, first_rows);
+    else first_rows();
+    double acc = 0.0;
+    float top = __builtin_nanf("");
+    int row = 0;                                                     // of the first run of rows that holds `top`
+    auto feed = [&](int round) {
+        const int u0 = u_first + round * kRound + wave * kRun;
+        float most = __builtin_nanf("");                             // (fmaxf passes NaN by: it ranks below every number)
+        float (*out)[64] = &s_rows[round & 1][wave * kRun];
+#pragma unroll
+        for (int e = 0; e < kRun; ++e) out[e][lane] = x[e];
+        if constexpr (PASS == 0) {
+            if (u0 >= every_first && u0 + kRun - 1 <= every_last) {  // the same in every lane
+#pragma unroll
+                for (int e = 0; e < kRun; ++e) most = fmaxf(most, x[e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < kRun; ++e) most = fmaxf(most, u0 + e >= lo && u0 + e <= hi ? x[e] : __builtin_nanf(""));      // (hi <= u_last)
+            }
+            const bool higher = most > top || (top != top && most == most);
+            top = higher ? most : top;
+            row = higher ? u0 : row;
+        }
+    };
+    double mu = 0.0;                                                 // (of the wavefront that adds)
+    auto term = [&](float x) {
+        if constexpr (PASS == 0) return (double)x;
+        const double dev = (double)x - mu;
+        return dev * dev;
+    };
+    auto add = [&](int round) {
+        const float (*in)[64] = s_rows[round & 1];
+        float y[2][kRun];
+        auto read = [&](int f) {
+#pragma unroll
+            for (int e = 0; e < kRun; ++e) y[f & 1][e] = in[f * kRun + e][lane];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read(0);
+#pragma unroll
+        for (int f = 0; f < kFeeders; ++f) {
+            if (f + 1 < kFeeders) read(f + 1);
+            const int u0 = u_first + round * kRound + f * kRun;
+            if (u0 >= every_first && u0 + kRun - 1 <= every_last) {  // the same in every lane
+#pragma unroll
+                for (int e = 0; e < kRun; ++e) acc = acc + term(y[f & 1][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < kRun; ++e) {
+                    const double t = term(y[f & 1][e]);
+                    acc = acc + (u0 + e >= lo && u0 + e <= hi ? t : 0.0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // A round is laid out while the one before it is added, so that a barrier a round is enough.
+    if (wave < kFeeders) {
+        feed(0);
+        fetch();
+        __syncthreads();
+        for (int round = 0; round < rounds; ++round) {
+            if (round + 1 < rounds) feed(round + 1);
+            fetch();
+            __syncthreads();
+        }
+    } else {
+        __syncthreads();
+        if constexpr (PASS == 1) mu = ordered_sum(Nt, s_sums) / window_size(Nt, p.w);
+        for (int round = 0; round < rounds; ++round) {
+            add(round);
+            __syncthreads();
+        }
+    }
+    if constexpr (PASS == 0) {
+        if (wave < kFeeders) {
+            s_top[wave][lane] = top;
+            s_row[wave][lane] = row;
+        }
+        __syncthreads();
+        if (wave != kFeeders || v >= Nt) return;
+#pragma unroll
+        for (int f = 0; f < kFeeders; ++f) {
+            const float t = s_top[f][lane];
+            const int r = s_row[f][lane];
+            const bool higher = t > top || (top != top && t == t);
+            row = higher || (t == top && r < row) ? r : row;
+            top = higher ? t : top;
+        }
+        sums[p.pair * Nt + v] = acc;
+        tops[p.pair * Nt + v] = top;
+        rows[p.pair * Nt + v] = row;
+    } else {
+        if (wave == kFeeders) {
+            // Agent-scope stores are written through to where all XCDs see them, and are waited for before they are counted; the
+            // last workgroup reads them by agent-scope loads, behind the count.  (A release fence instead writes back all that the
+            // XCD's L2 holds, 672 times: 75 us.)
+            if (v < Nt) __hip_atomic_store(&devs[p.pair * Nt + v], acc, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            if (lane == 0) s_last = __hip_atomic_fetch_add(&stats[p.pair].best, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == tiles - 1;
+        }
+        __syncthreads();
+        if (!s_last) return;
+        lay_out<true, kSumThreads>(devs + p.pair * Nt, Nt, s_sums, []() {});
+        if (wave == 0) s_top[0][0] = highest(tops + p.pair * Nt, Nt);
+        __syncthreads();
+        if (wave != kFeeders) return;
+        const double denom = sqrt(ordered_sum(Nt, s_sums) / window_size(Nt, p.w)) + 1e-6;
+        const double tau = ((p.flags >> 1) & 3) == 1 ? tau_near : tau_far;     // class 1 = NEAR (decay length >= block size)
+        set_stats(S, p, N, Nt, mu, denom, tau, s_top[0][0], tops, rows, stats);
+    }
+}
+
 // Link bytes and the density rule in one pass over the scores.  A workgroup owns a query block (Bs rows) and 1024 key columns;
 // a thread takes four consecutive columns, of every kGroups-th row, and keeps their numbers of links in the bytes of one
 // word (a count is at most 128), so that a wavefront reads 1 KB runs and writes 256-byte ones and the link bytes are not read
 // again; only scores inside some row's window are read.  Bound by memory: at 8192 tokens 41 us, 67 MB written and some 65 MB
-// read.  (Link bytes, safeguard and density in three launches took 90 us, the whole call 168 us where it takes 101.)
+// read.  (Link bytes, safeguard and density in three launches took 90 us.)
 // kGroups = 4 (1024 threads) up to kSmallGrid workgroups, two per compute unit: calls at 128 workgroups 42 us against 49, at 512
 // 152 against 171 (block size 128) and 62 against 62 (32), at 750 73 against 68.  grid: (Sb * ceil(N / 1024), masks, B).
 constexpr int kBlockCols = 1024;
@@ -697,11 +787,16 @@ hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uin
     float* tops = reinterpret_cast<float*>(stats + (size_t)B * masks * Nf * Nf);
     int32_t* rows = reinterpret_cast<int32_t*>(tops + columns);
     const unsigned pairs = (unsigned)Nf * Nf, cols = (Nt + 63) / 64;
+    int64_t judged = 0;                                     // pairs of a mask
+    for (int t = 2; t < Nf; ++t) judged += (tab.flags[t] & 1) ? 2 * (Nf - t) : 0;
     const size_t lds = (size_t)((Nt + 15) & ~15) * sizeof(double);
-    hipLaunchKernelGGL(k_link_sums<0>, dim3(pairs * cols, masks, B), dim3(64), 0, s, scores, tab, N, Nt, Nf, sums, devs, tops, rows, stats);
-    hipLaunchKernelGGL(k_link_sums<1>, dim3(pairs * cols, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, sums, devs, tops, rows, stats);
-    hipLaunchKernelGGL(k_link_stats, dim3(pairs, masks, B), dim3(64), lds, s, scores, tab, N, Nt, Nf, g.Sb, tau_near, tau_far,
-                       devs, tops, rows, stats, counts);
+    auto sum_up = [&](auto pass0, auto pass1, int threads) {
+        const dim3 grid(pairs * cols, masks, B);
+        hipLaunchKernelGGL(pass0, grid, dim3(threads), 0, s, scores, tab, N, Nt, Nf, g.Sb, tau_near, tau_far, sums, devs, tops, rows, stats, counts);
+        hipLaunchKernelGGL(pass1, grid, dim3(threads), lds, s, scores, tab, N, Nt, Nf, g.Sb, tau_near, tau_far, sums, devs, tops, rows, stats, counts);
+    };
+    if (judged * cols * masks * B <= kSumGrid) sum_up(k_link_sums<0, 3>, k_link_sums<1, 3>, 256);
+    else sum_up(k_link_sums<0, 1>, k_link_sums<1, 1>, 128);
     const dim3 grid((unsigned)g.Sb * ((N + kBlockCols - 1) / kBlockCols), masks, B);
     if ((int64_t)grid.x * masks * B <= kSmallGrid)
         hipLaunchKernelGGL(k_link_blocks<4>, grid, dim3(1024), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
