@@ -503,20 +503,32 @@ __device__ __forceinline__ void load_wave_row(const uint64_t* __restrict__ class
         r.n_far += __popcll(r.m_far[i]);
     }
 }
-// the row's keep words and count: forced blocks, keys that reach c_near, FAR keys that reach c_far
+// a row's keep words, one per lane (a store for each slot's pair costs three times the instructions), and its count
+template <int kSlots, class Kept>
+__device__ __forceinline__ void store_keep_words(int64_t row, int Sb, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts, Kept&& kept_of) {
+    static_assert(2 * kSlots <= 64, "a word per lane");
+    const int lane = lane_id(), words = (Sb + 31) / 32;
+    int kept = 0;
+    uint32_t word = 0u;
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+        const uint64_t m = kept_of(i);                            // (past the row's end: 0)
+        kept += __popcll(m);
+        asm("v_writelane_b32 %0, %1, %2" : "+v"(word) : "s"((uint32_t)m), "n"(2 * i));
+        asm("v_writelane_b32 %0, %1, %2" : "+v"(word) : "s"((uint32_t)(m >> 32)), "n"(2 * i + 1));
+    }
+    if (lane < words) keepbits[row * words + lane] = word;
+    if (lane == 0) counts[row] = kept;
+}
+// forced blocks, keys that reach c_near, FAR keys that reach c_far
 template <int kSlots>
 __device__ __forceinline__ void store_wave_row(const WaveRow<kSlots>& r, uint64_t c_near, uint64_t c_far, bool two_ratio, int64_t row,
                                                int Sb, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts) {
-    const int lane = lane_id(), words = (Sb + 31) / 32;
-    int kept = 0;
-#pragma unroll
-    for (int i = 0; i < kSlots; ++i) {
+    store_keep_words<kSlots>(row, Sb, keepbits, counts, [&](int i) {
         uint64_t m = r.m_forced[i] | __ballot(r.w.c[i] >= c_near);
         if (two_ratio) m |= __ballot(r.w.c[i] >= c_far) & r.m_far[i];
-        kept += __popcll(m);
-        if (lane < 2 && 2 * i + lane < words) keepbits[row * words + 2 * i + lane] = lane ? (uint32_t)(m >> 32) : (uint32_t)m;
-    }
-    if (lane == 0) counts[row] = kept;
+        return m;
+    });
 }
 __device__ __forceinline__ int bits_of(int Sb) {                        // of a key-block index
     int bits = 0;
@@ -571,12 +583,48 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 
 // Cumulative mass for rows of at most 1024 key blocks, one wave per row.  The rule is a sum of fp64 exponentials one by
 // one in score order, compared with tau times the whole sum: a serial chain behind a sort, if taken literally (k_select:
-// 208 us at 40 x 591 rows; this kernel 32 with scores of a smooth field, 20 to 160 over other distributions).  Only the place where the prefix crosses the target is wanted, so it is
+// 208 us at 40 x 591 rows; this kernel 23 with scores of a smooth field, more over other distributions; the vector ALU is busy for
+// 84 % of it, so what counts is instructions a row: 538 before the keys were made without a test each and the keep words
+// stored as one register, 29 us).  Only the place where the prefix crosses the target is wanted, so it is
 // looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
 // bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) is decided by
 // the literal chain, in this wave.
 // LDS per wave: keys[cap] u64 | mass[cap] f64 over bins[256] u64 (the chain comes when the bins are done with), cap a power of two
 // >= the largest selectable count of a row.  A quarter more rows in flight than with bins of their own, at 256 keys.
+//
+// One row in registers: keys as in WaveRow with all blocks in front of FAR ones, made for every position of the row; m_sel says which
+// of them count.
+template <int kSlots>
+struct MassRow {
+    uint64_t c[kSlots], m_sel[kSlots], m_forced[kSlots];
+    int n;
+};
+template <int kSlots>
+__device__ __forceinline__ void load_mass_row(const uint64_t* __restrict__ class_bits, const float* __restrict__ scores, int64_t row,
+                                              int qb, int Sb, MassRow<kSlots>& r) {
+    const int lane = lane_id();
+    const char* srow = reinterpret_cast<const char*>(scores + row * Sb);
+    const uint64_t* cb = class_bits + (int64_t)qb * (kSlots * 3);
+    float sc[kSlots];                             // every load before the first is used; past the row's end its last entry
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) sc[i] = *reinterpret_cast<const float*>(srow + min((uint32_t)lane * 4u + (uint32_t)i * 256u, (uint32_t)(Sb - 1) * 4u));
+    r.n = 0;
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+        r.m_sel[i] = cb[i * 3 + 0];
+        r.m_forced[i] = cb[i * 3 + 2];
+        r.n += __popcll(r.m_sel[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+        const uint32_t v = score_image(sc[i]), block = 0x7fffffffu - (uint32_t)(i * 64) - (uint32_t)lane;      // (the complement of its index)
+        r.c[i] = ((uint64_t)(0x80000000u | (v >> 1)) << 32) | ((v << 31) | block);
+    }
+}
+template <int kSlots>
+__device__ __forceinline__ uint64_t kept_of_mass_row(const MassRow<kSlots>& r, int i, uint64_t threshold) {
+    return r.m_forced[i] | (__ballot(r.c[i] >= threshold) & r.m_sel[i]);
+}
 constexpr int kBins = 256, kMaxTaken = 8;      // keys taken one by one from a bin
 __host__ __device__ inline size_t select_mass_lds_bytes(int cap) { return (size_t)cap * 8 + (cap > kBins ? (size_t)cap * 8 : kBins * 8); }
 
@@ -741,7 +789,7 @@ __device__ __forceinline__ Crossing mass_crossing(int n, float top, float bin_sc
 // The threshold of the cumulative-mass rule: every selectable key that reaches it is kept.  `mine`: select_mass_lds_bytes(cap) of LDS
 // that belong to this wave.
 template <int kSlots, int kLevels>
-__device__ __forceinline__ uint64_t select_mass_row(const WaveRow<kSlots>& r, const SelectArgs& a, unsigned char* mine, int cap) {
+__device__ __forceinline__ uint64_t select_mass_row(const MassRow<kSlots>& r, const SelectArgs& a, unsigned char* mine, int cap) {
     const int lane = lane_id();
     uint64_t* keys = reinterpret_cast<uint64_t*>(mine);
     double* mass = reinterpret_cast<double*>(mine + (size_t)cap * 8);
@@ -753,7 +801,7 @@ __device__ __forceinline__ uint64_t select_mass_row(const WaveRow<kSlots>& r, co
 #pragma unroll
         for (int i = 0; i < kSlots; ++i) {
             const int pos = at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(r.m_sel[i] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)r.m_sel[i], 0u));
-            if (__builtin_amdgcn_inverse_ballot_w64(r.m_sel[i])) keys[pos] = r.w.c[i];
+            if (__builtin_amdgcn_inverse_ballot_w64(r.m_sel[i])) keys[pos] = r.c[i];
             at += __popcll(r.m_sel[i]);
         }
         wave_lds_fence();
@@ -812,10 +860,10 @@ __global__ __launch_bounds__(kThreads) void k_select_mass(const uint64_t* __rest
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + wave;
     if (row >= rows_total) return;
-    WaveRow<kSlots> r;
-    load_wave_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, a, r);
+    MassRow<kSlots> r;
+    load_mass_row<kSlots>(class_bits, scores, row, (int)(row % Sb), Sb, r);
     const uint64_t threshold = select_mass_row<kSlots, kLevels>(r, a, smem + (size_t)wave * select_mass_lds_bytes(cap), cap);
-    store_wave_row<kSlots>(r, threshold, ~0ull, false, row, Sb, keepbits, counts);
+    store_keep_words<kSlots>(row, Sb, keepbits, counts, [&](int i) { return kept_of_mass_row(r, i, threshold); });
 }
 
 // The whole mask in one launch where it has at most 32 rows of at most 32 key blocks (a row is one lane mask): a workgroup of
@@ -842,13 +890,19 @@ __global__ __launch_bounds__(64 * kShortWaves) void k_mask_short(const uint64_t*
         const int qb = i * kShortWaves + wave;
         kept[i] = 0ull;
         if (qb >= Sb) continue;                                            // the same in every lane
-        WaveRow<kSlots> r;
-        load_wave_row<kSlots>(class_bits, scores, mask_id * Sb + qb, qb, Sb, a, r);
-        uint64_t c_near, c_far = ~0ull;
-        if constexpr (kMass) c_near = select_mass_row<kSlots, 3>(r, a, smem + (size_t)wave * select_mass_lds_bytes(cap), cap);
-        else select_wave_row<kSlots>(r, bits_of(Sb), a, reinterpret_cast<uint64_t*>(smem) + wave * 64, &c_near, &c_far);
-        kept[i] = r.m_forced[0] | __ballot(r.w.c[0] >= c_near);
-        if (!kMass && a.two_ratio) kept[i] |= __ballot(r.w.c[0] >= c_far) & r.m_far[0];
+        if constexpr (kMass) {
+            MassRow<kSlots> r;
+            load_mass_row<kSlots>(class_bits, scores, mask_id * Sb + qb, qb, Sb, r);
+            const uint64_t threshold = select_mass_row<kSlots, 3>(r, a, smem + (size_t)wave * select_mass_lds_bytes(cap), cap);
+            kept[i] = kept_of_mass_row(r, 0, threshold);
+        } else {
+            WaveRow<kSlots> r;
+            load_wave_row<kSlots>(class_bits, scores, mask_id * Sb + qb, qb, Sb, a, r);
+            uint64_t c_near, c_far;
+            select_wave_row<kSlots>(r, bits_of(Sb), a, reinterpret_cast<uint64_t*>(smem) + wave * 64, &c_near, &c_far);
+            kept[i] = r.m_forced[0] | __ballot(r.w.c[0] >= c_near);
+            if (a.two_ratio) kept[i] |= __ballot(r.w.c[0] >= c_far) & r.m_far[0];
+        }
         if (lane == 0) s_count[qb] = __popcll(kept[i]);
     }
     __syncthreads();
@@ -1174,12 +1228,16 @@ hipError_t launch_select_zscore(const uint8_t* class_map, const float* scores, i
 // one contiguous run.
 __device__ __forceinline__ void emit_row(uint32_t wv, int Sb, long long pos, int32_t* __restrict__ out, int64_t capacity) {
     const int lane = lane_id(), stretches = (Sb + 63) / 64;
+    char* at = reinterpret_cast<char*>(out + pos);                          // (the same in every lane; places of the row are 32-bit offsets)
+    const int64_t left = capacity - pos;
+    const uint32_t room = left <= 0 ? 0u : left < 0x7fffffff ? (uint32_t)left : 0x7fffffffu;
+    uint32_t done = 0u;
     for (int i = 0; i < stretches; ++i) {                                  // wave-uniform
         const uint32_t lo = __builtin_amdgcn_readlane(wv, 2 * i), hi = __builtin_amdgcn_readlane(wv, 2 * i + 1);
-        const uint32_t mine = (lane < 32) ? (lo >> lane) : (hi >> (lane - 32));
-        const long long p = pos + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
-        if ((mine & 1u) && p < capacity) out[p] = i * 64 + lane;
-        pos += __popc(lo) + __popc(hi);
+        const uint64_t m = ((uint64_t)hi << 32) | lo;
+        const uint32_t place = (uint32_t)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, done));
+        if (__builtin_amdgcn_inverse_ballot_w64(m) && place < room) *reinterpret_cast<int32_t*>(at + place * 4u) = i * 64 + lane;
+        done += (uint32_t)__popcll(m);
     }
 }
 
@@ -1210,11 +1268,14 @@ __global__ __launch_bounds__(64) void k_emit_wave(const uint32_t* __restrict__ k
     emit_row(wv, Sb, before, colidx + mask_id * capacity, capacity);
 }
 
-// Four rows of one mask per workgroup, a wave each, whose bitmaps are on their way while the workgroup adds up the counts of the
-// mask's earlier rows, once for all four.  (Each wave for itself: 13 us of launch at 40 masks of 591 rows where this takes 11;
-// 8 masks of 2000 rows, whole call, 148 -> 144.  Eight rows: 1 us less at 40 x 591, up to 0.3 us more at 4 x 591; sixteen: 2 more.)
-// grid: B * masks * ceil(Sb / 4).
-constexpr int kEmitRows = 4;
+// kRows rows of one mask per workgroup, whose bitmaps are on their way while the workgroup adds up the counts of the mask's earlier
+// rows, once for all of them.  (Each wave for itself: 13 us of launch at 40 masks of 591 rows where four rows take 11.7 and eight 10.6;
+// 8 masks of 2000 rows, whole call, 148 -> 144.)  Eight where many rows wait, four where more workgroups count for more: whole
+// calls, four / eight / sixteen, 3716 rows 13.0 / 13.6 / 15.5 us, 4440 11.5 / 11.8 / 12.6, 7608 17.6 / 17.2 / 17.7, 23 640 34.3 / 33.2 / 32.8
+// and 36.6 / 35.1 / 35.2, uniform rule at 35 460 16.4 / 14.7 / 14.2.
+// grid: B * masks * ceil(Sb / kRows).
+constexpr int64_t kEmitEightRows = 6000;
+template <int kEmitRows>
 __global__ __launch_bounds__(kThreads) void k_emit_rows(const uint32_t* __restrict__ keepbits, const int32_t* __restrict__ counts, int Sb,
                                                         int shared, int32_t* __restrict__ rowptr, int32_t* __restrict__ colidx,
                                                         int64_t capacity, int64_t* __restrict__ nnz) {
@@ -1234,11 +1295,13 @@ __global__ __launch_bounds__(kThreads) void k_emit_rows(const uint32_t* __restri
     }
     const int own = (lane < kEmitRows && q0 + lane < Sb) ? counts[src + q0 + lane] : 0;
     int before = 0;                                                        // (at most 2048 rows of 2048 blocks: 32 bits hold it)
-    int c[8];
+    for (int i0 = 0; i0 < q0; i0 += 4 * kThreads) {                        // (once, or twice: q0 < 2048)
+        int c[4];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) c[e] = tid + e * kThreads < q0 ? counts[src + tid + e * kThreads] : 0;      // q0 < 2048
+        for (int e = 0; e < 4; ++e) c[e] = counts[src + min(i0 + e * kThreads + tid, q0 - 1)];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) before += c[e];
+        for (int e = 0; e < 4; ++e) before += i0 + e * kThreads + tid < q0 ? c[e] : 0;
+    }
     before = wave_prefix(before);
     if (lane == 63) s_part[wave] = before;
     __syncthreads();
@@ -1296,8 +1359,9 @@ hipError_t launch_emit(const uint32_t* keepbits, const int32_t* counts, int B, i
         hipLaunchKernelGGL(k_emit_rows_at, dim3((unsigned)((rows_total + kWaves - 1) / kWaves)), dim3(kThreads), 0, s, keepbits, (uint32_t)rows_total,
                            Sb, shared ? 1 : 0, rowptr, colidx, capacity);
     } else if (rows_total >= kWaveSelectPackRows) {
-        hipLaunchKernelGGL(k_emit_rows, dim3((unsigned)((int64_t)B * masks * ((Sb + kEmitRows - 1) / kEmitRows))), dim3(kThreads), 0, s, keepbits,
-                           counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
+        const int per = rows_total >= kEmitEightRows ? 8 : 4;
+        hipLaunchKernelGGL(per == 8 ? k_emit_rows<8> : k_emit_rows<4>, dim3((unsigned)((int64_t)B * masks * ((Sb + per - 1) / per))), dim3(kThreads), 0, s,
+                           keepbits, counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
     } else {
         hipLaunchKernelGGL(k_emit_wave, dim3((unsigned)rows_total), dim3(64), 0, s, keepbits, counts, Sb, shared ? 1 : 0, rowptr, colidx, capacity, nnz);
     }
