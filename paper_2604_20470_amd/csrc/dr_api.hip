@@ -18,7 +18,7 @@ using namespace dr;
 // code this name is only a handle for hipGetSymbolAddress (dr_create resolves it, per device); kernels get the address.
 // Behind it lie the work queues of the attention kernel.
 constexpr size_t kStaticScratchBytes = 16u << 20, kQueueBytes = 256;
-static_assert(kAttnQueues * sizeof(int32_t) <= kQueueBytes, "work queues");
+static_assert(kAttnQueueWords * sizeof(int32_t) <= kQueueBytes, "work queues");
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes + kQueueBytes];
 
 struct dr_ctx {

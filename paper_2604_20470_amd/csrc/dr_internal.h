@@ -106,17 +106,23 @@ struct AttnArgs {
     // scratch of the bf16 MFMA paths: one word per wave of a 128-query work item, non-zero when the fast pass found
     // rows outside the accuracy range of its pre-scaled Q; those items are then taken again with fp32 scaling.
     // NULL: no second pass.
+    // The 256-query kernel at block size 128 leaves lists instead.  First a word per query block (b, h, qb), cleared by the pre-pass and
+    // counted up by the waves that flag it; behind them the flagged blocks of queue x, in no order, from word
+    // 2 x ceil(pairs / kAttnQueues) on (two to a pair at most), their number in the queue words.
     int32_t* flags;              // [B * H * ceil(N / 128) * 4]
-    int32_t* queue;              // [kAttnQueues] work queues of the 256-query kernel; set by its list-merging pre-pass
+    // [3][kAttnQueues] slots drawn from the work queues of the 256-query kernel; flagged items of each; those that the second pass
+    // has drawn.  Set by the list-merging pre-pass.
+    int32_t* queue;
     int32_t cus;                 // compute units of the device
 };
 constexpr int kAttnQueues = 8;   // one per XCD
+constexpr int kAttnQueueWords = 3 * kAttnQueues;
 // Any d in {64,128}, Bs in {32,64,128}, f32 or bf16 storage; fp32 accuracy (32-bit operands split for the bf16 matrix cores).
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s);
 // bf16 storage, d = 128, Bs = 128: MFMA path.  Returns hipErrorNotSupported for other shapes.
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s);
 bool attn_mfma_supported(const AttnArgs& a);
-// The second pass of launch_attn_mfma alone: the items flagged in a.flags, with fp32 exponent scaling.
+// The second pass of launch_attn_mfma_pair at block size 128: the items that it has listed, with fp32 exponent scaling.
 hipError_t launch_attn_mfma_second_pass(const AttnArgs& a, hipStream_t s);
 // bf16 storage, d = 128, Bs = 128, N >= 64: MFMA path that walks pairs of adjacent query blocks (one wave per SIMD,
 // 64 queries per wave); needs gcol / gcount / flags.  Rows it flags must be taken again by the second pass above.
@@ -125,7 +131,7 @@ hipError_t launch_attn_mfma_duo(const AttnArgs& a, int grid, hipStream_t s);    
 bool attn_mfma_pair_supported(const AttnArgs& a);
 // Merged key-block lists of every group of L (2, 4 or 8) consecutive CSR rows: a.gcol (laid out like colidx, a group's
 // entries at the colidx offset of its first row; entry = key block | rows-that-list-it << 28, << 24 for eight) and a.gcount.
-// queue_start >= 0: a.queue is set to that value as well.  flagged_only: only the groups (of 128 rows) that a.flags marks.
+// queue_start >= 0: a.queue is set to that value as well, and the words that count flags are cleared (block size 128).  flagged_only: only the groups (of 128 rows) that a.flags marks.
 hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s, int queue_start = -1, bool flagged_only = false);
 // bf16 storage, d = 128, Bs = 32 or 64: MFMA path that walks the union of the CSR rows of a 128-query group.
 hipError_t launch_attn_mfma_small(const AttnArgs& a, hipStream_t s);

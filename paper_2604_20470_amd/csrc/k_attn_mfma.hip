@@ -381,23 +381,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     attn_item<false>(a, item, smem);
 }
 
-// Second pass: the flagged items only.  Usually none is, so the grid is small and every workgroup looks at its share of
-// the flag words, one item per thread and step (a workgroup per item would spend 28 us at 23 640 items on starting
-// workgroups that leave at once; one item per workgroup and step, 27 us on dependent loads).  Flagged rows come in
-// clusters (the tokens of one object), and a flagged item costs a whole walk, so neighbouring items must not fall to one
-// workgroup: runs of `slots` consecutive items (one per workgroup of an XCD) are dealt to the XCDs in turn.  With
-// contiguous shares the slowest of 1024 workgroups took 5 to 7 items where 229 to 619 of 22 296 were flagged (33 frames of
-// 45 x 80 tokens x 24 heads): 2.55 ms; dealt, the whole call went from 33.4 to 31.4 ms on one box.
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
+// Second pass behind the fast pass above: the flagged items only.  Usually none is, so the grid is small and every workgroup looks at its
+// share of the flag words, one item per thread and step.
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_flagged(AttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ unsigned char s_flagged[kThreads];
-    constexpr int kXcds = 8;                                             // the grid is a multiple of it
-    const int total_items = a.Sb * a.td.H * a.td.B;
-    const int slots = (int)gridDim.x / kXcds, xcd = (int)blockIdx.x % kXcds, slot = (int)blockIdx.x / kXcds;
-    const int runs = (total_items + slots - 1) / slots, mine_runs = (runs - xcd + kXcds - 1) / kXcds;      // this XCD's
-    for (int base = 0; base < mine_runs; base += kThreads) {
-        auto item_of = [&](int j) -> int64_t { return ((int64_t)(base + j) * kXcds + xcd) * slots + slot; };
-        const int64_t mine = item_of((int)threadIdx.x);
+    const int64_t total_items = (int64_t)a.Sb * a.td.H * a.td.B;
+    for (int64_t base = blockIdx.x; base < total_items; base += (int64_t)kThreads * gridDim.x) {
+        const int64_t mine = base + (int64_t)threadIdx.x * gridDim.x;
         int flagged = 0;
         if (mine < total_items) {
             const int4 f = *reinterpret_cast<const int4*>(a.flags + mine * 4);
@@ -406,12 +397,54 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         if (!__syncthreads_or(flagged)) continue;
         s_flagged[threadIdx.x] = (unsigned char)flagged;
         __syncthreads();
-        for (int j = 0; j < kThreads && base + j < mine_runs; ++j) {
+        for (int j = 0; j < kThreads; ++j) {
             if (!s_flagged[j]) continue;          // the same for every thread
-            attn_item<true>(a, (int)item_of(j), smem);
+            attn_item<true>(a, (int)(base + (int64_t)j * gridDim.x), smem);
             __syncthreads();          // the next item's tile loads overwrite LDS that slower waves may still be reading
         }
         __syncthreads();
+    }
+}
+
+// Second pass behind the 256-query kernel, which lists its flagged items by the queue (an eighth of the launch) they lie in.  A flagged
+// item costs a whole walk and they come in clusters (the tokens of one object), so they are drawn one by one, an XCD's workgroups
+// from its own eighth first: neighbouring items, which read the same keys, share an L2.  (Every workgroup for the flagged ones of a
+// fixed share of the items: with 229 of 22 296 flagged, 33 frames of 45 x 80 tokens x 24 heads, one of them took two, with 619
+// three: 1.28 -> 0.87 ms for 229, and a launch without any 4.7 -> 2.6 us.)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    __shared__ int s_item;
+    constexpr int kXcds = kAttnQueues;
+    const int pairs = (a.Sb + 1) / 2 * a.td.H * a.td.B, per = (pairs + kXcds - 1) / kXcds;
+    const int32_t* count = a.queue + kAttnQueues;
+    int listed[kXcds], all = 0;
+#pragma unroll
+    for (int i = 0; i < kXcds; ++i) {
+        listed[i] = min(count[i], 2 * per);
+        all |= listed[i];
+    }
+    if (all == 0) return;
+    for (;;) {
+        if (threadIdx.x == 0) {
+            int item = -1;
+#pragma unroll
+            for (int i = 0; i < kXcds; ++i) {                  // (unrolled: the counts stay in registers)
+                const int x = ((int)blockIdx.x + i) % kXcds;
+                int n = 0;
+#pragma unroll
+                for (int e = 0; e < kXcds; ++e) n = e == x ? listed[e] : n;
+                if (item < 0 && __hip_atomic_load(&a.queue[2 * kAttnQueues + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) {
+                    const int at = atomicAdd(&a.queue[2 * kAttnQueues + x], 1);
+                    if (at < n) item = a.flags[a.Sb * a.td.H * a.td.B + 2 * x * per + at];
+                }
+            }
+            s_item = item;
+        }
+        __syncthreads();
+        const int item = __builtin_amdgcn_readfirstlane(s_item);
+        if (item < 0) return;
+        attn_item<true>(a, item, smem);
+        __syncthreads();          // the next item's tile loads overwrite LDS that slower waves may still be reading
     }
 }
 
@@ -422,35 +455,27 @@ bool attn_mfma_supported(const AttnArgs& a) {
     return a.bf16 && a.td.d == kD && a.Bs == kBs && a.td.stride_n * 2 * kChunkKeys < (1ll << 31);
 }
 
-static hipError_t allow_lds() {
-    for (const void* k : {reinterpret_cast<const void*>(k_attn_mfma), reinterpret_cast<const void*>(k_attn_mfma_second_pass)}) {
-        hipError_t attr = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        if (attr != hipSuccess) return attr;
-    }
-    return hipSuccess;
-}
-
-static void launch_second(const AttnArgs& a, hipStream_t s) {
-    const int total = a.Sb * a.td.H * a.td.B;
-    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min((total + 7) / 8 * 8, 1024)), dim3(kThreads), kLdsBytes, s, a);
-}
+static hipError_t allow_lds(const void* kern) { return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes); }
 
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) {
     if (!attn_mfma_supported(a)) return hipErrorNotSupported;
-    hipError_t attr = allow_lds();
-    if (attr != hipSuccess) return attr;
+    for (const void* k : {reinterpret_cast<const void*>(k_attn_mfma), reinterpret_cast<const void*>(k_attn_mfma_flagged)}) {
+        hipError_t attr = allow_lds(k);
+        if (attr != hipSuccess) return attr;
+    }
     const int total = a.Sb * a.td.H * a.td.B;
     const int grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
     hipLaunchKernelGGL(k_attn_mfma, dim3(grid), dim3(kThreads), kLdsBytes, s, a);
-    if (a.flags) launch_second(a, s);
+    if (a.flags) hipLaunchKernelGGL(k_attn_mfma_flagged, dim3(std::min(total, 1024)), dim3(kThreads), kLdsBytes, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_mfma_second_pass(const AttnArgs& a, hipStream_t s) {
-    if (!attn_mfma_supported(a) || !a.flags) return hipErrorNotSupported;
-    hipError_t attr = allow_lds();
+    if (!attn_mfma_supported(a) || !a.flags || !a.queue) return hipErrorNotSupported;
+    hipError_t attr = allow_lds(reinterpret_cast<const void*>(k_attn_mfma_second_pass));
     if (attr != hipSuccess) return attr;
-    launch_second(a, s);
+    const int total = a.Sb * a.td.H * a.td.B;
+    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min(total, 2 * a.cus)), dim3(kThreads), kLdsBytes, s, a);      // (two fit a CU)
     return hipGetLastError();
 }
 

@@ -442,7 +442,7 @@ __global__ __launch_bounds__(256) void k_group_union(const int32_t* __restrict__
                                                      int64_t colidx_stride, int Sb, int groups,
                                                      int32_t* __restrict__ gcol, int32_t* __restrict__ gcount,
                                                      int32_t* __restrict__ queue, int queue_start,
-                                                     const int32_t* __restrict__ flags, int H) {
+                                                     const int32_t* __restrict__ flags, int H, int32_t* __restrict__ clear, int n_clear) {
     extern __shared__ uint32_t pres[];                 // [L][words]
     __shared__ int s_wave[4];
     const int g = blockIdx.x, m = blockIdx.y, b = blockIdx.z;
@@ -460,7 +460,9 @@ __global__ __launch_bounds__(256) void k_group_union(const int32_t* __restrict__
             any |= flags[(((int64_t)b * H + (masks == 1 ? i >> 2 : m)) * groups + g) * 4 + (i & 3)];
         if (!__syncthreads_or(any)) return;
     }
-    if (queue && blockIdx.x == 0 && m == 0 && b == 0 && tid < kAttnQueues) queue[tid] = queue_start;
+    if (queue && blockIdx.x == 0 && m == 0 && b == 0 && tid < kAttnQueueWords) queue[tid] = tid < kAttnQueues ? queue_start : 0;
+    if (clear)
+        for (int i = ((b * masks + m) * (int)gridDim.x + g) * 256 + tid; i < n_clear; i += (int)(gridDim.x * gridDim.y * gridDim.z) * 256) clear[i] = 0;
     for (int i = tid; i < L * words; i += 256) pres[i] = 0u;
     __syncthreads();
     const int row0 = min(g * L, Sb), row1 = min(g * L + L, Sb);
@@ -560,7 +562,8 @@ hipError_t launch_group_union(int L, const AttnArgs& a, hipStream_t s, int queue
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(kern, grid, dim3(256), lds, s, a.rowptr, a.colidx, a.colidx_stride, a.Sb, groups, a.gcol, a.gcount,
-                           queue_start >= 0 ? a.queue : nullptr, queue_start, flagged_only ? a.flags : nullptr, a.td.H);
+                           queue_start >= 0 ? a.queue : nullptr, queue_start, flagged_only ? a.flags : nullptr, a.td.H,
+                           queue_start >= 0 && a.Bs == 128 ? a.flags : nullptr, a.Sb * a.td.H * a.td.B);
         return hipGetLastError();
     };
     if (L == 8) return launch(k_group_union<8>);
