@@ -25,6 +25,8 @@
 #include "attn_mfma_common.h"
 #include "dr_internal.h"
 
+#include <type_traits>
+
 namespace dr {
 namespace {
 
@@ -51,14 +53,16 @@ struct Plan {
     static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : 4 / kQ;        // streams of key tiles
     static constexpr int kThreads = 64 * kQ * kS;
     static constexpr int kTileBytes = 32 * (kAlone ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
-    static constexpr int kT = !kAlone && ((BF16 && D == 64) || (!BF16 && D == 64 && kS == 1)) ? 2 : 1;   // 32-key tiles per stream and stage
+    // bf16 rows go to LDS as they are, straight from memory, a stage of 64 keys ahead
+    static constexpr bool kDirect = BF16 && D == 64 && !kAlone;
+    static constexpr int kT = !kAlone && D == 64 && kS == 1 ? 2 : 1;      // 32-key tiles per stream and stage
     static constexpr int kTiles = kS * kT;                          // of a stage
     static constexpr int kRows = kAlone ? 32 : kTiles * 32;         // of an LDS region
     static constexpr int kStageBytes = kTiles * kTileBytes;
     // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide its vector instructions behind: they go
     // between the matrix instructions, with a second buffer, where two fit
-    static constexpr int kBuffers = !kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024 ? 2 : 1;
-    static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : BF16 && D == 64 && BS == 128 ? 4 : 2;      // wavefronts, at least
+    static constexpr int kBuffers = kDirect || (!kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024) ? 2 : 1;
+    static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : kDirect ? 4 : 2;      // wavefronts, at least
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
     static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainRows * kPlainKeys);
     static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
@@ -376,14 +380,15 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 
     const uint32_t lds0 = lds_addr(smem);
     const uint32_t v_base = P::kAlone ? (uint32_t)ws * P::kTileBytes : (uint32_t)P::kIn * kPart;
+    const uint32_t stream = P::kDirect ? (uint32_t)(ws * P::kT * 32 * P::kRowBytes) : 0u;      // (the others add it to a tile's place)
     uint32_t k_addr[kKS], v_addr[kDB];
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) k_addr[ks] = lds0 + l32 * P::kRowBytes + k_piece<D>(ks * 2 + half, l32) * 16;
+    for (int ks = 0; ks < kKS; ++ks) k_addr[ks] = lds0 + stream + l32 * P::kRowBytes + k_piece<D>(ks * 2 + half, l32) * 16;
     {
         const int v_e = (lane & 15) >> 2, v_c = lane & 3, v_grp = (lane >> 4) & 1;
 #pragma unroll
         for (int db = 0; db < kDB; ++db)
-            v_addr[db] = lds0 + v_base + (half * 4 + v_e) * P::kRowBytes + v_piece<D>(db * 4 + v_grp * 2 + (v_c >> 1), v_e) * 16 + (v_c & 1) * 8;
+            v_addr[db] = lds0 + v_base + stream + (half * 4 + v_e) * P::kRowBytes + v_piece<D>(db * 4 + v_grp * 2 + (v_c >> 1), v_e) * 16 + (v_c & 1) * 8;
     }
 
     // softmax of a logit tile (keys x queries) and its share of O; `tile`: LDS offset of its values
@@ -522,6 +527,82 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             if (j + 1 < own) fetch_own(j + 1);
             use_tile(s, valid, 0u);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    } else if constexpr (P::kDirect) {
+        // Stage g = rows 64 g .. of the listed blocks one after the other, two buffers: the next stage's rows are on their way, without
+        // a register, while this one is multiplied, and a barrier a stage keeps the four wavefronts together.  A wavefront fetches
+        // sixteen rows of K and of V, eight rows an instruction; the swizzles are folded into the lanes' addresses.
+        static_assert(P::kTiles == 2 && P::kRowUnits == 8 && P::kThreads == 256, "stages of 64 rows");
+        constexpr int kStagesPerBlock = BS / 64;
+        const int n_stages = it.n_list * kStagesPerBlock;
+        auto row_of = [&](int g) {             // clamped: a malformed list cannot address outside K / V
+            const int e = g / kStagesPerBlock;
+            if (e - wbase >= 64) {             // wavefront-uniform
+                wbase = e;
+                win = it.list[min(wbase + lane, it.n_list - 1)];
+                asm volatile("" : "+v"(win));
+            }
+            return min(max(__builtin_amdgcn_readlane(win, e - wbase), 0), a.Sb - 1) * BS + g % kStagesPerBlock * 64;
+        };
+        auto to_lds = [&](const char* from, uint32_t to) {      // sixteen bytes a lane; counted by hand
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from), "s"(to) : "memory", "m0");
+        };
+        const char *from_k[2], *from_v[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int r = wave * 16 + i * 8 + (lane >> 3);
+            from_k[i] = it.K + (int64_t)r * it.row_bytes + k_piece<D>(lane & 7, r) * 16;      // (the swizzles are their own inverses)
+            from_v[i] = it.V + (int64_t)r * it.row_bytes + v_piece<D>(lane & 7, r) * 16;
+        }
+        const uint32_t to0 = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)wave * 2048u);
+        auto issue = [&](int row0, uint32_t buffer) {
+            const int64_t at = (int64_t)row0 * it.row_bytes;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const char *k = from_k[i] + at, *v = from_v[i] + at;
+                if (row0 + 64 > N) {           // wavefront-uniform: rows past the sequence's end are read again from its last
+                    const int r = wave * 16 + i * 8 + (lane >> 3);
+                    const int64_t back = (int64_t)max(row0 + r - (N - 1), 0) * it.row_bytes;
+                    k -= back;
+                    v -= back;
+                }
+                to_lds(k, to0 + buffer + i * 1024u);
+                to_lds(v, to0 + buffer + kPart + i * 1024u);
+            }
+        };
+        int row_next = 0;
+        if (n_stages > 0) {
+            row_next = row_of(0);
+            issue(row_next, 0u);
+        }
+        auto stage = [&](int g, auto which) {
+            constexpr uint32_t kHere = decltype(which)::value * P::kStageBytes, kThere = P::kStageBytes - kHere;
+            const int row = row_next;
+            DR_WAIT_VMCNT0();                  // this wavefront's rows of the stage have arrived; behind the barrier, everyone's
+            DR_BARRIER();                      // (and everyone has read the stage before, whose place is filled next)
+            if (g + 1 < n_stages) {
+                row_next = row_of(g + 1);
+                issue(row_next, kThere);
+            }
+#pragma unroll
+            for (int c = 0; c < P::kT; ++c) {
+                const uint32_t tile = kHere + (uint32_t)(c * 32 * P::kRowBytes);
+                const int valid = N - row - (ws * P::kT + c) * 32;      // keys of the tile (only the sequence's end has fewer than 32)
+                if (valid <= 0) continue;                               // wavefront-uniform
+                v16f s;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s[j] = 0.f;
+                v8bf kf[kKS];
+#pragma unroll
+                for (int ks = 0; ks < kKS; ++ks) kf[ks] = *(lds_v8)(uintptr_t)(k_addr[ks] + tile);
+#pragma unroll
+                for (int ks = 0; ks < kKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks][0], s, 0, 0, 0);
+                use_tile(s, valid, tile);
+            }
+        };
+        for (int g = 0; g < n_stages; g += 2) {
+            stage(g, std::integral_constant<uint32_t, 0>{});
+            if (g + 1 < n_stages) stage(g + 1, std::integral_constant<uint32_t, 1>{});
         }
     } else if constexpr (P::kBuffers == 2) {
         // One wavefront per SIMD issues in order, so the vector instructions of a tile (the exponentials, the split of its
