@@ -50,18 +50,24 @@ struct Plan {
     // block size 32: nobody shares a wavefront's key tiles, so each walks alone (keys straight to registers, values through
     // an LDS region of its own, no barrier), eight to a workgroup where their regions fit two per SIMD
     static constexpr bool kAlone = BS == 32;
-    static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : 4 / kQ;        // streams of key tiles
+    // Two streams of four query groups and a second buffer: a query block's list takes half as many steps, and a launch of up to one
+    // workgroup a compute unit leaves no SIMD with a single wavefront.  Against one stream (two workgroups of four wavefronts a
+    // compute unit): 48 blocks of 2048 tokens x 3 heads 71.7 -> 53.2 us, 240 blocks 92.1 -> 72.3, 384 258 -> 252, 564 975 -> 903, 720 465 -> 410;
+    // 1320 blocks, which leave 40 to a sixth round, 697 -> 709.  (At block size 64, where two streams are the rule, four measured 44.0 ->
+    // 34.4 at 84 blocks, 75 -> 81 at 320, 531 -> 555 at 1760: they stay two.)
+    static constexpr bool kEight = !BF16 && D == 64 && BS == 128;
+    static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : (kEight ? 8 : 4) / kQ;        // streams of key tiles
     static constexpr int kThreads = 64 * kQ * kS;
     static constexpr int kTileBytes = 32 * (kAlone ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
     // bf16 rows go to LDS as they are, straight from memory, a stage of 64 keys ahead
     static constexpr bool kDirect = BF16 && D == 64 && !kAlone;
-    static constexpr int kT = !kAlone && D == 64 && kS == 1 ? 2 : 1;      // 32-key tiles per stream and stage
+    static constexpr int kT = kDirect && kS == 1 ? 2 : 1;      // 32-key tiles per stream and stage
     static constexpr int kTiles = kS * kT;                          // of a stage
     static constexpr int kRows = kAlone ? 32 : kTiles * 32;         // of an LDS region
     static constexpr int kStageBytes = kTiles * kTileBytes;
     // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide its vector instructions behind: they go
     // between the matrix instructions, with a second buffer, where two fit
-    static constexpr int kBuffers = kDirect || (!kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024) ? 2 : 1;
+    static constexpr int kBuffers = kDirect || kEight || (!kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024) ? 2 : 1;
     static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : kDirect ? 4 : 2;      // wavefronts, at least
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
     static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainRows * kPlainKeys);
@@ -604,7 +610,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             stage(g, std::integral_constant<uint32_t, 0>{});
             if (g + 1 < n_stages) stage(g + 1, std::integral_constant<uint32_t, 1>{});
         }
-    } else if constexpr (P::kBuffers == 2) {
+    } else if constexpr (P::kBuffers == 2 && !P::kEight) {
         // One wavefront per SIMD issues in order, so the vector instructions of a tile (the exponentials, the split of its
         // probabilities, the split of the rows fetched for later tiles) stand between matrix instructions that do not wait for
         // them, some five to each: the softmax of tile g under the logits of tile g + 1, the splits of rows under the products
@@ -906,7 +912,52 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             __syncthreads();
         }
     } else {
+    // a tile's logits, its softmax and its share of O; `at`: LDS offset of the stage
+    auto take_tile = [&](int g, int c, int row, uint32_t at) {
+        const int valid = N - row;                               // keys of the tile (only the sequence's end has fewer than 32)
+        if (!(g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0)) return;      // wavefront-uniform
+        const uint32_t tile = at + (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
+        v16f s;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) s[j] = 0.f;
+        // the fragments of a step are read while the step before is multiplied
+        v8bf kf[2][P::kIn];
+#pragma unroll
+        for (int i = 0; i < P::kIn; ++i) kf[0][i] = *(lds_v8)(uintptr_t)(k_addr[0] + tile + i * kPart);
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            if (ks + 1 < kKS) {
+#pragma unroll
+                for (int i = 0; i < P::kIn; ++i) kf[(ks + 1) & 1][i] = *(lds_v8)(uintptr_t)(k_addr[ks + 1] + tile + i * kPart);
+            }
+            s = mfma_parts<P::kIn, P::kIn>(kf[ks & 1], qf[ks], s);
+        }
+        use_tile(s, valid, tile);
+    };
     if (stages > 0) fetch(0);
+    if constexpr (P::kEight) {
+        // One workgroup of eight wavefronts fills a compute unit, so nobody else runs while it waits: a second buffer, a barrier a
+        // stage, the next stage split and the one after it on its way ahead of this one's products.
+        if (stages > 0) {
+            store(0);
+#pragma unroll
+            for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
+            if (stages > 1) fetch(1);
+        }
+        for (int g = 0; g < stages; ++g) {
+            __syncthreads();                     // the stage is laid out, the one before is consumed
+            int row[P::kT];
+#pragma unroll
+            for (int c = 0; c < P::kT; ++c) {
+                row[c] = row0[c];
+                row0[c] = row0_next[c];
+            }
+            if (g + 1 < stages) store((g + 1) & 1);
+            if (g + 2 < stages) fetch(g + 2);
+#pragma unroll
+            for (int c = 0; c < P::kT; ++c) take_tile(g, c, row[c], (uint32_t)(g & 1) * P::kStageBytes);
+        }
+    } else {
     for (int g = 0; g < stages; ++g) {
         if constexpr (!BF16 && D == 128) {
             // the Q parts are only ever operands of matrix instructions: they live in accumulation registers
@@ -924,27 +975,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
         __syncthreads();
         if (g + 1 < stages) fetch(g + 1);
 #pragma unroll
-        for (int c = 0; c < P::kT; ++c) {
-            const int valid = N - row0[c];                       // keys of the tile (only the sequence's end has fewer than 32)
-            if (!(g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0)) continue;      // wavefront-uniform
-            const uint32_t tile = (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
-            v16f s;
-#pragma unroll
-            for (int j = 0; j < 16; ++j) s[j] = 0.f;
-            // the fragments of a step are read while the step before is multiplied
-            v8bf kf[2][P::kIn];
-#pragma unroll
-            for (int i = 0; i < P::kIn; ++i) kf[0][i] = *(lds_v8)(uintptr_t)(k_addr[0] + tile + i * kPart);
-#pragma unroll
-            for (int ks = 0; ks < kKS; ++ks) {
-                if (ks + 1 < kKS) {
-#pragma unroll
-                    for (int i = 0; i < P::kIn; ++i) kf[(ks + 1) & 1][i] = *(lds_v8)(uintptr_t)(k_addr[ks + 1] + tile + i * kPart);
-                }
-                s = mfma_parts<P::kIn, P::kIn>(kf[ks & 1], qf[ks], s);
-            }
-            use_tile(s, valid, tile);
-        }
+        for (int c = 0; c < P::kT; ++c) take_tile(g, c, row0[c], 0u);
+    }
     }
     }
 
