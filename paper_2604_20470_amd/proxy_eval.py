@@ -54,17 +54,18 @@ def proxy_loss(ctx: dr.Context, Q, K, Nf: int, Hg: int, Wg: int, Bs: int, mode: 
     shape = dr.shape_of(Q, Nf, Hg, Wg, Bs)
     Sb = shape.Sb
     masks = 1 if params.head_fuse > 0 else H
+    # the scores are under way while the host prepares the rest
+    tokens = mode == MODE_TOKENS     # ratio_or_tau is tau_1; tau_2 comes from params
+    side = N if tokens else Sb
+    scores = torch.empty((B, masks, side, side), dtype=torch.float32, device=Q.device)
+    (dr.dr_token_scores if tokens else dr.dr_block_scores)(ctx, shape, Q, K, params.head_fuse, scores)
     cap, _ = dr.dr_mask_capacity(ctx, shape, lam, params)
-    scores = torch.empty((B, masks, Sb, Sb), dtype=torch.float32, device=Q.device)
     rowptr = torch.empty((B, masks, Sb + 1), dtype=torch.int32, device=Q.device)
     colidx = torch.empty((B, masks, cap), dtype=torch.int32, device=Q.device)
     nnz = torch.empty((B, masks), dtype=torch.int64, device=Q.device)
-    if mode == MODE_TOKENS:          # ratio_or_tau is tau_1; tau_2 comes from params
-        tscores = torch.empty((B, masks, N, N), dtype=torch.float32, device=Q.device)
-        dr.dr_token_scores(ctx, shape, Q, K, params.head_fuse, tscores)
-        dr.dr_build_mask_tokens(ctx, shape, ratio_or_tau, lam, params, tscores, rowptr, colidx, cap, nnz)
+    if tokens:
+        dr.dr_build_mask_tokens(ctx, shape, ratio_or_tau, lam, params, scores, rowptr, colidx, cap, nnz)
     else:
-        dr.dr_block_scores(ctx, shape, Q, K, params.head_fuse, scores)
         dr.dr_build_mask(ctx, shape, mode, ratio_or_tau, lam, params, scores, rowptr, colidx, cap, nnz)
     out = torch.empty(3, dtype=torch.float64, device=Q.device)
     dr.dr_proxy_objective(ctx, shape, Q, K, rowptr, colidx, masks, cap, nnz, target, alpha, out)
