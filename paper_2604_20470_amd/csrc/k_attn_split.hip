@@ -43,7 +43,8 @@ typedef __attribute__((address_space(3))) const v8bf* lds_v8;
 typedef __attribute__((address_space(3))) v4s* lds_v4;
 typedef float v4f32 __attribute__((ext_vector_type(4)));
 
-template <bool BF16, int D, int BS>
+// FEW: a launch of at most one workgroup a compute unit (bf16, d = 64, block size 32)
+template <bool BF16, int D, int BS, bool FEW = false>
 struct Plan {
     static constexpr int kIn = BF16 ? 1 : 3;                        // parts of Q, K, V
     static constexpr int kQ = BS / 32;                              // wavefronts along the queries
@@ -58,7 +59,12 @@ struct Plan {
     static constexpr bool kEight = !BF16 && D == 64 && BS == 128;
     static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : (kEight ? 8 : 4) / kQ;        // streams of key tiles
     static constexpr int kThreads = 64 * kQ * kS;
-    static constexpr int kTileBytes = 32 * (kAlone ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
+    // bf16 rows straight from memory to LDS, the keys as well: fewer instructions and registers (120, four wavefronts a SIMD), a longer
+    // way for a key.  17 550 tokens x 12 heads 815 -> 724 us, 6144 x 8 119 -> 100, 384 query blocks 21.9 -> 18.9; 192 and 168 blocks, with
+    // a few tiles a wavefront, 12.7 -> 13.1 and 11.9 -> 12.5: launches of up to one workgroup a compute unit keep the registers
+    // (the results are the same bits).
+    static constexpr bool kAloneDirect = kAlone && BF16 && D == 64 && !FEW;
+    static constexpr int kTileBytes = 32 * (kAlone && !kAloneDirect ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
     // bf16 rows go to LDS as they are, straight from memory, a stage of 64 keys ahead
     static constexpr bool kDirect = BF16 && D == 64 && !kAlone;
     static constexpr int kT = kDirect && kS == 1 ? 2 : 1;      // 32-key tiles per stream and stage
@@ -68,7 +74,7 @@ struct Plan {
     // one wavefront per SIMD (fp32, d = 128: 96 registers of Q parts) has nobody to hide its vector instructions behind: they go
     // between the matrix instructions, with a second buffer, where two fit
     static constexpr int kBuffers = kDirect || kEight || (!kAlone && !BF16 && D == 128 && 2 * kStageBytes <= 128 * 1024) ? 2 : 1;
-    static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : kDirect ? 4 : 2;      // wavefronts, at least
+    static constexpr int kPerSimd = !BF16 && D == 128 ? 1 : kDirect || kAloneDirect ? 4 : 2;      // wavefronts, at least
     static constexpr int kPlainRows = kThreads / 8, kPlainKeys = BS == 32 ? 32 : 64;
     static constexpr int kPlainBytes = 4 * (kPlainRows * D + kPlainKeys * (D + 1) + kPlainRows * kPlainKeys);
     static constexpr int kMergeBytes = (kS - 1) * kQ * 32 * D * 4 + kS * kQ * 64 * 4;
@@ -260,9 +266,9 @@ __device__ __forceinline__ bool holds_huge_keys(const Item& it) {
     return most >= kHuge;
 }
 
-template <bool BF16, int D, int BS>
+template <bool BF16, int D, int BS, bool FEW>
 __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
-    using P = Plan<BF16, D, BS>;
+    using P = Plan<BF16, D, BS, FEW>;
     constexpr int kDB = D / 32, kKS = D / 16;       // channel blocks of O, contraction steps of a logit tile
     constexpr int kPart = P::kRows * P::kRowBytes;  // bytes of one part of K (or V) of a stage
     constexpr int kTPB = BS / 32;                   // 32-key tiles of a key block
@@ -385,11 +391,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     float ref = -INFINITY, l_run = 0.f;      // exponent reference of this lane's query (log2 units), this half's normaliser
 
     const uint32_t lds0 = lds_addr(smem);
-    const uint32_t v_base = P::kAlone ? (uint32_t)ws * P::kTileBytes : (uint32_t)P::kIn * kPart;
-    const uint32_t stream = P::kDirect ? (uint32_t)(ws * P::kT * 32 * P::kRowBytes) : 0u;      // (the others add it to a tile's place)
+    const uint32_t v_base = P::kAlone ? (uint32_t)ws * P::kTileBytes + (P::kAloneDirect ? kPart : 0) : (uint32_t)P::kIn * kPart;
+    const uint32_t stream = P::kDirect ? (uint32_t)(ws * P::kT * 32 * P::kRowBytes) : 0u, alone = P::kAloneDirect ? (uint32_t)ws * P::kTileBytes : 0u;      // (the others add it to a tile's place)
     uint32_t k_addr[kKS], v_addr[kDB];
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) k_addr[ks] = lds0 + stream + l32 * P::kRowBytes + k_piece<D>(ks * 2 + half, l32) * 16;
+    for (int ks = 0; ks < kKS; ++ks) k_addr[ks] = lds0 + stream + alone + l32 * P::kRowBytes + k_piece<D>(ks * 2 + half, l32) * 16;
     {
         const int v_e = (lane & 15) >> 2, v_c = lane & 3, v_grp = (lane >> 4) & 1;
 #pragma unroll
@@ -398,7 +404,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     }
 
     // softmax of a logit tile (keys x queries) and its share of O; `tile`: LDS offset of its values
-    auto use_tile = [&](v16f& s, int valid, uint32_t tile) {
+    auto use_tile = [&](v16f& s, int valid, uint32_t tile, auto&& before_values) {
                     if (valid < 32) {
                         int base = half * 4;
                         asm volatile("" : "+v"(base));                   // (a branch, not sixteen selects on every tile)
@@ -440,6 +446,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 #pragma unroll
                         for (int db = 0; db < kDB; ++db) asm volatile("" : "+v"(o[db]));
                     }
+                    before_values();
                     v8bf pf[2][3];
                     split8(p[0], pf[0]);
 #pragma unroll
@@ -469,7 +476,64 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                     }
     };
 
-    if constexpr (P::kAlone) {
+    auto to_lds = [&](const char* from, uint32_t to) {          // sixteen bytes a lane; counted by hand
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from), "s"(to) : "memory", "m0");
+    };
+    if constexpr (P::kAloneDirect) {
+        // A stream's tiles one after the other through a place of its own, without a barrier: the next tile's keys are fetched as soon as
+        // this one's are read, its values when the products with this one's are made, so either has half a tile's time to arrive.
+        // Four loads each, in turn: where four are on their way at most, the ones before them have arrived.
+        const int own = (it.n_list - ws + P::kS - 1) / P::kS;
+        int base = 0, at = own > 0 ? it.list[min(ws + lane * P::kS, it.n_list - 1)] : 0;
+        asm volatile("" : "+v"(at));
+        auto row_of = [&](int j) {             // clamped: a malformed list cannot address outside K / V
+            if (j - base >= 64) {              // wavefront-uniform
+                base = j;
+                at = it.list[min(ws + (base + lane) * P::kS, it.n_list - 1)];
+                asm volatile("" : "+v"(at));   // (waited for here, and not counted among the tiles' loads)
+            }
+            return min(max(__builtin_amdgcn_readlane(at, j - base), 0), a.Sb - 1) * 32;
+        };
+        const int r0 = lane >> 3;              // + 8 i in load i; the swizzles are their own inverses, that of V the same for every i
+        const char* from_k[2];
+        const char* from_v = it.V + (int64_t)r0 * it.row_bytes + v_piece<D>(lane & 7, r0) * 16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) from_k[i] = it.K + (int64_t)r0 * it.row_bytes + k_piece<D>(lane & 7, r0 + 8 * i) * 16;
+        const uint32_t to0 = __builtin_amdgcn_readfirstlane(lds0 + alone);
+        auto issue = [&](int row0, bool values) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const char* from = (values ? from_v : from_k[i & 1]) + (int64_t)(row0 + 8 * i) * it.row_bytes;
+                if (row0 + 32 > N) from -= (int64_t)max(row0 + 8 * i + r0 - (N - 1), 0) * it.row_bytes;      // past the end: the last row again
+                to_lds(from, to0 + (values ? kPart : 0) + i * 1024u);
+            }
+        };
+        int row = 0;
+        if (own > 0) {
+            row = row_of(0);
+            issue(row, false);
+            issue(row, true);
+        }
+        for (int j = 0; j < own; ++j) {
+            const int row_next = row_of(min(j + 1, own - 1));      // (behind the last tile: that tile again, read by nobody)
+            asm volatile("s_waitcnt vmcnt(4)" ::: "memory");       // the keys are there
+            v8bf kf[kKS];
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) kf[ks] = *(lds_v8)(uintptr_t)k_addr[ks];
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(kf[0]), "+v"(kf[1]), "+v"(kf[2]), "+v"(kf[3]) :: "memory");      // and read
+            issue(row_next, false);
+            v16f s;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < kKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks][0], s, 0, 0, 0);
+            use_tile(s, N - row, 0u, []() { asm volatile("s_waitcnt vmcnt(4)" ::: "memory"); });      // the values are there
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // and read
+            issue(row_next, true);
+            row = row_next;
+        }
+        DR_WAIT_VMCNT0();                      // none may land in what the merge lays out
+    } else if constexpr (P::kAlone) {
         // stream s takes tiles s, s + kS, ..: lane i of the window holds the stream's entry base + i
         constexpr int kWaveRows = 64 / P::kRowUnits, NX = BF16 ? 1 : 2;
         const int own = (it.n_list - ws + P::kS - 1) / P::kS;
@@ -531,7 +595,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 s = mfma_parts<P::kIn, P::kIn>(kf, qf[ks], s);
             }
             if (j + 1 < own) fetch_own(j + 1);
-            use_tile(s, valid, 0u);
+            use_tile(s, valid, 0u, []() {});
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     } else if constexpr (P::kDirect) {
@@ -549,9 +613,6 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 asm volatile("" : "+v"(win));
             }
             return min(max(__builtin_amdgcn_readlane(win, e - wbase), 0), a.Sb - 1) * BS + g % kStagesPerBlock * 64;
-        };
-        auto to_lds = [&](const char* from, uint32_t to) {      // sixteen bytes a lane; counted by hand
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" :: "v"(from), "s"(to) : "memory", "m0");
         };
         const char *from_k[2], *from_v[2];
 #pragma unroll
@@ -603,7 +664,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
                 for (int ks = 0; ks < kKS; ++ks) kf[ks] = *(lds_v8)(uintptr_t)(k_addr[ks] + tile);
 #pragma unroll
                 for (int ks = 0; ks < kKS; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks][0], s, 0, 0, 0);
-                use_tile(s, valid, tile);
+                use_tile(s, valid, tile, []() {});
             }
         };
         for (int g = 0; g < n_stages; g += 2) {
@@ -932,7 +993,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             }
             s = mfma_parts<P::kIn, P::kIn>(kf[ks & 1], qf[ks], s);
         }
-        use_tile(s, valid, tile);
+        use_tile(s, valid, tile, []() {});
     };
     if (stages > 0) fetch(0);
     if constexpr (P::kEight) {
@@ -1098,18 +1159,18 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // share stages behind barriers, 24 to 30 us with eight that walk alone.
 // The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two or three, and bf16
 // d = 64 at block size 128, which fits 128 registers, four.
-template <bool BF16, int D, int BS>
-__global__ __launch_bounds__((Plan<BF16, D, BS>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS>::kPerSimd)))
-void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS>(a); }
+template <bool BF16, int D, int BS, bool FEW>
+__global__ __launch_bounds__((Plan<BF16, D, BS, FEW>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS, FEW>::kPerSimd)))
+void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS, FEW>(a); }
 
-template <bool BF16, int D, int BS>
+template <bool BF16, int D, int BS, bool FEW = false>
 hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
-    using P = Plan<BF16, D, BS>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS>),
+    using P = Plan<BF16, D, BS, FEW>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS, FEW>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, P::kLdsBytes);
     if (e != hipSuccess) return e;
     const int total = a.Sb * a.td.H * a.td.B, grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
-    hipLaunchKernelGGL((k_attn_split<BF16, D, BS>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
+    hipLaunchKernelGGL((k_attn_split<BF16, D, BS, FEW>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
     return hipGetLastError();
 }
 
@@ -1121,6 +1182,7 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
 }  // namespace
 
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s) {
+    if (a.td.d == 64 && a.bf16 && a.Bs == 32 && (int64_t)a.Sb * a.td.H * a.td.B <= a.cus) return launch_t<true, 64, 32, true>(a, s);
     if (a.td.d == 64) return a.bf16 ? launch_d<true, 64>(a, s) : launch_d<false, 64>(a, s);
     if (a.td.d == 128) return a.bf16 ? launch_d<true, 128>(a, s) : launch_d<false, 128>(a, s);
     return hipErrorNotSupported;

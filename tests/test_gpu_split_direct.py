@@ -1,4 +1,4 @@
-"""bf16 attention at d = 64, whose rows go straight from memory to LDS in stages of 64: sequences that end anywhere in a stage, tensors of
+"""bf16 attention at d = 64, whose rows go straight from memory to LDS (stages of 64, at block size 32 a tile of 32 per wavefront): sequences that end anywhere in a stage, tensors of
 any row and head stride (rows 2^31 bytes apart among them), lists in any order and with entries that name no block."""
 import math
 
@@ -32,7 +32,7 @@ def check(O, lse, want, want_lse):
     assert (lse.double() - want_lse).abs().max() < 1e-5
 
 
-@pytest.mark.parametrize("bs", [64, 128])
+@pytest.mark.parametrize("bs", [32, 64, 128])
 @pytest.mark.parametrize("N", [1, 31, 32, 33, 63, 64, 65, 95, 97, 127, 128, 129, 191, 193, 257, 700])
 @pytest.mark.parametrize("layout", ["plain", "strided"])
 def test_every_end_of_the_sequence(bs, N, layout):
@@ -56,7 +56,7 @@ def test_every_end_of_the_sequence(bs, N, layout):
     check(O, lse, *reference(Q, K, V, keep, bs))
 
 
-@pytest.mark.parametrize("bs", [64, 128])
+@pytest.mark.parametrize("bs", [32, 64, 128])
 def test_rows_two_gigabytes_apart(bs):
     N, stride = 5, 1 << 30
     g = torch.Generator(device="cuda").manual_seed(1)
@@ -72,7 +72,7 @@ def test_rows_two_gigabytes_apart(bs):
     check(O, lse, *reference(Q, K, V, torch.ones(1, 1, dtype=torch.bool, device="cuda"), bs))
 
 
-@pytest.mark.parametrize("bs", [64, 128])
+@pytest.mark.parametrize("bs", [32, 64, 128])
 def test_entries_that_name_no_block_are_clamped(bs):
     N = 3 * bs - 5
     g = torch.Generator(device="cuda").manual_seed(2)
@@ -81,3 +81,18 @@ def test_entries_that_name_no_block_are_clamped(bs):
     colidx = torch.tensor([[[-7, 1, 99]]], dtype=torch.int32, device="cuda")
     O, lse = attend(Q, K, V, rowptr, colidx, bs)
     check(O, lse, *reference(Q, K, V, torch.eye(3, dtype=torch.bool, device="cuda"), bs))
+
+
+@pytest.mark.parametrize("H", [8, 9, 16])                        # 32 blocks each: 256 workgroups, 288, 512
+def test_few_and_many_workgroups_give_the_same_bits(H):
+    N, bs = 1000, 32
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q, K, V = (torch.randn(1, H, N, 64, generator=g, device="cuda").bfloat16() for _ in range(3))
+    Sb = -(-N // bs)
+    rowptr = (torch.arange(Sb + 1, dtype=torch.int32) * Sb).view(1, 1, -1).cuda()
+    colidx = torch.arange(Sb, dtype=torch.int32).repeat(Sb).view(1, 1, -1).cuda()
+    O, lse = attend(Q, K, V, rowptr, colidx, bs)
+    check(O, lse, *reference(Q, K, V, torch.ones(Sb, Sb, dtype=torch.bool, device="cuda"), bs))
+    for h in range(H):
+        own_O, own_lse = attend(*(t[:, h:h + 1].contiguous() for t in (Q, K, V)), rowptr, colidx, bs)
+        assert torch.equal(own_O[0, 0], O[0, h]) and torch.equal(own_lse[0, 0], lse[0, h])
