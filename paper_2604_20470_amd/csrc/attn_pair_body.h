@@ -830,7 +830,8 @@ __device__ __forceinline__ void attn_pair_body() {
             const int blk = (b * a.td.H + h) * groups128 + (q0_own >> 7);
             if (atomicAdd(&a.flags[blk], 1) == 0) {
                 const int per = (items + kXcds - 1) / kXcds, of = item / per;
-                a.flags[a.td.B * a.td.H * groups128 + 2 * of * per + atomicAdd(&a.queue[kAttnQueues + of], 1)] = blk;
+                const int at = atomicAdd(&a.queue[kAttnQueues + of], 1);       // (beyond its room only if calls overlap on this scratch)
+                if (at < 2 * slots_of_queue(of, items)) a.flags[a.td.B * a.td.H * groups128 + 2 * of * per + at] = blk;
             }
         }
     } else if (a.flags && (q0_own >> 7) < groups128) {

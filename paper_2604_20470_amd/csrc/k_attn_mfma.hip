@@ -450,7 +450,7 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
     int listed[kXcds], all = 0;
 #pragma unroll
     for (int i = 0; i < kXcds; ++i) {
-        listed[i] = min(count[i], 2 * per);
+        listed[i] = max(0, min(count[i], 2 * min(per, pairs - i * per)));
         all |= listed[i];
     }
     if (all == 0) return;
@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
                     if (at < n) item = a.flags[a.Sb * a.td.H * a.td.B + 2 * x * per + at];
                 }
             }
-            s_item = item;
+            s_item = min(item, a.Sb * a.td.H * a.td.B - 1);      // (words that overlapping calls have mixed up name some block)
         }
         __syncthreads();
         const int item = __builtin_amdgcn_readfirstlane(s_item);
