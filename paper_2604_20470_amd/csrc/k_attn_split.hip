@@ -13,7 +13,8 @@
 // and walks every kS-th group of 32-key tiles, so that block sizes 64 and 32, whose rows share no key list, still fill
 // four or eight wavefronts (the streams' partial sums are merged at the end, in a fixed order).  Keys and values of a
 // stage (kT tiles per stream) are fetched to registers while the stage before is computed, split once by the workgroup and
-// left in LDS as bf16 parts; at block size 32 no wavefront shares a tile with another, and each fetches and splits its own.  The logits are produced transposed, S^T = K Q^T (32x32x16), so that a lane's sixteen values
+// left in LDS as bf16 parts (bf16 rows at d = 64 go straight to LDS); at block size 32 no wavefront shares a tile with another, and each
+// fetches and splits its own.  The logits are produced transposed, S^T = K Q^T (32x32x16), so that a lane's sixteen values
 // belong to one query, and the split probabilities are already the B operand of O^T += V^T P^T; V^T fragments come
 // from the row-major parts with the transposing LDS read.
 // Softmax is online in fp32; the exponent reference of a query is moved only when a tile's probabilities outgrow it by
@@ -1157,8 +1158,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // d = 64 1.15e-6 -> 0.7e-6; log-sum-exp 3.3e-8..4.8e-8 -> 2.9e-8..3.8e-8.
 // Block size 32, fp32 d = 64, 2048 tokens x 2 heads, all blocks: 700 us with the vector ALU, 45 us with four wavefronts that
 // share stages behind barriers, 24 to 30 us with eight that walk alone.
-// The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; the others run two or three, and bf16
-// d = 64 at block size 128, which fits 128 registers, four.
+// The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; those at d = 64 run two, bf16 at d = 64,
+// which fits 128 registers, four, bf16 at d = 128 two or three.
 template <bool BF16, int D, int BS, bool FEW>
 __global__ __launch_bounds__((Plan<BF16, D, BS, FEW>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS, FEW>::kPerSimd)))
 void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS, FEW>(a); }
