@@ -298,8 +298,8 @@ dr_status dr_sparse_attn_fwd_static(dr_ctx* ctx, const dr_shape* shape, const vo
  *                 blocks, so dr_mask_capacity bounds nnz here too
  *   links         optional device uint8 [B, masks, N, N]: receives the link matrix (1 = kept); NULL: the context
  *                 holds it in scratch of that size (DR_ERR_NOMEM if that allocation fails)
- *   For frames of more than 128 tokens, and beyond 12 * 2^20 token pairs in all masks, the context also holds the column
- *   sums of the frame pairs: 24 * Nf * N bytes, and 8 * Nf * Nf of statistics, per mask (DR_ERR_NOMEM likewise; frames of
+ *   For frames of more than 128 tokens (of one mask alone, 115), and beyond 12 * 2^20 token pairs in all masks, the context also
+ *   holds the column sums of the frame pairs: 24 * Nf * N bytes, and 8 * Nf * Nf of statistics, per mask (DR_ERR_NOMEM likewise; frames of
  *   at most 128 tokens do without, more slowly and with the same results, where that cannot be allocated or `stream` is being captured).
  *   params->gamma, theta_c, theta_m, head_fuse (number of masks), has_tau_far, tau_far are read.
  *   N <= 16384 and Hg * Wg <= 4096, else DR_ERR_UNSUPPORTED.  First use of a geometry synchronises once, like

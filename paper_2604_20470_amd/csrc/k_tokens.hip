@@ -127,14 +127,21 @@ struct PairAt {
     int64_t mask, pair;           // (b, m) flattened; index into per-pair arrays
     bool judged;                  // t >= 2 and retained: its links are decided by score
 };
+// kScalar: the flags come by a scalar load of their word (of a byte there is none), ahead of all else; k_link_sums gains 0.3 % by it,
+// k_pair_links_small, which has other work meanwhile, loses 2 to 5 %.
+template <bool kScalar>
 __device__ __forceinline__ PairAt pair_at(const FrameTab& tab, int Nf, int pair) {
     PairAt p;
     p.i = pair / Nf;
     p.j = pair % Nf;
     p.t = abs(p.i - p.j);
-    uint32_t word;                // (a scalar load, as of w: of a byte there is none)
-    __builtin_memcpy(&word, tab.flags + (p.t & ~3), 4);
-    p.flags = (int)(word >> (8 * (p.t & 3))) & 255;
+    if constexpr (kScalar) {
+        uint32_t word;
+        __builtin_memcpy(&word, tab.flags + (p.t & ~3), 4);
+        p.flags = (int)(word >> (8 * (p.t & 3))) & 255;
+    } else {
+        p.flags = tab.flags[p.t];
+    }
     p.w = tab.w[p.t];
     p.mask = (int64_t)blockIdx.z * gridDim.y + blockIdx.y;
     p.pair = p.mask * Nf * Nf + pair;
@@ -314,7 +321,7 @@ __global__ __launch_bounds__(64 * (kFeeders + 1)) void k_link_sums(const float* 
     __shared__ int s_last;
     const int tiles = (Nt + 63) / 64;
     const int pair = blockIdx.x / tiles, v0 = (blockIdx.x % tiles) * 64;
-    const PairAt p = pair_at(tab, Nf, pair);
+    const PairAt p = pair_at<true>(tab, Nf, pair);
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if constexpr (PASS == 0) {
         for (int r = (int)(blockIdx.x * kSumThreads + threadIdx.x); r < Sb; r += (int)gridDim.x * kSumThreads) counts[p.mask * Sb + r] = 0;
@@ -591,13 +598,17 @@ __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __re
 }
 
 // The same for pairs of small frames in one launch: a workgroup holds the pair's scores in LDS (two such workgroups share a CU at
-// 128 tokens) and makes the statistics, the bytes and the safeguard itself; the density rule follows.  Where there is little
-// work four launches cost more than two, where there is much the serial chains of a workgroup do: whole calls, four launches /
-// two, 4 frames of 64 tokens, block size 128: 19 / 13 us; 33 of 64: 31 / 26; 16 of 128: 37 / 35; 33 of 96 (10 million token
-// pairs): 57 / 46; 33 of 121 (16 million): 63 / 71; 60 of 128: 91 / 134; 128 of 64: 73 / 87.
+// 128 tokens, three from 115 down) and makes the statistics, the bytes and the safeguard itself; the density rule follows.  Where
+// there is little work three launches cost more than two, where there is much the serial chains of a workgroup do, and for one
+// mask of frames above 115 tokens they do as well: whole calls, the three launches above / these two, 16 frames of 64 tokens 27.9 / 20.2 us;
+// 33 of 64: 30.1 / 25.8; 20 of 96: 34.9 / 34.9; 33 of 96 (10 million token pairs): 47.0 / 44.9; 50 of 96 (23 million): 60.9 / 65.6; 33 of 121: 53.3 / 70.8;
+// 9 of 120: 30.7 / 33.0; 16 of 128: 31.0 / 35.9; 24 of 128 (9 million): 42.0 / 46.9; 60 of 128: 80 / 133; several masks, 16 of 117 x 2: 47.9 / 46.5;
+// 10 of 120 x 4: 43.8 / 40.3.
 constexpr int64_t kSmallPairs = 12 << 20;
+constexpr int kThreePerCu = 115;
 inline bool small_frames(int B, int masks, int N, int Nf) {
-    return N / Nf <= kSmallFrame && (int64_t)B * masks * N * N <= kSmallPairs;
+    const int Nt = N / Nf;
+    return Nt <= kSmallFrame && (int64_t)B * masks * N * N <= kSmallPairs && (Nt <= kThreePerCu || (int64_t)B * masks > 1);
 }
 // grid: (Nf * Nf, masks, B).  LDS: Nt doubles | Nt * Nt floats.
 __global__ __launch_bounds__(kThreads) void k_pair_links_small(const float* __restrict__ scores, FrameTab tab, int N, int Nt, int Nf,
@@ -607,7 +618,7 @@ __global__ __launch_bounds__(kThreads) void k_pair_links_small(const float* __re
     __shared__ unsigned long long s_best;
     __shared__ unsigned int s_kept;
     float* S = reinterpret_cast<float*>(col + Nt);
-    const PairAt p = pair_at(tab, Nf, (int)blockIdx.x);
+    const PairAt p = pair_at<false>(tab, Nf, (int)blockIdx.x);
     const int64_t at0 = p.mask * N * N + (int64_t)p.i * Nt * N + (int64_t)p.j * Nt;
     const int tid = threadIdx.x, size = Nt * Nt;
     if (!p.judged) {

@@ -18,7 +18,16 @@ pytestmark = pytest.mark.gpu
     (17, 1, 199, 1.0), (18, 1, 200, 1.0), (19, 7, 19, 0.5), (17, 1, 449, 1.0),      # 1680 workgroups and more
 ])
 def test_links_and_masks_bit_exact_call_after_call(frames, hg, wg, gamma):
-    B, H = 1, 2
+    call_after_call(frames, hg, wg, gamma, 2)
+
+
+@pytest.mark.parametrize("frames,hg,wg,heads", [(9, 5, 23, 1), (9, 4, 29, 1), (9, 4, 29, 2), (16, 8, 16, 1), (16, 8, 16, 2), (6, 7, 18, 1)])
+def test_frames_on_both_sides_of_a_workgroup_a_pair(frames, hg, wg, heads):      # 115 tokens, 116, 128, 126
+    call_after_call(frames, hg, wg, 1.0, heads)
+
+
+def call_after_call(frames, hg, wg, gamma, H):
+    B = 1
     wl = Workload("rounds", 95, B, H, 64, frames, hg, wg, 32, "f32", "iid", "dynamic", 0.5, 0.9, 1.0, head_fuse=0)
     run = GpuRun(wl, params=dr.MaskParams(gamma=gamma, head_fuse=0))
     N = wl.N
@@ -35,3 +44,39 @@ def test_links_and_masks_bit_exact_call_after_call(frames, hg, wg, gamma):
         for m in range(H):
             assert (got[0, m].astype(bool) == o.select_token_links(sc[0, m], N, wl.Nt, tab, tau, tau)).all()
         assert_masks_equal(rowptr, colidx, nnz, o.build_mask_from_tokens(sc, N, wl.Nt, wl.Bs, tab, 0.15, 0.60, tau))
+
+
+def test_first_call_of_frames_of_116_to_128_tokens_may_be_captured():
+    """One mask of such frames asks for the sums' scratch where it can be had; in a capture the frame pairs go the way without, same bits."""
+    frames, hg, wg, bs = 9, 8, 16, 32
+    N = frames * hg * wg
+    Sb = N // bs
+    shape, params = dr.Shape(1, 1, N, 64, frames, hg, wg, bs, 0, 0, N * 64, N * 64, 64), dr.MaskParams(head_fuse=1)
+    scores = torch.randn(1, 1, N, N, generator=torch.Generator().manual_seed(9)).cuda()
+
+    def outputs(cap):
+        return [torch.zeros(*s, dtype=t, device="cuda") for s, t in (((1, 1, Sb + 1), torch.int32), ((1, 1, cap), torch.int32), ((1, 1), torch.int64),
+                                                                      ((1, 1, N, N), torch.uint8))]
+
+    def tokens(ctx, cap, out):
+        dr.dr_build_mask_tokens(ctx, shape, 0.4, 1.0, params, scores, out[0], out[1], cap, out[2], out[3])
+
+    ctx = dr.Context(0)
+    cap, _ = dr.dr_mask_capacity(ctx, shape, 1.0, params)
+    want, got = outputs(cap), outputs(cap)
+    tokens(ctx, cap, want)
+    ctx = dr.Context(0)
+    dr.dr_build_mask(ctx, shape, dr.MODE_DYNAMIC, 0.5, 1.0, params, torch.zeros(1, 1, Sb, Sb, device="cuda"), got[0], got[1], cap, got[2])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tokens(ctx, cap, got)
+    for _ in range(3):
+        for t in got:
+            t.fill_(7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        n = int(want[2])
+        assert n > 0 and torch.equal(got[0], want[0]) and torch.equal(got[2], want[2]) and torch.equal(got[3], want[3])
+        assert torch.equal(got[1][..., :n], want[1][..., :n])
