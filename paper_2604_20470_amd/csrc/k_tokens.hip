@@ -469,7 +469,11 @@ __global__ __launch_bounds__(64 * (kFeeders + 1)) void k_link_sums(const float* 
 // 152 against 171 (block size 128) and 62 against 62 (32), at 750 73 against 68.  grid: (Sb * ceil(N / 1024), masks, B).
 constexpr int kBlockCols = 1024;
 constexpr int64_t kSmallGrid = 512;
-template <int kGroups>
+// kPast: link bytes go past the caches, which they and the scores no longer fit: whole calls through them / past them, 4 frames of 4096 tokens
+// (268 million link bytes) 317 / 263 us, 16 of 1024 327 / 312, 8 of 1792 (205) 251 / 233, 12 of 1024 (151) 166.5 / 163.8, 33 of 256 x 2 masks (143)
+// 195.4 / 190.9, 8 of 1020 x 2 (133) 198.0 / 204.4, 10 of 1024 (105) 128.1 / 130.4.
+constexpr int64_t kPastCaches = 140000000;
+template <int kGroups, bool kPast = false>
 __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __restrict__ scores, FrameTab tab, const PairStat* __restrict__ stats,
                                                                const uint8_t* __restrict__ class_map, Geometry g,
                                                                uint8_t* __restrict__ links, uint32_t* __restrict__ keepbits,
@@ -564,7 +568,8 @@ __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __re
                     out &= present;
                 }
                 const int64_t at = at0 + (int64_t)row * N;
-                if (n == 4) __builtin_memcpy(links + at, &out, 4);
+                if constexpr (kPast) __builtin_nontemporal_store(out, reinterpret_cast<uint32_t*>(links + at));      // (n is 4: rows of whole words)
+                else if (n == 4) __builtin_memcpy(links + at, &out, 4);
                 else for (int e = 0; e < n; ++e) links[at + e] = (uint8_t)(out >> (8 * e));
                 cnt += out;
             }
@@ -811,6 +816,8 @@ hipError_t launch_token_mask(const float* scores, const FrameTab& tab, const uin
     const dim3 grid((unsigned)g.Sb * ((N + kBlockCols - 1) / kBlockCols), masks, B);
     if ((int64_t)grid.x * masks * B <= kSmallGrid)
         hipLaunchKernelGGL(k_link_blocks<4>, grid, dim3(1024), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
+    else if ((int64_t)B * masks * N * N >= kPastCaches && N % 4 == 0 && (reinterpret_cast<uintptr_t>(links) & 3) == 0)
+        hipLaunchKernelGGL((k_link_blocks<1, true>), grid, dim3(256), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
     else
         hipLaunchKernelGGL(k_link_blocks<1>, grid, dim3(256), 0, s, scores, tab, stats, class_map, g, links, keepbits, counts);
     return hipGetLastError();
