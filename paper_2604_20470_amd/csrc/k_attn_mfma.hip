@@ -229,15 +229,10 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
 
 // One work item = one query block of one (batch, head).  kExact = false: the fast pass; each wave leaves in a.flags
 // (when given) whether any of its rows lies outside the accuracy range of the pre-scaled Q (see kExactLimit).
-// kExact = true: the exponent scale applied in fp32 (the caller has checked that the item is flagged).  Flagged items are few and a
-// walk is a chain of chunks whose latencies nothing hides, so eight wavefronts take one: two streams of four, every other
-// block each, in step, merged through LDS at the end (33 frames of 45 x 80 tokens x 24 heads, 229 items flagged: 0.87 -> 0.54 ms).
-constexpr int kExactStreams = 2, kExactThreads = kExactStreams * kThreads;
+// kExact = true: the exponent scale applied in fp32 (the caller has checked that the item is flagged).
 template <bool kExact>
 __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned char* smem) {
-    constexpr int kStreams = kExact ? kExactStreams : 1;
-    const int lane = threadIdx.x & 63, wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = wave_all % kWaves, stream = wave_all / kWaves;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int half = lane >> 5, l32 = lane & 31;
     const int qb = item % a.Sb, h = (item / a.Sb) % a.td.H, b = item / (a.Sb * a.td.H);
     const int N = a.td.N;
@@ -269,7 +264,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
         }
     }
 
-    const uint32_t lds0 = lds_addr(smem) + (uint32_t)stream * kLdsBytes;
+    const uint32_t lds0 = lds_addr(smem);
     LoadPlan lp;
     lp.row_bytes = row_bytes;
     lp.piece = lane & 15;
@@ -302,11 +297,11 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
 #pragma unroll
         for (int j = 0; j < 16; ++j) st.o[db][j] = 0.f;
 
-    // The row's key-block list is walked through a 64-entry register window (lane i holds the stream's entry base + i):
+    // The row's key-block list is walked through a 64-entry register window (lane i holds entry base + i):
     // the per-block index comes from v_readlane, so no memory access sits on the loop's critical path.
-    const int n_blocks = end - beg, n_own = (n_blocks - stream + kStreams - 1) / kStreams;
+    const int n_blocks = end - beg;
     const int last_blk_chunks = (N - (a.Sb - 1) * kBs + kChunkKeys - 1) / kChunkKeys;   // 1 or 2
-    auto load_window = [&](int base) { return (n_blocks > 0) ? ci[beg + min(stream + (base + lane) * kStreams, n_blocks - 1)] : 0; };
+    auto load_window = [&](int base) { return (n_blocks > 0) ? ci[beg + min(base + lane, n_blocks - 1)] : 0; };
     auto entry = [&](int win, int blk) {      // clamped, so that a malformed list cannot address outside K/V
         return min(max(__builtin_amdgcn_readlane(win, blk & 63), 0), a.Sb - 1);
     };
@@ -317,55 +312,30 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
     asm volatile("" : "+v"(win));
-    int kb_next = (n_own > 0) ? entry(win, 0) : -1;
+    int kb_next = (n_blocks > 0) ? entry(win, 0) : -1;
     if (kb_next >= 0) issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1);
     DR_WAIT_VMCNT0();
     // Loop invariant at each barrier: every wave has waited for its own share of the chunk about to be
     // consumed, and has finished reading the previous chunk, whose stage the next loads overwrite.
-    // A block is two chunks (stage 0, then stage 1); only the sequence's last block can have one.  Two barriers a block whatever
-    // it holds, and for a stream without one: the streams stay in step.
-    for (int blk = 0; blk * kStreams < n_blocks; ++blk) {
+    // A block is two chunks (stage 0, then stage 1); only the sequence's last block can have one.
+    for (int blk = 0; blk < n_blocks; ++blk) {
         const int kb = kb_next;
-        const bool has = kb >= 0;
         const int key0 = kb * kBs;
         const int n_chunks = (kb == a.Sb - 1) ? last_blk_chunks : 2;
         DR_BARRIER();
-        if (has) chunk_body<0, kExact>(rd, qf, st, first, N - key0, half, [&]() { if (n_chunks == 2) issue_chunk<1>(lp, Kh, Vh, key0 + kChunkKeys, N - 1); });
+        chunk_body<0, kExact>(rd, qf, st, first, N - key0, half, [&]() { if (n_chunks == 2) issue_chunk<1>(lp, Kh, Vh, key0 + kChunkKeys, N - 1); });
         DR_WAIT_VMCNT0();
-        if (((blk + 1) & 63) == 0 && blk + 1 < n_own) win = load_window(blk + 1);
-        kb_next = (blk + 1 < n_own) ? entry(win, blk + 1) : -1;
-        DR_BARRIER();
-        auto issue_next = [&]() { if (kb_next >= 0) issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1); };
-        if (has && n_chunks == 2) chunk_body<1, kExact>(rd, qf, st, first, N - key0 - kChunkKeys, half, issue_next);
-        else issue_next();
-        DR_WAIT_VMCNT0();
-    }
-    if constexpr (kStreams == 2) {
-        if (n_blocks > 1) {                   // (both streams have taken a block)
-            float* sO = reinterpret_cast<float*>(smem + kLdsBytes) + wave * (64 * 64) + lane;      // [wave][value][lane]
-            float* sM = reinterpret_cast<float*>(smem) + wave * 128 + lane;                        // reference, share of the normaliser
-            __syncthreads();                  // the last chunks are read
-            if (stream == 1) {
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) sO[(db * 16 + j) * 64] = st.o[db][j];
-                sM[0] = st.m_ref;
-                sM[64] = st.l_part;
-            }
-            __syncthreads();
-            if (stream == 0) {
-                const float top = fmaxf(st.m_ref, sM[0]);
-                const float mine = __builtin_amdgcn_exp2f(st.m_ref - top), other = __builtin_amdgcn_exp2f(sM[0] - top);
-                st.l_part = st.l_part * mine + sM[64] * other;
-                st.m_ref = top;
-#pragma unroll
-                for (int db = 0; db < 4; ++db)
-#pragma unroll
-                    for (int j = 0; j < 16; ++j) st.o[db][j] = st.o[db][j] * mine + sO[(db * 16 + j) * 64] * other;
-            }
+        if (((blk + 1) & 63) == 0 && blk + 1 < n_blocks) win = load_window(blk + 1);
+        kb_next = (blk + 1 < n_blocks) ? entry(win, blk + 1) : -1;
+        if (n_chunks == 2) {
+            DR_BARRIER();
+            chunk_body<1, kExact>(rd, qf, st, first, N - key0 - kChunkKeys, half, [&]() { if (kb_next >= 0) issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1); });
+            DR_WAIT_VMCNT0();
+        } else if (kb_next >= 0) {   // only for a list that is not ascending: nothing was prefetched, load serially
+            DR_BARRIER();
+            issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1);
+            DR_WAIT_VMCNT0();
         }
-        if (stream != 0) return;
     }
 
     // ---- epilogue: normalise and store O (row = query l32, channels db*32 + (j/4)*8 + 4*half + j%4) ----
@@ -413,11 +383,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
 // Second pass behind the fast pass above: the flagged items only.  Usually none is, so the grid is small and every workgroup looks at its
 // share of the flag words, one item per thread and step.
-__global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_flagged(AttnArgs a) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_flagged(AttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-    __shared__ unsigned char s_flagged[kExactThreads];
+    __shared__ unsigned char s_flagged[kThreads];
     const int64_t total_items = (int64_t)a.Sb * a.td.H * a.td.B;
-    for (int64_t base = blockIdx.x; base < total_items; base += (int64_t)kExactThreads * gridDim.x) {
+    for (int64_t base = blockIdx.x; base < total_items; base += (int64_t)kThreads * gridDim.x) {
         const int64_t mine = base + (int64_t)threadIdx.x * gridDim.x;
         int flagged = 0;
         if (mine < total_items) {
@@ -427,7 +397,7 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
         if (!__syncthreads_or(flagged)) continue;
         s_flagged[threadIdx.x] = (unsigned char)flagged;
         __syncthreads();
-        for (int j = 0; j < kExactThreads; ++j) {
+        for (int j = 0; j < kThreads; ++j) {
             if (!s_flagged[j]) continue;          // the same for every thread
             attn_item<true>(a, (int)(base + (int64_t)j * gridDim.x), smem);
             __syncthreads();          // the next item's tile loads overwrite LDS that slower waves may still be reading
@@ -440,8 +410,8 @@ __global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2
 // item costs a whole walk and they come in clusters (the tokens of one object), so they are drawn one by one, an XCD's workgroups
 // from its own eighth first: neighbouring items, which read the same keys, share an L2.  (Every workgroup for the flagged ones of a
 // fixed share of the items: with 229 of 22 296 flagged, 33 frames of 45 x 80 tokens x 24 heads, one of them took two, with 619
-// three: 1.28 -> 0.87 ms for 229, before the two streams; a launch without any 4.7 -> 2.6 us.)
-__global__ __launch_bounds__(kExactThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
+// three: 1.28 -> 0.87 ms for 229, and a launch without any 4.7 -> 2.6 us.)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ int s_item;
     constexpr int kXcds = kAttnQueues;
@@ -485,26 +455,27 @@ bool attn_mfma_supported(const AttnArgs& a) {
     return a.bf16 && a.td.d == kD && a.Bs == kBs && a.td.stride_n * 2 * kChunkKeys < (1ll << 31);
 }
 
-static hipError_t allow_lds(const void* kern, int bytes) { return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); }
+static hipError_t allow_lds(const void* kern) { return hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes); }
 
 hipError_t launch_attn_mfma(const AttnArgs& a, hipStream_t s) {
     if (!attn_mfma_supported(a)) return hipErrorNotSupported;
-    hipError_t attr = allow_lds(reinterpret_cast<const void*>(k_attn_mfma), kLdsBytes);
-    if (attr == hipSuccess) attr = allow_lds(reinterpret_cast<const void*>(k_attn_mfma_flagged), kExactStreams * kLdsBytes);
-    if (attr != hipSuccess) return attr;
+    for (const void* k : {reinterpret_cast<const void*>(k_attn_mfma), reinterpret_cast<const void*>(k_attn_mfma_flagged)}) {
+        hipError_t attr = allow_lds(k);
+        if (attr != hipSuccess) return attr;
+    }
     const int total = a.Sb * a.td.H * a.td.B;
     const int grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
     hipLaunchKernelGGL(k_attn_mfma, dim3(grid), dim3(kThreads), kLdsBytes, s, a);
-    if (a.flags) hipLaunchKernelGGL(k_attn_mfma_flagged, dim3(std::min(total, 1024)), dim3(kExactThreads), kExactStreams * kLdsBytes, s, a);
+    if (a.flags) hipLaunchKernelGGL(k_attn_mfma_flagged, dim3(std::min(total, 1024)), dim3(kThreads), kLdsBytes, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_attn_mfma_second_pass(const AttnArgs& a, hipStream_t s) {
     if (!attn_mfma_supported(a) || !a.flags || !a.queue) return hipErrorNotSupported;
-    hipError_t attr = allow_lds(reinterpret_cast<const void*>(k_attn_mfma_second_pass), kExactStreams * kLdsBytes);
+    hipError_t attr = allow_lds(reinterpret_cast<const void*>(k_attn_mfma_second_pass));
     if (attr != hipSuccess) return attr;
     const int total = a.Sb * a.td.H * a.td.B;
-    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min(total, a.cus)), dim3(kExactThreads), kExactStreams * kLdsBytes, s, a);      // (one fits a CU)
+    hipLaunchKernelGGL(k_attn_mfma_second_pass, dim3(std::min(total, 2 * a.cus)), dim3(kThreads), kLdsBytes, s, a);      // (two fit a CU)
     return hipGetLastError();
 }
 
