@@ -21,6 +21,13 @@ constexpr float kExpScale = (float)(1.4426950408889634 / 11.313708498984760);
 // |logit| (about |logit| * 2^-9 per channel, random in sign).  Rows whose largest exponent, in units of log2, is
 // beyond this limit in magnitude (44 in natural units) are taken again with the scale applied in fp32.
 constexpr float kExactLimit = 64.0f;
+// A query has no exponent reference before the first 64 keys that it can see.  The fast pass takes a chunk's maximum from this exponent
+// on (below it the factor 2^-maximum on the sums, still 0, would be infinite, and the chunk's probabilities are 0 against a reference
+// of 0 as well); the fp32-scaled pass any finite one.
+constexpr float kFirstFloor = -126.0f;
+// A reference that moves up by more than this, in units of log2, starts anew: whatever it had summed has weight 0, and the logits
+// are taken again as the products give them, because relative to the old reference they have lost their low bits.
+constexpr float kFarMove = 4096.0f;
 
 // The barrier carries no memory fence on purpose: a fence would drain the prefetch of the next
 // chunk.  Ordering of the direct-to-LDS loads is enforced by the explicit vmcnt waits.
@@ -47,6 +54,36 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t x) {
 __device__ __forceinline__ float max_across_halves(float x) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+
+// How the exponent reference of a lane's query moves where a chunk's maximum is `top` (fast pass: relative to the reference, whose negative
+// the logits start from; kExact: of the logits as the products give them).  `m_ref` and `unset`, the lanes whose query has none
+// yet, are updated; what was summed so far counts alpha times, and the chunk's exponents are kExact: scale * logit - base - delta,
+// else logit - delta.  A query that sees none of the chunk's keys (logits of -inf) stays without a reference.
+struct Move { float base, delta, alpha; };
+template <bool kExact>
+__device__ __forceinline__ Move move_reference(float top, float& m_ref, uint64_t& unset) {
+    const bool none = __builtin_amdgcn_inverse_ballot_w64(unset);
+    Move mv;
+    if constexpr (kExact) {
+        const bool anew = none || __builtin_fmaf(top, kExpScale, -m_ref) > kFarMove;
+        mv.base = anew ? 0.f : m_ref;
+        const float mx = __builtin_fmaf(top, kExpScale, -mv.base);
+        const bool nothing = anew && !(mx > -INFINITY);
+        mv.delta = nothing ? 0.f : anew ? mx : fmaxf(mx, 0.f);
+        mv.alpha = anew ? 0.f : __builtin_amdgcn_exp2f(-mv.delta);
+        m_ref = mv.base + mv.delta;
+        unset = __ballot(nothing);
+    } else {
+        const bool nothing = none && !(top >= kFirstFloor);
+        mv.base = 0.f;
+        mv.delta = nothing ? 0.f : none ? top : fmaxf(top, 0.f);
+        mv.alpha = __builtin_amdgcn_exp2f(-mv.delta);
+        m_ref += mv.delta;
+        unset = __ballot(nothing);
+    }
+    return mv;
 }
 
 }  // namespace mfma

@@ -25,7 +25,7 @@
 //
 // Softmax.  Q is pre-multiplied by log2(e)/sqrt(d) and every logit accumulation starts from -m_ref, so
 // the first product delivers the exponent of 2 directly.  The exponent reference m_ref of a query is set
-// to the row maximum of the first chunk and afterwards moved only when needed: softmax is invariant to
+// to the row maximum of the first chunk whose keys it can see and afterwards moved only when needed: softmax is invariant to
 // the reference, and fp32 / bf16 share one exponent range, so a stale reference costs no accuracy as
 // long as nothing overflows.  The guard is the chunk's own contribution to the normaliser (a lane's 32
 // probabilities, summed with v_dot2c_f32_bf16 from the bf16-rounded values, i.e. exactly what the second
@@ -88,8 +88,9 @@ __device__ __forceinline__ void issue_chunk(const LoadPlan& lp, const char* Kh, 
 struct State {
     v16f o[4];        // O^T accumulators: channel block db, value j -> channel db*32 + (j/4)*8 + 4*half + j%4
     v16f cinit;       // -m_ref in all sixteen values: the C operand that starts every logit accumulation
-    float m_ref;      // exponent reference of this lane's query column, in log2 units (0 before the first chunk)
+    float m_ref;      // exponent reference of this lane's query column, in log2 units (0 before it has one)
     float l_part;     // this lane's share of the normaliser
+    uint64_t unset;   // lanes whose query has no reference yet (both halves of a column alike)
 };
 
 struct ReadPlan {
@@ -98,8 +99,7 @@ struct ReadPlan {
 };
 
 template <int STAGE, bool kExact, class F>
-__device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[8], State& st, bool& first,
-                                           int valid, int half, F&& issue) {
+__device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[8], State& st, int valid, int half, F&& issue) {
     typedef __attribute__((address_space(3))) const v8bf* lds_v8;
     typedef __attribute__((address_space(3))) v4s* lds_v4;
     constexpr uint32_t kK = STAGE * kStageBytes, kV = STAGE * kStageBytes + kTileBytes;
@@ -107,7 +107,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // ---- S^T = K Q^T : [64 keys x 32 queries], two independent accumulator chains ----
     // Q is pre-scaled by log2(e)/sqrt(d) and the accumulation starts from -m_ref, so the MFMA output is directly
     // the exponent of 2: no per-element scale or subtract is left for the vector ALU.  (kExact: Q is taken as
-    // stored, the accumulation starts from zero and the scale and the reference are applied in fp32 afterwards.)
+    // stored, the accumulation starts from zero and the scale and the reference are applied in fp32 to each exponent.)
     v16f s[2];
     if constexpr (kExact) {
 #pragma unroll
@@ -130,13 +130,6 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
         for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) s[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mb][ks], qf[ks], s[mb], 0, 0, 0);
-    }
-    if constexpr (kExact) {
-        const float cs = kExpScale, neg_ref = -st.m_ref;
-#pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] = __builtin_fmaf(s[mb][j], cs, neg_ref);
     }
     __builtin_amdgcn_sched_barrier(0);
     // ---- V^T fragments: issued now so that they land while the softmax runs ----
@@ -166,12 +159,12 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // ---- online softmax, per query column ----
     // The exponentials are taken against the current reference straight away; the chunk's share of the normaliser
     // doubles as the overflow guard (it bounds every probability of the lane), so the row maximum is only formed
-    // on the rare path that moves the reference (and on the first chunk, where no reference exists yet).
+    // on the rare path that moves the reference (and while a query has none).
     v8bf pf[2][2];
     v2bf ones;
     ones[0] = (__bf16)1.0f;
     ones[1] = (__bf16)1.0f;
-    auto exps = [&](float& lsum) {
+    auto exps = [&](float& lsum, auto&& exponent) {
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -179,8 +172,8 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
                     v2bf pk;
-                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i]);
-                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i + 1]);
+                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i]));
+                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i + 1]));
                     lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);
                     pf[mb][t][i] = pk[0];
                     pf[mb][t][i + 1] = pk[1];
@@ -188,31 +181,30 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
             }
     };
     float lc = 0.f;
-    if (!first) exps(lc);
-    if (first || __any(!(lc <= kSumLimit))) {
+    const float neg_ref = -st.m_ref;
+    if (st.unset == 0) exps(lc, [&](float x) { return kExact ? __builtin_fmaf(x, kExpScale, neg_ref) : x; });
+    if (st.unset != 0 || __any(!(lc <= kSumLimit))) {
         float mx = -INFINITY;
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
             for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[mb][j]);
-        mx = max_across_halves(mx);                         // finite: every chunk holds at least one valid key
-        const float delta = first ? mx : fmaxf(mx, 0.f);
-        const float alpha = __builtin_amdgcn_exp2f(-delta);
-        st.m_ref += delta;
-        st.l_part *= alpha;
+        const Move mv = move_reference<kExact>(max_across_halves(mx), st.m_ref, st.unset);
+        st.l_part *= mv.alpha;
+        if constexpr (!kExact) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) st.cinit[j] -= delta;
+            for (int j = 0; j < 16; ++j) st.cinit[j] -= mv.delta;
+        }
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] -= delta;
+            for (int j = 0; j < 16; ++j) s[mb][j] = (kExact ? __builtin_fmaf(s[mb][j], kExpScale, -mv.base) : s[mb][j]) - mv.delta;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) st.o[db][j] *= alpha;
-        first = false;
+            for (int j = 0; j < 16; ++j) st.o[db][j] *= mv.alpha;
         lc = 0.f;
-        exps(lc);
+        exps(lc, [](float x) { return x; });
     }
     st.l_part += lc;
 
@@ -289,7 +281,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
     State st;
     st.m_ref = 0.f;
     st.l_part = 0.f;
-    bool first = true;
+    st.unset = ~0ull;
 #pragma unroll
     for (int j = 0; j < 16; ++j) st.cinit[j] = 0.f;
 #pragma unroll
@@ -323,13 +315,13 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
         const int key0 = kb * kBs;
         const int n_chunks = (kb == a.Sb - 1) ? last_blk_chunks : 2;
         DR_BARRIER();
-        chunk_body<0, kExact>(rd, qf, st, first, N - key0, half, [&]() { if (n_chunks == 2) issue_chunk<1>(lp, Kh, Vh, key0 + kChunkKeys, N - 1); });
+        chunk_body<0, kExact>(rd, qf, st, N - key0, half, [&]() { if (n_chunks == 2) issue_chunk<1>(lp, Kh, Vh, key0 + kChunkKeys, N - 1); });
         DR_WAIT_VMCNT0();
         if (((blk + 1) & 63) == 0 && blk + 1 < n_blocks) win = load_window(blk + 1);
         kb_next = (blk + 1 < n_blocks) ? entry(win, blk + 1) : -1;
         if (n_chunks == 2) {
             DR_BARRIER();
-            chunk_body<1, kExact>(rd, qf, st, first, N - key0 - kChunkKeys, half, [&]() { if (kb_next >= 0) issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1); });
+            chunk_body<1, kExact>(rd, qf, st, N - key0 - kChunkKeys, half, [&]() { if (kb_next >= 0) issue_chunk<0>(lp, Kh, Vh, kb_next * kBs, N - 1); });
             DR_WAIT_VMCNT0();
         } else if (kb_next >= 0) {   // only for a list that is not ascending: nothing was prefetched, load serially
             DR_BARRIER();
@@ -360,7 +352,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
     }
     if constexpr (!kExact) {
         if (a.flags) {
-            const bool out_of_range = qrow < N && l > 0.f && !(fabsf(st.m_ref + __log2f(l)) <= kExactLimit);
+            // (l = 0 where keys are listed: every exponential underflowed)
+            const bool out_of_range = qrow < N && (l > 0.f ? !(fabsf(st.m_ref + __log2f(l)) <= kExactLimit) : l == 0.f && n_blocks > 0);
             const int any = __any(out_of_range) ? 1 : 0;
             if (lane == 0) a.flags[(int64_t)item * 4 + wave] = any;
         }

@@ -90,6 +90,7 @@ struct State {
     v16f o[4];
     float m_ref;
     float l_part;
+    uint64_t unset;   // lanes whose query has no exponent reference yet
 };
 
 // The swizzles are xors on the 16-byte piece index and the LDS block is 1 KB aligned, so the address of contraction
@@ -103,9 +104,8 @@ struct ReadPlan {
 // one at byte offset sel_off of the K and V tiles (0 or 32 rows).  valid0 / valid1: number of real keys in the
 // (first / second) half processed (>= 32: all).
 template <int STAGE, int MBM, bool kExact, class F>
-__device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[8], State& st, bool& first,
-                                           int valid0, int valid1, float init0, float init1, uint32_t sel_off, int half,
-                                           F&& issue) {
+__device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[8], State& st, int valid0, int valid1, float init0, float init1,
+                                           uint32_t sel_off, int half, F&& issue) {
     typedef __attribute__((address_space(3))) const v8bf* lds_v8;
     typedef __attribute__((address_space(3))) v4s* lds_v4;
     constexpr uint32_t kK = STAGE * kStageBytes, kV = STAGE * kStageBytes + kTileBytes;
@@ -131,7 +131,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // The accumulation starts from -m_ref, so the matrix instruction delivers the logits relative to the exponent
     // reference (the accumulators have to be initialised anyway; the Bs = 128 kernel keeps this vector in registers).
     // (kExact: Q is taken as stored, the accumulation starts from zero, and the exponent scale and the reference are
-    // applied in fp32 afterwards.)
+    // applied in fp32 to each exponent.)
     v16f s[2];
     const float c0 = kExact ? 0.f : init0 - st.m_ref, c1 = kExact ? 0.f : init1 - st.m_ref;
 #pragma unroll
@@ -157,11 +157,12 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
         __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (kExact) {
-        const float cs = kExpScale, a0 = init0 - st.m_ref, a1 = init1 - st.m_ref;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
+            if ((mb ? init1 : init0) != 0.f) {         // wavefront-uniform
 #pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] = __builtin_fmaf(s[mb][j], cs, mb ? a1 : a0);
+                for (int j = 0; j < 16; ++j) s[mb][j] = -INFINITY;
+            }
     }
     v8bf vfa[2][4];
     read_v(MB0, vfa);                              // lands while the softmax runs
@@ -184,7 +185,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     v2bf ones;
     ones[0] = (__bf16)1.0f;
     ones[1] = (__bf16)1.0f;
-    auto exps = [&](float& lsum) {
+    auto exps = [&](float& lsum, auto&& exponent) {
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
@@ -192,8 +193,8 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
                     v2bf pk;
-                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i]);
-                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i + 1]);
+                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i]));
+                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i + 1]));
                     lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);
                     pf[mb][t][i] = pk[0];
                     pf[mb][t][i + 1] = pk[1];
@@ -201,29 +202,26 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
             }
     };
     float lc = 0.f;
-    if (!first) exps(lc);
-    if (first || __any(!(lc <= kSumLimit))) {
+    const float neg_ref = -st.m_ref;
+    if (st.unset == 0) exps(lc, [&](float x) { return kExact ? __builtin_fmaf(x, kExpScale, neg_ref) : x; });
+    if (st.unset != 0 || __any(!(lc <= kSumLimit))) {
         float mx = -INFINITY;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
             for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[mb][j]);
-        mx = max_across_halves(mx);        // finite: the first active sub-block of a chunk starts a key block
-        const float delta = first ? mx : fmaxf(mx, 0.f);
-        const float alpha = __builtin_amdgcn_exp2f(-delta);
-        st.m_ref += delta;
-        st.l_part *= alpha;
+        const Move mv = move_reference<kExact>(max_across_halves(mx), st.m_ref, st.unset);
+        st.l_part *= mv.alpha;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] -= delta;
+            for (int j = 0; j < 16; ++j) s[mb][j] = (kExact ? __builtin_fmaf(s[mb][j], kExpScale, -mv.base) : s[mb][j]) - mv.delta;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) st.o[db][j] *= alpha;
-        first = false;
+            for (int j = 0; j < 16; ++j) st.o[db][j] *= mv.alpha;
         lc = 0.f;
-        exps(lc);
+        exps(lc, [](float x) { return x; });
     }
     st.l_part += lc;
 
@@ -310,7 +308,7 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
     State st;
     st.m_ref = 0.f;
     st.l_part = 0.f;
-    bool first = true;
+    st.unset = ~0ull;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -369,12 +367,12 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
         const int mbm = (int)((c.rows0 >> my_row) & 1u) | (int)(((c.rows1 >> my_row) & 1u) << 1);
         const int valid0 = N - c.kb0 * BS;
         if (BS == 64) {
-            if (mbm == 3) chunk_body<STAGE, 3, kExact>(rd, qf, st, first, valid0, valid0 - 32, 0.f, 0.f, 0u, half, issue);
+            if (mbm == 3) chunk_body<STAGE, 3, kExact>(rd, qf, st, valid0, valid0 - 32, 0.f, 0.f, 0u, half, issue);
             else issue();
         } else {
             const int valid1 = (c.kb1 >= 0) ? N - c.kb1 * BS : 32;
             if (mbm != 0)
-                chunk_body<STAGE, 3, kExact>(rd, qf, st, first, valid0, valid1, (mbm & 1) ? 0.f : -INFINITY,
+                chunk_body<STAGE, 3, kExact>(rd, qf, st, valid0, valid1, (mbm & 1) ? 0.f : -INFINITY,
                                      (mbm & 2) ? 0.f : -INFINITY, 0u, half, issue);
             else issue();
         }
@@ -424,7 +422,8 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
     }
     if constexpr (!kExact) {
         if (a.flags) {
-            const bool out_of_range = qrow < N && l > 0.f && !(fabsf(st.m_ref + __log2f(l)) <= kExactLimit);
+            const int qb = min(qrow / BS, a.Sb - 1);      // (l = 0 where keys are listed: every exponential underflowed)
+            const bool out_of_range = qrow < N && (l > 0.f ? !(fabsf(st.m_ref + __log2f(l)) <= kExactLimit) : l == 0.f && rp[qb + 1] > rp[qb]);
             const int any = __any(out_of_range) ? 1 : 0;
             if (lane == 0) a.flags[(int64_t)item * 4 + wave] = any;
         }

@@ -24,13 +24,18 @@ def attend(Q, K, V, lists, bs):
     return O, lse
 
 
-def check_rows(O, lse, Q, K, V, rows, keys):
+def check_rows(O, lse, Q, K, V, rows, keys, scaled_q=False):
     """Rows `rows` of one head against fp64 over the keys `keys`.  The probabilities are rounded to bf16 (2^-8 each, in the sum of O and in the
-    normaliser alike) and so is O; what is left, logits summed in 32 bits, is 128 products of 2^-24 of the largest."""
-    s = Q[rows].double() @ K[keys].double().T / math.sqrt(Q.shape[-1])
+    normaliser alike) and so is O; what is left, logits summed in 32 bits, is 128 products of 2^-24 of the largest of weight.
+    scaled_q: the fast pass, whose scaled Q is rounded to bf16 again, 2^-8 of every product."""
+    q, k = Q[rows].double(), K[keys].double()
+    s = q @ k.T / math.sqrt(Q.shape[-1])
     p, v = torch.softmax(s, -1), V[keys].double()
     want, want_lse = p @ v, torch.logsumexp(s, -1)
-    slack = 128 * 2.0 ** -24 * s.abs().amax(-1)
+    weight = p > 2.0 ** -60
+    slack = 128 * 2.0 ** -24 * torch.where(weight, s.abs(), 0.0).amax(-1)
+    if scaled_q:
+        slack = slack + 2.0 ** -8 * torch.where(weight, q.abs() @ k.abs().T / math.sqrt(Q.shape[-1]), 0.0).amax(-1)
     spread = torch.stack([(p * (v[:, c] - want[:, c:c + 1]).abs()).sum(-1) for c in range(v.shape[1])], -1)
     assert ((O[rows].double() - want).abs() <= 2.0 ** -8 * (1.02 * spread + 1.02 * want.abs()) + 2 * slack[:, None] * spread + 1e-6).all()
     assert ((lse[rows].double() - want_lse).abs() <= 2.0 ** -8 + slack + 2.0 ** -22 * want_lse.abs()).all()
