@@ -21,13 +21,11 @@ constexpr float kExpScale = (float)(1.4426950408889634 / 11.313708498984760);
 // |logit| (about |logit| * 2^-9 per channel, random in sign).  Rows whose largest exponent, in units of log2, is
 // beyond this limit in magnitude (44 in natural units) are taken again with the scale applied in fp32.
 constexpr float kExactLimit = 64.0f;
-// A query has no exponent reference before the first 64 keys that it can see.  The fast pass takes a chunk's maximum from this exponent
-// on (below it the factor 2^-maximum on the sums, still 0, would be infinite, and the chunk's probabilities are 0 against a reference
-// of 0 as well); the fp32-scaled pass any finite one.
-constexpr float kFirstFloor = -126.0f;
-// A reference that moves up by more than this, in units of log2, starts anew: whatever it had summed has weight 0, and the logits
-// are taken again as the products give them, because relative to the old reference they have lost their low bits.
-constexpr float kFarMove = 4096.0f;
+// The first chunk of a row sets its exponent reference, but to no less than this (units of log2).  Fast pass: what the chunk's keys weigh
+// against -126 is lost where a later key lies 2^7 above, and a row that ends without a sum is flagged.  fp32-scaled pass: relative to
+// a reference far below, the logits of later keys would lose their low bits; a row that ends without a sum is walked again, and
+// may begin this much below its largest exponent.
+constexpr float kFastFloor = -126.0f, kExactFloor = -4096.0f;
 
 // The barrier carries no memory fence on purpose: a fence would drain the prefetch of the next
 // chunk.  Ordering of the direct-to-LDS loads is enforced by the explicit vmcnt waits.
@@ -57,33 +55,19 @@ __device__ __forceinline__ float max_across_halves(float x) {
 }
 
 
-// How the exponent reference of a lane's query moves where a chunk's maximum is `top` (fast pass: relative to the reference, whose negative
-// the logits start from; kExact: of the logits as the products give them).  `m_ref` and `unset`, the lanes whose query has none
-// yet, are updated; what was summed so far counts alpha times, and the chunk's exponents are kExact: scale * logit - base - delta,
-// else logit - delta.  A query that sees none of the chunk's keys (logits of -inf) stays without a reference.
-struct Move { float base, delta, alpha; };
-template <bool kExact>
-__device__ __forceinline__ Move move_reference(float top, float& m_ref, uint64_t& unset) {
-    const bool none = __builtin_amdgcn_inverse_ballot_w64(unset);
-    Move mv;
-    if constexpr (kExact) {
-        const bool anew = none || __builtin_fmaf(top, kExpScale, -m_ref) > kFarMove;
-        mv.base = anew ? 0.f : m_ref;
-        const float mx = __builtin_fmaf(top, kExpScale, -mv.base);
-        const bool nothing = anew && !(mx > -INFINITY);
-        mv.delta = nothing ? 0.f : anew ? mx : fmaxf(mx, 0.f);
-        mv.alpha = anew ? 0.f : __builtin_amdgcn_exp2f(-mv.delta);
-        m_ref = mv.base + mv.delta;
-        unset = __ballot(nothing);
-    } else {
-        const bool nothing = none && !(top >= kFirstFloor);
-        mv.base = 0.f;
-        mv.delta = nothing ? 0.f : none ? top : fmaxf(top, 0.f);
-        mv.alpha = __builtin_amdgcn_exp2f(-mv.delta);
-        m_ref += mv.delta;
-        unset = __ballot(nothing);
+// Behind a walk of the fp32-scaled pass: whether the workgroup has rows that list keys but are without a sum, and whose largest exponent
+// is a number; their floor then is set by it.  Called by all waves.  largest(): of this lane's query column, as the product of Q and K gives
+// it, not scaled.
+template <class F>
+__device__ __forceinline__ bool walk_again(float l_part, bool listed, float& floor, F&& largest) {
+    const bool none = listed && l_part + __shfl_xor(l_part, 32) == 0.f;
+    bool low = false;
+    if (__any(none)) {
+        const float best = largest() * kExpScale;
+        low = none && best > -INFINITY && best + kExactFloor < floor;      // (behind the second walk: no)
+        if (low) floor = best + kExactFloor;
     }
-    return mv;
+    return __syncthreads_or(low);
 }
 
 }  // namespace mfma

@@ -25,7 +25,7 @@
 //
 // Softmax.  Q is pre-multiplied by log2(e)/sqrt(d) and every logit accumulation starts from -m_ref, so
 // the first product delivers the exponent of 2 directly.  The exponent reference m_ref of a query is set
-// to the row maximum of the first chunk whose keys it can see and afterwards moved only when needed: softmax is invariant to
+// to the row maximum of the first chunk (kFastFloor, kExactFloor at least) and afterwards moved only when needed: softmax is invariant to
 // the reference, and fp32 / bf16 share one exponent range, so a stale reference costs no accuracy as
 // long as nothing overflows.  The guard is the chunk's own contribution to the normaliser (a lane's 32
 // probabilities, summed with v_dot2c_f32_bf16 from the bf16-rounded values, i.e. exactly what the second
@@ -88,9 +88,10 @@ __device__ __forceinline__ void issue_chunk(const LoadPlan& lp, const char* Kh, 
 struct State {
     v16f o[4];        // O^T accumulators: channel block db, value j -> channel db*32 + (j/4)*8 + 4*half + j%4
     v16f cinit;       // -m_ref in all sixteen values: the C operand that starts every logit accumulation
-    float m_ref;      // exponent reference of this lane's query column, in log2 units (0 before it has one)
+    float m_ref;      // exponent reference of this lane's query column, in log2 units (0 before the first chunk)
     float l_part;     // this lane's share of the normaliser
-    uint64_t unset;   // lanes whose query has no reference yet (both halves of a column alike)
+    float floor;      // kExact: the least reference that the first chunk sets
+    bool first;       // no chunk has been taken
 };
 
 struct ReadPlan {
@@ -107,7 +108,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // ---- S^T = K Q^T : [64 keys x 32 queries], two independent accumulator chains ----
     // Q is pre-scaled by log2(e)/sqrt(d) and the accumulation starts from -m_ref, so the MFMA output is directly
     // the exponent of 2: no per-element scale or subtract is left for the vector ALU.  (kExact: Q is taken as
-    // stored, the accumulation starts from zero and the scale and the reference are applied in fp32 to each exponent.)
+    // stored, the accumulation starts from zero and the scale and the reference are applied in fp32 afterwards.)
     v16f s[2];
     if constexpr (kExact) {
 #pragma unroll
@@ -130,6 +131,13 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
         for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
             for (int mb = 0; mb < 2; ++mb) s[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[mb][ks], qf[ks], s[mb], 0, 0, 0);
+    }
+    if constexpr (kExact) {
+        const float cs = kExpScale, neg_ref = -st.m_ref;
+#pragma unroll
+        for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) s[mb][j] = __builtin_fmaf(s[mb][j], cs, neg_ref);
     }
     __builtin_amdgcn_sched_barrier(0);
     // ---- V^T fragments: issued now so that they land while the softmax runs ----
@@ -159,12 +167,12 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // ---- online softmax, per query column ----
     // The exponentials are taken against the current reference straight away; the chunk's share of the normaliser
     // doubles as the overflow guard (it bounds every probability of the lane), so the row maximum is only formed
-    // on the rare path that moves the reference (and while a query has none).
+    // on the rare path that moves the reference (and on the first chunk, where no reference exists yet).
     v8bf pf[2][2];
     v2bf ones;
     ones[0] = (__bf16)1.0f;
     ones[1] = (__bf16)1.0f;
-    auto exps = [&](float& lsum, auto&& exponent) {
+    auto exps = [&](float& lsum) {
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
@@ -172,8 +180,8 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
                     v2bf pk;
-                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i]));
-                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i + 1]));
+                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i]);
+                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i + 1]);
                     lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);
                     pf[mb][t][i] = pk[0];
                     pf[mb][t][i + 1] = pk[1];
@@ -181,30 +189,31 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
             }
     };
     float lc = 0.f;
-    const float neg_ref = -st.m_ref;
-    if (st.unset == 0) exps(lc, [&](float x) { return kExact ? __builtin_fmaf(x, kExpScale, neg_ref) : x; });
-    if (st.unset != 0 || __any(!(lc <= kSumLimit))) {
+    if (!st.first) exps(lc);
+    if (st.first || __any(!(lc <= kSumLimit))) {
         float mx = -INFINITY;
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
             for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[mb][j]);
-        const Move mv = move_reference<kExact>(max_across_halves(mx), st.m_ref, st.unset);
-        st.l_part *= mv.alpha;
-        if constexpr (!kExact) {
+        mx = max_across_halves(mx);
+        const float delta = st.first ? fmaxf(mx, kExact ? st.floor : kFastFloor) : fmaxf(mx, 0.f);
+        const float alpha = kExact && st.first ? 0.f : __builtin_amdgcn_exp2f(-delta);      // (first: the sums are 0)
+        st.m_ref += delta;
+        st.l_part *= alpha;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) st.cinit[j] -= mv.delta;
-        }
+        for (int j = 0; j < 16; ++j) st.cinit[j] -= delta;
 #pragma unroll
         for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] = (kExact ? __builtin_fmaf(s[mb][j], kExpScale, -mv.base) : s[mb][j]) - mv.delta;
+            for (int j = 0; j < 16; ++j) s[mb][j] -= delta;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) st.o[db][j] *= mv.alpha;
+            for (int j = 0; j < 16; ++j) st.o[db][j] *= alpha;
+        st.first = false;
         lc = 0.f;
-        exps(lc, [](float x) { return x; });
+        exps(lc);
     }
     st.l_part += lc;
 
@@ -278,17 +287,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
         }
     }
 
-    State st;
-    st.m_ref = 0.f;
-    st.l_part = 0.f;
-    st.unset = ~0ull;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) st.cinit[j] = 0.f;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) st.o[db][j] = 0.f;
-
     // The row's key-block list is walked through a 64-entry register window (lane i holds entry base + i):
     // the per-block index comes from v_readlane, so no memory access sits on the loop's critical path.
     const int n_blocks = end - beg;
@@ -297,6 +295,36 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
     auto entry = [&](int win, int blk) {      // clamped, so that a malformed list cannot address outside K/V
         return min(max(__builtin_amdgcn_readlane(win, blk & 63), 0), a.Sb - 1);
     };
+    // the largest logit of each query column, straight from memory: rare
+    auto largest = [&]() {
+        float mx = -INFINITY;
+        for (int blk = 0; blk < n_blocks; ++blk) {
+            const int key0 = min(max(__builtin_amdgcn_readfirstlane(ci[beg + blk]), 0), a.Sb - 1) * kBs;
+            for (int t = key0; t < min(key0 + kBs, N); t += 32) {
+                const char* src = Kh + (int64_t)min(t + l32, N - 1) * row_bytes + half * 16;      // (past the end: the last key again)
+                v16f s;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s[j] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const v8bf*>(src + ks * 32), qf[ks], s, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[j]);
+            }
+        }
+        return max_across_halves(mx);
+    };
+    State st;
+    st.floor = kExactFloor;
+    do {
+    st.m_ref = 0.f;
+    st.l_part = 0.f;
+    st.first = true;
+#pragma unroll
+    for (int j = 0; j < 16; ++j) st.cinit[j] = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) st.o[db][j] = 0.f;
     int win = load_window(0);
     // Pin the Q fragments and the window as "arrived" before the loop: otherwise the compiler, which cannot see
     // the hand-issued tile loads, re-waits for its own outstanding loads inside the loop with counts that
@@ -329,6 +357,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, int item, unsigned 
             DR_WAIT_VMCNT0();
         }
     }
+    if constexpr (!kExact) break;
+    } while (walk_again(st.l_part, n_blocks > 0, st.floor, largest));
 
     // ---- epilogue: normalise and store O (row = query l32, channels db*32 + (j/4)*8 + 4*half + j%4) ----
     char* Oh = reinterpret_cast<char*>(a.O) + head_off;

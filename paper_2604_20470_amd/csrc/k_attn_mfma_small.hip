@@ -90,7 +90,8 @@ struct State {
     v16f o[4];
     float m_ref;
     float l_part;
-    uint64_t unset;   // lanes whose query has no exponent reference yet
+    float floor;      // kExact: the least reference that the first chunk sets
+    bool first;       // no chunk has been taken
 };
 
 // The swizzles are xors on the 16-byte piece index and the LDS block is 1 KB aligned, so the address of contraction
@@ -131,7 +132,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     // The accumulation starts from -m_ref, so the matrix instruction delivers the logits relative to the exponent
     // reference (the accumulators have to be initialised anyway; the Bs = 128 kernel keeps this vector in registers).
     // (kExact: Q is taken as stored, the accumulation starts from zero, and the exponent scale and the reference are
-    // applied in fp32 to each exponent.)
+    // applied in fp32 afterwards.)
     v16f s[2];
     const float c0 = kExact ? 0.f : init0 - st.m_ref, c1 = kExact ? 0.f : init1 - st.m_ref;
 #pragma unroll
@@ -157,12 +158,11 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
         __builtin_amdgcn_sched_barrier(0);
     }
     if constexpr (kExact) {
+        const float cs = kExpScale, a0 = init0 - st.m_ref, a1 = init1 - st.m_ref;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
-            if ((mb ? init1 : init0) != 0.f) {         // wavefront-uniform
 #pragma unroll
-                for (int j = 0; j < 16; ++j) s[mb][j] = -INFINITY;
-            }
+            for (int j = 0; j < 16; ++j) s[mb][j] = __builtin_fmaf(s[mb][j], cs, mb ? a1 : a0);
     }
     v8bf vfa[2][4];
     read_v(MB0, vfa);                              // lands while the softmax runs
@@ -185,7 +185,7 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
     v2bf ones;
     ones[0] = (__bf16)1.0f;
     ones[1] = (__bf16)1.0f;
-    auto exps = [&](float& lsum, auto&& exponent) {
+    auto exps = [&](float& lsum) {
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
@@ -193,8 +193,8 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
 #pragma unroll
                 for (int i = 0; i < 8; i += 2) {
                     v2bf pk;
-                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i]));
-                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(exponent(s[mb][t * 8 + i + 1]));
+                    pk[0] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i]);
+                    pk[1] = (__bf16)__builtin_amdgcn_exp2f(s[mb][t * 8 + i + 1]);
                     lsum = __builtin_amdgcn_fdot2_f32_bf16(pk, ones, lsum, false);
                     pf[mb][t][i] = pk[0];
                     pf[mb][t][i + 1] = pk[1];
@@ -202,26 +202,29 @@ __device__ __forceinline__ void chunk_body(const ReadPlan& rd, const v8bf (&qf)[
             }
     };
     float lc = 0.f;
-    const float neg_ref = -st.m_ref;
-    if (st.unset == 0) exps(lc, [&](float x) { return kExact ? __builtin_fmaf(x, kExpScale, neg_ref) : x; });
-    if (st.unset != 0 || __any(!(lc <= kSumLimit))) {
+    if (!st.first) exps(lc);
+    if (st.first || __any(!(lc <= kSumLimit))) {
         float mx = -INFINITY;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
             for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[mb][j]);
-        const Move mv = move_reference<kExact>(max_across_halves(mx), st.m_ref, st.unset);
-        st.l_part *= mv.alpha;
+        mx = max_across_halves(mx);
+        const float delta = st.first ? fmaxf(mx, kExact ? st.floor : kFastFloor) : fmaxf(mx, 0.f);
+        const float alpha = kExact && st.first ? 0.f : __builtin_amdgcn_exp2f(-delta);      // (first: the sums are 0)
+        st.m_ref += delta;
+        st.l_part *= alpha;
 #pragma unroll
         for (int mb = MB0; mb < MB1; ++mb)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) s[mb][j] = (kExact ? __builtin_fmaf(s[mb][j], kExpScale, -mv.base) : s[mb][j]) - mv.delta;
+            for (int j = 0; j < 16; ++j) s[mb][j] -= delta;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) st.o[db][j] *= mv.alpha;
+            for (int j = 0; j < 16; ++j) st.o[db][j] *= alpha;
+        st.first = false;
         lc = 0.f;
-        exps(lc, [](float x) { return x; });
+        exps(lc);
     }
     st.l_part += lc;
 
@@ -305,15 +308,6 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
         rd.v_base = lds0 + r0 * kRowBytes + ((piece ^ (v_e << 2)) << 4) + (v_c & 1) * 8;
     }
 
-    State st;
-    st.m_ref = 0.f;
-    st.l_part = 0.f;
-    st.unset = ~0ull;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) st.o[db][j] = 0.f;
-
     // ---- the group's pre-merged list: entry = key block | (rows listing it) << 28, through a 64-entry register window ----
     const int gmask = (a.mask_heads == 1) ? 0 : h;
     const int64_t gid = ((int64_t)b * a.mask_heads + gmask) * groups + qg;
@@ -321,11 +315,11 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
     const int64_t goff = min(max((int64_t)__builtin_amdgcn_readfirstlane(rp[first_row]), (int64_t)0), a.colidx_stride);   // as in k_group_union
     const int32_t* gl = a.gcol + ((int64_t)b * a.mask_heads + gmask) * a.colidx_stride + goff;
     const int cnt = __builtin_amdgcn_readfirstlane(a.gcount[gid]);
-    int pos = 0;
-    int win = (cnt > 0) ? gl[min(lane, cnt - 1)] : 0;
+    int pos = 0, win = 0;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) asm volatile("" : "+v"(qf[ks]));
-    asm volatile("" : "+v"(win));
+    State st;
+    st.floor = kExactFloor;
     auto next_entry = [&](int& kb, uint32_t& rows) {
         if (pos >= cnt) { kb = kNoBlock; rows = 0; return; }
         const uint32_t e = (uint32_t)__builtin_amdgcn_readlane(win, pos & 63);
@@ -378,6 +372,37 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
         }
     };
 
+    // the largest logit of each query column, straight from memory: rare
+    auto largest = [&]() {
+        float mx = -INFINITY;
+        for (int e = 0; e < cnt; ++e) {
+            const uint32_t entry = (uint32_t)__builtin_amdgcn_readfirstlane(gl[e]);
+            if (!((entry >> 28 >> my_row) & 1u)) continue;
+            const int key0 = min((int)(entry & 0x0fffffffu), a.Sb - 1) * BS;
+            for (int t = key0; t < min(key0 + BS, N); t += 32) {
+                const char* src = Kh + (int64_t)min(t + l32, N - 1) * row_bytes + half * 16;      // (past the end: the last key again)
+                v16f s;
+#pragma unroll
+                for (int j = 0; j < 16; ++j) s[j] = 0.f;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const v8bf*>(src + ks * 32), qf[ks], s, 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < 16; ++j) mx = fmaxf(mx, s[j]);
+            }
+        }
+        return max_across_halves(mx);
+    };
+    do {
+    st.m_ref = 0.f;
+    st.l_part = 0.f;
+    st.first = true;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) st.o[db][j] = 0.f;
+    pos = 0;
+    win = (cnt > 0) ? gl[min(lane, cnt - 1)] : 0;
+    asm volatile("" : "+v"(win));
     Chunk cur = fetch();
     if (cur.valid) {
         issue0(cur);
@@ -399,6 +424,8 @@ __device__ __forceinline__ void attn_small_body(const AttnArgs& a) {
             cur = nxt;
         }
     }
+    if constexpr (!kExact) break;
+    } while (walk_again(st.l_part, cnt > 0, st.floor, largest));
 
     // ---- epilogue ----
     char* Oh = reinterpret_cast<char*>(a.O) + head_off;
