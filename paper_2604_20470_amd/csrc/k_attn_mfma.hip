@@ -433,13 +433,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 // item costs a whole walk and they come in clusters (the tokens of one object), so they are drawn one by one, an XCD's workgroups
 // from its own eighth first: neighbouring items, which read the same keys, share an L2.  (Every workgroup for the flagged ones of a
 // fixed share of the items: with 229 of 22 296 flagged, 33 frames of 45 x 80 tokens x 24 heads, one of them took two, with 619
-// three: 1.28 -> 0.87 ms for 229, and a launch without any 4.7 -> 2.6 us.)
+// three: 1.28 -> 0.87 ms for 229, and a launch without any 4.7 -> 2.6 us.)  The first item of a workgroup needs no draw, and none is
+// made where the lists hold no more than those (with a draw for each, 384 of 384 flagged, 6144 tokens x 8 heads, whole call
+// 212 us, now 204; 4 of 384 168.6 and 166.0).
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_attn_mfma_second_pass(AttnArgs a) {
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     __shared__ int s_item;
     constexpr int kXcds = kAttnQueues;
-    const int pairs = (a.Sb + 1) / 2 * a.td.H * a.td.B, per = (pairs + kXcds - 1) / kXcds;
+    const int pairs = (a.Sb + 1) / 2 * a.td.H * a.td.B, per = (pairs + kXcds - 1) / kXcds, last = a.Sb * a.td.H * a.td.B - 1;
     const int32_t* count = a.queue + kAttnQueues;
+    const int32_t* lists = a.flags + last + 1;
+    const int own = (int)blockIdx.x % kXcds, first = (int)blockIdx.x / kXcds;
     int listed[kXcds], all = 0;
 #pragma unroll
     for (int i = 0; i < kXcds; ++i) {
@@ -447,27 +451,47 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         all |= listed[i];
     }
     if (all == 0) return;
+    int mine = 0;
+    bool more = false;                        // items beyond the workgroups' first ones
+#pragma unroll
+    for (int i = 0; i < kXcds; ++i) {
+        mine = i == own ? listed[i] : mine;
+        more |= listed[i] > ((int)gridDim.x + kXcds - 1 - i) / kXcds;
+    }
+    int item = first < mine ? lists[2 * own * per + first] : -1;
     for (;;) {
+        item = min(__builtin_amdgcn_readfirstlane(item), last);      // (words that overlapping calls have mixed up name some block)
+        if (item >= 0) attn_item<true>(a, item, smem);
+        if (!more) return;
         if (threadIdx.x == 0) {
-            int item = -1;
+            item = -1;
+            for (;;) {
+                int drawn[kXcds];
 #pragma unroll
-            for (int i = 0; i < kXcds; ++i) {                  // (unrolled: the counts stay in registers)
-                const int x = ((int)blockIdx.x + i) % kXcds;
-                int n = 0;
+                for (int i = 0; i < kXcds; ++i) drawn[i] = __hip_atomic_load(&a.queue[2 * kAttnQueues + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int step = kXcds, from = 0, room = 0;                // to the nearest list with items left
 #pragma unroll
-                for (int e = 0; e < kXcds; ++e) n = e == x ? listed[e] : n;
-                if (item < 0 && __hip_atomic_load(&a.queue[2 * kAttnQueues + x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < n) {
-                    const int at = atomicAdd(&a.queue[2 * kAttnQueues + x], 1);
-                    if (at < n) item = a.flags[a.Sb * a.td.H * a.td.B + 2 * x * per + at];
+                for (int i = 0; i < kXcds; ++i) {
+                    const int begun = ((int)gridDim.x + kXcds - 1 - i) / kXcds, to = (i - own + kXcds) % kXcds;
+                    if (begun + drawn[i] < listed[i] && to < step) {
+                        step = to;
+                        from = begun;
+                        room = listed[i];
+                    }
+                }
+                if (step == kXcds) break;
+                const int x = (own + step) % kXcds, at = from + atomicAdd(&a.queue[2 * kAttnQueues + x], 1);
+                if (at < room) {
+                    item = lists[2 * x * per + at];
+                    break;
                 }
             }
-            s_item = min(item, a.Sb * a.td.H * a.td.B - 1);      // (words that overlapping calls have mixed up name some block)
+            s_item = item;
         }
-        __syncthreads();
-        const int item = __builtin_amdgcn_readfirstlane(s_item);
+        __syncthreads();          // (the next item's tile loads overwrite LDS that slower waves may still be reading)
+        item = s_item;
+        __syncthreads();          // (and it its place)
         if (item < 0) return;
-        attn_item<true>(a, item, smem);
-        __syncthreads();          // the next item's tile loads overwrite LDS that slower waves may still be reading
     }
 }
 

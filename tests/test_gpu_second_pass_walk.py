@@ -16,11 +16,12 @@ def csr(lists):
     return rowptr, torch.tensor([kb for l in lists for kb in l], dtype=torch.int32).view(1, 1, -1).cuda()
 
 
-def attend(Q, K, V, lists, bs):
+def attend(Q, K, V, lists, bs, ctx=None):
     B, H, N, _ = Q.shape
     O, lse = torch.full_like(Q, 7.0), torch.zeros(B, H, N, device="cuda")
     rowptr, colidx = csr(lists)
-    dr.dr_sparse_attn_fwd(dr.Context(0), dr.shape_of(Q, 1, 1, N, bs), Q, K, V, rowptr, colidx, 1, colidx.shape[2], O, lse)
+    rowptr, colidx = rowptr.repeat(B, 1, 1), colidx.repeat(B, 1, 1)
+    dr.dr_sparse_attn_fwd(ctx or dr.Context(0), dr.shape_of(Q, 1, 1, N, bs), Q, K, V, rowptr, colidx, 1, colidx.shape[2], O, lse)
     return O, lse
 
 
@@ -79,3 +80,24 @@ def test_lists_of_every_length_against_64_bits(order):
         rows = torch.arange(qb * bs, min(qb * bs + bs, N), device="cuda")
         keys = torch.cat([torch.arange(kb * bs, min(kb * bs + bs, N), device="cuda") for kb in lists[qb]])
         assert check_rows(O[0, 0], lse[0, 0], Q[0, 0], K[0, 0], V[0, 0], rows, keys).abs().max() > 46.0
+
+
+@pytest.mark.parametrize("heads", [(0, 10), (13, 17), (30, 40), (0, 40)])     # of the first batch: 120 blocks of one queue; some of two; ..
+def test_clusters_of_flagged_blocks_are_drawn_from_any_xcd(monkeypatch, heads):
+    """More flagged blocks in one queue than its own workgroups, 64 on 256 compute units: the others' take part, call after call."""
+    B, H, Sb = 2, 40, 12
+    N = Sb * 128 - 9
+    g = torch.Generator(device="cuda").manual_seed(heads[1])
+    Q, K, V = (torch.randn(B, H, N, 128, generator=g, device="cuda").bfloat16() for _ in range(3))
+    Q[0, heads[0]:heads[1]] *= 20
+    lists = [list(range(Sb))] * Sb
+    ctx = dr.Context(0)
+    monkeypatch.setenv("DR_ATTN_PAIRS", "0")
+    want_O, want_lse = attend(Q, K, V, lists, 128)
+    flagged = torch.nn.functional.pad(want_lse.abs() > 46.0, (0, 9)).view(B, H, Sb, 128).any(-1)
+    assert int(flagged.sum()) >= 11 * (heads[1] - heads[0])
+    rows = flagged.repeat_interleave(128, 2)[:, :, :N]
+    for _ in range(3):
+        O, lse = attend(Q, K, V, lists, 128, ctx)
+        assert torch.equal(O[rows], want_O[rows]) and torch.equal(lse[rows], want_lse[rows])
+        assert (O.float() - want_O.float()).abs().max() < 4e-2
