@@ -44,8 +44,10 @@ typedef __attribute__((address_space(3))) const v8bf* lds_v8;
 typedef __attribute__((address_space(3))) v4s* lds_v4;
 typedef float v4f32 __attribute__((ext_vector_type(4)));
 
-// FEW: a launch of at most one workgroup a compute unit (bf16, d = 64, block size 32)
-template <bool BF16, int D, int BS, bool FEW = false>
+// L: launches of few query blocks, of at most one workgroup a compute unit (bf16, d = 64, block size 32), or of many (fp32, d = 64, block size
+// 128); the results are the same bits
+constexpr int kAnyLaunch = 0, kFewBlocks = 1, kManyBlocks = 2;
+template <bool BF16, int D, int BS, int L = kAnyLaunch>
 struct Plan {
     static constexpr int kIn = BF16 ? 1 : 3;                        // parts of Q, K, V
     static constexpr int kQ = BS / 32;                              // wavefronts along the queries
@@ -54,21 +56,24 @@ struct Plan {
     static constexpr bool kAlone = BS == 32;
     // Two streams of four query groups and a second buffer: a query block's list takes half as many steps, and a launch of up to one
     // workgroup a compute unit leaves no SIMD with a single wavefront.  Against one stream (two workgroups of four wavefronts a
-    // compute unit): 48 blocks of 2048 tokens x 3 heads 71.7 -> 53.2 us, 240 blocks 92.1 -> 72.3, 384 258 -> 252, 564 975 -> 903, 720 465 -> 410;
-    // 1320 blocks, which leave 40 to a sixth round, 697 -> 709.  (At block size 64, where two streams are the rule, four measured 44.0 ->
-    // 34.4 at 84 blocks, 75 -> 81 at 320, 531 -> 555 at 1760: they stay two.)
-    static constexpr bool kEight = !BF16 && D == 64 && BS == 128;
+    // compute unit): 96 blocks of 1024 tokens 57.9 -> 43.6 us, 240 of 2048 84 -> 65, of 10 240 169 -> 126, 720 258 -> 247.  (At block size 64,
+    // where two streams are the rule, four measured 44.0 -> 34.4 at 84 blocks, 75 -> 81 at 320, 531 -> 555 at 1760: they stay two.)
+    static constexpr bool kTwo = !BF16 && D == 64 && BS == 128, kEight = kTwo && L != kManyBlocks;
+    // Where many blocks wait, two independent workgroups of four wavefronts a compute unit get more done than one of eight that keep step:
+    // one stream / eight wavefronts / in turn, 4000 blocks of 5120 tokens 1135 / 1191 / 1138 us, of 2048 785 / 841 / 790, 1440 of 1024 180 / 194 / 181,
+    // 320 of 256 26.9 / 33.1 / 27.4.  They take the two streams in turn, with the first one's sums in registers meanwhile.
+    static constexpr int kTurns = kTwo && !kEight ? 2 : 1;
     static constexpr int kS = kAlone ? (!BF16 && D == 128 ? 4 : 8) : (kEight ? 8 : 4) / kQ;        // streams of key tiles
     static constexpr int kThreads = 64 * kQ * kS;
     // bf16 rows straight from memory to LDS, the keys as well: fewer instructions and registers (120, four wavefronts a SIMD), a longer
     // way for a key.  17 550 tokens x 12 heads 815 -> 724 us, 6144 x 8 119 -> 100, 384 query blocks 21.9 -> 18.9; 192 and 168 blocks, with
     // a few tiles a wavefront, 12.7 -> 13.1 and 11.9 -> 12.5: launches of up to one workgroup a compute unit keep the registers
     // (the results are the same bits).
-    static constexpr bool kAloneDirect = kAlone && BF16 && D == 64 && !FEW;
+    static constexpr bool kAloneDirect = kAlone && BF16 && D == 64 && L != kFewBlocks;
     static constexpr int kTileBytes = 32 * (kAlone && !kAloneDirect ? 1 : 2) * kIn * 2 * D;          // 32 keys of (K and) V, all parts
     // bf16 rows go to LDS as they are, straight from memory, a stage of 64 keys ahead
     static constexpr bool kDirect = BF16 && D == 64 && !kAlone;
-    static constexpr int kT = kDirect && kS == 1 ? 2 : 1;      // 32-key tiles per stream and stage
+    static constexpr int kT = (kDirect && kS == 1) || kTurns == 2 ? 2 : 1;      // 32-key tiles per stream and stage
     static constexpr int kTiles = kS * kT;                          // of a stage
     static constexpr int kRows = kAlone ? 32 : kTiles * 32;         // of an LDS region
     static constexpr int kStageBytes = kTiles * kTileBytes;
@@ -169,9 +174,9 @@ struct Item {
 // where the block has them: a row is lost only when every logit of its first chunk is -inf (nothing finite to subtract), and
 // shorter chunks lose more rows.  Keys and values take turns in one LDS area, so that this pass, which is rarely made, asks
 // for little more than the walk does.
-template <bool BF16, int D, int BS>
+template <bool BF16, int D, int BS, int L>
 __device__ __forceinline__ void plain_block(const Item& it, float* lds) {
-    using P = Plan<BF16, D, BS>;
+    using P = Plan<BF16, D, BS, L>;
     constexpr int R = P::kPlainRows, C = P::kPlainKeys, DC = D / 8, LPT = C / 8;
     float* sQ = lds;
     float* sX = sQ + R * D;                    // keys, then values
@@ -267,9 +272,9 @@ __device__ __forceinline__ bool holds_huge_keys(const Item& it) {
     return most >= kHuge;
 }
 
-template <bool BF16, int D, int BS, bool FEW>
+template <bool BF16, int D, int BS, int L>
 __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
-    using P = Plan<BF16, D, BS, FEW>;
+    using P = Plan<BF16, D, BS, L>;
     constexpr int kDB = D / 32, kKS = D / 16;       // channel blocks of O, contraction steps of a logit tile
     constexpr int kPart = P::kRows * P::kRowBytes;  // bytes of one part of K (or V) of a stage
     constexpr int kTPB = BS / 32;                   // 32-key tiles of a key block
@@ -326,8 +331,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     }
 
     // ---- the walk.  Tile t of the row = keys (t % kTPB) * 32 .. + 31 of its key block t / kTPB; stage g holds tiles
-    // g * kTiles .., stream s the kT consecutive ones from s * kT on.  The list is held in a 64-entry register window. ----
-    const int n_tiles = it.n_list * kTPB, stages = (n_tiles + P::kTiles - 1) / P::kTiles;
+    // g * kTiles .., stream s the kT consecutive ones from s * kT on (in turns: every second tile, from the turn's own on).  The list is
+    // held in a 64-entry register window. ----
+    const int n_tiles = it.n_list * kTPB, stages = (n_tiles / P::kTurns + P::kTiles - 1) / P::kTiles;
+    int turn = 0;
+    auto tile_of = [&](int g, int i) { return (g * P::kTiles + i) * P::kTurns + turn; };
     int wbase = 0, win = it.n_list > 0 ? it.list[min(lane, it.n_list - 1)] : 0;
     auto tile_row0 = [&](int t) {          // t < n_tiles, its key block inside the window; clamped: a malformed list cannot address outside K / V
         const int kb = min(max(__builtin_amdgcn_readlane(win, t / kTPB - wbase), 0), a.Sb - 1);
@@ -338,19 +346,19 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     Raw rk[P::kPasses], rv[P::kPasses];
     int row0_next[P::kT], row0[P::kT];
     auto fetch = [&](int g) {
-        const int e_first = g * P::kTiles / kTPB, e_last = min(((g + 1) * P::kTiles - 1) / kTPB, it.n_list - 1);
+        const int e_first = tile_of(g, 0) / kTPB, e_last = min(tile_of(g, P::kTiles - 1) / kTPB, it.n_list - 1);
         if (e_last - wbase >= 64) {          // wavefront-uniform
             wbase = e_first;
             win = it.list[min(wbase + lane, it.n_list - 1)];
         }
 #pragma unroll
-        for (int c = 0; c < P::kT; ++c) row0_next[c] = tile_row0(min(g * P::kTiles + ws * P::kT + c, n_tiles - 1));
+        for (int c = 0; c < P::kT; ++c) row0_next[c] = tile_row0(min(tile_of(g, ws * P::kT + c), n_tiles - 1));
 #pragma unroll
         for (int p = 0; p < P::kPasses; ++p) {
             constexpr int kWaveRows = 64 / P::kRowUnits;          // rows of one wavefront and pass: they lie in one tile
             static_assert(32 % kWaveRows == 0, "a wavefront's rows lie in one tile");
             const int wave_row = (p * P::kThreads + wave * 64) / P::kRowUnits;
-            const int r = tile_row0(min(g * P::kTiles + wave_row / 32, n_tiles - 1)) + wave_row % 32;      // the same in every lane
+            const int r = tile_row0(min(tile_of(g, wave_row / 32), n_tiles - 1)) + wave_row % 32;      // the same in every lane
             const int64_t base = (int64_t)r * it.row_bytes;
             int64_t off = base + lane_off;
             if (r + kWaveRows > N) off = (int64_t)min(r + lane / P::kRowUnits, N - 1) * it.row_bytes + (lane % P::kRowUnits) * (8 * ES);
@@ -977,7 +985,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
     // a tile's logits, its softmax and its share of O; `at`: LDS offset of the stage
     auto take_tile = [&](int g, int c, int row, uint32_t at) {
         const int valid = N - row;                               // keys of the tile (only the sequence's end has fewer than 32)
-        if (!(g * P::kTiles + ws * P::kT + c < n_tiles && valid > 0)) return;      // wavefront-uniform
+        if (!(tile_of(g, ws * P::kT + c) < n_tiles && valid > 0)) return;      // wavefront-uniform
         const uint32_t tile = at + (uint32_t)((ws * P::kT + c) * 32 * P::kRowBytes);
         v16f s;
 #pragma unroll
@@ -996,11 +1004,11 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
         }
         use_tile(s, valid, tile, []() {});
     };
-    if (stages > 0) fetch(0);
     if constexpr (P::kEight) {
         // One workgroup of eight wavefronts fills a compute unit, so nobody else runs while it waits: a second buffer, a barrier a
         // stage, the next stage split and the one after it on its way ahead of this one's products.
         if (stages > 0) {
+            fetch(0);
             store(0);
 #pragma unroll
             for (int c = 0; c < P::kT; ++c) row0[c] = row0_next[c];
@@ -1020,6 +1028,8 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
             for (int c = 0; c < P::kT; ++c) take_tile(g, c, row[c], (uint32_t)(g & 1) * P::kStageBytes);
         }
     } else {
+    auto walk = [&]() {
+    if (stages > 0) fetch(0);
     for (int g = 0; g < stages; ++g) {
         if constexpr (!BF16 && D == 128) {
             // the Q parts are only ever operands of matrix instructions: they live in accumulation registers
@@ -1039,11 +1049,39 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 #pragma unroll
         for (int c = 0; c < P::kT; ++c) take_tile(g, c, row0[c], 0u);
     }
+    };
+    walk();
+    if constexpr (P::kTurns == 2) {
+        v16f o_first[kDB];
+#pragma unroll
+        for (int db = 0; db < kDB; ++db) {
+            o_first[db] = o[db];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[db][j] = 0.f;
+        }
+        const float ref_first = ref, l_first = l_run + __shfl_xor(l_run, 32);
+        ref = -INFINITY;
+        l_run = 0.f;
+        turn = 1;
+        wbase = 0;
+        if (it.n_list > 0) win = it.list[min(lane, it.n_list - 1)];
+        walk();
+        // as two streams are merged below
+        const float l_second = l_run + __shfl_xor(l_run, 32), top = fmaxf(fmaxf(-INFINITY, ref_first), ref);
+        const float first = (ref_first == top) ? 1.0f : __builtin_amdgcn_exp2f(ref_first - top);
+        const float second = (ref == top) ? 1.0f : __builtin_amdgcn_exp2f(ref - top);
+        l_run = __builtin_fmaf(l_first, first, l_second * second);
+#pragma unroll
+        for (int db = 0; db < kDB; ++db)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) o[db][j] = __builtin_fmaf(o_first[db][j], first, o[db][j] * second);
+        ref = top;
+    }
     }
     }
 
     // ---- merge the streams of a query group (stream order), normalise, store ----
-    float l = l_run + __shfl_xor(l_run, 32);
+    float l = P::kTurns == 2 ? l_run : l_run + __shfl_xor(l_run, 32);
     if constexpr (P::kS > 1) {
         __syncthreads();
         float* sO = reinterpret_cast<float*>(smem);                           // [kS - 1][kQ][32 channels-and-queries x kDB]
@@ -1145,7 +1183,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
         if (it.lse && half == 0)      // the two terms in 64 bits: the reference is a rounded multiple of the scale
             it.lse[qrow] = (l > 0.f) ? (float)((double)ref * 0.69314718055994531 + log((double)l)) : -INFINITY;
     }
-    if (plain) plain_block<BF16, D, BS>(it, reinterpret_cast<float*>(smem));
+    if (plain) plain_block<BF16, D, BS, L>(it, reinterpret_cast<float*>(smem));
 }
 
 // Measured against the vector-ALU kernel before it (one thread, eight logits and D / 8 channels of a row; 16 TFLOP/s at
@@ -1160,18 +1198,18 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs& a) {
 // share stages behind barriers, 24 to 30 us with eight that walk alone.
 // The fp32 kernels at d = 128 hold 96 registers of Q parts and run one wavefront per SIMD; those at d = 64 run two, bf16 at d = 64,
 // which fits 128 registers, four, bf16 at d = 128 two or three.
-template <bool BF16, int D, int BS, bool FEW>
-__global__ __launch_bounds__((Plan<BF16, D, BS, FEW>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS, FEW>::kPerSimd)))
-void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS, FEW>(a); }
+template <bool BF16, int D, int BS, int L>
+__global__ __launch_bounds__((Plan<BF16, D, BS, L>::kThreads)) __attribute__((amdgpu_waves_per_eu(Plan<BF16, D, BS, L>::kPerSimd)))
+void k_attn_split(AttnArgs a) { attn_split_body<BF16, D, BS, L>(a); }
 
-template <bool BF16, int D, int BS, bool FEW = false>
+template <bool BF16, int D, int BS, int L = kAnyLaunch>
 hipError_t launch_t(const AttnArgs& a, hipStream_t s) {
-    using P = Plan<BF16, D, BS, FEW>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS, FEW>),
+    using P = Plan<BF16, D, BS, L>;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_attn_split<BF16, D, BS, L>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, P::kLdsBytes);
     if (e != hipSuccess) return e;
     const int total = a.Sb * a.td.H * a.td.B, grid = (total + 7) / 8 * 8;          // every XCD gets the same number of slots
-    hipLaunchKernelGGL((k_attn_split<BF16, D, BS, FEW>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
+    hipLaunchKernelGGL((k_attn_split<BF16, D, BS, L>), dim3(grid), dim3(P::kThreads), P::kLdsBytes, s, a);
     return hipGetLastError();
 }
 
@@ -1182,8 +1220,17 @@ hipError_t launch_d(const AttnArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// fp32, d = 64, block size 128: the number of query blocks beyond which their workgroups take the streams in turn.  The shorter a walk, the more
+// its ends, where all eight wavefronts wait, weigh: blocks per compute unit at which eight wavefronts cease to be faster, one or two rows of
+// blocks (256 tokens) 1.0, 8 rows 1 to 3, 16 rows 2 to 4.5, 24 and 32 rows 6.5 to 7.5, 40 and 80 rows 8.  (Eight / in turn: 800 blocks of 256
+// tokens 68.8 / 53.8 us, 320 of 1024 69.4 / 72.6 and 91.5 / 82.9, 1040 of 2048 262 / 253, 1200 272 / 287, 1536 of 3072 403 / 415, 1920 543 / 523,
+// 1800 of 5120 592 / 603, 2560 779 / 743.)
+static int64_t many_blocks(const AttnArgs& a) { return (int64_t)a.cus * (a.Sb <= 8 ? 1 : a.Sb <= 16 ? 4 : a.Sb <= 32 ? 7 : 8); }
+
 hipError_t launch_attn_split(const AttnArgs& a, hipStream_t s) {
-    if (a.td.d == 64 && a.bf16 && a.Bs == 32 && (int64_t)a.Sb * a.td.H * a.td.B <= a.cus) return launch_t<true, 64, 32, true>(a, s);
+    const int64_t blocks = (int64_t)a.Sb * a.td.H * a.td.B;
+    if (a.td.d == 64 && a.bf16 && a.Bs == 32 && blocks <= a.cus) return launch_t<true, 64, 32, kFewBlocks>(a, s);
+    if (a.td.d == 64 && !a.bf16 && a.Bs == 128 && blocks > many_blocks(a)) return launch_t<false, 64, 128, kManyBlocks>(a, s);
     if (a.td.d == 64) return a.bf16 ? launch_d<true, 64>(a, s) : launch_d<false, 64>(a, s);
     if (a.td.d == 128) return a.bf16 ? launch_d<true, 128>(a, s) : launch_d<false, 128>(a, s);
     return hipErrorNotSupported;
