@@ -503,6 +503,9 @@ __device__ __forceinline__ void load_wave_row(const uint64_t* __restrict__ class
         r.n_far += __popcll(r.m_far[i]);
     }
 }
+// The compiler's own v_writelane (it has no builtin), between whose sources and other vector instructions the compiler keeps the wait states
+// that the chip asks for; inline assembly it does not look into.
+__device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t old) __asm("llvm.amdgcn.writelane.i32");
 // a row's keep words, one per lane (a store for each slot's pair costs three times the instructions), and its count
 template <int kSlots, class Kept>
 __device__ __forceinline__ void store_keep_words(int64_t row, int Sb, uint32_t* __restrict__ keepbits, int32_t* __restrict__ counts, Kept&& kept_of) {
@@ -514,8 +517,8 @@ __device__ __forceinline__ void store_keep_words(int64_t row, int Sb, uint32_t* 
     for (int i = 0; i < kSlots; ++i) {
         const uint64_t m = kept_of(i);                            // (past the row's end: 0)
         kept += __popcll(m);
-        asm("v_writelane_b32 %0, %1, %2" : "+v"(word) : "s"((uint32_t)m), "n"(2 * i));
-        asm("v_writelane_b32 %0, %1, %2" : "+v"(word) : "s"((uint32_t)(m >> 32)), "n"(2 * i + 1));
+        word = write_lane((uint32_t)m, 2 * i, word);
+        word = write_lane((uint32_t)(m >> 32), 2 * i + 1, word);
     }
     if (lane < words) keepbits[row * words + lane] = word;
     if (lane == 0) counts[row] = kept;
