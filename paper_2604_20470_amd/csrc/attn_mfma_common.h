@@ -21,11 +21,12 @@ constexpr float kExpScale = (float)(1.4426950408889634 / 11.313708498984760);
 // |logit| (about |logit| * 2^-9 per channel, random in sign).  Rows whose largest exponent, in units of log2, is
 // beyond this limit in magnitude (44 in natural units) are taken again with the scale applied in fp32.
 constexpr float kExactLimit = 64.0f;
-// The first chunk of a row sets its exponent reference, but to no less than this (units of log2).  Fast pass: what the chunk's keys weigh
-// against -126 is lost where a later key lies 2^7 above, and a row that ends without a sum is flagged.  fp32-scaled pass: relative to
-// a reference far below, the logits of later keys would lose their low bits; a row that ends without a sum is walked again, and
-// may begin this much below its largest exponent.
+// The first chunk of a row sets its exponent reference, but to no less than this (units of log2).  Fast pass: below -126 the factor
+// 2^-reference would be infinite; a row whose exponents all lie below -64 is flagged anyway.  fp32-scaled pass: relative to a reference
+// far below, the logits of later keys would lose their low bits; a row whose sum ends below kLeastSum (1 or more where its reference
+// was not held back) is walked again, and may begin this much below its largest exponent.
 constexpr float kFastFloor = -126.0f, kExactFloor = -4096.0f;
+constexpr float kLeastSum = 0x1p-40f;      // powers of 2 end at 2^-126: what a row of 2^20 keys loses there weighs less than 2^-46
 
 // The barrier carries no memory fence on purpose: a fence would drain the prefetch of the next
 // chunk.  Ordering of the direct-to-LDS loads is enforced by the explicit vmcnt waits.
@@ -55,12 +56,12 @@ __device__ __forceinline__ float max_across_halves(float x) {
 }
 
 
-// Behind a walk of the fp32-scaled pass: whether the workgroup has rows that list keys but are without a sum, and whose largest exponent
-// is a number; their floor then is set by it.  Called by all waves.  largest(): of this lane's query column, as the product of Q and K gives
-// it, not scaled.
+// Behind a walk of the fp32-scaled pass: whether the workgroup has rows that list keys but sum to less than kLeastSum, and whose largest
+// exponent is a number; their floor then is set by it.  Called by all waves.  largest(): of this lane's query column, as the product of Q
+// and K gives it, not scaled.
 template <class F>
 __device__ __forceinline__ bool walk_again(float l_part, bool listed, float& floor, F&& largest) {
-    const bool none = listed && l_part + __shfl_xor(l_part, 32) == 0.f;
+    const bool none = listed && l_part + __shfl_xor(l_part, 32) < kLeastSum;
     bool low = false;
     if (__any(none)) {
         const float best = largest() * kExpScale;

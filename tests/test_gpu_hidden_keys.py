@@ -68,3 +68,19 @@ def test_rows_without_keys_beside_rows_of_the_second_pass(monkeypatch, bs, pairs
             assert bool((O[0, 0, rows] == 0).all()) and bool(torch.isneginf(lse[0, 0, rows]).all())
         else:
             check_rows(O[0, 0], lse[0, 0], Q[0, 0], K[0, 0], V[0, 0], rows, torch.arange(N, device="cuda"))
+
+
+@pytest.mark.parametrize("bs", [128, 64, 32])
+@pytest.mark.parametrize("more", [0.0, -60.0, -90.0, -108.0, -130.0])
+def test_rows_at_the_edge_of_what_the_first_walk_sums(bs, more):
+    """All exponents between 100 and 140 (units of log2) below the least reference of the second pass, where powers of 2 end."""
+    N = 200
+    Q, K, V = inputs(N, 1, 0.0, [], False)
+    K[..., 127], Q[..., 126], K[..., 126] = -33024.0, 1.0, more
+    Sb = -(-N // bs)
+    O, lse = attend(Q, K, V, [list(range(Sb))] * Sb, bs)
+    q, k = Q[0, 0].double(), K[0, 0].double()
+    s = q @ k.T / 128 ** 0.5
+    want, want_lse = torch.softmax(s, -1) @ V[0, 0].double(), torch.logsumexp(s, -1)
+    # logits of size 33 000 in 32 bits, four roundings of 2^-24 each in their sum: 2^-7 of the unscaled logit, and as much of the exponent
+    assert (O[0, 0].double() - want).abs().max() < 3e-2 and (lse[0, 0].double() - want_lse).abs().max() < 8e-3
