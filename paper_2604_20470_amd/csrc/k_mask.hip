@@ -587,8 +587,8 @@ __global__ __launch_bounds__(kThreads) void k_select_wave(const uint64_t* __rest
 // Cumulative mass for rows of at most 1024 key blocks, one wave per row.  The rule is a sum of fp64 exponentials one by
 // one in score order, compared with tau times the whole sum: a serial chain behind a sort, if taken literally (k_select:
 // 208 us at 40 x 591 rows; this kernel 23 with scores of a smooth field, more over other distributions; the vector ALU is busy for
-// 84 % of it, so what counts is instructions a row: 538 before the keys were made without a test each and the keep words
-// stored as one register, 29 us).  Only the place where the prefix crosses the target is wanted, so it is
+// 92 % of the time that a compute unit has work, so what counts is instructions a row: 463, and 538, 29 us, before the keys were
+// made without a test each and the keep words stored as one register).  Only the place where the prefix crosses the target is wanted, so it is
 // looked for with fixed-point masses, without sorting (mass_crossing), first in 32 and, where those cannot tell, in 64
 // bits; a row whose target lies within the error of the 64-bit sums (equal scores that hit it exactly, tau = 1) is decided by
 // the literal chain, in this wave.

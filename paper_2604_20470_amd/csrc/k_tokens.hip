@@ -303,7 +303,10 @@ __device__ __forceinline__ void set_stats(const float* __restrict__ S, const Pai
 // LDS, up to four rounds: 16 to 18 and 33 to 45.)  Where workgroups wait for a place a feeder each is enough, and more of them
 // are in flight: whole calls, alone / three feeders / one, by the number of workgroups, 192: 128 / 98 / 126 us; 384: 335 / 309 / 389;
 // 672: 101 / 89 / 104; 880: 61.4 / 54.7 / 57.2; 1344: 70.1 / 68.8 / 70.0; 1680: 102 / 104 / 98; 2024: 78.7 / 77.5 / 72.4; 2394: 120 / 112 / 108;
-// 3720: 101 / 111 / 100; 6486: 98.1 / 98.9 / 87.8.  Drawn at six a compute unit, what the LDS of three feeders lets it hold.
+// 3720: 101 / 111 / 100; 6486: 98.1 / 98.9 / 87.8.  Drawn at six workgroups on each of 256 compute units, as measured: what LDS lets a unit hold of
+// three feeders' workgroups is six in pass 0, but four in pass 1 at 1024 tokens a frame and two at 4096, and yet three are faster there (8 frames of
+// 2048, 1344 workgroups: 308 / 322 us with three / one, 4 of 4096 x 4 masks, 1536: 1005 / 1083, 10 of 1600, 1800: 321 / 340), while short frames
+// would have the line lower (20 of 256, 1304: 65.1 / 63.8, 15 of 512, 1456: 97.9 / 95.2).
 // Pass 1: the workgroup that is last of its pair to store its sums forms the pair's statistics (arrivals are counted in the
 // `best` of the pair, which pass 0 clears); nobody waits for another.  Pass 0 also clears the kept counts of the mask's rows, to
 // which k_link_blocks adds.
@@ -608,7 +611,9 @@ __global__ __launch_bounds__(256 * kGroups) void k_link_blocks(const float* __re
 // mask of frames above 115 tokens they do as well: whole calls, the three launches above / these two, 16 frames of 64 tokens 27.9 / 20.2 us;
 // 33 of 64: 30.1 / 25.8; 20 of 96: 34.9 / 34.9; 33 of 96 (10 million token pairs): 47.0 / 44.9; 50 of 96 (23 million): 60.9 / 65.6; 33 of 121: 53.3 / 70.8;
 // 9 of 120: 30.7 / 33.0; 16 of 128: 31.0 / 35.9; 24 of 128 (9 million): 42.0 / 46.9; 60 of 128: 80 / 133; several masks, 16 of 117 x 2: 47.9 / 46.5;
-// 10 of 120 x 4: 43.8 / 40.3.
+// 10 of 120 x 4: 43.8 / 40.3.  (In another run the latter two measured 36.5 / 38.9 and 43.1 / 39.3, 16 of 128 x 2 33.3 / 42.1, 19 of 128 x 2 45.0 / 63.8,
+// 13 of 128 x 4 44.6 / 64.1, 9 of 128 x 8 46.4 / 51.3: several masks keep the two launches, as they always have, although the three are the
+// faster ones at most sizes.)
 constexpr int64_t kSmallPairs = 12 << 20;
 constexpr int kThreePerCu = 115;
 inline bool small_frames(int B, int masks, int N, int Nf) {
